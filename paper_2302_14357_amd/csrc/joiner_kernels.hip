@@ -6,7 +6,7 @@
 // formed once (add, tanh/relu, round to bf16) and the product is a bf16 MFMA
 // GEMM with fp32 accumulation whose epilogue adds the bias and stores the
 // logits once.  The same GEMM serves the LSTM gates and the predictor
-// projection.  A plain fp32 path exists for fp32 models.
+// projection.  fp32 models have a GEMM of their own.
 #include "tbs_internal.h"
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -164,53 +164,5 @@ hipError_t launch_joiner_prep(hipStream_t st, const Dims &d, int dtype, int act,
         hipLaunchKernelGGL(k_joiner_prep_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, rows, d.Dj, act,
                            (const float *)enc, pool_p, rv.row_enc, rv.row_slot, (float *)amat, rows_dev);
     }
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------ fp32 GEMM (fp32 models)
-// C[M,N] = A[M,K] * B[N,K]^T + bias, 64x64 tile, 4x4 outputs per thread.
-__global__ void __launch_bounds__(256)
-k_gemm_f32(const float *__restrict__ A, const float *__restrict__ B, const float *__restrict__ bias,
-           float *__restrict__ C, int M, int N, int K, const int *__restrict__ out_row, long ldc) {
-    __shared__ float sA[16][64 + 1], sB[16][64 + 1];
-    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
-    float acc[4][4] = {};
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        for (int i = tid; i < 64 * 16; i += 256) {
-            int r = i / 16, k = i % 16;
-            int gm = m0 + r, gn = n0 + r, gk = k0 + k;
-            sA[k][r] = (gm < M && gk < K) ? A[(long)gm * K + gk] : 0.f;
-            sB[k][r] = (gn < N && gk < K) ? B[(long)gn * K + gk] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < 16; ++k) {
-            float a[4], b[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) { a[i] = sA[k][ty * 4 + i]; b[i] = sB[k][tx * 4 + i]; }
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-        __syncthreads();
-    }
-    for (int i = 0; i < 4; ++i) {
-        int gm = m0 + ty * 4 + i;
-        if (gm >= M) continue;
-        long orow = out_row ? out_row[gm] : gm;
-        for (int j = 0; j < 4; ++j) {
-            int gn = n0 + tx * 4 + j;
-            if (gn < N) C[orow * ldc + gn] = acc[i][j] + (bias ? bias[gn] : 0.f);
-        }
-    }
-}
-
-hipError_t launch_gemm_f32(hipStream_t st, const float *A, const float *B, const float *bias, float *C, int M, int N,
-                           int K, const int *out_row, long ldc) {
-    if (M <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_gemm_f32, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, A, B, bias, C, M, N, K,
-                       out_row, ldc);
     return hipGetLastError();
 }

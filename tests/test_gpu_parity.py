@@ -139,6 +139,18 @@ def test_joiner_expand_tiny_fp32():
     _check_joiner_expand(SHAPES["tiny"], U=1, N=2, S=3, seg=16, tol=1e-4)  # ragged last segment (2 frames)
 
 
+@pytest.mark.parametrize("d,V,U,N,S", [(4, 20, 1, 2, 1), (128, 64, 3, 4, 3), (132, 33, 2, 3, 2), (640, 70, 4, 5, 3), (772, 1028, 13, 5, 5),
+                                       (6, 31, 2, 3, 3), (1030, 129, 3, 4, 2)])
+def test_fp32_dense_layers_widths(d, V, U, N, S):
+    """The fp32 GEMM at the edges of its K tiles (one chunk, one tile, a tile and a chunk, as many tiles as
+    stages, more; widths that are no whole 16-byte chunks take the other kernel) and of its 32x32 tiles."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=U, vocab=V, d=d, hidden=d), dtype="f32")
+    _check_joiner_expand(shape, U=U, N=N, S=S, seg=0, tol=1e-4, sample_pairs=8)
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=np.minimum(np.arange(U) + 4, 9))
+    _check_decode(shape, model, offsets, enc, N, S)
+
+
 @pytest.mark.parametrize("kernel", ["auto", "generic"])
 @pytest.mark.parametrize("N,S", [(5, 3), (2, 1), (10, 5), (3, 50), (4, 12), (32, 2)])
 def test_joiner_expand_small_bf16(N, S, kernel):
