@@ -66,7 +66,7 @@ hipError_t launch_init_batch(hipStream_t st, const Dims &d, BView B, AView A0, A
 // The workgroup ranks B and writes A; then it moves the survivors' predictor state into this
 // segment's arena (slot r=0): the arena of the segment before last is reused, and a survivor may have
 // been carried, untouched, from there.  In the slot layout it also forms the joiner input rows of the
-// segment's first round, act(e_t + p) as bf16 (Section 3.1), from the p values it is moving.
+// segment's first round, act(e_t + p) (Section 3.1), from the p values it is moving.
 // A SIMD issues an instruction of one of its waves every few cycles, so what counts in a kernel of
 // this size is the number of instructions per SIMD: a workgroup is four waves, one per SIMD, and in
 // the slot layout, where a small batch leaves most of the chip idle, `parts` workgroups share an
@@ -81,12 +81,17 @@ __device__ __forceinline__ unsigned seg_bf16(float f) {   // nearest, ties to ev
 }
 #define SEG_THREADS 256
 #define SEG_ENC_LOADS ((TBS_FIXED_SMAX * 1024 / 4 + SEG_THREADS - 1) / SEG_THREADS)   // 8-byte pieces of S rows of up to 1024 columns, per thread
+// four encoder values of a frame, in the storage type of the model
+template <bool F32> struct SegPiece { typedef uint2 type; };
+template <> struct SegPiece<true> { typedef float4 type; };
+template <bool F32>
 __global__ void __launch_bounds__(SEG_THREADS)
 k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv, float *pool_p,
                 float *pool_h, float *pool_c, long pool_rows, FixedView fx) {
     __shared__ int s_src[TBS_MAX_BEAM], s_dst[TBS_MAX_BEAM];
     __shared__ int s_n;
-    __shared__ uint2 s_enc[TBS_FIXED_SMAX * 1024 / 4];   // the segment's frames, [frame][4 columns]
+    typedef typename SegPiece<F32>::type EP;
+    __shared__ EP s_enc[TBS_FIXED_SMAX * 1024 / 4];   // the segment's frames, [frame][4 columns]
     const int parts = fx.parts > 1 ? fx.parts : 1;
     const int u = blockIdx.x / parts, part = blockIdx.x - u * parts, tid = threadIdx.x;
     const bool first = part == 0;
@@ -109,14 +114,14 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
     // exists in either case: a request behind a condition would make every later wait a wait for all.
     const bool rows_here = fx.on && fx.amat != nullptr && sp > 0;
     const int cp = d.Dj >> 2;   // pieces of four columns in a row
-    uint2 ev[SEG_ENC_LOADS];
+    EP ev[SEG_ENC_LOADS];
     {
-        const bf16_t *ebase = rows_here ? fx.enc + ((long)fx.utt_off[u] + (long)seg * d.S) * d.Dj
-                                        : reinterpret_cast<const bf16_t *>(pool_p);
+        const EP *ebase = rows_here ? static_cast<const EP *>(fx.enc) + ((long)fx.utt_off[u] + (long)seg * d.S) * cp
+                                    : reinterpret_cast<const EP *>(pool_p);
         const int pieces = rows_here ? sp * cp : 1;
 #pragma unroll
         for (int q = 0; q < SEG_ENC_LOADS; ++q)
-            ev[q] = reinterpret_cast<const uint2 *>(ebase)[min(tid + q * SEG_THREADS, pieces - 1)];   // (rows follow each other)
+            ev[q] = ebase[min(tid + q * SEG_THREADS, pieces - 1)];   // (rows follow each other)
     }
     if (tid == 0) {
         if (first) rv.utt_sp[u] = sp;
@@ -248,15 +253,21 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
                 if (rows_here && j < up) {
                     // (hypothesis k of the utterance is pair u*N + k: rows from pair * S)
                     const float p4[4] = {vp.x, vp.y, vp.z, vp.w};
-                    uint2 *arow = reinterpret_cast<uint2 *>(fx.amat + (long)(u * d.N + k) * d.S * d.Dj) + j;
+                    EP *arow = static_cast<EP *>(fx.amat) + (long)(u * d.N + k) * d.S * cp + j;
                     for (int t = 0; t < sp; ++t) {
-                        const uint2 e2 = s_enc[t * cp + j];
-                        const float e4[4] = {__uint_as_float(e2.x << 16), __uint_as_float(e2.x & 0xFFFF0000u),
-                                             __uint_as_float(e2.y << 16), __uint_as_float(e2.y & 0xFFFF0000u)};
-                        unsigned o[4];
+                        const EP e = s_enc[t * cp + j];
+                        if constexpr (F32) {
+                            arow[(long)t * cp] = make_float4(
+                                tbs_joiner_act_f32(e.x + p4[0], fx.act), tbs_joiner_act_f32(e.y + p4[1], fx.act),
+                                tbs_joiner_act_f32(e.z + p4[2], fx.act), tbs_joiner_act_f32(e.w + p4[3], fx.act));
+                        } else {
+                            const float e4[4] = {__uint_as_float(e.x << 16), __uint_as_float(e.x & 0xFFFF0000u),
+                                                 __uint_as_float(e.y << 16), __uint_as_float(e.y & 0xFFFF0000u)};
+                            unsigned o[4];
 #pragma unroll
-                        for (int q = 0; q < 4; ++q) o[q] = seg_bf16(tbs_joiner_act(e4[q] + p4[q], fx.act));
-                        arow[(long)t * cp] = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+                            for (int q = 0; q < 4; ++q) o[q] = seg_bf16(tbs_joiner_act(e4[q] + p4[q], fx.act));
+                            arow[(long)t * cp] = make_uint2(o[0] | (o[1] << 16), o[2] | (o[3] << 16));
+                        }
                     }
                 }
             }
@@ -272,8 +283,13 @@ hipError_t launch_segment_begin(hipStream_t st, const Dims &d, int seg, const in
     FixedView f{};
     if (fx) f = *fx;
     if (f.parts > 1 && !f.on) return hipErrorInvalidValue;   // (only the slot layout's round kernel finishes what the parts leave)
-    hipLaunchKernelGGL(k_segment_begin, dim3(d.U * (f.parts > 1 ? f.parts : 1)), dim3(SEG_THREADS), 0, st, d, seg, utt_T, B, A, rv, pool_p,
-                       pool_h, pool_c, pool_rows, f);
+    const dim3 grid(d.U * (f.parts > 1 ? f.parts : 1)), block(SEG_THREADS);
+    if (f.on && f.f32)
+        hipLaunchKernelGGL(k_segment_begin<true>, grid, block, 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h, pool_c,
+                           pool_rows, f);
+    else
+        hipLaunchKernelGGL(k_segment_begin<false>, grid, block, 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h, pool_c,
+                           pool_rows, f);
     return hipGetLastError();
 }
 

@@ -6,10 +6,11 @@
 // of a decode (80 to 400 rows) what bounds a product is how many SIMDs work on it.  A workgroup
 // therefore owns one 32x32 tile and its four waves share K: wave w multiplies the w-th quarter of
 // every K tile and the four partial tiles are added up through LDS at the end, where a thread owns
-// four neighbouring columns of a row.  Measured over the three products of a round of 16 utterances x 5
-// hypotheses x 3 frames (240 x 1024 x 512, 80 x 2560 x 1280, 80 x 512 x 640): 10.5 us a launch on average,
-// against 122 us for the kernel of scalar multiply-adds on 64x64 tiles at the end of this file; the
-// matrix work of the largest is 4.3 us a wave.  K tiles of 128 floats go from global memory straight into LDS, as many
+// four neighbouring columns of a row.  Measured at 16 utterances x 5 hypotheses x 3 frames of
+// the Librispeech-like widths (240 x 1024 x 512, 80 x 2560 x 1280, 80 x 512 x 640): 10.5 us a launch on
+// average against 122 us for the kernel of scalar multiply-adds on 64x64 tiles at the end of this file.
+// With the fused epilogues (gates 80 x 2560 x 640 and the cell update 12.3 us, projection and joiner
+// input rows 8.9 us, joiner 7.4 us) a round is four launches instead of nine.  K tiles of 128 floats go from global memory straight into LDS, as many
 // requested at once as there are stages; rows are 512 bytes, chunk c (16 bytes) of row r sits at
 // position c ^ (r & 15), so that the 16-byte fragment reads of 16 neighbouring rows fall into
 // different banks.  A lane takes 4 consecutive K elements per read and the MFMA steps take them in the
@@ -19,7 +20,6 @@
 
 typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 
-#define GF_TILE 32
 #define GF_BK 128                         // floats of K per stage
 #define GF_CH (GF_BK / 4)                 // 16-byte chunks per LDS row
 #define GF_STAGE (2 * GF_TILE * GF_BK)    // floats of one stage: A rows, then B rows
@@ -32,28 +32,67 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float floatx16;
 // workgroup barrier that orders LDS traffic only (the direct loads of later stages stay in flight)
 __device__ __forceinline__ void gf_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+__device__ __forceinline__ float gf_sigmoid(float x) { return 1.f / (1.f + expf(-x)); }
+
+// MODE 0: C[out_row[r], :] = A[r, :] B^T + bias.
+// MODE 1: the product is the gate pre-activations of an LSTM layer (gate-interleaved columns, see
+// LstmEp), a thread's four columns are the gates of one hidden unit, and the epilogue is the cell update.
+// MODE 2: the product is the predictor projection of new hypotheses (row r = pair r); the epilogue also
+// forms the joiner input rows of the pair's frames (see JoinEp).
+// m_dev not null: M is an upper bound and the rows that exist are the first *m_dev; any_dev not null: rows
+// may be dead (state slot < 0) anywhere and the launch leaves at once when *any_dev is zero.
+// xcd_rows (MODE 0): every XCD computes a range of rows of its own, all their columns (see PartEp).
+template <int MODE>
 __global__ void __launch_bounds__(256)
 k_gemm_f32_mfma(const float *__restrict__ A, const float *__restrict__ B, const float *__restrict__ bias,
                 float *__restrict__ C, int M, int N, int K, const int *__restrict__ out_row, long ldc, int tiles_m,
-                int tiles_n, int ns) {
+                int tiles_n, int ns, LstmEp ep, JoinEp jp, const int *__restrict__ m_dev,
+                const int *__restrict__ any_dev, int xcd_rows) {
     extern __shared__ __attribute__((aligned(16))) float gf_smem[];   // ns stages
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // The 8 XCDs (workgroup id modulo 8) form a 2 x 4 grid over the tiles, so that each XCD's L2
     // fetches half of A and a quarter of B instead of all of both.
     const int tmx = (tiles_m + 1) >> 1, tnx = (tiles_n + 3) >> 2;
-    const int xcd = (int)blockIdx.x & 7, j = (int)blockIdx.x >> 3;
-    const int tile_m = (xcd >> 2) * tmx + j % tmx, tile_n = (xcd & 3) * tnx + j / tmx;
+    // (MODE 2 may run several workgroups per tile: the grid is then that many copies of the tile grid)
+    const int base_grid = 8 * tmx * tnx;
+    const int fgroup = MODE == 2 ? (int)blockIdx.x / base_grid : 0;
+    const int bid = (int)blockIdx.x - fgroup * base_grid;
+    const int xcd = bid & 7, j = bid >> 3;
+    int tile_m = (xcd >> 2) * tmx + j % tmx, tile_n = (xcd & 3) * tnx + j / tmx;
+    if (MODE == 0 && xcd_rows) {   // a row range per XCD, all its columns
+        const int tpx = (tiles_m + 7) >> 3;
+        tile_m = xcd * tpx + j % tpx;
+        tile_n = j / tpx;
+    }
     if (tile_m >= tiles_m || tile_n >= tiles_n) return;   // before any barrier
     const int kt = (K + GF_BK - 1) / GF_BK, kch = K >> 2;   // (K is a multiple of 4)
 
     // what the epilogue needs is requested first: loads retire in order, so it is there before the tiles
     const int erow = tile_m * GF_TILE + (tid >> 3), ecol = tile_n * GF_TILE + (tid & 7) * 4;
-    const int orow = out_row ? out_row[min(erow, M - 1)] : min(erow, M - 1);
+    const int erc = min(erow, M - 1);
+    int orow = erc;                              // MODE 0 and 2: destination row
+    int e_ps = 0, e_ns = 0, e_tok = 0;           // MODE 1: parent's and own state slot, last token
+    int e_row0 = 0, e_len = 0, e_f0 = 0;         // MODE 2: first joiner row, frames, first frame
+    if (MODE == 1) {
+        e_ps = ep.pslot[erc];
+        e_ns = ep.slot[erc];
+        e_tok = ep.tok[erc];   // (unconditionally: a load behind a condition would be waited for at once)
+    } else if (MODE == 2) {
+        orow = out_row[erc];
+        e_row0 = jp.pair_row0[erc];
+        e_len = jp.pair_len[erc];
+        e_f0 = jp.pair_frame0[erc];
+    } else if (out_row) {
+        orow = out_row[erc];
+    }
     float bv[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) bv[i] = bias ? bias[min(ecol + i, N - 1)] : 0.f;
     asm volatile("" ::: "memory");
+    const int m_live = m_dev ? min(*m_dev, M) : M;     // (the same in every lane)
+    if (tile_m * GF_TILE >= m_live) return;            // no row of this tile exists
+    if (any_dev && *any_dev == 0) return;
 
     // Direct loads: one instruction fills 1 KB of LDS = 2 rows of 512 bytes, lane l the 16 bytes at row
     // l/32, position l%32; the position holds chunk (l%32) ^ (row & 15) of the K tile.  Rows and
@@ -129,7 +168,50 @@ k_gemm_f32_mfma(const float *__restrict__ A, const float *__restrict__ B, const 
     }
 #pragma unroll
     for (int i = 0; i < 4; ++i) v[i] += bv[i];
-    if (erow >= M) return;
+    if (erow >= m_live) return;
+    if (MODE == 1) {
+        const int H = ep.H, unit = ecol >> 2;
+        if (unit >= H || e_ns < 0) return;
+        // everything the update reads from memory is requested before any of it is used (from addresses
+        // that are valid whether it is needed or not)
+        const float cp = ep.c_par[(long)e_ps * H + unit];
+        const float hp = (ep.h_par_next ? ep.h_par_next : ep.c_par)[(long)e_ps * H + unit];
+        if (ep.emb_gates) {
+            const float4 e = *reinterpret_cast<const float4 *>(ep.emb_gates + (long)e_tok * 4 * H + ecol);
+            v[0] += e.x; v[1] += e.y; v[2] += e.z; v[3] += e.w;
+        }
+        const float cn = gf_sigmoid(v[1]) * cp + gf_sigmoid(v[0]) * tanhf(v[2]);
+        const float hn = gf_sigmoid(v[3]) * tanhf(cn);
+        ep.c_new[(long)e_ns * H + unit] = cn;
+        ep.h_new[(long)e_ns * H + unit] = hn;
+        float *out = static_cast<float *>(ep.out);
+        if (ep.h_par_next == nullptr) {
+            out[(long)erow * H + unit] = hn;
+        } else {
+            out[(long)erow * 2 * H + unit] = hn;
+            out[(long)erow * 2 * H + H + unit] = hp;
+        }
+        return;
+    }
+    if (MODE == 2) {
+        if (ecol >= N || orow < 0) return;   // (N is a multiple of 4)
+        const int fgs = jp.fgroups > 1 ? jp.fgroups : 1;   // this workgroup's frames: fgroup, fgroup + fgs, ...
+        const float *enc = static_cast<const float *>(jp.enc) + (long)e_f0 * N + ecol;
+        float *amat = static_cast<float *>(jp.amat) + (long)e_row0 * N + ecol;
+        for (int t0 = fgroup; t0 < e_len; t0 += 4 * fgs) {
+            float4 e[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) e[q] = *reinterpret_cast<const float4 *>(enc + (long)min(t0 + q * fgs, e_len - 1) * N);
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                if (t0 + q * fgs < e_len)
+                    *reinterpret_cast<float4 *>(amat + (long)(t0 + q * fgs) * N) =
+                        make_float4(tbs_joiner_act_f32(e[q].x + v[0], jp.act), tbs_joiner_act_f32(e[q].y + v[1], jp.act),
+                                    tbs_joiner_act_f32(e[q].z + v[2], jp.act), tbs_joiner_act_f32(e[q].w + v[3], jp.act));
+        }
+        if (fgroup == 0) *reinterpret_cast<float4 *>(C + (long)orow * ldc + ecol) = make_float4(v[0], v[1], v[2], v[3]);
+        return;
+    }
     float *dst = C + (long)orow * ldc + ecol;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
@@ -181,40 +263,75 @@ static int gf_stages() {
     static int stages = -1;
     if (stages < 0) {
         int found = 0;
-        for (int ns = 5; ns >= 2 && !found; --ns)
-            if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_f32_mfma), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    (int)(ns * GF_STAGE * sizeof(float))) == hipSuccess)
+        for (int ns = 5; ns >= 2 && !found; --ns) {
+            const int bytes = (int)(ns * GF_STAGE * sizeof(float));
+            if (hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_f32_mfma<0>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess &&
+                hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_f32_mfma<1>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess &&
+                hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_f32_mfma<2>),
+                                    hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess)
                 found = ns;
+        }
         (void)hipGetLastError();
         stages = found;
     }
     return stages;
 }
 
-// Stages of a launch: up to 256 tiles every CU has one workgroup and all K tiles (up to five) are asked
-// for at once; with more tiles two stages, so that two workgroups share a CU.
-static int gf_ns(long tiles, int K) {
+// Stages of a launch: up to 256 workgroups every CU has one and all K tiles (up to five) are asked for
+// at once; with more of them two stages, so that two workgroups share a CU.
+static int gf_ns(long wgs, int K) {
     const int kt = (K + GF_BK - 1) / GF_BK, ns_max = gf_stages();
-    if (tiles > 256 || kt < 2) return 2;
+    if (wgs > 256 || kt < 2) return 2;
     return kt < ns_max ? kt : ns_max;
 }
 
-static bool gf_aligned(const void *A, const void *B, int K) {
-    return K % 4 == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15) == 0 && gf_stages() >= 2;
+static long gf_tiles(int n) { return (n + GF_TILE - 1) / GF_TILE; }
+
+// can the MFMA kernel run the product, and has it at most max_tiles tiles?
+bool gemm_f32_fits(const void *A, const void *B, int M, int N, int K, int max_tiles) {
+    return K % 4 == 0 && ((reinterpret_cast<uintptr_t>(A) | reinterpret_cast<uintptr_t>(B)) & 15) == 0 && gf_stages() >= 2 &&
+           gf_tiles(M) * gf_tiles(N) <= max_tiles;
+}
+
+template <int MODE>
+static hipError_t gf_launch(hipStream_t st, const float *A, const float *B, const float *bias, float *C, int M, int N, int K,
+                            const int *out_row, long ldc, const LstmEp &ep, const JoinEp &jp, const int *m_dev,
+                            const int *any_dev, bool xcd_rows, int copies) {
+    const long tm = gf_tiles(M), tn = gf_tiles(N);
+    const int ns = gf_ns(tm * tn * copies, K);
+    const long grid = xcd_rows ? 8 * ((tm + 7) / 8) * tn : 8 * ((tm + 1) / 2) * ((tn + 3) / 4) * copies;
+    hipLaunchKernelGGL(k_gemm_f32_mfma<MODE>, dim3((unsigned)grid), dim3(256), ns * GF_STAGE * sizeof(float), st, A, B, bias,
+                       C, M, N, K, out_row, ldc, (int)tm, (int)tn, ns, ep, jp, m_dev, any_dev, xcd_rows ? 1 : 0);
+    return hipGetLastError();
 }
 
 hipError_t launch_gemm_f32(hipStream_t st, const float *A, const float *B, const float *bias, float *C, int M, int N,
-                           int K, const int *out_row, long ldc) {
+                           int K, const int *out_row, long ldc, const int *m_dev, bool xcd_rows) {
     if (M <= 0) return hipSuccess;
-    if (!gf_aligned(A, B, K)) {
-        hipLaunchKernelGGL(k_gemm_f32_any, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, A, B, bias, C, M, N, K,
-                           out_row, ldc);
-        return hipGetLastError();
-    }
-    const int tiles_m = (M + GF_TILE - 1) / GF_TILE, tiles_n = (N + GF_TILE - 1) / GF_TILE;
-    const int ns = gf_ns((long)tiles_m * tiles_n, K);
-    const long grid = 8L * ((tiles_m + 1) / 2) * ((tiles_n + 3) / 4);
-    hipLaunchKernelGGL(k_gemm_f32_mfma, dim3((unsigned)grid), dim3(256), ns * GF_STAGE * sizeof(float), st, A, B, bias, C, M,
-                       N, K, out_row, ldc, tiles_m, tiles_n, ns);
+    if (gemm_f32_fits(A, B, M, N, K, INT_MAX))
+        return gf_launch<0>(st, A, B, bias, C, M, N, K, out_row, ldc, LstmEp{}, JoinEp{}, m_dev, nullptr, xcd_rows, 1);
+    if (m_dev || xcd_rows) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_gemm_f32_any, dim3((N + 63) / 64, (M + 63) / 64), dim3(256), 0, st, A, B, bias, C, M, N, K,
+                       out_row, ldc);
     return hipGetLastError();
+}
+
+hipError_t launch_gemm_lstm_f32(hipStream_t st, const float *A, const float *Wp, const float *biasp, int M, int K,
+                                const LstmEp &ep, const int *m_dev, const int *any_dev) {
+    if (M <= 0) return hipSuccess;
+    if (!gemm_f32_fits(A, Wp, M, 4 * ep.H, K, INT_MAX)) return hipErrorInvalidValue;
+    return gf_launch<1>(st, A, Wp, biasp, nullptr, M, 4 * ep.H, K, nullptr, 0, ep, JoinEp{}, m_dev, any_dev, false, 1);
+}
+
+hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, const float *bias, float *C, int M, int N,
+                                int K, const int *out_row, long ldc, const JoinEp &jp, const int *m_dev,
+                                const int *any_dev) {
+    if (M <= 0) return hipSuccess;
+    if (!gemm_f32_fits(A, B, M, N, K, INT_MAX) || N % 4 || ldc % 4 || !out_row ||
+        (reinterpret_cast<uintptr_t>(jp.enc) & 15) || (reinterpret_cast<uintptr_t>(jp.amat) & 15))
+        return hipErrorInvalidValue;
+    return gf_launch<2>(st, A, B, bias, C, M, N, K, out_row, ldc, LstmEp{}, jp, m_dev, any_dev, false,
+                        jp.fgroups > 1 ? jp.fgroups : 1);
 }

@@ -514,11 +514,12 @@ k_gemm_small(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const f
             *reinterpret_cast<float4 *>(ep.h_new + (long)e_ns * H + j0) = make_float4(hn[0], hn[1], hn[2], hn[3]);
             const uint2 hb = make_uint2((unsigned)gs_bf16(hn[0]) | ((unsigned)gs_bf16(hn[1]) << 16),
                                         (unsigned)gs_bf16(hn[2]) | ((unsigned)gs_bf16(hn[3]) << 16));
+            bf16_t *out16 = static_cast<bf16_t *>(ep.out);
             if (ep.h_par_next == nullptr) {
-                *reinterpret_cast<uint2 *>(ep.out16 + (long)row * H + j0) = hb;
+                *reinterpret_cast<uint2 *>(out16 + (long)row * H + j0) = hb;
             } else {
-                *reinterpret_cast<uint2 *>(ep.out16 + (long)row * 2 * H + j0) = hb;
-                *reinterpret_cast<uint2 *>(ep.out16 + (long)row * 2 * H + H + j0) =
+                *reinterpret_cast<uint2 *>(out16 + (long)row * 2 * H + j0) = hb;
+                *reinterpret_cast<uint2 *>(out16 + (long)row * 2 * H + H + j0) =
                     make_uint2((unsigned)gs_bf16(hp.x) | ((unsigned)gs_bf16(hp.y) << 16),
                                (unsigned)gs_bf16(hp.z) | ((unsigned)gs_bf16(hp.w) << 16));
             }
@@ -655,7 +656,7 @@ k_gemm_small(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const f
             for (int q = 0; q < 4; ++q) {
                 // (a row that does not exist has no descriptor: frame 0 keeps the address valid)
                 const long fr = row < m_live ? (long)e_f0 + max(min(fgroup + q * fgs, len - 1), 0) : 0;
-                const uint4 *src = reinterpret_cast<const uint4 *>(jp.enc + fr * N + c0c);
+                const uint4 *src = reinterpret_cast<const uint4 *>(static_cast<const bf16_t *>(jp.enc) + fr * N + c0c);
                 ev0[q][0] = src[0];
                 ev0[q][1] = src[1];
             }
@@ -680,7 +681,7 @@ k_gemm_small(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const f
                         ev[q][1] = ev0[q][1];
                     } else {
                         const uint4 *src = reinterpret_cast<const uint4 *>(
-                            jp.enc + (long)(e_f0 + min(fgroup + (i0 + q) * fgs, len - 1)) * N + c0);
+                            static_cast<const bf16_t *>(jp.enc) + (long)(e_f0 + min(fgroup + (i0 + q) * fgs, len - 1)) * N + c0);
                         ev[q][0] = src[0];
                         ev[q][1] = src[1];
                     }
@@ -698,7 +699,7 @@ k_gemm_small(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const f
                             const float hi = tbs_joiner_act(__uint_as_float(w[i] & 0xFFFF0000u) + p[2 * i + 1], jp.act);
                             o[i] = (unsigned)gs_bf16(lo) | ((unsigned)gs_bf16(hi) << 16);
                         }
-                        uint4 *dstp = reinterpret_cast<uint4 *>(jp.amat + (long)(e_ps + t) * N + c0);
+                        uint4 *dstp = reinterpret_cast<uint4 *>(static_cast<bf16_t *>(jp.amat) + (long)(e_ps + t) * N + c0);
                         dstp[0] = make_uint4(o[0], o[1], o[2], o[3]);
                         dstp[1] = make_uint4(o[4], o[5], o[6], o[7]);
                     }

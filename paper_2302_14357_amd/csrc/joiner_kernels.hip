@@ -19,8 +19,6 @@ __device__ __forceinline__ bf16_t f2bf(float f) {
 }
 __device__ __forceinline__ float bf2f(bf16_t b) { return __uint_as_float(((unsigned)b) << 16); }
 
-__device__ __forceinline__ float joiner_act(float x, int act) { return act == 0 ? tanhf(x) : fmaxf(x, 0.f); }
-
 // ------------------------------------------------------------------ activation rows
 // a[r, :] = act(e[row_enc[r], :] + p[row_slot[r], :]), 8 elements per thread.
 // (rows_dev: when not null the row count is read from device memory and `rows` only sized the
@@ -131,12 +129,29 @@ __global__ void k_joiner_prep_fixed(int rows, int Dj, int S, int act, const bf16
     *reinterpret_cast<uint4 *>(amat + (long)r * Dj + c * 8) = make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-hipError_t launch_joiner_prep_fixed(hipStream_t st, const Dims &d, int act, const bf16_t *enc, const float *pool_p,
-                                    RowView rv, bf16_t *amat) {
+__global__ void k_joiner_prep_fixed_f32(int rows, int Dj, int S, int act, const float *__restrict__ enc,
+                                        const float *__restrict__ pool_p, const int *__restrict__ pair_len,
+                                        const int *__restrict__ pair_frame0, const int *__restrict__ pair_slot,
+                                        float *__restrict__ amat) {
+    const long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    if (idx >= (long)rows * Dj) return;
+    const int r = (int)(idx / Dj), c = (int)(idx - (long)r * Dj);
+    const int j = r / S, t = r - j * S;
+    if (t >= pair_len[j]) return;
+    amat[idx] = tbs_joiner_act_f32(enc[((long)pair_frame0[j] + t) * Dj + c] + pool_p[(long)pair_slot[j] * Dj + c], act);
+}
+
+hipError_t launch_joiner_prep_fixed(hipStream_t st, const Dims &d, int dtype, int act, const void *enc, const float *pool_p,
+                                    RowView rv, void *amat) {
     const int rows = d.U * d.N * d.S;
-    const long n = (long)rows * (d.Dj / 8);
-    hipLaunchKernelGGL(k_joiner_prep_fixed, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, rows, d.Dj, d.S, act,
-                       enc, pool_p, rv.pair_len, rv.pair_frame0, rv.pair_slot, amat);
+    const long n = (long)rows * (dtype == 1 ? d.Dj / 8 : d.Dj);
+    const dim3 grid((unsigned)((n + 255) / 256)), block(256);
+    if (dtype == 1)
+        hipLaunchKernelGGL(k_joiner_prep_fixed, grid, block, 0, st, rows, d.Dj, d.S, act, (const bf16_t *)enc, pool_p,
+                           rv.pair_len, rv.pair_frame0, rv.pair_slot, (bf16_t *)amat);
+    else
+        hipLaunchKernelGGL(k_joiner_prep_fixed_f32, grid, block, 0, st, rows, d.Dj, d.S, act, (const float *)enc, pool_p,
+                           rv.pair_len, rv.pair_frame0, rv.pair_slot, (float *)amat);
     return hipGetLastError();
 }
 
@@ -148,7 +163,7 @@ __global__ void k_joiner_prep_f32(int rows, int Dj, int act, const float *__rest
     long idx = (long)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= (long)rows * Dj) return;
     int r = (int)(idx / Dj), j = (int)(idx % Dj);
-    amat[idx] = joiner_act(enc[(long)row_enc[r] * Dj + j] + pool_p[(long)row_slot[r] * Dj + j], act);
+    amat[idx] = tbs_joiner_act_f32(enc[(long)row_enc[r] * Dj + j] + pool_p[(long)row_slot[r] * Dj + j], act);
 }
 
 hipError_t launch_joiner_prep(hipStream_t st, const Dims &d, int dtype, int act, int rows, const void *enc,

@@ -1,8 +1,8 @@
 // UpdatePredictorOutput of Algorithm 1: for every hypothesis created in this
 // round, run the prediction network one step from its parent's recurrent state
-// (Section 3.1: g(u) = predictor(y)).  Embedding lookup and state gather build
-// the LSTM input rows, the gate pre-activations are one GEMM against the
-// concatenated [W_ih | W_hh] matrix, the cell update is a pointwise kernel, and
+// (Section 3.1: g(u) = predictor(y)).  A state gather builds the LSTM input rows
+// (the embedding's share of the gates is a table), the gate pre-activations are
+// one GEMM against W_hh (later layers: the concatenated [W_ih | W_hh] matrix), the cell update is a pointwise kernel, and
 // the projection to the joint space is a GEMM that scatters into the state pool.
 #include "tbs_internal.h"
 
@@ -14,52 +14,27 @@ __device__ __forceinline__ bf16_t f2bf_p(float f) {
 
 __device__ __forceinline__ float sigmoidf_(float x) { return 1.f / (1.f + expf(-x)); }
 
-// xh[j, :] = [ embed[token_j, 0:E] | h_parent_j(layer 0)[0:H] ]
-// (Both gather kernels take the number of pairs from device memory and leave when launched
-// beyond it: the host enqueues them on the largest possible grid before it knows the count.)
-__global__ void k_pred_gather(Dims d, int dtype, AView A, RowView rv, const void *embed, const float *pool_h,
-                              void *xh) {
+// The embedding half of the first layer's gates is a table made once (embed * W_ih^T + b for every
+// token), so the first layer's input row of a new hypothesis is its parent's h.
+// (The kernel takes the number of pairs from device memory and leaves when launched beyond it: the
+// host enqueues it on the largest possible grid before it knows the count.)
+__global__ void k_pred_gather_h(Dims d, int dtype, RowView rv, const float *pool_h, void *xh) {
     int j = blockIdx.x;
     if (j >= rv.counts[TBS_CNT_PAIRS]) return;
-    int u = rv.pair_u[j], h = rv.pair_h[j];
-    long a = (long)u * d.N + h;
-    int tok = A.token[a];
-    long ps = A.pslot[a];
-    int W = d.E + d.H;
+    const float *src = pool_h + (long)rv.pair_pslot[j] * d.H;
     if (dtype == 1) {
-        const bf16_t *em = (const bf16_t *)embed + (long)tok * d.E;
-        bf16_t *x = (bf16_t *)xh + (long)j * W;
-        for (int i = threadIdx.x; i < d.E; i += blockDim.x) x[i] = em[i];
-        for (int i = threadIdx.x; i < d.H; i += blockDim.x) x[d.E + i] = f2bf_p(pool_h[ps * d.H + i]);
+        bf16_t *x = (bf16_t *)xh + (long)j * d.H;
+        for (int i = threadIdx.x; i < d.H; i += blockDim.x) x[i] = f2bf_p(src[i]);
     } else {
-        const float *em = (const float *)embed + (long)tok * d.E;
-        float *x = (float *)xh + (long)j * W;
-        for (int i = threadIdx.x; i < d.E; i += blockDim.x) x[i] = em[i];
-        for (int i = threadIdx.x; i < d.H; i += blockDim.x) x[d.E + i] = pool_h[ps * d.H + i];
+        float *x = (float *)xh + (long)j * d.H;
+        for (int i = threadIdx.x; i < d.H; i += blockDim.x) x[i] = src[i];
     }
 }
 
-hipError_t launch_pred_gather(hipStream_t st, const Dims &d, int dtype, int pairs, AView A, RowView rv,
-                              const void *embed, const float *pool_h, void *xh) {
+hipError_t launch_pred_gather_h(hipStream_t st, const Dims &d, int dtype, int pairs, RowView rv, const float *pool_h,
+                                void *xh) {
     if (pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pred_gather, dim3(pairs), dim3(256), 0, st, d, dtype, A, rv, embed, pool_h, xh);
-    return hipGetLastError();
-}
-
-// bf16 models: the embedding half of the first layer's gates is a table made once
-// (embed * W_ih^T + b for every token), so the per-round input is only the parent's h.
-__global__ void k_pred_gather_h(Dims d, AView A, RowView rv, const float *pool_h, bf16_t *xh) {
-    int j = blockIdx.x;
-    if (j >= rv.counts[TBS_CNT_PAIRS]) return;
-    long ps = rv.pair_pslot[j];
-    bf16_t *x = xh + (long)j * d.H;
-    for (int i = threadIdx.x; i < d.H; i += blockDim.x) x[i] = f2bf_p(pool_h[ps * d.H + i]);
-}
-
-hipError_t launch_pred_gather_h(hipStream_t st, const Dims &d, int pairs, AView A, RowView rv, const float *pool_h,
-                                bf16_t *xh) {
-    if (pairs <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_pred_gather_h, dim3(pairs), dim3(256), 0, st, d, A, rv, pool_h, xh);
+    hipLaunchKernelGGL(k_pred_gather_h, dim3(pairs), dim3(256), 0, st, d, dtype, rv, pool_h, xh);
     return hipGetLastError();
 }
 
@@ -70,7 +45,7 @@ __global__ void k_lstm_pointwise(Dims d, int dtype, int layer, AView A, RowView 
     int j = blockIdx.x;
     long ps = rv.pair_pslot[j], ns = rv.pair_slot[j];   // parent's and own state slot
     const float *g = gates + (long)j * 4 * d.H;
-    // first layer of bf16 models: the embedding half of the gates (and the bias) comes from the table
+    // first layer: the embedding half of the gates (and the bias) comes from the table
     const float *eg = emb_gates ? emb_gates + (long)rv.pair_tok[j] * 4 * d.H : nullptr;
     const float *c_par = pool_c + ((long)layer * pool_rows + ps) * d.H;
     float *c_new = pool_c + ((long)layer * pool_rows + ns) * d.H;

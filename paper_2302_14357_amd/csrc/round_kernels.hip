@@ -19,16 +19,27 @@ __device__ __forceinline__ unsigned round_bf16(float f) {   // nearest, ties to 
     v += 0x7FFFu + ((v >> 16) & 1u);
     return v >> 16;
 }
+// four values of an input row of the first LSTM layer, in the storage type of the model
+template <bool F32> struct RoundPiece { typedef uint2 type; };
+template <> struct RoundPiece<true> { typedef float4 type; };
+template <bool F32>
+__device__ __forceinline__ typename RoundPiece<F32>::type round_piece(const float4 &v) {
+    if constexpr (F32)
+        return v;
+    else
+        return make_uint2(round_bf16(v.x) | (round_bf16(v.y) << 16), round_bf16(v.z) | (round_bf16(v.w) << 16));
+}
 
 // S1NP > 0: segments of one frame (the standard breadth-first search, Eq. 1) in the slot layout.  The
 // joiner GEMM kept no logits: `logits` points at its row partials (see PartEp), tiles_n per row, and
 // the expansion of a hypothesis is the merge of its row's partials by one wave (TW = 1, SMAX = 1),
 // lane l taking tile l with a list of up to S1NP candidates in registers.
-template <int TW, int NV4, int SMAX, int S1NP>
+template <int TW, int NV4, int SMAX, int S1NP, bool F32>
 __global__ void __launch_bounds__(1024)
 k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, AView An, BView B, RowView rv,
         int2 *nodes, float *__restrict__ row_stats, float *__restrict__ delta_nb, FixedView fx, int tiles_n) {
     constexpr int TT = TW * 64;
+    typedef typename RoundPiece<F32>::type XP;
     typedef ExpandShared<SMAX, TW> TeamShared;
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     // LDS: the utterance's B list for the select step, one TeamShared per team, then what the teams
@@ -124,8 +135,8 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     in.dphi = s_dphi;
     in.lc = s_lc;
     in.slot_rows = fx.on;
-    // Slot layout: the first LSTM layer's input rows of the hypotheses this round makes are bf16 copies
-    // of their parents' h.  The parents are among this utterance's H hypotheses, so every team asks for
+    // Slot layout: the first LSTM layer's input rows of the hypotheses this round makes are copies (bf16
+    // models: rounded) of their parents' h.  The parents are among this utterance's H hypotheses, so every team asks for
     // its own hypothesis' h now, beside the logits, and at the end writes it out once for every new
     // hypothesis made from it: the end of the kernel then has no memory round trip of its own.
     constexpr int HP = (160 + TT - 1) / TT;   // 16-byte pieces per thread for h up to 640 wide
@@ -298,16 +309,14 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
         __syncthreads();
         const int total = s_out.total;
         if (live) {
-            uint2 hb[HP];
+            XP hb[HP];
 #pragma unroll
-            for (int q = 0; q < HP; ++q)
-                hb[q] = make_uint2((unsigned)round_bf16(hpar[q].x) | ((unsigned)round_bf16(hpar[q].y) << 16),
-                                   (unsigned)round_bf16(hpar[q].z) | ((unsigned)round_bf16(hpar[q].w) << 16));
+            for (int q = 0; q < HP; ++q) hb[q] = round_piece<F32>(hpar[q]);
             for (int i = 0; i < total; ++i)
                 if (s_out.parent[i] == team) {
 #pragma unroll
                     for (int q = 0; q < HP; ++q)
-                        if (tid + TT * q < H4) reinterpret_cast<uint2 *>(fx.xh)[(long)(u * N + i) * H4 + tid + TT * q] = hb[q];
+                        if (tid + TT * q < H4) static_cast<XP *>(fx.xh)[(long)(u * N + i) * H4 + tid + TT * q] = hb[q];
                 }
         }
     } else if (fx.on && fx.xh) {
@@ -317,9 +326,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
         for (int idx = (int)threadIdx.x; idx < total * H4; idx += (int)blockDim.x) {
             const int h = idx / H4, i = idx - h * H4;
             const float4 v = reinterpret_cast<const float4 *>(fx.pool_h + (long)s_out.pslot[h] * d.H)[i];
-            reinterpret_cast<uint2 *>(fx.xh)[(long)(u * N + h) * H4 + i] =
-                make_uint2((unsigned)round_bf16(v.x) | ((unsigned)round_bf16(v.y) << 16),
-                           (unsigned)round_bf16(v.z) | ((unsigned)round_bf16(v.w) << 16));
+            static_cast<XP *>(fx.xh)[(long)(u * N + h) * H4 + i] = round_piece<F32>(v);
         }
     }
 }
@@ -340,16 +347,16 @@ static int round_variant(const Dims &d) {
 
 bool round_fits(const Dims &d) { return round_variant(d) != 0; }
 
-template <int TW, int NV4, int SMAX, int S1NP = 0>
-static hipError_t round_launch(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
+template <int TW, int NV4, int SMAX, int S1NP, bool F32>
+static hipError_t round_launch_t(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
                                AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
-                               const FixedView &fx, int tiles_n = 0) {
+                               const FixedView &fx, int tiles_n) {
     const size_t b_list = ((size_t)d.BCAP * (sizeof(double) + sizeof(u64) + 3 * sizeof(int)) + 15) & ~(size_t)15;
     const size_t shm = b_list + (S1NP > 0 ? 0 : (size_t)d.N * sizeof(ExpandShared<SMAX, TW>)) +
                        sizeof(float) * ((size_t)d.N * SMAX + d.N + 2 * (size_t)d.N * d.N);
     static size_t attr_for = 0;
     if (shm > attr_for) {   // (static LDS of the select step comes on top: raise the limit to what the launch needs)
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_round<TW, NV4, SMAX, S1NP>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_round<TW, NV4, SMAX, S1NP, F32>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_for = shm;
@@ -358,9 +365,21 @@ static hipError_t round_launch(hipStream_t st, const Dims &d, int round, int dro
     const int threads = d.N * TW * 64 + (d.N * TW * 64 + 64 <= 1024 ? 64 : 0);
     // (with a row range per XCD: eight workgroups, one per XCD, for each place in the longest XCD's list)
     const int grid = fx.on && fx.xcd_rows > 0 ? 8 * (fx.xcd_rows / (d.N * d.S) + 1) : d.U;
-    hipLaunchKernelGGL((k_round<TW, NV4, SMAX, S1NP>), dim3(grid), dim3(threads), shm, st, d, round, drop, logits, A, An,
+    hipLaunchKernelGGL((k_round<TW, NV4, SMAX, S1NP, F32>), dim3(grid), dim3(threads), shm, st, d, round, drop, logits, A, An,
                        B, rv, nodes, row_stats, delta_nb, fx, tiles_n);
     return hipGetLastError();
+}
+
+template <int TW, int NV4, int SMAX, int S1NP = 0>
+static hipError_t round_launch(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
+                               AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
+                               const FixedView &fx, int tiles_n = 0) {
+    if constexpr (S1NP == 0)   // (only bf16 models run without logits)
+        if (fx.f32)
+            return round_launch_t<TW, NV4, SMAX, S1NP, true>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats,
+                                                             delta_nb, fx, tiles_n);
+    return round_launch_t<TW, NV4, SMAX, S1NP, false>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb,
+                                                      fx, tiles_n);
 }
 
 hipError_t launch_round(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A, AView An,

@@ -80,7 +80,7 @@ struct tbs_ctx {
     int *cand_tok;
 
     void *wcat[TBS_MAX_LAYERS];
-    float *emb_gates;   // bf16 models: [V, 4H] = embed * W_ih(layer 0)^T + b(layer 0)
+    float *emb_gates;   // [V, 4H] = embed * W_ih(layer 0)^T + b(layer 0)
     // gate-interleaved copies (row 4j+g = gate g of unit j) for the GEMM that updates the cell in its
     // epilogue: layer 0 [4H, H] (recurrent half), layers >= 1 [4H, 2H]; biases of layers >= 1; the table
     void *wperm[TBS_MAX_LAYERS];
@@ -419,18 +419,17 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->emb_gates_perm = nullptr;
     char *wih0p = nullptr;      // scratch of the table's construction
     float *b0p = nullptr;
-    if (cfg->dtype == 1) {
-        rc |= dev_alloc(c, &c->emb_gates, (size_t)d.V * 4 * d.H);
-        rc |= dev_alloc(c, &c->emb_gates_perm, (size_t)d.V * 4 * d.H);
-        rc |= dev_alloc(c, &wih0p, (size_t)4 * d.H * d.E * 2);
-        rc |= dev_alloc(c, &b0p, (size_t)4 * d.H);
-        for (int l = 0; l < d.L; ++l) {
-            char *p = nullptr;
-            rc |= dev_alloc(c, &p, (size_t)4 * d.H * (l == 0 ? d.H : 2 * d.H) * 2);
-            c->wperm[l] = p;
-            c->bperm[l] = nullptr;
-            if (l > 0) rc |= dev_alloc(c, &c->bperm[l], (size_t)4 * d.H);
-        }
+    const int eb = elem_bytes(c);
+    rc |= dev_alloc(c, &c->emb_gates, (size_t)d.V * 4 * d.H);
+    rc |= dev_alloc(c, &c->emb_gates_perm, (size_t)d.V * 4 * d.H);
+    rc |= dev_alloc(c, &wih0p, (size_t)4 * d.H * d.E * eb);
+    rc |= dev_alloc(c, &b0p, (size_t)4 * d.H);
+    for (int l = 0; l < d.L; ++l) {
+        char *p = nullptr;
+        rc |= dev_alloc(c, &p, (size_t)4 * d.H * (l == 0 ? d.H : 2 * d.H) * eb);
+        c->wperm[l] = p;
+        c->bperm[l] = nullptr;
+        if (l > 0) rc |= dev_alloc(c, &c->bperm[l], (size_t)4 * d.H);
     }
     rc |= dev_alloc(c, &c->res_count, U);
     rc |= dev_alloc(c, &c->res_len, UN);
@@ -485,25 +484,23 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
             return TBS_EHIP;
         }
     }
-    if (c->emb_gates) {
+    {
         // gate-interleaved copies: the table through the permuted input weights and bias of layer 0,
         // the recurrent (layers >= 1: concatenated) weights and biases directly
-        e = launch_permute_gate_rows(c->stream, w->w_ih[0], wih0p, d.H, (long)d.E * 2);
+        e = launch_permute_gate_rows(c->stream, w->w_ih[0], wih0p, d.H, (long)d.E * eb);
         if (e == hipSuccess) e = launch_permute_gate_rows(c->stream, w->b_lstm[0], b0p, d.H, 4);
         if (e == hipSuccess)
-            e = launch_gemm_bf16(c->stream, (const bf16_t *)w->embed, (const bf16_t *)wih0p, b0p, c->emb_gates_perm, d.V,
-                                 4 * d.H, d.E, nullptr, 4L * d.H);
+            e = gemm(c, w->embed, wih0p, b0p, c->emb_gates_perm, d.V, 4 * d.H, d.E, nullptr, 4L * d.H);
         for (int l = 0; l < d.L && e == hipSuccess; ++l) {
             if (l == 0) {
-                e = launch_permute_gate_rows(c->stream, w->w_hh[0], c->wperm[0], d.H, (long)d.H * 2);
+                e = launch_permute_gate_rows(c->stream, w->w_hh[0], c->wperm[0], d.H, (long)d.H * eb);
             } else {
-                e = launch_permute_gate_rows(c->stream, c->wcat[l], c->wperm[l], d.H, (long)2 * d.H * 2);
+                e = launch_permute_gate_rows(c->stream, c->wcat[l], c->wperm[l], d.H, (long)2 * d.H * eb);
                 if (e == hipSuccess) e = launch_permute_gate_rows(c->stream, w->b_lstm[l], c->bperm[l], d.H, 4);
             }
         }
         if (e == hipSuccess)
-            e = launch_gemm_bf16(c->stream, (const bf16_t *)w->embed, (const bf16_t *)w->w_ih[0], w->b_lstm[0],
-                             c->emb_gates, d.V, 4 * d.H, d.E, nullptr, 4L * d.H);
+            e = gemm(c, w->embed, w->w_ih[0], w->b_lstm[0], c->emb_gates, d.V, 4 * d.H, d.E, nullptr, 4L * d.H);
         if (e != hipSuccess) {
             c->last_hip = (int)e;
             tbs_free(c);
@@ -521,7 +518,28 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     return TBS_OK;
 }
 
-static bool predictor_all_fused(const tbs_ctx *c, int M, int max_tiles = GS_TILES);
+static bool predictor_all_fused(const tbs_ctx *c, int M, bool slots);
+
+// Can the small-problem GEMM of the model's type run the joiner over M rows, a gate GEMM with the cell
+// update, the projection with the joiner input rows?  slots: within the slot layout's limits, otherwise
+// those of the row lists.
+static bool joiner_small(const tbs_ctx *c, int M, bool slots) {
+    const Dims &d = c->cur;
+    if (c->cfg.dtype == 1) return gemm_small_fits(M, d.V, d.Dj, slots ? GS_TILES_FIXED : GS_TILES);
+    return gemm_f32_fits(c->amat, c->w.w_out, M, d.V, d.Dj, slots ? GF_TILES_FIXED : GF_TILES);
+}
+static bool lstm_small(const tbs_ctx *c, int M, int layer, bool slots) {
+    const Dims &d = c->cur;
+    const int K = layer == 0 ? d.H : 2 * d.H;
+    if (c->cfg.dtype == 1) return gemm_lstm_fits(M, d.H, K, slots ? GS_TILES_FIXED : GS_TILES);
+    return gemm_f32_fits(c->xh[0], c->wperm[layer], M, 4 * d.H, K, slots ? GF_TILES_FIXED : GF_TILES);
+}
+static bool proj_small(const tbs_ctx *c, int M, bool slots) {
+    const Dims &d = c->cur;
+    if (c->cfg.dtype == 1) return gemm_join_fits(M, d.Dj, d.H, slots ? GS_TILES_FIXED : GS_TILES);
+    return d.Dj % 4 == 0 && (reinterpret_cast<uintptr_t>(c->enc) & 15) == 0 &&
+           gemm_f32_fits(c->htop, c->w.w_proj, M, d.Dj, d.H, slots ? GF_TILES_FIXED : GF_TILES);
+}
 
 // The slot layout serves a batch when every kernel of a round has its small-shape form: the joiner
 // GEMM over all U*N*S rows in one wave of workgroups, the one-kernel expansion + select/merge, the
@@ -544,11 +562,10 @@ static bool one_frame_ok(const tbs_ctx *c) {
 
 static bool fixed_layout_ok(const tbs_ctx *c) {
     const Dims &d = c->cur;
-    if (c->cfg.dtype != 1 || (c->cfg.debug & (2 | 8 | 16 | 32 | 64 | 128 | 256)) || c->cfg.joiner_chunk_rows > 0)
-        return false;
+    if ((c->cfg.debug & (2 | 8 | 16 | 32 | 64 | 128 | 256)) || c->cfg.joiner_chunk_rows > 0) return false;
     if ((d.H & 3) || (long)d.max_nodes - 1 < (long)d.U) return false;
-    return (round_fits(d) || one_frame_ok(c)) && gemm_small_fits(d.U * d.N * d.S, d.V, d.Dj, GS_TILES_FIXED) &&
-           predictor_all_fused(c, d.U * d.N, GS_TILES_FIXED);
+    return (round_fits(d) || one_frame_ok(c)) && joiner_small(c, d.U * d.N * d.S, true) &&
+           predictor_all_fused(c, d.U * d.N, true);
 }
 
 // The joiner input rows act(e + p) of the current row lists (Section 3.1), as a kernel of its own.  rows =
@@ -814,7 +831,7 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
             HIPCHK(c, launch_select_merge(c->stream, c->cur, c->round, drop, c->logits, c->row_lc, c->dphi,
                                           c->cand_score, c->cand_tok, A, An, c->B, c->rv, c->nodes));
         // small batches: the row list kernel also writes the first LSTM layer's input rows
-        const bool fused_gather = c->emb_gates && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 &&
+        const bool fused_gather = c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 &&
                                   (long)c->cur.U * c->cur.N <= 1024;
         HIPCHK(c, launch_rowfill(c->stream, c->cur, c->seg, c->utt_off, An, c->rv, c->nodes, 1, c->h_counts_dev,
                                  ++c->seq, fused_gather ? c->pool_h : nullptr,
@@ -826,12 +843,7 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
     // waits for the counts and enqueues the rest, which would otherwise leave the GPU idle.
     if (!gathered) {
         ProfScope ps(c, TBS_K_PREDICTOR, 0);
-        if (c->emb_gates)
-            HIPCHK(c, launch_pred_gather_h(c->stream, c->cur, c->cur.U * c->cur.N, An, c->rv, c->pool_h,
-                                           (bf16_t *)c->xh[0]));
-        else
-            HIPCHK(c, launch_pred_gather(c->stream, c->cur, c->cfg.dtype, c->cur.U * c->cur.N, An, c->rv, c->w.embed,
-                                         c->pool_h, c->xh[0]));
+        HIPCHK(c, launch_pred_gather_h(c->stream, c->cur, c->cfg.dtype, c->cur.U * c->cur.N, c->rv, c->pool_h, c->xh[0]));
     }
     // Small batches: the LSTM layers of the predictor step go out now, sized for every hypothesis
     // the round could have created and reading the number it did create from device memory.  The
@@ -844,7 +856,7 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
     c->pred_ahead = 0;
     c->join_ahead = false;
     c->a_cur ^= 1;   // (the new hypotheses are the current group from here on)
-    if (!(c->cfg.debug & 64) && predictor_all_fused(c, c->cur.U * c->cur.N)) {
+    if (!(c->cfg.debug & 64) && predictor_all_fused(c, c->cur.U * c->cur.N, false)) {
         ProfScope ps(c, TBS_K_PREDICTOR, 0);
         const int rc = predictor_launch(c, c->cur.U * c->cur.N, c->rv.counts + TBS_CNT_PAIRS, 1);
         if (rc) return rc;
@@ -859,20 +871,18 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
 // UpdatePredictorOutput for the first M pairs (or, with m_dev, for as many as *m_dev says once the
 // kernels run: then M is the upper bound the launches are sized for, and only the forms that can
 // read their row count from device memory may be used: see predictor_all_fused).
-static bool predictor_all_fused(const tbs_ctx *c, int M, int max_tiles) {
-    const Dims &d = c->cur;
-    if (c->cfg.dtype != 1 || !c->emb_gates || (c->cfg.debug & (8 | 16))) return false;
-    for (int l = 0; l < d.L; ++l)
-        if (!gemm_lstm_fits(M, d.H, l == 0 ? d.H : 2 * d.H, max_tiles)) return false;
-    return gemm_join_fits(M, d.Dj, d.H, max_tiles);
+static bool predictor_all_fused(const tbs_ctx *c, int M, bool slots) {
+    if (c->cfg.debug & (8 | 16)) return false;
+    for (int l = 0; l < c->cur.L; ++l)
+        if (!lstm_small(c, M, l, slots)) return false;
+    return proj_small(c, M, slots);
 }
 
 static int64_t predictor_madds(const tbs_ctx *c, int64_t pairs) {   // multiply-adds of its GEMMs
     const Dims &d = c->cur;
     int64_t n = pairs * d.Dj * d.H;
     for (int l = 0; l < d.L; ++l) {
-        const int in_dim = l == 0 ? d.E : d.H;
-        n += pairs * 4 * d.H * ((l == 0 && c->emb_gates) ? d.H : in_dim + d.H);
+        n += pairs * 4 * d.H * (l == 0 ? d.H : 2 * d.H);
     }
     return n;
 }
@@ -882,9 +892,8 @@ static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const
     AView &A = c->A[c->a_cur];
     // (the input rows of the first layer were gathered behind select/merge)
     for (int l = 0; l < d.L && part != 2; ++l) {
-        int in_dim = l == 0 ? d.E : d.H;
-        const int K = (l == 0 && c->emb_gates) ? d.H : in_dim + d.H;
-        if (c->emb_gates && !(c->cfg.debug & 8) && gemm_lstm_fits(M, d.H, K, c->fixed ? GS_TILES_FIXED : GS_TILES)) {
+        const int K = l == 0 ? d.H : 2 * d.H;
+        if (!(c->cfg.debug & 8) && lstm_small(c, M, l, c->fixed)) {
             // small problem: the cell update runs in the epilogue of the gate GEMM
             const bool last = l + 1 == d.L;
             LstmEp ep;
@@ -896,42 +905,51 @@ static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const
             ep.c_new = c->pool_c + (size_t)l * c->pool_rows * d.H;
             ep.h_new = c->pool_h + (size_t)l * c->pool_rows * d.H;
             ep.h_par_next = last ? nullptr : c->pool_h + (size_t)(l + 1) * c->pool_rows * d.H;
-            ep.out16 = (bf16_t *)(last ? c->htop : c->xh[(l + 1) & 1]);
+            ep.out = last ? c->htop : c->xh[(l + 1) & 1];
             ep.H = d.H;
             ProfScope pg(c, TBS_K_GEMM, (m_dev || any_dev) ? 0 : (int64_t)M * 4 * d.H * K);
-            HIPCHK(c, launch_gemm_lstm(c->stream, (const bf16_t *)c->xh[l & 1], (const bf16_t *)c->wperm[l], c->bperm[l],
-                                       M, K, ep, m_dev, any_dev));
+            if (c->cfg.dtype == 1)
+                HIPCHK(c, launch_gemm_lstm(c->stream, (const bf16_t *)c->xh[l & 1], (const bf16_t *)c->wperm[l],
+                                           c->bperm[l], M, K, ep, m_dev, any_dev));
+            else
+                HIPCHK(c, launch_gemm_lstm_f32(c->stream, (const float *)c->xh[l & 1], (const float *)c->wperm[l],
+                                               c->bperm[l], M, K, ep, m_dev, any_dev));
             continue;
         }
         if (m_dev || any_dev) return TBS_ESTATE;   // (predictor_all_fused was not asked)
-        if (l == 0 && c->emb_gates)
+        if (l == 0)
             HIPCHK(c, gemm(c, c->xh[0], c->w.w_hh[0], nullptr, c->gates, M, 4 * d.H, d.H, nullptr, 4L * d.H));
         else
-            HIPCHK(c, gemm(c, c->xh[l & 1], c->wcat[l], c->w.b_lstm[l], c->gates, M, 4 * d.H, in_dim + d.H, nullptr,
+            HIPCHK(c, gemm(c, c->xh[l & 1], c->wcat[l], c->w.b_lstm[l], c->gates, M, 4 * d.H, K, nullptr,
                            4L * d.H));
         HIPCHK(c, launch_lstm_pointwise(c->stream, d, c->cfg.dtype, M, l, A, c->rv, c->gates, c->pool_h, c->pool_c,
                                         c->pool_rows, c->xh[(l + 1) & 1], c->htop, l == 0 ? c->emb_gates : nullptr));
     }
     if (part == 1) return TBS_OK;
-    if (c->cfg.dtype == 1 && !(c->cfg.debug & 16) && gemm_join_fits(M, d.Dj, d.H, c->fixed ? GS_TILES_FIXED : GS_TILES)) {
+    if (!(c->cfg.debug & 16) && proj_small(c, M, c->fixed)) {
         // small problem: the projection's epilogue also makes the joiner input rows of the coming
         // round (every row of that round belongs to one of these pairs)
         JoinEp jp;
         jp.pair_row0 = c->rv.pair_row0;
         jp.pair_len = c->rv.pair_len;
         jp.pair_frame0 = c->rv.pair_frame0;
-        jp.enc = (const bf16_t *)c->enc;
-        jp.amat = (bf16_t *)c->amat;
+        jp.enc = c->enc;
+        jp.amat = c->amat;
         jp.act = c->cfg.act;
         // (a small problem leaves most CUs idle: as many workgroups per tile as the segment has frames,
         // each forming the joiner input rows of one frame, while they fit one wave of workgroups)
         {
-            const long tiles = (long)((M + 63) / 64) * ((d.Dj + 63) / 64);
+            const int te = c->cfg.dtype == 1 ? 64 : GF_TILE;
+            const long tiles = (long)((M + te - 1) / te) * ((d.Dj + te - 1) / te);
             jp.fgroups = (c->cfg.debug & 2048) ? 1 : (int)std::max(1L, std::min((long)d.S, 256 / std::max(tiles, 1L)));
         }
         ProfScope pg(c, TBS_K_GEMM, (m_dev || any_dev) ? 0 : (int64_t)M * d.Dj * d.H);
-        HIPCHK(c, launch_gemm_join(c->stream, (const bf16_t *)c->htop, (const bf16_t *)c->w.w_proj, c->w.b_proj,
-                                   c->pool_p, M, d.Dj, d.H, c->rv.pair_slot, d.Dj, jp, m_dev, any_dev));
+        if (c->cfg.dtype == 1)
+            HIPCHK(c, launch_gemm_join(c->stream, (const bf16_t *)c->htop, (const bf16_t *)c->w.w_proj, c->w.b_proj,
+                                       c->pool_p, M, d.Dj, d.H, c->rv.pair_slot, d.Dj, jp, m_dev, any_dev));
+        else
+            HIPCHK(c, launch_gemm_join_f32(c->stream, (const float *)c->htop, (const float *)c->w.w_proj, c->w.b_proj,
+                                           c->pool_p, M, d.Dj, d.H, c->rv.pair_slot, d.Dj, jp, m_dev, any_dev));
         c->prep_ahead = true;
     } else {
         if (m_dev || any_dev) return TBS_ESTATE;
@@ -996,8 +1014,19 @@ int tbs_result(tbs_ctx *c, int32_t *tokens, int32_t *lens, double *logscores, in
 // want the counts at launch).
 static bool segment_ahead_ok(const tbs_ctx *c) {
     const Dims &d = c->cur;
-    return !(c->cfg.debug & 64) && c->prof_kernel < 0 && c->cfg.dtype == 1 && d.R >= 1 &&
-           gemm_small_fits(d.U * d.N * d.S, d.V, d.Dj) && predictor_all_fused(c, d.U * d.N);
+    return !(c->cfg.debug & 64) && c->prof_kernel < 0 && d.R >= 1 && joiner_small(c, d.U * d.N * d.S, false) &&
+           predictor_all_fused(c, d.U * d.N, false);
+}
+
+// the joiner GEMM of a call whose row count is known on the device only
+static hipError_t joiner_ahead(tbs_ctx *c, const int *rows_dev) {
+    const Dims &d = c->cur;
+    const int M = d.U * d.N * d.S;
+    if (c->cfg.dtype == 1)
+        return launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out, c->logits, M, d.V,
+                                d.Dj, nullptr, d.V, 0, rows_dev);
+    return launch_gemm_f32(c->stream, (const float *)c->amat, (const float *)c->w.w_out, c->w.b_out, c->logits, M, d.V, d.Dj,
+                           nullptr, d.V, rows_dev);
 }
 
 static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
@@ -1014,8 +1043,7 @@ static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
     HIPCHK(c, launch_rowfill(c->stream, d, c->seg, c->utt_off, A, c->rv, c->nodes, 0, c->h_counts_dev, ++c->seq));
     HIPCHK(c, joiner_rows(c, d.U * d.N * d.S, rows_dev));
     // first round: joiner, expansion, select/merge, row list, predictor step
-    HIPCHK(c, launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out, c->logits,
-                               d.U * d.N * d.S, d.V, d.Dj, nullptr, d.V, 0, rows_dev));
+    HIPCHK(c, joiner_ahead(c, rows_dev));
     c->n_launches += 1;
     const int drop = c->cfg.max_rounds_per_segment > 0 && c->round >= c->cfg.max_rounds_per_segment;
     if (round_fused_ok(c)) {
@@ -1027,11 +1055,11 @@ static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
         HIPCHK(c, launch_select_merge(c->stream, d, c->round, drop, c->logits, c->row_lc, c->dphi, c->cand_score,
                                       c->cand_tok, A, An, c->B, c->rv, c->nodes));
     }
-    const bool fused_gather = !(c->cfg.debug & 32) && (d.H & 3) == 0 && (long)d.U * d.N <= 1024;
+    const bool fused_gather = c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (d.H & 3) == 0 && (long)d.U * d.N <= 1024;
     HIPCHK(c, launch_rowfill(c->stream, d, c->seg, c->utt_off, An, c->rv, c->nodes, 1, c->h_counts_dev, ++c->seq,
                              fused_gather ? c->pool_h : nullptr, fused_gather ? (bf16_t *)c->xh[0] : nullptr));
     if (!fused_gather)
-        HIPCHK(c, launch_pred_gather_h(c->stream, d, d.U * d.N, An, c->rv, c->pool_h, (bf16_t *)c->xh[0]));
+        HIPCHK(c, launch_pred_gather_h(c->stream, d, c->cfg.dtype, d.U * d.N, c->rv, c->pool_h, c->xh[0]));
     c->a_cur ^= 1;
     const int rc = predictor_launch(c, d.U * d.N, pairs_dev);
     if (rc) return rc;
@@ -1039,8 +1067,7 @@ static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
     c->pred_ahead = 2;
     c->join_ahead = false;
     if (c->round + 1 <= d.R) {   // and the joiner GEMM of the second round
-        HIPCHK(c, launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out, c->logits,
-                                   d.U * d.N * d.S, d.V, d.Dj, nullptr, d.V, 0, rows_dev));
+        HIPCHK(c, joiner_ahead(c, rows_dev));
         c->join_ahead = true;
     }
     HIPCHK(c, wait_counts(c));
@@ -1121,7 +1148,8 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
     fx.live_sum = c->live_sum;
     fx.host_live = c->h_live_dev;
     fx.pool_h = c->pool_h;
-    fx.xh = (bf16_t *)c->xh[0];
+    fx.xh = c->xh[0];
+    fx.f32 = c->cfg.dtype == 0;
     // A = ChooseNBest(B), B = [], the first round's pair descriptors and joiner input rows
     const int head_seq = fx.seq = ++c->seq;
     // (the head kernel also forms the first round's joiner input rows where it moves p in 16-byte pieces
@@ -1129,16 +1157,15 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
     // or where debug bit 10 asks for it)
     const bool rows_in_head = ((d.Dj | d.H) & 3) == 0 && d.Dj <= 1024 && d.S <= TBS_FIXED_SMAX &&
                               !(c->cfg.debug & 1024);
-    fx.amat = rows_in_head ? (bf16_t *)c->amat : nullptr;
-    fx.enc = (const bf16_t *)c->enc;
+    fx.amat = rows_in_head ? c->amat : nullptr;
+    fx.enc = c->enc;
     fx.act = c->cfg.act;
     fx.parts = d.U > 256 ? 1 : (d.U > 128 ? 2 : 4);   // (a small batch leaves most CUs idle: several workgroups share an utterance)
     HIPCHK(c, launch_segment_begin(c->stream, d, c->seg, c->utt_T, c->B, c->A[c->a_cur], c->rv, c->pool_p, c->pool_h,
                                    c->pool_c, c->pool_rows, &fx));
     if (!rows_in_head) {
         ProfScope ps(c, TBS_K_PREP, 0);
-        HIPCHK(c, launch_joiner_prep_fixed(c->stream, d, c->cfg.act, (const bf16_t *)c->enc, c->pool_p, c->rv,
-                                           (bf16_t *)c->amat));
+        HIPCHK(c, launch_joiner_prep_fixed(c->stream, d, c->cfg.dtype, c->cfg.act, c->enc, c->pool_p, c->rv, c->amat));
     }
     fx.amat = nullptr;
     const int M = d.U * d.N * d.S;
@@ -1146,10 +1173,11 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
     // utterance's rows, where every XCD gets rows, its range holds whole utterances and its tiles fit
     // its 32 CUs, two workgroups each)
     {
-        const int rpx = gemm_small_xcd_rows(M);
-        const long wgs = (long)(rpx / 64) * ((d.V + 63) / 64);
-        const long tiles = (long)((M + 63) / 64) * ((d.V + 63) / 64);   // (more than 256: two workgroups share a CU)
-        fx.xcd_rows = (!(c->cfg.debug & 4096) && (M + 63) / 64 >= 8 && d.N * d.S <= rpx && wgs <= (tiles > 256 ? 64 : 32)) ? rpx : 0;
+        const int te = c->cfg.dtype == 1 ? 64 : GF_TILE;
+        const int rpx = gemm_small_xcd_rows(M, te);
+        const long tn = (d.V + te - 1) / te, wgs = (long)(rpx / te) * tn;
+        const long tiles = (long)((M + te - 1) / te) * tn;   // (more than 256: two workgroups share a CU)
+        fx.xcd_rows = (!(c->cfg.debug & 4096) && (M + te - 1) / te >= 8 && d.N * d.S <= rpx && wgs <= (tiles > 256 ? 64 : 32)) ? rpx : 0;
     }
     // (S = 1 without logits: the GEMM's partials go out per 16-column piece where the round kernel's wave
     // has a lane for each of them, which spares the GEMM the merge of a tile's four)
@@ -1167,9 +1195,12 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
                 const PartEp pe{c->part, d.N, d.blank, s1_pieces, fx.xcd_rows};
                 HIPCHK(c, launch_gemm_part(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out, M, d.V,
                                            d.Dj, pe));
-            } else {
+            } else if (c->cfg.dtype == 1) {
                 HIPCHK(c, launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out,
                                            c->logits, M, d.V, d.Dj, nullptr, d.V, 4, nullptr, fx.xcd_rows != 0));
+            } else {
+                HIPCHK(c, launch_gemm_f32(c->stream, (const float *)c->amat, (const float *)c->w.w_out, c->w.b_out,
+                                          c->logits, M, d.V, d.Dj, nullptr, d.V, nullptr, fx.xcd_rows != 0));
             }
         }
         AView &A = c->A[c->a_cur], &An = c->A[c->a_cur ^ 1];

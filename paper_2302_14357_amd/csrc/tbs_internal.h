@@ -76,11 +76,12 @@ struct FixedView {
     int *host_live;       // pinned [2, U], half seq & 1: (seq << 8) | (trie full << 6) | hypotheses made
     int seq;
     const float *pool_h;  // first LSTM layer's h by state slot, and where the new hypotheses' input rows go:
-    bf16_t *xh;           // xh[j, :] = bf16(h of the parent of pair j)   (null: not wanted)
+    void *xh;             // xh[j, :] = h of the parent of pair j, as bf16 or fp32 by `f32`   (null: not wanted)
+    int f32;              // fp32 model: xh, amat and enc hold floats, otherwise bf16
     // head of a segment only: where the joiner input rows of the survivors go (null: a kernel of its own
     // makes them), the projected encoder frames and the joiner activation
-    bf16_t *amat;
-    const bf16_t *enc;
+    void *amat;
+    const void *enc;
     int act;
     int parts;            // workgroups per utterance of the kernel that starts a segment (0 = 1)
     int xcd_rows;         // round kernel: not 0 = joiner rows per XCD (workgroup b runs on XCD b % 8 and takes an
@@ -112,6 +113,9 @@ __device__ __forceinline__ float tbs_joiner_act(float x, int act) {
     return 1.f - 2.f * __builtin_amdgcn_rcpf(t + 1.f);
 }
 
+// ... and of fp32 models
+__device__ __forceinline__ float tbs_joiner_act_f32(float x, int act) { return act == 0 ? tanhf(x) : fmaxf(x, 0.f); }
+
 // LSTM cell update done in the epilogue of the gate GEMM (small problems): the weight rows are
 // stored gate-interleaved (row 4j+g = gate g of hidden unit j, gate order i, f, g, o), so a 64-wide
 // output tile holds all four gates of 16 units.
@@ -121,7 +125,8 @@ struct LstmEp {
     const float *c_par;              // cell states of this layer, indexed by slot
     float *c_new, *h_new;            // the same pools, written at the row's own slot
     const float *h_par_next;         // hidden states of the next layer (null for the last layer)
-    bf16_t *out16;                   // last layer: [rows, H] top hidden state; else [rows, 2H] next layer's input
+    void *out;                       // bf16 or fp32 by the model: last layer [rows, H] top hidden state, else
+                                     // [rows, 2H] next layer's input
     int H;
 };
 
@@ -130,8 +135,8 @@ struct LstmEp {
 // the joiner rows pair_row0[r] ..: amat[row, :] = act(enc[frame, :] + projection).
 struct JoinEp {
     const int *pair_row0, *pair_len, *pair_frame0;
-    const bf16_t *enc;   // [frames, Dj]
-    bf16_t *amat;        // [rows, Dj]
+    const void *enc;     // [frames, Dj], bf16 or fp32 by the model
+    void *amat;          // [rows, Dj], likewise
     int act;             // 0 tanh, 1 relu
     int fgroups;         // workgroups per tile (0 = 1): each computes the tile and forms the joiner input rows of
                          // the frames t = its number, + fgroups, ...; the first also stores the projection
@@ -165,8 +170,8 @@ hipError_t launch_segment_begin(hipStream_t st, const Dims &d, int seg, const in
 // the same by pairs (bf16; the pair count is read from the row lists' counts in device memory)
 hipError_t launch_joiner_prep_pairs(hipStream_t st, const Dims &d, int act, const bf16_t *enc, const float *pool_p,
                                     RowView rv, bf16_t *amat);
-hipError_t launch_joiner_prep_fixed(hipStream_t st, const Dims &d, int act, const bf16_t *enc, const float *pool_p,
-                                    RowView rv, bf16_t *amat);
+hipError_t launch_joiner_prep_fixed(hipStream_t st, const Dims &d, int dtype, int act, const void *enc, const float *pool_p,
+                                    RowView rv, void *amat);
 // gather_h / gather_xh not null: also writes gather_xh[pair, :] = bf16(gather_h[parent slot, :]) (H wide)
 hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt_off, AView A, RowView rv,
                           int2 *nodes, int assign_nodes, int *host_counts, int seq, const float *gather_h = nullptr,
@@ -175,15 +180,29 @@ hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt
 hipError_t launch_joiner_prep(hipStream_t st, const Dims &d, int dtype, int act, int rows, const void *enc,
                               const float *pool_p, RowView rv, void *amat, const int *rows_dev = nullptr,
                               const int *row_begin = nullptr);
+// m_dev, xcd_rows as for launch_gemm_bf16 below
 hipError_t launch_gemm_f32(hipStream_t st, const float *A, const float *B, const float *bias, float *C, int M, int N,
-                           int K, const int *out_row, long ldc);
+                           int K, const int *out_row, long ldc, const int *m_dev = nullptr, bool xcd_rows = false);
+// the fp32 forms of the fused GEMMs below (operands of which every row starts at a 16-byte boundary)
+bool gemm_f32_fits(const void *A, const void *B, int M, int N, int K, int max_tiles);
+hipError_t launch_gemm_lstm_f32(hipStream_t st, const float *A, const float *Wp, const float *biasp, int M, int K,
+                                const LstmEp &ep, const int *m_dev, const int *any_dev);
+hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, const float *bias, float *C, int M, int N,
+                                int K, const int *out_row, long ldc, const JoinEp &jp, const int *m_dev,
+                                const int *any_dev);
+#define GF_TILE 32            // fp32: edge of a tile
+#define GF_TILES 1024         // fp32: tiles of 32 x 32 up to which the fused forms serve the row lists
+#define GF_TILES_FIXED 1280   // ... and the slot layout: measured at N = 5 on the Librispeech-like widths (most tiles of
+                              // a round's products: ms per decode with slots / row lists) 640: 12.5 / 16.0, 800: 10.6 /
+                              // 11.4, 960: 12.5 / 13.5, 1200: 20.8 / 22.1, 1440: 15.4 / 15.2, 1600: 13.9 / 13.4 and
+                              // 25.5 / 24.5, 1920: 18.8 / 17.3
 // m_dev (launch_gemm_bf16 only where gemm_small_fits; the fused forms always): the launch is enqueued
 // before the host knows the row count; M is an upper bound and the count is read from *m_dev
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel = 0, const int *m_dev = nullptr,
                             bool xcd_rows = false);
 // rows per XCD when k_gemm_small gives every XCD a row range of its own (PartEp::xcd_rows)
-inline int gemm_small_xcd_rows(int M) { return 64 * ((((M + 63) / 64) + 7) / 8); }
+inline int gemm_small_xcd_rows(int M, int tile) { return tile * ((((M + tile - 1) / tile) + 7) / 8); }
 hipError_t launch_gemm_bf16_rows(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C,
                                  int m_max, int N, int K, long ldc, const int *m_begin, const int *m_end);
 #define GS_TILES 320          // tiles of 64 x 64 up to which the small-problem GEMM kernel is chosen by size
@@ -223,10 +242,8 @@ bool round_s1_fits(const Dims &d);
 // (tiles_n: partials per row, in column order: the vocabulary's 64-column tiles, or their 16-column pieces)
 hipError_t launch_round_s1(hipStream_t st, const Dims &d, int round, int drop, const float *part, int tiles_n, AView A,
                            AView An, BView B, RowView rv, int2 *nodes, const FixedView *fx);
-hipError_t launch_pred_gather(hipStream_t st, const Dims &d, int dtype, int pairs, AView A, RowView rv,
-                              const void *embed, const float *pool_h, void *xh);
-hipError_t launch_pred_gather_h(hipStream_t st, const Dims &d, int pairs, AView A, RowView rv, const float *pool_h,
-                                bf16_t *xh);
+hipError_t launch_pred_gather_h(hipStream_t st, const Dims &d, int dtype, int pairs, RowView rv, const float *pool_h,
+                                void *xh);
 hipError_t launch_lstm_pointwise(hipStream_t st, const Dims &d, int dtype, int pairs, int layer, AView A, RowView rv,
                                  const float *gates, float *pool_h, float *pool_c, long pool_rows, void *xh_next,
                                  void *htop, const float *emb_gates);

@@ -330,6 +330,21 @@ def test_decode_peaked_model_long_hypotheses(dtype, N, S, cap, bb, min_len):
     assert info["max_len_checked"] >= min_len, info
 
 
+@pytest.mark.parametrize("debug", [0, 8, 16, 1024, 2048])
+@pytest.mark.parametrize("d,hidden,layers,V,U,N,S", [(64, 64, 1, 32, 1, 2, 3), (132, 36, 2, 100, 5, 5, 5), (1028, 68, 1, 64, 3, 3, 2),
+                                                     (64, 128, 3, 1024, 9, 16, 1)])
+def test_decode_fp32_fixed_places(d, hidden, layers, V, U, N, S, debug):
+    """fp32 models in the slot layout and, by debug bits, with row lists (8), with the cell update and the
+    joiner input rows as kernels of their own (16), the first round's rows as a kernel of its own (1024; it
+    serves d > 1024 in any case), one workgroup per projection tile (2048): same arithmetic, same oracle."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=U, vocab=V, d=d, hidden=hidden, layers=layers), dtype="f32")
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=np.arange(U) * 2 + 3)
+    _, st = _gpu_decode(shape, model, offsets, enc, N, S, debug=debug)
+    assert st["path"]["fixed_places"] == (debug not in (8, 16))
+    _check_decode(shape, model, offsets, enc, N, S, debug=debug)
+
+
 def test_decode_peaked_model_librispeech_widths():
     """The same at the headline widths (Dj=512, V=1024, LSTM 640, N=5, S=3)."""
     import dataclasses
