@@ -159,9 +159,9 @@ __device__ __forceinline__ void expand_pair_info_at(ExpandPair<SMAX> &pi, int pa
     cfloat_p dold = (cfloat_p)A.dhat + ((long)u * d.N + h) * d.S;
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) pi.dold[t] = t < pi.sp ? dold[t] : -INFINITY;
-    cfloat_p lb = (cfloat_p)logits + (long)pi.row0 * d.V + d.blank;
+    cfloat_p lb = (cfloat_p)logits + (long)pi.row0 * d.Vl + d.blank;
 #pragma unroll
-    for (int t = 0; t < SMAX; ++t) pi.lblank[t] = t < pi.sp ? lb[(long)t * d.V] : 0.f;
+    for (int t = 0; t < SMAX; ++t) pi.lblank[t] = t < pi.sp ? lb[(long)t * d.Vl] : 0.f;
 }
 
 template <int SMAX>
@@ -174,9 +174,9 @@ __device__ __forceinline__ void expand_pair_info(ExpandPair<SMAX> &pi, int pair,
     cfloat_p dold = (cfloat_p)A.dhat + ((long)u * d.N + h) * d.S;
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) pi.dold[t] = t < pi.sp ? dold[t] : -INFINITY;
-    cfloat_p lb = (cfloat_p)logits + (long)pi.row0 * d.V + d.blank;
+    cfloat_p lb = (cfloat_p)logits + (long)pi.row0 * d.Vl + d.blank;
 #pragma unroll
-    for (int t = 0; t < SMAX; ++t) pi.lblank[t] = t < pi.sp ? lb[(long)t * d.V] : 0.f;
+    for (int t = 0; t < SMAX; ++t) pi.lblank[t] = t < pi.sp ? lb[(long)t * d.Vl] : 0.f;
 }
 
 // One pass over memory: this thread's columns of every row of the pair.  Every request is made
@@ -184,14 +184,14 @@ __device__ __forceinline__ void expand_pair_info(ExpandPair<SMAX> &pi, int pair,
 // expand_pair discards them), so that the loads are straight-line code with scalar row bases.
 template <int NV4, int SMAX, int TT>
 __device__ __forceinline__ void expand_load(float (&e)[SMAX][NV4 * 4], const float *__restrict__ logits, int row0,
-                                            int sp, int V, int tid) {
-    const int V4 = V >> 2;
+                                            int sp, int Vl, int tid) {
+    const int V4 = Vl >> 2;
     unsigned off[NV4];   // byte offsets within a row
 #pragma unroll
     for (int q = 0; q < NV4; ++q) off[q] = 16u * (unsigned)min(tid + TT * q, V4 - 1);
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) {
-        const char *row = reinterpret_cast<const char *>(logits + ((long)row0 + max(min(t, sp - 1), 0)) * V);
+        const char *row = reinterpret_cast<const char *>(logits + ((long)row0 + max(min(t, sp - 1), 0)) * Vl);
 #pragma unroll
         for (int q = 0; q < NV4; ++q) {
             const float4 x = *reinterpret_cast<const float4 *>(row + off[q]);
@@ -236,10 +236,10 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
     constexpr int NC = NV4 * 4;  // columns per thread
     constexpr int TW = TT / 64;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int V = d.V, V4 = V >> 2;
+    const int V = d.V, V4 = d.Vl >> 2;
     // Rows past S' and columns past V hold copies of real logits (see expand_load): copies leave a
     // row maximum unchanged, the row sums skip the copied columns, the copied rows get coefficient
-    // zero and the copied columns score zero below.
+    // zero and the copied columns score zero below.  (The columns between V and Vl hold -inf: e = 0.)
     float mrow[SMAX];
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) {
@@ -353,9 +353,9 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
 #pragma unroll
         for (int q = 0; q < NV4; ++q) {
             const int i4 = t2 + TT * q;
-            if (i4 < V4)
-                reinterpret_cast<float4 *>(delta_nb + (long)pi.pair * V)[i4] =
-                    make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (4 * i4 + c < V) delta_nb[(long)pi.pair * V + 4 * i4 + c] = v[4 * q + c];
         }
     }
     // ---- candidates of this wave: every score >= tau, where tau is a lower bound of the wave's

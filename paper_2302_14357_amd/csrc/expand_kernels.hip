@@ -17,13 +17,12 @@
 
 #include "expand_device.h"
 
-template <bool VEC4>
 __global__ void __launch_bounds__(EXP_THREADS)
 k_expand(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *__restrict__ row_lc,
          float *__restrict__ dphi, float *__restrict__ cand_score, int *__restrict__ cand_tok,
          float *__restrict__ row_stats, float *__restrict__ delta_nb, const int *__restrict__ pairs_dev,
          int pair_base) {
-    extern __shared__ float s_dnb[];  // [V]
+    extern __shared__ __attribute__((aligned(16))) float s_dnb[];  // [Vl]
     __shared__ float s_m[TBS_MAX_SEG], s_z[TBS_MAX_SEG], s_b[TBS_MAX_SEG], s_lc[TBS_MAX_SEG];
     __shared__ float s_rv[EXP_WAVES];
     __shared__ int s_rk[EXP_WAVES];
@@ -31,29 +30,19 @@ k_expand(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *_
     if (pairs_dev && pair >= *pairs_dev) return;   // (enqueued on an upper-bound grid, see k_expand_reg)
     const int u = rv.pair_u[pair], h = rv.pair_h[pair];
     const int row0 = rv.pair_row0[pair], sp = rv.pair_len[pair];
-    const int V = d.V;
-    const float *L = logits + (long)row0 * V;
+    const int V = d.V, Vl = d.Vl;   // (the columns past V hold -inf: they add nothing and score 0)
+    const float *L = logits + (long)row0 * Vl;
 
     // ---- softmax statistics of each row: one wave per row, no barriers inside
     for (int t = wave; t < sp; t += EXP_WAVES) {
-        const float *row = L + (long)t * V;
+        const float4 *r4 = reinterpret_cast<const float4 *>(L + (long)t * Vl);
         float m = -INFINITY, z = 0.f;
-        if (VEC4) {
-            const float4 *r4 = reinterpret_cast<const float4 *>(row);
-            for (int i = lane; i < V / 4; i += 64) {
-                float4 x = r4[i];
-                float mx = fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
-                float mn = fmaxf(m, mx);
-                z = z * __expf(m - mn) + __expf(x.x - mn) + __expf(x.y - mn) + __expf(x.z - mn) + __expf(x.w - mn);
-                m = mn;
-            }
-        } else {
-            for (int i = lane; i < V; i += 64) {
-                float x = row[i];
-                float mn = fmaxf(m, x);
-                z = z * __expf(m - mn) + __expf(x - mn);
-                m = mn;
-            }
+        for (int i = lane; i < Vl / 4; i += 64) {
+            float4 x = r4[i];
+            float mx = fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w));
+            float mn = fmaxf(m, mx);
+            z = z * __expf(m - mn) + __expf(x.x - mn) + __expf(x.y - mn) + __expf(x.z - mn) + __expf(x.w - mn);
+            m = mn;
         }
         for (int off = 32; off > 0; off >>= 1) {
             float m2 = __shfl_xor(m, off), z2 = __shfl_xor(z, off);
@@ -62,7 +51,7 @@ k_expand(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *_
         if (lane == 0) {
             s_m[t] = m;
             s_z[t] = z;
-            s_b[t] = __expf(row[d.blank] - m) / z;
+            s_b[t] = __expf(L[(long)t * Vl + d.blank] - m) / z;
         }
     }
     __syncthreads();
@@ -88,25 +77,17 @@ k_expand(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *_
     __syncthreads();
 
     // ---- Eq. 4-6: delta_nb[k] = sum_t exp(l[t,k] + lc_t), streamed
-    if (VEC4) {
-        for (int i = tid; i < V / 4; i += EXP_THREADS) {
-            float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-            for (int t = 0; t < sp; ++t) {
-                float4 x = reinterpret_cast<const float4 *>(L + (long)t * V)[i];
-                float lc = s_lc[t];
-                acc.x += __expf(x.x + lc);
-                acc.y += __expf(x.y + lc);
-                acc.z += __expf(x.z + lc);
-                acc.w += __expf(x.w + lc);
-            }
-            reinterpret_cast<float4 *>(s_dnb)[i] = acc;
+    for (int i = tid; i < Vl / 4; i += EXP_THREADS) {
+        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        for (int t = 0; t < sp; ++t) {
+            float4 x = reinterpret_cast<const float4 *>(L + (long)t * Vl)[i];
+            float lc = s_lc[t];
+            acc.x += __expf(x.x + lc);
+            acc.y += __expf(x.y + lc);
+            acc.z += __expf(x.z + lc);
+            acc.w += __expf(x.w + lc);
         }
-    } else {
-        for (int k = tid; k < V; k += EXP_THREADS) {
-            float acc = 0.f;
-            for (int t = 0; t < sp; ++t) acc += __expf(L[(long)t * V + k] + s_lc[t]);
-            s_dnb[k] = acc;
-        }
+        reinterpret_cast<float4 *>(s_dnb)[i] = acc;
     }
     __syncthreads();
     if (tid == 0) s_dnb[d.blank] = 0.f;  // blank is not a non-blank expansion
@@ -174,7 +155,7 @@ k_expand_reg(Dims d, const float *__restrict__ logits, AView A, RowView rv, floa
     ExpandPair<SMAX> pi;
     expand_pair_info(pi, pair, d, A, rv, logits);
     float e[SMAX][NV4 * 4];
-    expand_load<NV4, SMAX, EXP_THREADS>(e, logits, pi.row0, pi.sp, d.V, (int)threadIdx.x);
+    expand_load<NV4, SMAX, EXP_THREADS>(e, logits, pi.row0, pi.sp, d.Vl, (int)threadIdx.x);
     expand_pair<NV4, SMAX, EXP_THREADS>(e, pi, sm, d, (int)threadIdx.x, true, row_lc + pi.row0, dphi + pi.pair,
                                         cand_score + (long)pi.pair * d.N, cand_tok + (long)pi.pair * d.N, row_stats,
                                         delta_nb);
@@ -193,15 +174,15 @@ hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *
                          float *delta_nb, int force_generic, const int *pairs_dev, int pair_base) {
     if (pairs <= 0) return hipSuccess;
     if (pairs_dev && pair_base) return hipErrorInvalidValue;   // (a piece is launched with its size known)
-    size_t shm = (size_t)d.V * sizeof(float);
-    if (d.V % 4 == 0 && !force_generic) {
+    size_t shm = (size_t)d.Vl * sizeof(float);
+    if (!force_generic) {
 #define TBS_EXPAND_REG(NV4, SMAX)                                                                              \
     {                                                                                                          \
         expand_reg_launch<NV4, SMAX>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok, row_stats, \
                                      delta_nb, pairs_dev, pair_base);                                          \
         return hipGetLastError();                                                                              \
     }
-        const int nv4 = (d.V / 4 + EXP_THREADS - 1) / EXP_THREADS;
+        const int nv4 = (d.Vl / 4 + EXP_THREADS - 1) / EXP_THREADS;
         if (nv4 <= 1 && d.S <= 3) TBS_EXPAND_REG(1, 3)
         if (nv4 <= 1 && d.S <= 5) TBS_EXPAND_REG(1, 5)
         if (nv4 <= 1 && d.S <= 16) TBS_EXPAND_REG(1, 16)
@@ -210,11 +191,7 @@ hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *
         if (nv4 <= 4 && d.S <= 5) TBS_EXPAND_REG(4, 5)
 #undef TBS_EXPAND_REG
     }
-    if (d.V % 4 == 0)
-        hipLaunchKernelGGL(k_expand<true>, dim3(pairs), dim3(EXP_THREADS), shm, st, d, logits, A, rv, row_lc, dphi,
-                           cand_score, cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
-    else
-        hipLaunchKernelGGL(k_expand<false>, dim3(pairs), dim3(EXP_THREADS), shm, st, d, logits, A, rv, row_lc, dphi,
-                           cand_score, cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
+    hipLaunchKernelGGL(k_expand, dim3(pairs), dim3(EXP_THREADS), shm, st, d, logits, A, rv, row_lc, dphi, cand_score,
+                       cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
     return hipGetLastError();
 }

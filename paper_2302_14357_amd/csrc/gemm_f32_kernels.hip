@@ -10,10 +10,10 @@
 // the Librispeech-like widths (240 x 1024 x 512, 80 x 2560 x 1280, 80 x 512 x 640): 10.5 us a launch on
 // average against 122 us for the kernel of scalar multiply-adds on 64x64 tiles at the end of this file.
 // With the fused epilogues (gates 80 x 2560 x 640 and the cell update 12.3 us, projection and joiner
-// input rows 8.9 us, joiner 7.4 us) a round is four launches instead of nine.  K tiles of 128 floats go from global memory straight into LDS, as many
-// requested at once as there are stages; rows are 512 bytes, chunk c (16 bytes) of row r sits at
-// position c ^ (r & 15), so that the 16-byte fragment reads of 16 neighbouring rows fall into
-// different banks.  A lane takes 4 consecutive K elements per read and the MFMA steps take them in the
+// input rows 8.9 us, joiner 7.4 us) a round is four launches instead of nine.
+// K tiles of 128 floats go from global memory straight into LDS, as many requested at once as there are
+// stages; rows are 512 bytes, chunk c (16 bytes) of row r sits at position c ^ (r & 15), so that the
+// 16-byte fragment reads of 16 neighbouring rows fall into different banks.  A lane takes 4 consecutive K elements per read and the MFMA steps take them in the
 // order in which they lie (any order of K that A and B share is the same sum).
 #include "tbs_internal.h"
 #include <climits>
@@ -213,9 +213,13 @@ k_gemm_f32_mfma(const float *__restrict__ A, const float *__restrict__ B, const 
         return;
     }
     float *dst = C + (long)orow * ldc + ecol;
+    if (ecol + 3 < N && (ldc & 3) == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0) {
+        *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-        if (ecol + i < N) dst[i] = v[i];
+        for (int i = 0; i < 4; ++i)
+            if (ecol + i < N) dst[i] = v[i];
+    }
 }
 
 // Rows that are not whole 16-byte pieces (K not a multiple of 4, or an operand at an odd address):

@@ -165,6 +165,18 @@ hipError_t launch_stream_copy(hipStream_t st, int U, const void *src, void *dst,
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ padding of the logit rows
+__global__ void k_logit_pads(float *logits, long rows, int V, int Vl) {
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int pad = Vl - V;
+    if (i < rows * pad) logits[(i / pad) * Vl + V + i % pad] = -INFINITY;
+}
+hipError_t launch_logit_pads(hipStream_t st, float *logits, long rows, int V, int Vl) {
+    if (Vl <= V || rows <= 0) return hipSuccess;
+    hipLaunchKernelGGL(k_logit_pads, dim3((unsigned)((rows * (Vl - V) + 255) / 256)), dim3(256), 0, st, logits, rows, V, Vl);
+    return hipGetLastError();
+}
+
 // ------------------------------------------------------------------ timing yardstick
 __global__ void k_empty() {}
 hipError_t launch_empty(hipStream_t st) {

@@ -88,7 +88,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
             // whatever they hold)
             const int t = min(lane_w, d.S - 1);
             doldv = A.dhat[((long)u * N + team_c) * d.S + t];
-            lbv = logits[((long)(u * N + team_c) * d.S + t) * d.V + d.blank];
+            lbv = logits[((long)(u * N + team_c) * d.S + t) * d.Vl + d.blank];
         }
     } else {
         fg = select_figs(u, A, B, rv);
@@ -101,7 +101,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool early = S1NP == 0 && fx.on && !(own_wave && sel_wave);
     const int hslot = fx.on && fx.xh ? A.slot[(long)u * N + team_c] : 0;   // (of a hypothesis that may not exist)
     float e[SMAX][NV4 * 4];
-    if (S1NP == 0 && early) expand_load<NV4, SMAX, TT>(e, logits, (u * N + team_c) * d.S, d.S, d.V, tid);
+    if (S1NP == 0 && early) expand_load<NV4, SMAX, TT>(e, logits, (u * N + team_c) * d.S, d.S, d.Vl, tid);
     if (fx.on) {
         fg.sp = __builtin_amdgcn_readlane(figv, TBS_FIG_SP);
         fg.cntA = __builtin_amdgcn_readlane(figv, TBS_FIG_CNT);
@@ -230,7 +230,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
             }
         }
         if (!early) {
-            expand_load<NV4, SMAX, TT>(e, logits, pi.row0, pi.sp, d.V, tid);
+            expand_load<NV4, SMAX, TT>(e, logits, pi.row0, pi.sp, d.Vl, tid);
         } else {
 #pragma unroll
             for (int t = 0; t < SMAX; ++t)
@@ -338,8 +338,8 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
 // values per thread it costs in reductions, candidate lists and their merge, and the waves of a
 // workgroup share four SIMDs.  The template keeps teams of several waves.
 static int round_variant(const Dims &d) {
-    if (d.V % 4 || d.S > 5 || d.N > 16) return 0;
-    const int v4 = d.V / 4;
+    if (d.S > 5 || d.N > 16) return 0;
+    const int v4 = d.Vl / 4;
     const int nv4 = v4 <= 64 ? 1 : (v4 <= 128 ? 2 : 4);
     if (v4 > 64 * nv4) return 0;
     return nv4 * 10 + (d.S <= 3 ? 3 : 5);

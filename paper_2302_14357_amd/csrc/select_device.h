@@ -214,9 +214,9 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
             // round trip runs beside the merge and the ranking instead of behind them.
             if (pre_x) {
                 const int c = min(lane, nc - 1), tokc = max(tok_mine, 0);
-                const float *lrow = logits + (long)(urow0 + (int)(((float)c + 0.5f) * rcp_n) * (in.slot_rows ? d.S : sp)) * d.V + tokc;
+                const float *lrow = logits + (long)(urow0 + (int)(((float)c + 0.5f) * rcp_n) * (in.slot_rows ? d.S : sp)) * d.Vl + tokc;
 #pragma unroll
-                for (int q = 0; q < SEL_PRE_FRAMES; ++q) xpre[q] = lrow[(long)min(q, sp - 1) * d.V];
+                for (int q = 0; q < SEL_PRE_FRAMES; ++q) xpre[q] = lrow[(long)min(q, sp - 1) * d.Vl];
             }
         }
         if (do_merge) {
@@ -377,7 +377,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                     for (int t0 = 0; t0 < sp; t0 += 8) {   // (eight logits asked for before the first is used)
                         float xv[8];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) xv[q] = logits[(long)(row0 + min(t0 + q, sp - 1)) * d.V + tok];
+                        for (int q = 0; q < 8; ++q) xv[q] = logits[(long)(row0 + min(t0 + q, sp - 1)) * d.Vl + tok];
 #pragma unroll
                         for (int q = 0; q < 8; ++q)
                             if (t0 + q < sp) {

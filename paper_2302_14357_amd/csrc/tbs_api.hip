@@ -321,6 +321,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     d.N = cfg->beam_n;
     d.S = cfg->seg_s;
     d.V = cfg->vocab;
+    d.Vl = (cfg->vocab + 3) & ~3;
     d.Dj = cfg->d_joint;
     d.blank = cfg->blank_id;
     d.R = cfg->rounds_capacity > 0 ? cfg->rounds_capacity : 32;
@@ -382,7 +383,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         rc |= dev_alloc(c, &p, (size_t)M * d.Dj * elem_bytes(c));
         c->amat = p;
     }
-    rc |= dev_alloc(c, &c->logits, (size_t)M * d.V);
+    rc |= dev_alloc(c, &c->logits, (size_t)M * d.Vl);
     c->part = nullptr;
     // (room for a partial per 16-column piece where the round kernel has a lane for each, else per 64-column tile)
     if (d.S == 1 && cfg->dtype == 1)
@@ -507,7 +508,8 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
             return TBS_EHIP;
         }
     }
-    e = hipStreamSynchronize(c->stream);
+    e = launch_logit_pads(c->stream, c->logits, M, d.V, d.Vl);
+    if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         c->last_hip = (int)e;
         tbs_free(c);
@@ -730,7 +732,7 @@ static int joiner_expand_pieces(tbs_ctx *c, int rows, int piece) {
             ProfScope ps(c, TBS_K_JOINER, units);
             ProfScope pg(c, TBS_K_GEMM, (int64_t)units * d.V * d.Dj);
             HIPCHK(c, launch_gemm_bf16_rows(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out,
-                                            c->logits, m_max, d.V, d.Dj, d.V, rb, re));
+                                            c->logits, m_max, d.V, d.Dj, d.Vl, rb, re));
         }
         {
             ProfScope ps(c, TBS_K_EXPAND, units);
@@ -774,7 +776,7 @@ int tbs_joiner_segment(tbs_ctx *c) {
     {
         ProfScope ps(c, TBS_K_JOINER, rows);
         HIPCHK(c, gemm(c, c->amat, c->w.w_out, c->w.b_out, c->logits, rows, c->cur.V, c->cur.Dj, nullptr,
-                       c->cur.V));
+                       c->cur.Vl));
     }
     c->n_launches += 1;
     c->state = ST_JOINED;
@@ -1024,9 +1026,9 @@ static hipError_t joiner_ahead(tbs_ctx *c, const int *rows_dev) {
     const int M = d.U * d.N * d.S;
     if (c->cfg.dtype == 1)
         return launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out, c->logits, M, d.V,
-                                d.Dj, nullptr, d.V, 0, rows_dev);
+                                d.Dj, nullptr, d.Vl, 0, rows_dev);
     return launch_gemm_f32(c->stream, (const float *)c->amat, (const float *)c->w.w_out, c->w.b_out, c->logits, M, d.V, d.Dj,
-                           nullptr, d.V, rows_dev);
+                           nullptr, d.Vl, rows_dev);
 }
 
 static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
@@ -1197,10 +1199,10 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
                                            d.Dj, pe));
             } else if (c->cfg.dtype == 1) {
                 HIPCHK(c, launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out,
-                                           c->logits, M, d.V, d.Dj, nullptr, d.V, 4, nullptr, fx.xcd_rows != 0));
+                                           c->logits, M, d.V, d.Dj, nullptr, d.Vl, 4, nullptr, fx.xcd_rows != 0));
             } else {
                 HIPCHK(c, launch_gemm_f32(c->stream, (const float *)c->amat, (const float *)c->w.w_out, c->w.b_out,
-                                          c->logits, M, d.V, d.Dj, nullptr, d.V, nullptr, fx.xcd_rows != 0));
+                                          c->logits, M, d.V, d.Dj, nullptr, d.Vl, nullptr, fx.xcd_rows != 0));
             }
         }
         AView &A = c->A[c->a_cur], &An = c->A[c->a_cur ^ 1];
@@ -1432,7 +1434,12 @@ int tbs_debug_read(tbs_ctx *c, int32_t which, void *dst, size_t bytes) {
     }
     size_t n = std::min(have, bytes);
     hipError_t e = hipSuccess;
-    if (n) e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, c->stream);
+    if (which == TBS_BUF_LOGITS && d.Vl != d.V && n) {   // (rows handed out without their padding: whole rows, then what is left)
+        const size_t row = sizeof(float) * d.V, pitch = sizeof(float) * d.Vl, whole = n / row, rest = n % row;
+        if (whole) e = hipMemcpy2DAsync(dst, row, src, pitch, row, whole, hipMemcpyDeviceToHost, c->stream);
+        if (e == hipSuccess && rest)
+            e = hipMemcpyAsync((char *)dst + whole * row, (const char *)src + whole * pitch, rest, hipMemcpyDeviceToHost, c->stream);
+    } else if (n) e = hipMemcpyAsync(dst, src, n, hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (tmp) (void)hipFree(tmp);
     HIPCHK(c, e);

@@ -94,6 +94,8 @@ enum { TBS_FIG_SP = 0, TBS_FIG_CNT = 1, TBS_FIG_NB = 2, TBS_FIG_PAR = 3, TBS_FIG
 
 struct Dims {
     int U, N, S, V, Dj, blank;
+    int Vl;     // floats from one row of logits to the next: V rounded up to whole 16-byte pieces; the columns past V
+                // hold -inf from tbs_init on, so that a reader may take them for logits of probability 0
     int R;      // rounds capacity
     int BCAP;   // entries of B per utterance
     int E, H, L;
@@ -258,5 +260,6 @@ hipError_t launch_debug_fill_a(hipStream_t st, const Dims &d, AView A);
 // rows of row_bytes bytes: for every utterance u, n[u] rows from src row src_row[u] on to dst row
 // dst_row[u] on (desc = [src_row | dst_row | n], each [U]); the ranges of src and dst must not overlap
 hipError_t launch_stream_copy(hipStream_t st, int U, const void *src, void *dst, const int *desc, long row_bytes);
+hipError_t launch_logit_pads(hipStream_t st, float *logits, long rows, int V, int Vl);   // -inf into the columns past V
 hipError_t launch_empty(hipStream_t st);   // a kernel that does nothing (timing yardstick)
 hipError_t launch_set_sp(hipStream_t st, const Dims &d, int seg, const int *utt_T, RowView rv);

@@ -176,6 +176,19 @@ def test_expand_all_scores_equal(kernel):
     _check_joiner_expand(shape, U=3, N=6, S=3, seg=0, kernel=kernel, flat=True)
 
 
+@pytest.mark.parametrize("V,N,S", [(3, 2, 2), (257, 5, 3), (1023, 16, 5), (1021, 3, 1), (2049, 4, 3), (3001, 10, 5)])
+def test_vocabularies_that_are_no_whole_pieces(V, N, S):
+    """Logit rows padded to 16-byte pieces: vocabularies one, two and three columns short of a piece or just
+    past one, in the kernels that hold the logits in registers (the round kernel among them), against the
+    oracle; the padding must neither enter a softmax nor become a token."""
+    shape = small_bf16_shape(n_utts=4, vocab=V, d=128, hidden=128)
+    _check_joiner_expand(shape, U=4, N=N, S=S, seg=0, sample_pairs=6)
+    model, offsets, enc = build_case(shape, n_utts=4, lengths=np.array([7, 1, 9, 4]))
+    _, st = _gpu_decode(shape, model, offsets, enc, N, S)
+    assert st["path"]["fixed_places"] == (V <= 1024)
+    _check_decode(shape, model, offsets, enc, N, S)
+
+
 def test_joiner_expand_odd_vocab():
     shape = small_bf16_shape(n_utts=3, vocab=77, d=64, hidden=64)
     _check_joiner_expand(shape, U=3, N=4, S=3, seg=0)
