@@ -125,14 +125,17 @@ __device__ __forceinline__ void wave_argmax(float &bv, int &bk) {
 // is therefore written to be short: reductions in the integer domain or with the
 // DPP operand folded into the add, thresholds and ranks by counting against lane
 // values broadcast through scalar registers instead of rounds of arg-max.
-template <int SMAX, int TW>
-struct ExpandShared {
-    float pm[SMAX][TW], pz[SMAX][TW];   // per-wave row maxima and row sums
+template <int TW>
+struct ExpandBest {
     float cv[TW][EXP_CAND_CAP];   // candidates of each wave ...
     int ck[TW][EXP_CAND_CAP];
     float jv[TW * EXP_CAND_CAP];  // ... and all of them in one list, in any order
     int jk[TW * EXP_CAND_CAP];
-    int jn;                              // entries of the joint list
+    int jn;                              // entries of the joint list (cleared by the caller, a barrier ahead)
+};
+template <int SMAX, int TW>
+struct ExpandShared : ExpandBest<TW> {
+    float pm[SMAX][TW], pz[SMAX][TW];   // per-wave row maxima and row sums
 };
 
 // What a workgroup needs to know of one (utterance, hypothesis) pair besides its logits.
@@ -217,6 +220,154 @@ __device__ __forceinline__ float wave_max_ord(float f) {
     v = max(v, dpp_i<DPP_MIRROR>(v));
     return ord2f(max(max(__builtin_amdgcn_readlane(v, 0), __builtin_amdgcn_readlane(v, 16)),
                      max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48))));
+}
+
+// The N best of the scores v (thread tid holds columns 4 * (tid + TT * q) + c, zero where there is none),
+// by a team of TT threads, one workgroup-wide barrier inside.  cs / ct: logarithms and tokens in order
+// (-inf / -1 where there are fewer).  live = false: the team only keeps the barrier company.
+template <int NV4, int TT>
+__device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT / 64> &sm, const Dims &d, int tid, bool live,
+                                            float *cs, int *ct) {
+    constexpr int NC = NV4 * 4;  // columns per thread
+    constexpr int TW = TT / 64;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // ---- candidates of this wave: every score >= tau, where tau is a lower bound of the wave's
+    // N-th largest score (ties included, so usually only a few more than N qualify).  Scores are
+    // positive floats, ordered like their bit patterns.
+    float tau;
+    {
+        float lm = 0.f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) lm = fmaxf(lm, v[c]);
+        if (d.N <= 16) {
+            // N-th largest of the 16 quad maxima: each is a score of this wave, so the N-th largest
+            // of them cannot exceed the N-th largest of all.  The low four bits of a key give way to
+            // the quad's number, which makes the keys distinct; every lane counts the keys above its
+            // own, and the quad that counts N-1 holds the threshold (rounded down by those bits).
+            unsigned key = __float_as_uint(lm);
+            key = max(key, (unsigned)dpp_i<DPP_QUAD_SWAP1>((int)key));
+            key = max(key, (unsigned)dpp_i<DPP_QUAD_SWAP2>((int)key));
+            key = (key & ~15u) | (unsigned)(15 - (lane >> 2));
+            int above = 0;
+#pragma unroll
+            for (int g = 0; g < 16; ++g) above += (unsigned)__builtin_amdgcn_readlane((int)key, 4 * g) > key;
+            const u64 at = __ballot(above == d.N - 1);
+            const unsigned kth = (unsigned)__builtin_amdgcn_readlane((int)key, __ffsll((long long)at) - 1);
+            tau = __uint_as_float(kth & ~15u);
+        } else {
+            // N rounds of wave maximum over the thread maxima, one lane retiring per round
+            tau = 0.f;
+            for (int n = 0; n < d.N; ++n) {
+                tau = wave_max(lm);
+                if (!(tau > 0.f)) break;   // fewer than N positive maxima: every positive score qualifies
+                const u64 holders = __ballot(lm == tau);
+                if (lane == __ffsll((long long)holders) - 1) lm = -1.f;
+            }
+        }
+        // the smallest normal float stands for "any positive score"
+        tau = fmaxf(tau, 1.17549435e-38f);
+    }
+    int total = 0;
+    {
+#pragma unroll
+        for (int q = 0; q < NV4; ++q)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float x = v[4 * q + c];
+                const bool take = x >= tau;
+                const u64 m = __ballot(take);
+                if (m) {   // uniform
+                    const int pos = total + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
+                                                                           __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+                    if (take && pos < EXP_CAND_CAP) {
+                        sm.cv[wave][pos] = x;
+                        sm.ck[wave][pos] = 4 * (tid + TT * q) + c;
+                    }
+                    total += __popcll(m);
+                }
+            }
+    }
+    if (total > EXP_CAND_CAP) {
+        // many equal scores: take exactly the N best by N rounds of wave arg-max
+        total = 0;
+        for (int n = 0; n < d.N; ++n) {
+            float bv = 0.f;
+            int bk = 0x7fffffff;
+#pragma unroll
+            for (int q = 0; q < NV4; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    const float x = v[4 * q + c];
+                    if (x > bv) { bv = x; bk = 4 * (tid + TT * q) + c; }   // ascending columns
+                }
+            wave_argmax(bv, bk);
+            if (!(bv > 0.f)) break;
+            if (lane == 0) { sm.cv[wave][n] = bv; sm.ck[wave][n] = bk; }
+            total = n + 1;
+#pragma unroll
+            for (int q = 0; q < NV4; ++q)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (4 * (tid + TT * q) + c == bk) v[4 * q + c] = -1.f;
+        }
+    }
+    // append this wave's list to the joint list (the order of waves there does not matter: the
+    // merge below orders by score and token)
+    {
+        int base = 0;
+        if (lane == 0) base = atomicAdd(&sm.jn, total);
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (lane < total) {
+            sm.jv[base + lane] = sm.cv[wave][lane];
+            sm.jk[base + lane] = sm.ck[wave][lane];
+        }
+    }
+    __syncthreads();
+    // ---- merge (first wave): larger score first, smaller token on equal scores
+    if (wave == 0 && live) {
+        const int all = sm.jn;
+        if (all <= 64) {
+            // one candidate per lane, as a 64-bit key (score bits, inverted token) that orders like
+            // the rule above; the rank of a candidate is the number of keys above its own
+            const bool have = lane < all;
+            const float x = have ? sm.jv[lane] : 0.f;
+            const int k = have ? sm.jk[lane] : 0x7fffffff;
+            const u64 key = ((u64)__float_as_uint(x) << 32) | (unsigned)(0x7fffffff - k);
+            int rank = 0;
+            for (int j = 0; j < all; ++j) {
+                const u64 kj = ((u64)(unsigned)__builtin_amdgcn_readlane((int)(key >> 32), j) << 32) |
+                               (unsigned)__builtin_amdgcn_readlane((int)key, j);
+                rank += kj > key;
+            }
+            if (have && rank < d.N) { cs[rank] = __logf(x); ct[rank] = k; }
+            if (lane >= all && lane < d.N) { cs[lane] = -INFINITY; ct[lane] = -1; }
+        } else {
+            float cv[TW];
+            int ck[TW];
+#pragma unroll
+            for (int i = 0; i < TW; ++i) {
+                const bool have = lane + 64 * i < all;
+                cv[i] = have ? sm.jv[lane + 64 * i] : -1.f;
+                ck[i] = have ? sm.jk[lane + 64 * i] : 0x7fffffff;
+            }
+            for (int n = 0; n < d.N; ++n) {
+                float bv = -1.f;
+                int bk = 0x7fffffff;
+#pragma unroll
+                for (int i = 0; i < TW; ++i)
+                    if (cv[i] > bv || (cv[i] == bv && ck[i] < bk)) { bv = cv[i]; bk = ck[i]; }
+                wave_argmax(bv, bk);
+                if (lane == 0) {
+                    const bool ok = bv > 0.f && bk != 0x7fffffff;
+                    cs[n] = ok ? __logf(bv) : -INFINITY;
+                    ct[n] = ok ? bk : -1;
+                }
+#pragma unroll
+                for (int i = 0; i < TW; ++i)
+                    if (ck[i] == bk) { cv[i] = -1.f; ck[i] = 0x7fffffff; }
+            }
+        }
+    }
 }
 
 // (expand_pair meets the other teams of its workgroup at this many barriers; a wave of the workgroup
@@ -358,142 +509,5 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
                 if (4 * i4 + c < V) delta_nb[(long)pi.pair * V + 4 * i4 + c] = v[4 * q + c];
         }
     }
-    // ---- candidates of this wave: every score >= tau, where tau is a lower bound of the wave's
-    // N-th largest score (ties included, so usually only a few more than N qualify).  Scores are
-    // positive floats, ordered like their bit patterns.
-    float tau;
-    {
-        float lm = 0.f;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) lm = fmaxf(lm, v[c]);
-        if (d.N <= 16) {
-            // N-th largest of the 16 quad maxima: each is a score of this wave, so the N-th largest
-            // of them cannot exceed the N-th largest of all.  The low four bits of a key give way to
-            // the quad's number, which makes the keys distinct; every lane counts the keys above its
-            // own, and the quad that counts N-1 holds the threshold (rounded down by those bits).
-            unsigned key = __float_as_uint(lm);
-            key = max(key, (unsigned)dpp_i<DPP_QUAD_SWAP1>((int)key));
-            key = max(key, (unsigned)dpp_i<DPP_QUAD_SWAP2>((int)key));
-            key = (key & ~15u) | (unsigned)(15 - (lane >> 2));
-            int above = 0;
-#pragma unroll
-            for (int g = 0; g < 16; ++g) above += (unsigned)__builtin_amdgcn_readlane((int)key, 4 * g) > key;
-            const u64 at = __ballot(above == d.N - 1);
-            const unsigned kth = (unsigned)__builtin_amdgcn_readlane((int)key, __ffsll((long long)at) - 1);
-            tau = __uint_as_float(kth & ~15u);
-        } else {
-            // N rounds of wave maximum over the thread maxima, one lane retiring per round
-            tau = 0.f;
-            for (int n = 0; n < d.N; ++n) {
-                tau = wave_max(lm);
-                if (!(tau > 0.f)) break;   // fewer than N positive maxima: every positive score qualifies
-                const u64 holders = __ballot(lm == tau);
-                if (lane == __ffsll((long long)holders) - 1) lm = -1.f;
-            }
-        }
-        // the smallest normal float stands for "any positive score"
-        tau = fmaxf(tau, 1.17549435e-38f);
-    }
-    int total = 0;
-    {
-#pragma unroll
-        for (int q = 0; q < NV4; ++q)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                const float x = v[4 * q + c];
-                const bool take = x >= tau;
-                const u64 m = __ballot(take);
-                if (m) {   // uniform
-                    const int pos = total + (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32),
-                                                                           __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
-                    if (take && pos < EXP_CAND_CAP) {
-                        sm.cv[wave][pos] = x;
-                        sm.ck[wave][pos] = 4 * (tid + TT * q) + c;
-                    }
-                    total += __popcll(m);
-                }
-            }
-    }
-    if (total > EXP_CAND_CAP) {
-        // many equal scores: take exactly the N best by N rounds of wave arg-max
-        total = 0;
-        for (int n = 0; n < d.N; ++n) {
-            float bv = 0.f;
-            int bk = 0x7fffffff;
-#pragma unroll
-            for (int q = 0; q < NV4; ++q)
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const float x = v[4 * q + c];
-                    if (x > bv) { bv = x; bk = 4 * (tid + TT * q) + c; }   // ascending columns
-                }
-            wave_argmax(bv, bk);
-            if (!(bv > 0.f)) break;
-            if (lane == 0) { sm.cv[wave][n] = bv; sm.ck[wave][n] = bk; }
-            total = n + 1;
-#pragma unroll
-            for (int q = 0; q < NV4; ++q)
-#pragma unroll
-                for (int c = 0; c < 4; ++c)
-                    if (4 * (tid + TT * q) + c == bk) v[4 * q + c] = -1.f;
-        }
-    }
-    // append this wave's list to the joint list (the order of waves there does not matter: the
-    // merge below orders by score and token)
-    {
-        int base = 0;
-        if (lane == 0) base = atomicAdd(&sm.jn, total);
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (lane < total) {
-            sm.jv[base + lane] = sm.cv[wave][lane];
-            sm.jk[base + lane] = sm.ck[wave][lane];
-        }
-    }
-    __syncthreads();
-    // ---- merge (first wave): larger score first, smaller token on equal scores
-    if (wave == 0 && live) {
-        const int all = sm.jn;
-        if (all <= 64) {
-            // one candidate per lane, as a 64-bit key (score bits, inverted token) that orders like
-            // the rule above; the rank of a candidate is the number of keys above its own
-            const bool have = lane < all;
-            const float x = have ? sm.jv[lane] : 0.f;
-            const int k = have ? sm.jk[lane] : 0x7fffffff;
-            const u64 key = ((u64)__float_as_uint(x) << 32) | (unsigned)(0x7fffffff - k);
-            int rank = 0;
-            for (int j = 0; j < all; ++j) {
-                const u64 kj = ((u64)(unsigned)__builtin_amdgcn_readlane((int)(key >> 32), j) << 32) |
-                               (unsigned)__builtin_amdgcn_readlane((int)key, j);
-                rank += kj > key;
-            }
-            if (have && rank < d.N) { cs[rank] = __logf(x); ct[rank] = k; }
-            if (lane >= all && lane < d.N) { cs[lane] = -INFINITY; ct[lane] = -1; }
-        } else {
-            float cv[TW];
-            int ck[TW];
-#pragma unroll
-            for (int i = 0; i < TW; ++i) {
-                const bool have = lane + 64 * i < all;
-                cv[i] = have ? sm.jv[lane + 64 * i] : -1.f;
-                ck[i] = have ? sm.jk[lane + 64 * i] : 0x7fffffff;
-            }
-            for (int n = 0; n < d.N; ++n) {
-                float bv = -1.f;
-                int bk = 0x7fffffff;
-#pragma unroll
-                for (int i = 0; i < TW; ++i)
-                    if (cv[i] > bv || (cv[i] == bv && ck[i] < bk)) { bv = cv[i]; bk = ck[i]; }
-                wave_argmax(bv, bk);
-                if (lane == 0) {
-                    const bool ok = bv > 0.f && bk != 0x7fffffff;
-                    cs[n] = ok ? __logf(bv) : -INFINITY;
-                    ct[n] = ok ? bk : -1;
-                }
-#pragma unroll
-                for (int i = 0; i < TW; ++i)
-                    if (ck[i] == bk) { cv[i] = -1.f; ck[i] = 0x7fffffff; }
-            }
-        }
-    }
+    expand_best<NV4, TT>(v, sm, d, tid, live, cs, ct);
 }
-

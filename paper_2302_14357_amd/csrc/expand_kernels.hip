@@ -161,6 +161,187 @@ k_expand_reg(Dims d, const float *__restrict__ logits, AView A, RowView rv, floa
                                         delta_nb);
 }
 
+// ------------------------------------------------------------------ long segments
+// Segments too long for the registers of four waves: a wave takes whole rows (up to RPW of them, NQ
+// 16-byte pieces a lane and row), so a row's maximum and sum never leave its wave and every logit is
+// read from memory and exponentiated once.  The forward variable of Eq. 3 is a chain of S' steps; here it is
+// a prefix scan over the lanes of one wave, alpha_t = alpha_{t-1} b_{t-1} + d_old[t] as the composition
+// of the maps x -> x B + A, which takes log2(S') steps instead.  A and B are kept as mantissa * 2^exponent
+// (see ScanAlpha: the products leave the range of float).  The waves' shares of delta_nb (Eq. 6) meet in LDS,
+// and the first four waves take the N best.
+struct ScanPart {
+    float m;   // mantissa in [0.5, 1), or 0
+    int e;
+};
+__device__ __forceinline__ ScanPart scan_norm(float m, int e) {
+    int k;
+    m = frexpf(m, &k);
+    return {m, m != 0.f ? e + k : 0};
+}
+__device__ __forceinline__ ScanPart scan_mul(ScanPart a, ScanPart b) { return scan_norm(a.m * b.m, a.e + b.e); }
+__device__ __forceinline__ ScanPart scan_add(ScanPart a, ScanPart b) {
+    if (a.m == 0.f) return b;
+    if (b.m == 0.f) return a;
+    const int e = max(a.e, b.e);
+    return scan_norm(ldexpf(a.m, a.e - e) + ldexpf(b.m, b.e - e), e);
+}
+__device__ __forceinline__ ScanPart scan_up(ScanPart a, int by) { return {__shfl_up(a.m, by), __shfl_up(a.e, by)}; }
+__device__ __forceinline__ float scan_log(ScanPart a) {
+    return a.m > 0.f ? __logf(a.m) + (float)a.e * 0.69314718055994531f : -INFINITY;
+}
+// exp(x) / z (z = 1: exp(x)); zero for x = -inf
+__device__ __forceinline__ ScanPart scan_exp(float x, float z) {
+    if (!(x > -INFINITY)) return {0.f, 0};
+    const float l2 = x * 1.44269504088896341f, fl = floorf(l2);
+    return scan_norm(__builtin_amdgcn_exp2f(l2 - fl) / z, (int)fl);
+}
+
+#define LONG_FRAMES 64     // a lane per frame in the scan
+#define LONG_MIN_WAVES 4   // the N best are taken by the first four waves
+template <int NQ, int RPW>
+__global__ void __launch_bounds__(1024)
+k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *__restrict__ row_lc,
+              float *__restrict__ dphi, float *__restrict__ cand_score, int *__restrict__ cand_tok,
+              float *__restrict__ row_stats, float *__restrict__ delta_nb, const int *__restrict__ pairs_dev,
+              int pair_base) {
+    extern __shared__ __attribute__((aligned(16))) float4 s_part[];   // [waves][Vl / 4]
+    __shared__ ExpandBest<EXP_WAVES> sm;
+    __shared__ float s_m[LONG_FRAMES], s_z[LONG_FRAMES], s_lb[LONG_FRAMES], s_cf[LONG_FRAMES];
+    const int pair = pair_base + blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
+    if (pairs_dev && pair >= *pairs_dev) return;   // (enqueued on an upper-bound grid, see k_expand_reg)
+    const int u = ((cint_p)rv.pair_u)[pair], h = ((cint_p)rv.pair_h)[pair];
+    const int row0 = ((cint_p)rv.pair_row0)[pair], sp = ((cint_p)rv.pair_len)[pair];
+    const int V = d.V, Vl = d.Vl, V4 = Vl >> 2;
+    const float *L = logits + (long)row0 * Vl;
+    // this wave's rows: wave, wave + waves, ... (rows past S' repeat the last one, pieces past V the last piece)
+    float4 e[RPW][NQ];
+    float lblank[RPW];
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        const float *row = L + (long)min(wave + i * waves, sp - 1) * Vl;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) e[i][q] = reinterpret_cast<const float4 *>(row)[min(lane + 64 * q, V4 - 1)];
+        lblank[i] = row[d.blank];
+    }
+    const float ld = wave == 0 ? A.dhat[((long)u * d.N + h) * d.S + min(lane, d.S - 1)] : 0.f;
+    if (tid == 0) sm.jn = 0;
+#pragma unroll
+    for (int i = 0; i < RPW; ++i) {
+        const int t = wave + i * waves;
+        if (t >= sp) continue;   // (uniform)
+        float m = -INFINITY;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) m = fmaxf(m, fmaxf(fmaxf(e[i][q].x, e[i][q].y), fmaxf(e[i][q].z, e[i][q].w)));
+        m = wave_max_ord(m);
+        const float nm = -m * 1.44269504088896341f;
+        float z = 0.f;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) {
+            float4 &x = e[i][q];
+            x.x = __builtin_amdgcn_exp2f(fmaf(x.x, 1.44269504088896341f, nm));
+            x.y = __builtin_amdgcn_exp2f(fmaf(x.y, 1.44269504088896341f, nm));
+            x.z = __builtin_amdgcn_exp2f(fmaf(x.z, 1.44269504088896341f, nm));
+            x.w = __builtin_amdgcn_exp2f(fmaf(x.w, 1.44269504088896341f, nm));
+            if (lane + 64 * q < V4) z += (x.x + x.y) + (x.z + x.w);
+        }
+        z = wave_sum(z);
+        if (lane == 0) {
+            s_m[t] = m;
+            s_z[t] = z;
+            s_lb[t] = lblank[i] - m;
+        }
+    }
+    __syncthreads();
+    if (wave == 0) {   // lane t: frame t
+        const bool have = lane < sp;
+        const int t = min(lane, sp - 1);
+        const float m = s_m[t], z = s_z[t];
+        const ScanPart b = scan_exp(s_lb[t], z);              // blank probability of the frame
+        ScanPart a = scan_exp(have ? ld : -INFINITY, 1.f), f = scan_up(b, 1);   // alpha_t = alpha_{t-1} f + a
+        for (int by = 1; by < sp; by <<= 1) {
+            const ScanPart a2 = scan_up(a, by), f2 = scan_up(f, by);
+            if (lane >= by) {
+                a = scan_add(scan_mul(a2, f), a);
+                f = scan_mul(f2, f);
+            }
+        }
+        const float lc = scan_log(a) - __logf(z);             // log(alpha_t / Z_t)
+        if (have) {
+            s_cf[t] = __expf(lc);
+            row_lc[row0 + t] = lc - m;
+            if (lane == sp - 1) dphi[pair] = scan_log(scan_mul(a, b));   // Eq. 7
+            if (row_stats) {
+                row_stats[(long)(row0 + t) * 3 + 0] = m;
+                row_stats[(long)(row0 + t) * 3 + 1] = z;
+                row_stats[(long)(row0 + t) * 3 + 2] = ldexpf(b.m, b.e);
+            }
+        }
+    }
+    __syncthreads();
+    {   // this wave's share of Eq. 4-6
+        float4 acc[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int i = 0; i < RPW; ++i) {
+            const int t = wave + i * waves;
+            if (t >= sp) continue;   // (uniform)
+            const float cf = s_cf[t];
+#pragma unroll
+            for (int q = 0; q < NQ; ++q) {
+                acc[q].x += cf * e[i][q].x;
+                acc[q].y += cf * e[i][q].y;
+                acc[q].z += cf * e[i][q].z;
+                acc[q].w += cf * e[i][q].w;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < NQ; ++q)
+            if (lane + 64 * q < V4) s_part[wave * V4 + lane + 64 * q] = acc[q];
+    }
+    __syncthreads();
+    if (wave >= EXP_WAVES) {
+        __syncthreads();   // (the barrier inside expand_best)
+        return;
+    }
+    float v[4] = {0.f, 0.f, 0.f, 0.f};
+    if (tid < V4) {
+        const int shares = min(waves, sp);   // (a wave beyond S' had no row)
+        for (int w = 0; w < shares; ++w) {
+            const float4 x = s_part[w * V4 + tid];
+            v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int col = 4 * tid + c;
+        if (col == d.blank || col >= V) v[c] = 0.f;   // blank is not a non-blank expansion
+        if (delta_nb && col < V) delta_nb[(long)pair * V + col] = v[c];
+    }
+    expand_best<1, EXP_THREADS>(v, sm, d, tid, true, cand_score + (long)pair * d.N, cand_tok + (long)pair * d.N);
+}
+
+template <int NQ, int RPW>
+static hipError_t expand_long_launch(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
+                                     float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
+                                     float *delta_nb, const int *pairs_dev, int pair_base) {
+    int waves = (d.S + RPW - 1) / RPW;
+    if (waves < LONG_MIN_WAVES) waves = LONG_MIN_WAVES;
+    if (waves > 16) return hipErrorInvalidValue;
+    const size_t shm = (size_t)waves * d.Vl * sizeof(float);   // (at most 64 KB)
+    static size_t attr_for = 0;
+    if (shm > attr_for) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_expand_long<NQ, RPW>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+        if (e != hipSuccess) return e;
+        attr_for = shm;
+    }
+    hipLaunchKernelGGL((k_expand_long<NQ, RPW>), dim3(pairs), dim3(64 * waves), shm, st, d, logits, A, rv, row_lc, dphi,
+                       cand_score, cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
+    return hipGetLastError();
+}
+
 template <int NV4, int SMAX>
 static void expand_reg_launch(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                               float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
@@ -185,11 +366,28 @@ hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *
         const int nv4 = (d.Vl / 4 + EXP_THREADS - 1) / EXP_THREADS;
         if (nv4 <= 1 && d.S <= 3) TBS_EXPAND_REG(1, 3)
         if (nv4 <= 1 && d.S <= 5) TBS_EXPAND_REG(1, 5)
-        if (nv4 <= 1 && d.S <= 16) TBS_EXPAND_REG(1, 16)
         if (nv4 <= 2 && d.S <= 8) TBS_EXPAND_REG(2, 8)
         if (nv4 <= 4 && d.S <= 3) TBS_EXPAND_REG(4, 3)
         if (nv4 <= 4 && d.S <= 5) TBS_EXPAND_REG(4, 5)
 #undef TBS_EXPAND_REG
+        // Longer segments of a vocabulary that fits a lane's four pieces: two rows a wave up to 32 frames, four up
+        // to 64 (a workgroup has at most 16 waves).  Measured on the Librispeech-like batch of 64 at N = 5 (ms
+        // per decode; one / two / four rows a wave): S = 6: 21.3 / 21.3 / 21.3, 12: 20.1 / 20.0 / 20.1, 16: 20.8 /
+        // 20.6 / 21.0, 20: - / 22.4 / 22.7, 32: - / 25.2 / 25.4; a workgroup of four waves that holds up to 16
+        // frames' columns took 22.3 at S = 6, 22.0 at 12 and 23.0 at 16, the two-pass kernel 28.2 at 20, 47.7
+        // (here 32.6) at 50.
+        if (nv4 <= 1 && d.S <= LONG_FRAMES) {
+            const int rpw = d.S <= 32 ? 2 : 4;
+            const int nq = d.Vl <= 256 ? 1 : (d.Vl <= 512 ? 2 : 4);
+#define TBS_EXPAND_LONG(NQ, RPW)                                                                                       \
+    if (nq == NQ && rpw == RPW)                                                                                        \
+        return expand_long_launch<NQ, RPW>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok, row_stats, \
+                                           delta_nb, pairs_dev, pair_base);
+            TBS_EXPAND_LONG(1, 2) TBS_EXPAND_LONG(1, 4)
+            TBS_EXPAND_LONG(2, 2) TBS_EXPAND_LONG(2, 4)
+            TBS_EXPAND_LONG(4, 2) TBS_EXPAND_LONG(4, 4)
+#undef TBS_EXPAND_LONG
+        }
     }
     hipLaunchKernelGGL(k_expand, dim3(pairs), dim3(EXP_THREADS), shm, st, d, logits, A, rv, row_lc, dphi, cand_score,
                        cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
