@@ -34,10 +34,15 @@ __device__ __forceinline__ typename RoundPiece<F32>::type round_piece(const floa
 // joiner GEMM kept no logits: `logits` points at its row partials (see PartEp), tiles_n per row, and
 // the expansion of a hypothesis is the merge of its row's partials by one wave (TW = 1, SMAX = 1),
 // lane l taking tile l with a list of up to S1NP candidates in registers.
-template <int TW, int NV4, int SMAX, int S1NP, bool F32>
+// SLOTS: the slot layout with a wave for the select step and no debug output, known when the code is made.
+// A launch runs through its code once, so what other callers need stands in its way: with everything in
+// one body the kernel is 6700 instructions (45 KB), half of them for the other forms.
+template <int TW, int NV4, int SMAX, int S1NP, bool F32, bool SLOTS>
 __global__ void __launch_bounds__(1024)
 k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, AView An, BView B, RowView rv,
-        int2 *nodes, float *__restrict__ row_stats, float *__restrict__ delta_nb, FixedView fx, int tiles_n) {
+        int2 *nodes, float *__restrict__ row_stats_arg, float *__restrict__ delta_nb_arg, FixedView fx, int tiles_n) {
+    const bool on = SLOTS || fx.on;
+    float *row_stats = SLOTS ? nullptr : row_stats_arg, *delta_nb = SLOTS ? nullptr : delta_nb_arg;
     constexpr int TT = TW * 64;
     typedef typename RoundPiece<F32>::type XP;
     typedef ExpandShared<SMAX, TW> TeamShared;
@@ -56,7 +61,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     // go to the XCDs in turn) and takes the (b / 8)-th utterance whose first joiner row lies in that
     // XCD's range, so that it finds the utterance's logits in its own XCD's L2.
     int u = blockIdx.x;
-    if (fx.on && fx.xcd_rows > 0) {
+    if (on && fx.xcd_rows > 0) {
         const int x = (int)blockIdx.x & 7, R = N * d.S;
         const int u0 = (x * fx.xcd_rows + R - 1) / R, u1 = ((x + 1) * fx.xcd_rows + R - 1) / R;
         u = u0 + ((int)blockIdx.x >> 3);
@@ -66,7 +71,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     // Where the workgroup has room for one more wave, that wave belongs to the select step: it stages
     // B and A in LDS while the teams expand, and goes on when they are done.  Otherwise the first
     // wave does the select step after its share of the expansion.
-    const bool own_wave = (int)blockDim.x > N * TT;
+    const bool own_wave = SLOTS || (int)blockDim.x > N * TT;
     const bool sel_wave = own_wave ? (int)threadIdx.x >= N * TT : (int)threadIdx.x < WAVE;
     const int sel_lane = (int)threadIdx.x & 63;
     __shared__ SelectOut s_out;
@@ -81,7 +86,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const int team_c = team < N ? team : 0;   // (a team beyond N keeps its requests inside the utterance)
     int figv = 0;
     float doldv = 0.f, lbv = 0.f;
-    if (fx.on) {
+    if (on) {
         figv = fx.fig[u * TBS_FIG_SIZE + (lane_w & (TBS_FIG_SIZE - 1))];
         if (S1NP == 0) {
             // (and, lane t, the hypothesis' d_old[t] and the blank logit of its frame t: rows that exist
@@ -98,11 +103,11 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     // utterance's first place for a team beyond N: memory that exists whatever it holds); what turns
     // out not to be a frame of a live hypothesis is cleared below.  The utterance's figures and the
     // logits then take one memory round trip together instead of two in a row.
-    const bool early = S1NP == 0 && fx.on && !(own_wave && sel_wave);
-    const int hslot = fx.on && fx.xh ? A.slot[(long)u * N + team_c] : 0;   // (of a hypothesis that may not exist)
+    const bool early = S1NP == 0 && on && !(own_wave && sel_wave);
+    const int hslot = on && fx.xh ? A.slot[(long)u * N + team_c] : 0;   // (of a hypothesis that may not exist)
     float e[SMAX][NV4 * 4];
     if (S1NP == 0 && early) expand_load<NV4, SMAX, TT>(e, logits, (u * N + team_c) * d.S, d.S, d.Vl, tid);
-    if (fx.on) {
+    if (on) {
         fg.sp = __builtin_amdgcn_readlane(figv, TBS_FIG_SP);
         fg.cntA = __builtin_amdgcn_readlane(figv, TBS_FIG_CNT);
         fg.nB0 = __builtin_amdgcn_readlane(figv, TBS_FIG_NB);
@@ -116,7 +121,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const int H = sp > 0 ? fg.cntA : 0;
     if (H == 0) {   // (the same for the whole workgroup: nobody reaches a barrier)
         if (threadIdx.x == 0) An.count[u] = 0;
-        if (fx.on) {
+        if (on) {
             if (threadIdx.x == 0) fx.fig[u * TBS_FIG_SIZE + TBS_FIG_CNT] = 0;
             if ((int)threadIdx.x < N) pair_mark_dead(rv, u * N + (int)threadIdx.x, u, d.S);
             if (threadIdx.x == 0) {
@@ -127,21 +132,21 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
         return;
     }
     // (the utterance's pairs and rows follow each other: nothing is read from the pair list)
-    const int pair0 = fx.on ? u * N : rv.utt_pair0[u], urow0 = fg.urow0;
+    const int pair0 = on ? u * N : rv.utt_pair0[u], urow0 = fg.urow0;
     const bool live = team < H;
     SelectIn in;
     in.cand_score = s_cs;
     in.cand_tok = s_ct;
     in.dphi = s_dphi;
     in.lc = s_lc;
-    in.slot_rows = fx.on;
+    in.slot_rows = on;
     // Slot layout: the first LSTM layer's input rows of the hypotheses this round makes are copies (bf16
     // models: rounded) of their parents' h.  The parents are among this utterance's H hypotheses, so every team asks for
     // its own hypothesis' h now, beside the logits, and at the end writes it out once for every new
     // hypothesis made from it: the end of the kernel then has no memory round trip of its own.
     constexpr int HP = (160 + TT - 1) / TT;   // 16-byte pieces per thread for h up to 640 wide
     const int H4 = d.H >> 2;
-    const bool pre_h = fx.on && fx.xh && H4 <= TT * HP;
+    const bool pre_h = on && fx.xh && H4 <= TT * HP;
     float4 hpar[HP];
     if (own_wave && sel_wave) {
         select_merge_utt(1, d, round, drop, u, sel_lane, logits, in, fg, A, An, B, rv, nodes, s_raw, &s_out);
@@ -218,7 +223,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
                 pi.lblank[t] = t < sp ? __int_as_float(__builtin_amdgcn_readlane(__float_as_int(lbv), t)) : 0.f;
             }
         } else if (live) {
-            expand_pair_info_at(pi, pair0 + team, urow0 + team * (fx.on ? d.S : sp), sp, u, team, d, A, logits);
+            expand_pair_info_at(pi, pair0 + team, urow0 + team * (on ? d.S : sp), sp, u, team, d, A, logits);
         } else {   // a team without a hypothesis reads the utterance's first row and scores nothing
             pi.pair = pair0;
             pi.row0 = urow0;
@@ -265,7 +270,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     }
     if (sel_wave) {
         select_merge_utt(own_wave ? 5 : 0, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out);
-        if (fx.on) {
+        if (on) {
             // Slot layout: what a row list kernel would do for this utterance.  The new hypotheses
             // take trie nodes from the utterance's own range, their pairs get their descriptors, the
             // places of A beyond them are marked dead, and the host hears how many there are.
@@ -319,7 +324,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
                         if (tid + TT * q < H4) static_cast<XP *>(fx.xh)[(long)(u * N + i) * H4 + tid + TT * q] = hb[q];
                 }
         }
-    } else if (fx.on && fx.xh) {
+    } else if (on && fx.xh) {
         // (h too wide to wait in registers: read the parents' rows now)
         __syncthreads();
         const int total = s_out.total;
@@ -347,7 +352,7 @@ static int round_variant(const Dims &d) {
 
 bool round_fits(const Dims &d) { return round_variant(d) != 0; }
 
-template <int TW, int NV4, int SMAX, int S1NP, bool F32>
+template <int TW, int NV4, int SMAX, int S1NP, bool F32, bool SLOTS>
 static hipError_t round_launch_t(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
                                AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
                                const FixedView &fx, int tiles_n) {
@@ -356,7 +361,7 @@ static hipError_t round_launch_t(hipStream_t st, const Dims &d, int round, int d
                        sizeof(float) * ((size_t)d.N * SMAX + d.N + 2 * (size_t)d.N * d.N);
     static size_t attr_for = 0;
     if (shm > attr_for) {   // (static LDS of the select step comes on top: raise the limit to what the launch needs)
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_round<TW, NV4, SMAX, S1NP, F32>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_round<TW, NV4, SMAX, S1NP, F32, SLOTS>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_for = shm;
@@ -365,7 +370,7 @@ static hipError_t round_launch_t(hipStream_t st, const Dims &d, int round, int d
     const int threads = d.N * TW * 64 + (d.N * TW * 64 + 64 <= 1024 ? 64 : 0);
     // (with a row range per XCD: eight workgroups, one per XCD, for each place in the longest XCD's list)
     const int grid = fx.on && fx.xcd_rows > 0 ? 8 * (fx.xcd_rows / (d.N * d.S) + 1) : d.U;
-    hipLaunchKernelGGL((k_round<TW, NV4, SMAX, S1NP, F32>), dim3(grid), dim3(threads), shm, st, d, round, drop, logits, A, An,
+    hipLaunchKernelGGL((k_round<TW, NV4, SMAX, S1NP, F32, SLOTS>), dim3(grid), dim3(threads), shm, st, d, round, drop, logits, A, An,
                        B, rv, nodes, row_stats, delta_nb, fx, tiles_n);
     return hipGetLastError();
 }
@@ -374,12 +379,19 @@ template <int TW, int NV4, int SMAX, int S1NP = 0>
 static hipError_t round_launch(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
                                AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
                                const FixedView &fx, int tiles_n = 0) {
-    if constexpr (S1NP == 0)   // (only bf16 models run without logits)
-        if (fx.f32)
-            return round_launch_t<TW, NV4, SMAX, S1NP, true>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats,
-                                                             delta_nb, fx, tiles_n);
-    return round_launch_t<TW, NV4, SMAX, S1NP, false>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb,
-                                                      fx, tiles_n);
+    const bool slots = fx.on && (d.N * TW + 1) * 64 <= 1024 && !row_stats && !delta_nb;
+#define TBS_ROUND_LAUNCH(F32, SLOTS)                                                                                     \
+    return round_launch_t<TW, NV4, SMAX, S1NP, F32, SLOTS>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats,    \
+                                                           delta_nb, fx, tiles_n)
+    if constexpr (S1NP == 0) {   // (only bf16 models run without logits)
+        if (fx.f32) {
+            if (slots) TBS_ROUND_LAUNCH(true, true);
+            TBS_ROUND_LAUNCH(true, false);
+        }
+    }
+    if (slots) TBS_ROUND_LAUNCH(false, true);
+    TBS_ROUND_LAUNCH(false, false);
+#undef TBS_ROUND_LAUNCH
 }
 
 hipError_t launch_round(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A, AView An,
