@@ -469,13 +469,17 @@ hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt
 }
 
 // ------------------------------------------------------------------ select + merge
-// Second half of the inner loop of Algorithm 1, one utterance per wave.  The
+// Second half of the inner loop of Algorithm 1, one utterance per workgroup of two
+// waves: the first stages the lists and merges the blank expansions while the
+// second ranks the candidates; the first goes on when both are done (a chain of
+// dependent instructions on either: 256 utterances N = 10 S = 3 14.2 us with one
+// wave, 11.8 with two, 64 utterances N = 5 S = 20 12.2 and 10.5).  The
 // utterance's B list, its A entries and its H*N candidates are staged in LDS
 // with one round of parallel loads, all list work happens there, and B and the
 // new A are written back once, so the kernel costs a handful of memory round
 // trips instead of one per list operation.
 
-__global__ void __launch_bounds__(WAVE)
+__global__ void __launch_bounds__(2 * WAVE)
 k_select_merge(Dims d, int round, int drop, const float *logits, const float *row_lc,
                const float *dphi, const float *cand_score, const int *cand_tok, AView A, AView An, BView B,
                RowView rv, const int2 *nodes) {
@@ -489,7 +493,14 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
     in.dphi = dphi + pair0;
     in.lc = row_lc + fg.urow0;
     in.slot_rows = 0;
-    select_merge_utt(0, d, round, drop, u, (int)threadIdx.x, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    const int lane = (int)threadIdx.x & (WAVE - 1);
+    const bool first = __builtin_amdgcn_readfirstlane((int)threadIdx.x) < WAVE;
+    if (first) select_merge_utt(1, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    __syncthreads();
+    if (first) select_merge_utt(4, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    else select_merge_utt(3, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    __syncthreads();
+    if (first) select_merge_utt(5, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
 }
 
 hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int drop, const float *logits,
@@ -506,7 +517,7 @@ hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int dro
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(k_select_merge, dim3(d.U), dim3(WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
+    hipLaunchKernelGGL(k_select_merge, dim3(d.U), dim3(2 * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
                        cand_score, cand_tok, A, An, B, rv, nodes);
     return hipGetLastError();
 }

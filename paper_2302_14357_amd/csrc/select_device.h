@@ -105,6 +105,7 @@ __device__ __forceinline__ void sel_rank(const double *v, int n, int lane, F fn)
 }
 
 #define SEL_PRE_FRAMES 8   // segments up to this long have their candidates' logits asked for ahead of the ranking
+#define SEL_PRE_CANDS (2 * WAVE)   // ... where there are at most this many candidates (N <= 11)
 
 struct SelectIn {
     const float *cand_score;
@@ -155,7 +156,8 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
     __shared__ double s_thr;
     __shared__ int s_have_thr;
     __shared__ float s_dnew[TBS_MAX_SEG * TBS_MAX_BEAM];   // frame distributions of the new hypotheses, [frame][hypothesis]
-    __shared__ float s_xpre[SEL_PRE_FRAMES * WAVE];        // logits of the candidates' tokens, [frame][candidate]
+    __shared__ float s_xpre[SEL_PRE_FRAMES * SEL_PRE_CANDS];   // logits of the candidates' tokens, [frame][candidate]
+    __shared__ int s_kh[TBS_MAX_BEAM], s_ktok[TBS_MAX_BEAM];   // kept candidates, by place: hypothesis they extend, token
     const int N = d.N;
     const int sp = fg.sp, cntA = fg.cntA, urow0 = fg.urow0, nB0 = fg.nB0, parity = fg.parity;
     const int H = sp > 0 ? cntA : 0;
@@ -198,25 +200,30 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
         if (PHASE == 0) sel_sync();   // (A's scores, staged just above, are read by other lanes below)
         const int nc = H * N;
         const float rcp_n = __builtin_amdgcn_rcpf((float)N);   // c / N as (c + 0.5) * (1 / N): exact for c < 1024
-        const bool pre_x = logits != nullptr && nc <= WAVE && sp <= SEL_PRE_FRAMES && !drop;
-        float xpre[SEL_PRE_FRAMES];
+        const bool pre_x = logits != nullptr && nc <= SEL_PRE_CANDS && sp <= SEL_PRE_FRAMES && !drop;
+        float xpre[2][SEL_PRE_FRAMES];
         if (do_cand) {
-            int tok_mine = -1;   // (token of candidate `lane`)
+            int tok_mine = -1, tok_mine2 = -1;   // (tokens of the candidates `lane` and `lane + 64`)
             for (int c = lane; c < nc; c += WAVE) {
                 const int tok = in.cand_tok[c];
                 if (c == lane) tok_mine = tok;
+                if (c == lane + WAVE) tok_mine2 = tok;
                 s_ctok[c] = tok;
                 s_key[c] = tok >= 0 ? s_alogs[(int)(((float)c + 0.5f) * rcp_n)] + (double)in.cand_score[c] : nan("");
             }
             // The d of a new hypothesis (below) needs the logits of its token at the S' frames.  Which
-            // candidates become hypotheses is known only after the ranking, so where a lane per candidate
-            // suffices the logits of every candidate's token are asked for now and wait in registers: their
+            // candidates become hypotheses is known only after the ranking, so where two candidates per lane
+            // suffice the logits of every candidate's token are asked for now and wait in registers: their
             // round trip runs beside the merge and the ranking instead of behind them.
             if (pre_x) {
-                const int c = min(lane, nc - 1), tokc = max(tok_mine, 0);
-                const float *lrow = logits + (long)(urow0 + (int)(((float)c + 0.5f) * rcp_n) * (in.slot_rows ? d.S : sp)) * d.Vl + tokc;
+                auto ask = [&](float (&x)[SEL_PRE_FRAMES], int c, int tok) {
+                    const float *lrow = logits + (long)(urow0 + (int)(((float)c + 0.5f) * rcp_n) * (in.slot_rows ? d.S : sp)) * d.Vl +
+                                        max(tok, 0);
 #pragma unroll
-                for (int q = 0; q < SEL_PRE_FRAMES; ++q) xpre[q] = lrow[(long)min(q, sp - 1) * d.Vl];
+                    for (int q = 0; q < SEL_PRE_FRAMES; ++q) x[q] = lrow[(long)min(q, sp - 1) * d.Vl];
+                };
+                ask(xpre[0], min(lane, nc - 1), tok_mine);
+                if (nc > WAVE) ask(xpre[1], min(lane + WAVE, nc - 1), tok_mine2);
             }
         }
         if (do_merge) {
@@ -297,7 +304,10 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
             });
             if (pre_x) {
 #pragma unroll
-                for (int q = 0; q < SEL_PRE_FRAMES; ++q) s_xpre[q * WAVE + lane] = xpre[q];
+                for (int q = 0; q < SEL_PRE_FRAMES; ++q) {
+                    s_xpre[q * SEL_PRE_CANDS + lane] = xpre[0][q];
+                    if (nc > WAVE) s_xpre[q * SEL_PRE_CANDS + WAVE + lane] = xpre[1][q];
+                }
             }
         }
         if (!do_finish) return;   // (the caller's barrier stands between the parts)
@@ -323,6 +333,10 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                 An.count[u] = total;
                 if (out) out->total = total;
             }
+            // Longer segments, or more candidates: a lane takes (hypothesis, frame) pairs, then the frames of one
+            // hypothesis after the other.  (A lane per hypothesis that walks its frames alone took three
+            // passes of up to S' dependent steps.)
+            const bool by_frame = logits != nullptr && !pre_x && sp <= WAVE;
             if (keep) {
                 const int c = s_sel[lane];
                 const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)N));   // c / N for c < 256
@@ -353,13 +367,16 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                 // banks) between the pass that reads the logits and the one that writes the normalised
                 // result: going through the result array itself cost two more memory round trips.
                 float *dh = An.dhat + an * d.S;
-                if (pre_x) {
+                if (by_frame) {
+                    s_kh[pos] = h;
+                    s_ktok[pos] = tok;
+                } else if (pre_x) {
                     // (the S' <= 8 values stay in registers)
                     float x[SEL_PRE_FRAMES];
                     float mx = -INFINITY;
 #pragma unroll
                     for (int q = 0; q < SEL_PRE_FRAMES; ++q) {
-                        x[q] = s_xpre[q * WAVE + c] + in.lc[h * sp + min(q, sp - 1)];
+                        x[q] = s_xpre[q * SEL_PRE_CANDS + c] + in.lc[h * sp + min(q, sp - 1)];
                         if (q < sp) mx = fmaxf(mx, x[q]);
                     }
                     float sum = 0.f;
@@ -395,6 +412,28 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                     // (a caller without logits has segments of one frame: d normalised over one frame is (1))
                     dh[0] = 0.f;
                     for (int t = 1; t < d.S; ++t) dh[t] = -INFINITY;
+                }
+            }
+            if (by_frame && total > 0) {   // (uniform)
+                sel_sync();
+                const float rcp_sp = __builtin_amdgcn_rcpf((float)sp);   // (exact quotients up to 32 x 64 items)
+#pragma unroll 4
+                for (int it = lane; it < total * sp; it += WAVE) {
+                    const int k = (int)(((float)it + 0.5f) * rcp_sp), t = it - k * sp, h = s_kh[k];
+                    s_dnew[t * TBS_MAX_BEAM + k] = logits[(long)(urow0 + h * (in.slot_rows ? d.S : sp) + t) * d.Vl + s_ktok[k]] +
+                                                   in.lc[h * sp + t];
+                }
+                sel_sync();
+                for (int k = 0; k < total; ++k) {
+                    const float x = lane < sp ? s_dnew[lane * TBS_MAX_BEAM + k] : -INFINITY;
+                    float mx = x;
+#pragma unroll
+                    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+                    float sum = lane < sp ? __expf(x - mx) : 0.f;
+#pragma unroll
+                    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+                    const float lz = mx + __logf(sum);
+                    for (int t = lane; t < d.S; t += WAVE) An.dhat[((long)u * N + k) * d.S + t] = t < sp ? x - lz : -INFINITY;
                 }
             }
         }

@@ -358,6 +358,17 @@ def test_decode_fp32_fixed_places(d, hidden, layers, V, U, N, S, debug):
     _check_decode(shape, model, offsets, enc, N, S, debug=debug)
 
 
+@pytest.mark.parametrize("N,S", [(8, 3), (9, 5), (11, 8), (12, 8), (12, 2), (16, 5), (3, 9), (2, 64), (2, 65)])
+def test_decode_select_forms(N, S):
+    """The frame distributions of new hypotheses: from logits asked for ahead of the ranking (one or two
+    candidates a lane: beams to 8 and to 11, segments to 8 frames), by (hypothesis, frame) pairs (to 64
+    frames) and by a lane per hypothesis; on each side of the lines, in both layouts where both serve."""
+    shape = _peaked(small_bf16_shape(n_utts=3, vocab=64, d=128, hidden=128), 4.0, 6.0)
+    model, offsets, enc = build_case(shape, n_utts=3, lengths=np.array([S + 3, 2 * S, max(S - 1, 1)]))
+    for debug in (0, 256):   # (256: row lists also for small batches)
+        _check_decode(shape, model, offsets, enc, N, S, max_rounds=4, debug=debug)
+
+
 def test_decode_peaked_model_librispeech_widths():
     """The same at the headline widths (Dj=512, V=1024, LSTM 640, N=5, S=3)."""
     import dataclasses
