@@ -38,12 +38,14 @@ __device__ __forceinline__ typename RoundPiece<F32>::type round_piece(const floa
 // A launch runs through its code once, so what other callers need stands in its way: with everything in one
 // body the kernel was 36 KB, with only its own form it is 24 KB, and the four kernels of a round together fit
 // the 64 KB instruction cache (per launch: 64 utterances S = 3 13.1 -> 11.3-12.1 us, one utterance 11.2 ->
-// 10.4, 37 utterances N = 10 S = 5 21.3 -> 19.8).
-template <int TW, int NV4, int SMAX, int S1NP, bool F32, bool SLOTS>
+// 10.4, 37 utterances N = 10 S = 5 21.3 -> 19.8).  SLOTS = 2: beams up to 8 besides, whose candidates are at most
+// one a lane (with the forms for more of them in the body, one utterance decoded in 10.26 instead of 9.74 ms).
+template <int TW, int NV4, int SMAX, int S1NP, bool F32, int SLOTS>
 __global__ void __launch_bounds__(1024)
 k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, AView An, BView B, RowView rv,
         int2 *nodes, float *__restrict__ row_stats_arg, float *__restrict__ delta_nb_arg, FixedView fx, int tiles_n) {
     const bool on = SLOTS || fx.on;
+    constexpr bool FEW = SLOTS == 2;
     float *row_stats = SLOTS ? nullptr : row_stats_arg, *delta_nb = SLOTS ? nullptr : delta_nb_arg;
     constexpr int TT = TW * 64;
     typedef typename RoundPiece<F32>::type XP;
@@ -151,7 +153,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool pre_h = on && fx.xh && H4 <= TT * HP;
     float4 hpar[HP];
     if (own_wave && sel_wave) {
-        select_merge_utt(1, d, round, drop, u, sel_lane, logits, in, fg, A, An, B, rv, nodes, s_raw, &s_out);
+        select_merge_utt(1, d, round, drop, u, sel_lane, logits, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
         if constexpr (S1NP == 0) {
 #pragma unroll
             for (int b = 0; b < EXPAND_PAIR_BARRIERS; ++b) __syncthreads();
@@ -265,13 +267,13 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const float *lg = S1NP > 0 ? nullptr : logits;   // (no logits: d of a new hypothesis over one frame is (1))
     if (own_wave) {
         if (sel_wave)
-            select_merge_utt(4, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out);
+            select_merge_utt(4, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
         else if ((int)threadIdx.x < WAVE)
-            select_merge_utt(3, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out);
+            select_merge_utt(3, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
         __syncthreads();
     }
     if (sel_wave) {
-        select_merge_utt(own_wave ? 5 : 0, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out);
+        select_merge_utt(own_wave ? 5 : 0, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
         if (on) {
             // Slot layout: what a row list kernel would do for this utterance.  The new hypotheses
             // take trie nodes from the utterance's own range, their pairs get their descriptors, the
@@ -354,7 +356,7 @@ static int round_variant(const Dims &d) {
 
 bool round_fits(const Dims &d) { return round_variant(d) != 0; }
 
-template <int TW, int NV4, int SMAX, int S1NP, bool F32, bool SLOTS>
+template <int TW, int NV4, int SMAX, int S1NP, bool F32, int SLOTS>
 static hipError_t round_launch_t(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
                                AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
                                const FixedView &fx, int tiles_n) {
@@ -387,12 +389,14 @@ static hipError_t round_launch(hipStream_t st, const Dims &d, int round, int dro
                                                            delta_nb, fx, tiles_n)
     if constexpr (S1NP == 0) {   // (only bf16 models run without logits)
         if (fx.f32) {
-            if (slots) TBS_ROUND_LAUNCH(true, true);
-            TBS_ROUND_LAUNCH(true, false);
+            if (slots && d.N <= 8) TBS_ROUND_LAUNCH(true, 2);
+            if (slots) TBS_ROUND_LAUNCH(true, 1);
+            TBS_ROUND_LAUNCH(true, 0);
         }
     }
-    if (slots) TBS_ROUND_LAUNCH(false, true);
-    TBS_ROUND_LAUNCH(false, false);
+    if (slots && d.N <= 8) TBS_ROUND_LAUNCH(false, 2);
+    if (slots) TBS_ROUND_LAUNCH(false, 1);
+    TBS_ROUND_LAUNCH(false, 0);
 #undef TBS_ROUND_LAUNCH
 }
 

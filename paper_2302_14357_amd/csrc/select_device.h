@@ -129,6 +129,7 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
     return f;
 }
 
+// FEW (a constant): at most a wave's width of candidates and SEL_PRE_FRAMES frames, known when the code is made.
 // s_dyn: LDS for the utterance's B list, BCAP * (8 + 8 + 3 * 4) bytes, 16-byte aligned.
 // phase 0: the whole step.  phase 1: only what does not depend on the expansion (B and A staged in
 // LDS); phase 2: the rest, by the same wave: a caller whose expansion runs in the same kernel does
@@ -139,7 +140,8 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
 __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d, int round, int drop, int u, int lane,
                                                  const float *logits, SelectIn in, const SelectFigs &fg, AView A,
                                                  AView An, BView B, RowView rv, const int2 *nodes,
-                                                 unsigned char *s_dyn, SelectOut *out = nullptr) {
+                                                 unsigned char *s_dyn, SelectOut *out = nullptr,
+                                                 const bool FEW = false) {
     double *s_blogs = reinterpret_cast<double *>(s_dyn);
     u64 *s_bhash = reinterpret_cast<u64 *>(s_blogs + d.BCAP);
     int *s_bnode = reinterpret_cast<int *>(s_bhash + d.BCAP);
@@ -200,7 +202,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
         if (PHASE == 0) sel_sync();   // (A's scores, staged just above, are read by other lanes below)
         const int nc = H * N;
         const float rcp_n = __builtin_amdgcn_rcpf((float)N);   // c / N as (c + 0.5) * (1 / N): exact for c < 1024
-        const bool pre_x = logits != nullptr && nc <= SEL_PRE_CANDS && sp <= SEL_PRE_FRAMES && !drop;
+        const bool pre_x = FEW ? logits != nullptr && !drop : logits != nullptr && nc <= SEL_PRE_CANDS && sp <= SEL_PRE_FRAMES && !drop;
         float xpre[2][SEL_PRE_FRAMES];
         if (do_cand) {
             int tok_mine = -1, tok_mine2 = -1;   // (tokens of the candidates `lane` and `lane + 64`)
@@ -223,7 +225,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                     for (int q = 0; q < SEL_PRE_FRAMES; ++q) x[q] = lrow[(long)min(q, sp - 1) * d.Vl];
                 };
                 ask(xpre[0], min(lane, nc - 1), tok_mine);
-                if (nc > WAVE) ask(xpre[1], min(lane + WAVE, nc - 1), tok_mine2);
+                if (!FEW && nc > WAVE) ask(xpre[1], min(lane + WAVE, nc - 1), tok_mine2);
             }
         }
         if (do_merge) {
@@ -306,7 +308,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
 #pragma unroll
                 for (int q = 0; q < SEL_PRE_FRAMES; ++q) {
                     s_xpre[q * SEL_PRE_CANDS + lane] = xpre[0][q];
-                    if (nc > WAVE) s_xpre[q * SEL_PRE_CANDS + WAVE + lane] = xpre[1][q];
+                    if (!FEW && nc > WAVE) s_xpre[q * SEL_PRE_CANDS + WAVE + lane] = xpre[1][q];
                 }
             }
         }
@@ -336,7 +338,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
             // Longer segments, or more candidates: a lane takes (hypothesis, frame) pairs, then the frames of one
             // hypothesis after the other.  (A lane per hypothesis that walks its frames alone took three
             // passes of up to S' dependent steps.)
-            const bool by_frame = logits != nullptr && !pre_x && sp <= WAVE;
+            const bool by_frame = !FEW && logits != nullptr && !pre_x && sp <= WAVE;
             if (keep) {
                 const int c = s_sel[lane];
                 const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)N));   // c / N for c < 256
@@ -388,7 +390,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                     for (int q = 0; q < SEL_PRE_FRAMES; ++q)
                         if (q < d.S) dh[q] = q < sp ? x[q] - lz : -INFINITY;
                     for (int t = SEL_PRE_FRAMES; t < d.S; ++t) dh[t] = -INFINITY;
-                } else if (logits) {
+                } else if (!FEW && logits) {
                     float *sd = s_dnew + lane;
                     float mx = -INFINITY;
                     for (int t0 = 0; t0 < sp; t0 += 8) {   // (eight logits asked for before the first is used)
