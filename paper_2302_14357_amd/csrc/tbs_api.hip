@@ -63,6 +63,8 @@ struct tbs_ctx {
     bool expanded_ahead; // tbs_joiner_segment already ran the expansion, piece by piece behind the GEMM of each piece
     // slot layout (small shapes inside tbs_decode / tbs_push_segment, see FixedView)
     bool fixed;         // the current batch runs in the slot layout
+    bool no_slots;      // this decode is to run with row lists (see tbs_decode)
+    bool trie_full;     // an utterance's range of the trie was full
     bool s1;            // ... with segments of one frame and no logits (the joiner GEMM keeps row partials)
     float *part;        // [U*N, tiles of 64 columns, part_width(N)] row partials (seg_s = 1 only)
     int *utt_fig;       // [U, TBS_FIG_SIZE] each utterance's figures for the round kernel, among them its range of the trie
@@ -297,7 +299,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->last_hip = 0;
     c->h_counts = nullptr;
     c->h_live = nullptr;
-    c->fixed = false;
+    c->fixed = c->no_slots = c->trie_full = false;
     c->h_desc = nullptr;
     c->d_desc = nullptr;
     c->stream_enc = c->stream_tmp = nullptr;
@@ -562,8 +564,14 @@ static bool one_frame_ok(const tbs_ctx *c) {
     return !round_fits(d) || d.N <= 4 || (c->cfg.debug & 32768);
 }
 
+// fp32 models and vocabularies that are no whole 16-byte pieces take this layout for its speed only: where
+// its trie, an even share per utterance, does not hold what one trie for all would, they go without it
+// (a stream, whose lengths nobody knows, from the start; a decode is run again, see tbs_decode).
+static bool slots_by_choice(const tbs_ctx *c) { return c->cfg.dtype != 1 || c->cur.Vl != c->cur.V; }
+
 static bool fixed_layout_ok(const tbs_ctx *c) {
     const Dims &d = c->cur;
+    if (c->no_slots || (c->streaming && slots_by_choice(c))) return false;
     if ((c->cfg.debug & (2 | 8 | 16 | 32 | 64 | 128 | 256)) || c->cfg.joiner_chunk_rows > 0) return false;
     if ((d.H & 3) || (long)d.max_nodes - 1 < (long)d.U) return false;
     return (round_fits(d) || one_frame_ok(c)) && joiner_small(c, d.U * d.N * d.S, true) &&
@@ -631,6 +639,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->n_launches = 0;
     c->n_frames = frames;
     c->state = ST_BEGUN;
+    c->trie_full = false;
     c->fixed = fixed_layout_ok(c);
     c->s1 = c->fixed && one_frame_ok(c);
     return TBS_OK;
@@ -1256,7 +1265,10 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
         if (c->prof_kernel == TBS_K_PREDICTOR) c->prof_units += total;
         c->live_u = made;
         c->h_counts[TBS_CNT_PAIRS] = total;
-        if (full) return TBS_EOVERFLOW;
+        if (full) {
+            c->trie_full = true;
+            return TBS_EOVERFLOW;
+        }
         if (total == 0) break;
     }
     c->h_counts[TBS_CNT_ROWS] = 0;
@@ -1364,8 +1376,7 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
     return check_err_flags(c);
 }
 
-int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, int32_t U, int32_t *tokens,
-               int32_t *lens, double *logscores, int32_t *nbest_count, int32_t max_len) {
+static int decode_all(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, int32_t U) {
     int rc = tbs_begin(c, enc_proj, frame_offsets, U);
     if (rc) return rc;
     const int S = c->cur.S;
@@ -1373,6 +1384,18 @@ int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, i
     for (int seg = 0; seg < nseg; ++seg) {          // while t <= Length(enc)
         if ((rc = run_segment(c, seg))) return rc;
     }
+    return TBS_OK;
+}
+
+int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, int32_t U, int32_t *tokens,
+               int32_t *lens, double *logscores, int32_t *nbest_count, int32_t max_len) {
+    int rc = decode_all(c, enc_proj, frame_offsets, U);
+    if (rc == TBS_EOVERFLOW && c->trie_full && slots_by_choice(c)) {   // one trie for all utterances may hold them
+        c->no_slots = true;
+        rc = decode_all(c, enc_proj, frame_offsets, U);
+        c->no_slots = false;
+    }
+    if (rc) return rc;
     return tbs_result(c, tokens, lens, logscores, nbest_count, max_len);
 }
 

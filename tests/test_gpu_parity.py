@@ -358,6 +358,39 @@ def test_decode_fp32_fixed_places(d, hidden, layers, V, U, N, S, debug):
     _check_decode(shape, model, offsets, enc, N, S, debug=debug)
 
 
+@pytest.mark.parametrize("dtype,V", [("f32", 64), ("bf16", 63)])
+def test_small_trie_that_one_list_of_nodes_fits(dtype, V):
+    """A trie just large enough for all utterances together, too small for an even share of each: fp32 models
+    and vocabularies that are no whole 16-byte pieces then decode with row lists, to the same result; a stream of theirs
+    runs with row lists from the start."""
+    import dataclasses
+    N, S = 4, 3
+    shape = dataclasses.replace(small_bf16_shape(n_utts=5, vocab=V, d=128, hidden=128), dtype=dtype)
+    model, offsets, enc = build_case(shape, n_utts=5, lengths=np.array([3, 40, 8, 21, 13]))
+
+    def run(**kw):
+        """(token sequences, slot layout?) or None where the trie is too small"""
+        try:
+            got, st = _gpu_decode(shape, model, offsets, enc, N, S, **kw)
+        except RuntimeError:
+            return None
+        return [[y for y, _ in u] for u in got], st["path"]["fixed_places"]
+
+    want, slots = run()
+    assert slots
+    lo, hi = 16, 4 * N * (85 + 5 * S) + 16   # (row lists with lo nodes overflow, with hi they do not)
+    assert run(max_nodes=lo, debug=256) is None and run(max_nodes=hi, debug=256) == (want, False)
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if run(max_nodes=mid, debug=256) is None else (lo, mid)
+    assert run(max_nodes=hi) == (want, False)
+    assert run(max_nodes=lo) is None
+    tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=8)
+    tbs.stream_begin(5)
+    assert not tbs.path()["fixed_places"]
+    tbs.close()
+
+
 @pytest.mark.parametrize("N,S", [(8, 3), (9, 5), (11, 8), (12, 8), (12, 2), (16, 5), (3, 9), (2, 64), (2, 65)])
 def test_decode_select_forms(N, S):
     """The frame distributions of new hypotheses: from logits asked for ahead of the ranking (one or two
