@@ -73,6 +73,7 @@ struct tbs_ctx {
     int *h_live_dev;    // device view of the same memory
     std::vector<int> live_u;   // hypotheses each utterance takes into the coming round
     int64_t fx_calls, fx_joined;   // joiner invocations and frames joined, counted on the host in this layout
+    int fx_nodes;                  // and trie nodes taken
     int2 *nodes;
     long pool_rows;
     float *pool_p, *pool_h, *pool_c;
@@ -605,6 +606,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     HIPCHK(c, hipMemsetAsync(c->live_sum, 0, sizeof(int) * 2, c->stream));
     memset(c->h_live, 0, 2 * sizeof(int) * (size_t)c->d.U);
     c->fx_calls = c->fx_joined = 0;
+    c->fx_nodes = 0;
     // Slot layout: every utterance takes trie nodes from a range of its own, sized in proportion to
     // its length (a stream's utterances, whose lengths are not known, share equally); node 0 is the root.
     std::vector<int> fig((size_t)U * TBS_FIG_SIZE, 0);
@@ -1269,6 +1271,7 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
             c->trie_full = true;
             return TBS_EOVERFLOW;
         }
+        c->fx_nodes += total;
         if (total == 0) break;
     }
     c->h_counts[TBS_CNT_ROWS] = 0;
@@ -1401,9 +1404,10 @@ int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, i
 
 int tbs_stats(const tbs_ctx *c, int64_t *joiner_calls, int64_t *joined_frames, int64_t *frames, int64_t *launches) {
     if (!c) return TBS_EINVAL;
-    // (running sums kept by the row list kernel, as of the last counts the host waited for)
-    if (joiner_calls) *joiner_calls = c->fixed ? c->fx_calls : c->h_counts[TBS_CNT_ACC_CALLS];
-    if (joined_frames) *joined_frames = c->fixed ? c->fx_joined : c->h_counts[TBS_CNT_ACC_JOINED];
+    // (what the host counted in the slot layout and the running sums of the row list kernel, as of the last counts the
+    // host waited for: a batch that would run in the slot layout has row lists where the caller drives the steps)
+    if (joiner_calls) *joiner_calls = c->fx_calls + c->h_counts[TBS_CNT_ACC_CALLS];
+    if (joined_frames) *joined_frames = c->fx_joined + c->h_counts[TBS_CNT_ACC_JOINED];
     if (frames) *frames = c->n_frames;
     if (launches) *launches = c->n_launches;
     return TBS_OK;
@@ -1466,6 +1470,7 @@ int tbs_debug_read(tbs_ctx *c, int32_t which, void *dst, size_t bytes) {
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (tmp) (void)hipFree(tmp);
     HIPCHK(c, e);
+    if (which == TBS_BUF_COUNTS && n >= 3 * sizeof(int)) ((int *)dst)[2] += c->fx_nodes;   // (the slot layout's ranges)
     if (which == TBS_BUF_A_DHAT) {   // kept as logarithms, handed out as plain values
         float *v = (float *)dst;
         for (size_t i = 0; i < n / sizeof(float); ++i) v[i] = expf(v[i]);

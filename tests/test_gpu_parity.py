@@ -358,6 +358,37 @@ def test_decode_fp32_fixed_places(d, hidden, layers, V, U, N, S, debug):
     _check_decode(shape, model, offsets, enc, N, S, debug=debug)
 
 
+@pytest.mark.parametrize("dtype,V,S", [("f32", 64, 3), ("bf16", 64, 3), ("bf16", 63, 3), ("bf16", 63, 1)])
+def test_counters_of_steps_driven_by_the_caller(dtype, V, S):
+    """tbs_stats, and the trie nodes of TBS_BUF_COUNTS, say the same whether the step functions or tbs_decode ran the
+    batch, and in which layout (a batch that tbs_decode would run in the slot layout has row lists when stepped)."""
+    import dataclasses
+    N = 4
+    shape = dataclasses.replace(small_bf16_shape(n_utts=3, vocab=V, d=128, hidden=128), dtype=dtype)
+    model, offsets, enc = build_case(shape, n_utts=3, lengths=np.array([7, 4, 11]))
+    seen = []
+    for debug, steps in ((256, False), (0, False), (0, True)):
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug)
+        frames = tbs.upload_frames(enc)
+        if steps:
+            tbs.begin(frames, offsets)
+            for seg in range(-(-11 // S)):
+                rows = tbs.segment_begin(seg)
+                while rows > 0:
+                    tbs.joiner_segment()
+                    tbs.expand()
+                    tbs.select_merge()
+                    tbs.predictor_step()
+                    rows = tbs.counts()["rows"]
+        else:
+            tbs.decode(frames, offsets)
+            assert tbs.path()["fixed_places"] == (debug == 0)
+        seen.append((tbs.stats(), tbs.counts()["nodes"]))
+        tbs.close()
+    assert seen[0][0]["joiner_calls"] > 0 and seen[0][1] > 1
+    assert seen[0] == seen[1] == seen[2]
+
+
 @pytest.mark.parametrize("dtype,V", [("f32", 64), ("bf16", 63)])
 def test_small_trie_that_one_list_of_nodes_fits(dtype, V):
     """A trie just large enough for all utterances together, too small for an even share of each: fp32 models
