@@ -558,21 +558,23 @@ static bool proj_small(const tbs_ctx *c, int M, bool slots) {
 // 34.0 / 37.0, N = 10: 47.0 / 47.3.  The logits of a small batch never leave the cache, and picking the N
 // best of every 16 logits costs the GEMM N rounds of a 16-way arg-max: the partials serve beams up to 4,
 // the vocabularies the form with logits cannot hold, and debug bit 15.
-static bool one_frame_ok(const tbs_ctx *c) {
+static bool one_frame_fits(const tbs_ctx *c) {
     const Dims &d = c->cur;
-    if (!c->part || (c->cfg.debug & (1 | 512)) || !round_s1_fits(d) || !gemm_part_fits(d.U * d.N, d.V, d.Dj, d.N, GS_TILES_FIXED))
-        return false;
-    return !round_fits(d) || d.N <= 4 || (c->cfg.debug & 32768);
+    return c->part && !(c->cfg.debug & (1 | 512)) && round_s1_fits(d) && gemm_part_fits(d.U * d.N, d.V, d.Dj, d.N, GS_TILES_FIXED);
+}
+static bool one_frame_ok(const tbs_ctx *c) {
+    return one_frame_fits(c) && (!round_fits(c->cur) || c->cur.N <= 4 || (c->cfg.debug & 32768));
 }
 
 // fp32 models and vocabularies that are no whole 16-byte pieces take this layout for its speed only: where
-// its trie, an even share per utterance, does not hold what one trie for all would, they go without it
-// (a stream, whose lengths nobody knows, from the start; a decode is run again, see tbs_decode).
+// its trie, a share per utterance, does not hold what one trie for all would, they go without it (a stream,
+// whose lengths nobody knows, from the start; a decode is run again, see tbs_decode).  Not so the streams of
+// bf16 models with segments of one frame: the form without logits serves every vocabulary in this layout.
 static bool slots_by_choice(const tbs_ctx *c) { return c->cfg.dtype != 1 || c->cur.Vl != c->cur.V; }
 
 static bool fixed_layout_ok(const tbs_ctx *c) {
     const Dims &d = c->cur;
-    if (c->no_slots || (c->streaming && slots_by_choice(c))) return false;
+    if (c->no_slots || (c->streaming && slots_by_choice(c) && !one_frame_fits(c))) return false;
     if ((c->cfg.debug & (2 | 8 | 16 | 32 | 64 | 128 | 256)) || c->cfg.joiner_chunk_rows > 0) return false;
     if ((d.H & 3) || (long)d.max_nodes - 1 < (long)d.U) return false;
     return (round_fits(d) || one_frame_ok(c)) && joiner_small(c, d.U * d.N * d.S, true) &&

@@ -610,6 +610,22 @@ def test_streaming_in_pieces_equals_decode(N, S, pieces):
     _check_decode(shape, model, offsets, enc, N, S)
 
 
+@pytest.mark.parametrize("N,V", [(3, 63), (5, 63), (4, 1030), (6, 1030)])
+def test_streams_of_single_frames_in_fixed_places(N, V):
+    """Segments of one frame of a bf16 model run in the slot layout whatever the vocabulary, as a stream too (the form
+    without logits serves any), and a stream gives what the whole decode gives."""
+    shape = small_bf16_shape(n_utts=3, vocab=V, d=128, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=3, lengths=np.array([7, 1, 12]))
+    whole, st = _gpu_decode(shape, model, offsets, enc, N, 1)
+    assert st["path"]["fixed_places"]
+    tbs = make_tbs(shape, model, offsets, N, 1, stream_buffer_frames=4)
+    _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: 1 + (u + c) % 3)
+    assert tbs.path() == st["path"]
+    assert tbs.result() == whole
+    tbs.close()
+    _check_decode(shape, model, offsets, enc, N, 1)
+
+
 def test_streaming_partial_results_and_limits():
     """Between pushes B holds the result for the frames decoded so far: with no flush, that is the
     decode of each utterance's whole segments.  A push beyond the buffer is refused and
