@@ -63,8 +63,9 @@ struct tbs_ctx {
     bool expanded_ahead; // tbs_joiner_segment already ran the expansion, piece by piece behind the GEMM of each piece
     // slot layout (small shapes inside tbs_decode / tbs_push_segment, see FixedView)
     bool fixed;         // the current batch runs in the slot layout
-    bool no_slots;      // this decode is to run with row lists (see tbs_decode)
     bool trie_full;     // an utterance's range of the trie was full
+    double trie_share;  // trie nodes of the batch per frame (and S frames more per utterance)
+    double full_share;  // the largest such share that did not suffice (see slots_by_choice)
     bool s1;            // ... with segments of one frame and no logits (the joiner GEMM keeps row partials)
     float *part;        // [U*N, tiles of 64 columns, part_width(N)] row partials (seg_s = 1 only)
     int *utt_fig;       // [U, TBS_FIG_SIZE] each utterance's figures for the round kernel, among them its range of the trie
@@ -300,7 +301,8 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->last_hip = 0;
     c->h_counts = nullptr;
     c->h_live = nullptr;
-    c->fixed = c->no_slots = c->trie_full = false;
+    c->fixed = c->trie_full = false;
+    c->trie_share = c->full_share = 0.0;
     c->h_desc = nullptr;
     c->d_desc = nullptr;
     c->stream_enc = c->stream_tmp = nullptr;
@@ -567,14 +569,19 @@ static bool one_frame_ok(const tbs_ctx *c) {
 }
 
 // fp32 models and vocabularies that are no whole 16-byte pieces take this layout for its speed only: where
-// its trie, a share per utterance, does not hold what one trie for all would, they go without it (a stream,
-// whose lengths nobody knows, from the start; a decode is run again, see tbs_decode).  Not so the streams of
-// bf16 models with segments of one frame: the form without logits serves every vocabulary in this layout.
+// its trie, a share per utterance, may not hold what one trie for all would, they go without it.  A stream,
+// whose lengths nobody knows, does so from the start, and so does a batch with less of a trie than the default
+// sizing gives it; a decode that finds an utterance's share full all the same is run again with row lists (see
+// tbs_decode), and the context then keeps batches of no larger shares there.  bf16 models with segments of one
+// frame are not asked: the form without logits serves every vocabulary in this layout.
 static bool slots_by_choice(const tbs_ctx *c) { return c->cfg.dtype != 1 || c->cur.Vl != c->cur.V; }
 
 static bool fixed_layout_ok(const tbs_ctx *c) {
     const Dims &d = c->cur;
-    if (c->no_slots || (c->streaming && slots_by_choice(c) && !one_frame_fits(c))) return false;
+    if (slots_by_choice(c)) {
+        if (c->trie_share <= c->full_share) return false;
+        if (!one_frame_fits(c) && (c->streaming || c->trie_share < 4.0 * d.N)) return false;
+    }
     if ((c->cfg.debug & (2 | 8 | 16 | 32 | 64 | 128 | 256)) || c->cfg.joiner_chunk_rows > 0) return false;
     if ((d.H & 3) || (long)d.max_nodes - 1 < (long)d.U) return false;
     return (round_fits(d) || one_frame_ok(c)) && joiner_small(c, d.U * d.N * d.S, true) &&
@@ -626,6 +633,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
             fig[(size_t)u * TBS_FIG_SIZE + TBS_FIG_CAP] = (int)(n < 0 ? 0 : n);
             at += n < 0 ? 0 : n;
         }
+        c->trie_share = (double)pool / weight_all;
     }
     HIPCHK(c, hipMemcpyAsync(c->utt_fig, fig.data(), sizeof(int) * fig.size(), hipMemcpyHostToDevice, c->stream));
     // the host arrays above are read by the copies: finish them before returning
@@ -1394,11 +1402,15 @@ static int decode_all(tbs_ctx *c, const void *enc_proj, const int32_t *frame_off
 
 int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, int32_t U, int32_t *tokens,
                int32_t *lens, double *logscores, int32_t *nbest_count, int32_t max_len) {
+    if (!c) return TBS_EINVAL;
+    const int64_t units0 = c->prof_units;
+    const size_t ev0 = c->ev_used;
     int rc = decode_all(c, enc_proj, frame_offsets, U);
     if (rc == TBS_EOVERFLOW && c->trie_full && slots_by_choice(c)) {   // one trie for all utterances may hold them
-        c->no_slots = true;
+        c->full_share = std::max(c->full_share, c->trie_share);        // (this batch and its like: row lists from here on)
+        c->prof_units = units0;
+        c->ev_used = ev0;
         rc = decode_all(c, enc_proj, frame_offsets, U);
-        c->no_slots = false;
     }
     if (rc) return rc;
     return tbs_result(c, tokens, lens, logscores, nbest_count, max_len);

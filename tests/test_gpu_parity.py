@@ -422,6 +422,77 @@ def test_small_trie_that_one_list_of_nodes_fits(dtype, V):
     tbs.close()
 
 
+@pytest.mark.parametrize("dtype,V", [("f32", 64), ("bf16", 63)])
+def test_small_trie_is_decoded_once(dtype, V):
+    """A context whose trie is smaller than the default sizing: fp32 models and vocabularies that are no whole pieces run
+    every decode once, with row lists (counted by the work of the joiner launches)."""
+    import dataclasses
+    from paper_2302_14357_amd.tbs import KERNEL
+    N, S = 4, 3
+    shape = dataclasses.replace(small_bf16_shape(n_utts=5, vocab=V, d=128, hidden=128), dtype=dtype)
+    model, offsets, enc = build_case(shape, n_utts=5, lengths=np.array([3, 40, 8, 21, 13]))
+
+    def work(**kw):
+        tbs = make_tbs(shape, model, offsets, N, S, **kw)
+        frames, seen = tbs.upload_frames(enc), []
+        tbs.decode(frames, offsets)
+        nodes = tbs.counts()["nodes"]
+        tbs.profile_select(KERNEL.JOINER)
+        for _ in range(2):
+            tbs.decode(frames, offsets)
+            p = tbs.profile_read()
+            seen.append((p["launches"], p["units"]))
+        assert not tbs.path()["fixed_places"]
+        tbs.close()
+        return nodes, seen
+
+    nodes, want = work(debug=256)
+    assert work(debug=256, max_nodes=nodes + 1) == (nodes, want)   # (as many nodes as one trie for all needs)
+    assert work(max_nodes=nodes + 1) == (nodes, want)
+
+
+def test_share_of_the_trie_that_was_too_small_is_remembered():
+    """One utterance that emits more than its share of a trie of the default size: the first decode falls back to row
+    lists, and its work is counted once; later ones of no larger shares start with row lists; a batch with larger shares
+    runs in the slot layout again."""
+    import dataclasses
+    from paper_2302_14357_amd.tbs import KERNEL
+    N, S, U, cap = 2, 1, 9, 24
+    shape = dataclasses.replace(small_bf16_shape(n_utts=U, vocab=32, d=64, hidden=64), dtype="f32", act="relu")
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=np.full(U, 6))
+    # (a blank logit that the frames alone decide: the first utterance's make it hopeless, the others' certain)
+    model["w_out"] = np.zeros_like(model["w_out"])
+    model["w_out"][0, :] = 0.5
+    model["b_out"] = np.linspace(0.0, 0.3, 32).astype(np.float32)
+    model["b_out"][0] = -60.0
+    enc = np.full_like(enc, 8.0)
+    enc[:6] = -64.0
+
+    def contexts(debug, lens):
+        tbs = make_tbs(shape, model, offsets, N, S, max_rounds_per_segment=cap, debug=debug, max_utts=U,
+                       max_frames_total=int(offsets[-1]))
+        tbs.profile_select(KERNEL.JOINER)
+        out = []
+        for T in lens:
+            off = np.concatenate([[0], np.cumsum(T)]).astype(np.int32)
+            got = tbs.decode(tbs.upload_frames(enc[:off[-1]]), off)
+            p = tbs.profile_read()
+            out.append((got, p["units"], tbs.path()["fixed_places"]))
+        tbs.close()
+        return out
+
+    whole = np.full(U, 6)
+    # (alone and two frames long, the first utterance has the whole trie: its share is larger than it needs)
+    lists = contexts(256, [whole, whole, np.array([2])])
+    slots = contexts(0, [whole, whole, np.array([2])])
+    assert [s[2] for s in slots] == [False, False, True]
+    for a, b in zip(lists, slots):
+        assert a[1] == b[1]
+        for x, y in zip(a[0], b[0]):
+            assert [h[0] for h in x] == [h[0] for h in y]
+            np.testing.assert_allclose([h[1] for h in x], [h[1] for h in y], rtol=1e-5, atol=1e-5)
+
+
 @pytest.mark.parametrize("N,S", [(8, 3), (9, 5), (11, 8), (12, 8), (12, 2), (16, 5), (3, 9), (2, 64), (2, 65)])
 def test_decode_select_forms(N, S):
     """The frame distributions of new hypotheses: from logits asked for ahead of the ranking (one or two
