@@ -350,6 +350,29 @@ static void expand_reg_launch(hipStream_t st, const Dims &d, int pairs, const fl
                        cand_score, cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
 }
 
+// The kernel that expands segments of S frames of logit rows of Vl floats (tests ask it by this name).
+// Register forms (EXPAND_REG: 16-byte pieces a thread, most frames): the whole hypothesis in the registers of four waves.
+// Longer segments of a vocabulary that fits a lane's four pieces (EXPAND_LONG: pieces a lane, rows a wave): two rows a
+// wave up to 32 frames, four up to 64 (a workgroup has at most 16 waves).  Measured on the Librispeech-like batch of 64
+// at N = 5 (ms per decode; one / two / four rows a wave; four waves with eight / sixteen frames' columns in registers):
+// S = 6: 19.6 / 19.7 / 19.8 / 20.3 / 21.7, 8: 19.3 / 19.5 / - / 20.0 / 21.3, 12: 19.7 / 19.7 / 19.8 / - / 21.8, 16: 20.4 /
+// 20.4 / 20.6 / - / 22.7, 20: - / 21.8 / 22.1, 32: - / 24.4 / 24.5; the two-pass kernel took 28.0 at 20, 33.5 at 32 and
+// 44.3 (four rows a wave 30.9) at 50.  S = 8 elsewhere (two rows a wave / eight frames in registers): 4 utterances
+// 15.3 / 16.0, 200 25.9 / 27.0, 320 32.2 / 33.6, V = 500 20.0 / 20.8, V = 200 19.8 / 20.9, N = 10 26.0 / 27.0, 1000 shorter
+// utterances at N = 10 36.4 / 37.3.  (The body for 2048 columns, half of them copies here: 20.7 at S = 6, 20.4 at 8.)
+extern "C" int expand_form(int Vl, int S) {
+    const int nv4 = (Vl / 4 + EXP_THREADS - 1) / EXP_THREADS;
+    if (nv4 <= 1) {
+        if (S <= 3) return EXPAND_REG(1, 3);
+        if (S <= 5) return EXPAND_REG(1, 5);
+        if (S <= LONG_FRAMES) return EXPAND_LONG(Vl <= 256 ? 1 : (Vl <= 512 ? 2 : 4), S <= 32 ? 2 : 4);
+    }
+    if (nv4 <= 2 && S <= 8) return EXPAND_REG(2, 8);
+    if (nv4 <= 4 && S <= 3) return EXPAND_REG(4, 3);
+    if (nv4 <= 4 && S <= 5) return EXPAND_REG(4, 5);
+    return EXPAND_TWO_PASS;
+}
+
 hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                          float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
                          float *delta_nb, int force_generic, const int *pairs_dev, int pair_base) {
@@ -357,37 +380,24 @@ hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *
     if (pairs_dev && pair_base) return hipErrorInvalidValue;   // (a piece is launched with its size known)
     size_t shm = (size_t)d.Vl * sizeof(float);
     if (!force_generic) {
-#define TBS_EXPAND_REG(NV4, SMAX)                                                                              \
-    {                                                                                                          \
-        expand_reg_launch<NV4, SMAX>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok, row_stats, \
-                                     delta_nb, pairs_dev, pair_base);                                          \
-        return hipGetLastError();                                                                              \
-    }
-        const int nv4 = (d.Vl / 4 + EXP_THREADS - 1) / EXP_THREADS;
-        if (nv4 <= 1 && d.S <= 3) TBS_EXPAND_REG(1, 3)
-        if (nv4 <= 1 && d.S <= 5) TBS_EXPAND_REG(1, 5)
-        if (nv4 <= 2 && d.S <= 8) TBS_EXPAND_REG(2, 8)
-        if (nv4 <= 4 && d.S <= 3) TBS_EXPAND_REG(4, 3)
-        if (nv4 <= 4 && d.S <= 5) TBS_EXPAND_REG(4, 5)
-#undef TBS_EXPAND_REG
-        // Longer segments of a vocabulary that fits a lane's four pieces: two rows a wave up to 32 frames, four up
-        // to 64 (a workgroup has at most 16 waves).  Measured on the Librispeech-like batch of 64 at N = 5 (ms
-        // per decode; one / two / four rows a wave): S = 6: 21.3 / 21.3 / 21.3, 12: 20.1 / 20.0 / 20.1, 16: 20.8 /
-        // 20.6 / 21.0, 20: - / 22.4 / 22.7, 32: - / 25.2 / 25.4; a workgroup of four waves that holds up to 16
-        // frames' columns took 22.3 at S = 6, 22.0 at 12 and 23.0 at 16, the two-pass kernel 28.2 at 20, 47.7
-        // (here 32.6) at 50.
-        if (nv4 <= 1 && d.S <= LONG_FRAMES) {
-            const int rpw = d.S <= 32 ? 2 : 4;
-            const int nq = d.Vl <= 256 ? 1 : (d.Vl <= 512 ? 2 : 4);
+#define TBS_EXPAND_REG(NV4, SMAX)                                                                                      \
+    case EXPAND_REG(NV4, SMAX):                                                                                        \
+        expand_reg_launch<NV4, SMAX>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok, row_stats,       \
+                                     delta_nb, pairs_dev, pair_base);                                                  \
+        return hipGetLastError();
 #define TBS_EXPAND_LONG(NQ, RPW)                                                                                       \
-    if (nq == NQ && rpw == RPW)                                                                                        \
+    case EXPAND_LONG(NQ, RPW):                                                                                         \
         return expand_long_launch<NQ, RPW>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok, row_stats, \
                                            delta_nb, pairs_dev, pair_base);
+        switch (expand_form(d.Vl, d.S)) {
+            TBS_EXPAND_REG(1, 3) TBS_EXPAND_REG(1, 5) TBS_EXPAND_REG(2, 8) TBS_EXPAND_REG(4, 3) TBS_EXPAND_REG(4, 5)
             TBS_EXPAND_LONG(1, 2) TBS_EXPAND_LONG(1, 4)
             TBS_EXPAND_LONG(2, 2) TBS_EXPAND_LONG(2, 4)
             TBS_EXPAND_LONG(4, 2) TBS_EXPAND_LONG(4, 4)
-#undef TBS_EXPAND_LONG
+            default: break;
         }
+#undef TBS_EXPAND_REG
+#undef TBS_EXPAND_LONG
     }
     hipLaunchKernelGGL(k_expand, dim3(pairs), dim3(EXP_THREADS), shm, st, d, logits, A, rv, row_lc, dphi, cand_score,
                        cand_tok, row_stats, delta_nb, pairs_dev, pair_base);

@@ -227,6 +227,11 @@ bool gemm_part_fits(int M, int N, int K, int np, int max_tiles = GS_TILES);
 hipError_t launch_gemm_part(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, int M, int N, int K,
                             const PartEp &pe);
 hipError_t launch_permute_gate_rows(hipStream_t st, const void *src, void *dst, int H, long row_bytes);
+// which kernel expands segments of S frames of logit rows of Vl floats
+#define EXPAND_TWO_PASS 0
+#define EXPAND_REG(NV4, SMAX) (100 * (NV4) + (SMAX))
+#define EXPAND_LONG(NQ, RPW) (1000 + 10 * (NQ) + (RPW))
+extern "C" int expand_form(int Vl, int S);
 hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                          float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
                          float *delta_nb, int force_generic, const int *pairs_dev = nullptr, int pair_base = 0);

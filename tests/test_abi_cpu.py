@@ -54,6 +54,25 @@ def test_strerror_and_invalid_configs():
     L.tbs_free(None)
 
 
+@pytest.mark.parametrize("V,S,form", [
+    (1024, 3, "reg 1 3"), (1024, 4, "reg 1 5"), (1024, 5, "reg 1 5"),
+    (1024, 6, "long 4 2"), (1024, 7, "long 4 2"), (1024, 8, "long 4 2"), (256, 6, "long 1 2"), (260, 8, "long 2 2"), (2, 8, "long 1 2"),
+    (256, 32, "long 1 2"), (257, 33, "long 2 4"), (512, 64, "long 2 4"), (513, 32, "long 4 2"), (1023, 64, "long 4 4"),
+    (1024, 65, "two pass"), (1025, 3, "reg 2 8"), (1025, 8, "reg 2 8"), (2048, 8, "reg 2 8"), (1025, 9, "two pass"),
+    (2049, 3, "reg 4 3"), (4096, 5, "reg 4 5"), (2049, 6, "two pass"), (4097, 1, "two pass")])
+def test_expansion_kernel_by_size(V, S, form):
+    """Which kernel expands a call, on both sides of every line: four waves with the logits in registers to 5 frames (wider
+    vocabularies: to 8), k_expand_long from 6 to 64 frames of vocabularies up to 1024, two passes beyond."""
+    L, _ = _lib()
+    code = L.expand_form((V + 3) // 4 * 4, S)
+    kind, _, args = form.partition(" ")
+    if kind == "two":
+        assert code == 0
+    else:
+        a, b = (int(x) for x in args.split())
+        assert code == (100 * a + b if kind == "reg" else 1000 + 10 * a + b)
+
+
 def test_binding_has_no_oracle_or_cpu_path():
     """The product package must not import the oracle."""
     import paper_2302_14357_amd
