@@ -83,7 +83,7 @@ struct tbs_ctx {
     float *logits, *row_lc, *row_stats, *dphi, *delta_nb, *cand_score;
     int *cand_tok;
 
-    void *wcat[TBS_MAX_LAYERS];
+    void *wcat[TBS_MAX_LAYERS];   // layers >= 1: [4H, 2H] = [W_ih | W_hh]
     float *emb_gates;   // [V, 4H] = embed * W_ih(layer 0)^T + b(layer 0)
     // gate-interleaved copies (row 4j+g = gate g of unit j) for the GEMM that updates the cell in its
     // epilogue: layer 0 [4H, H] (recurrent half), layers >= 1 [4H, 2H]; biases of layers >= 1; the table
@@ -403,7 +403,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         rc |= dev_alloc(c, &c->row_stats, (size_t)M * 3);
         rc |= dev_alloc(c, &c->delta_nb, (size_t)UN * d.V);
     }
-    const int xw = std::max(d.E + d.H, 2 * d.H);
+    const int xw = d.L > 1 ? 2 * d.H : d.H;   // (the first layer's input row is h alone)
     for (int i = 0; i < 2; ++i) {
         char *p = nullptr;
         rc |= dev_alloc(c, &p, (size_t)UN * xw * elem_bytes(c));
@@ -415,10 +415,9 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         c->htop = p;
     }
     rc |= dev_alloc(c, &c->gates, (size_t)UN * 4 * d.H);
-    for (int l = 0; l < d.L; ++l) {
-        int in_dim = l == 0 ? d.E : d.H;
+    for (int l = 1; l < d.L; ++l) {
         char *p = nullptr;
-        rc |= dev_alloc(c, &p, (size_t)4 * d.H * (in_dim + d.H) * elem_bytes(c));
+        rc |= dev_alloc(c, &p, (size_t)4 * d.H * 2 * d.H * elem_bytes(c));
         c->wcat[l] = p;
     }
     c->emb_gates = nullptr;
@@ -480,10 +479,8 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         tbs_free(c);
         return TBS_EHIP;
     }
-    for (int l = 0; l < d.L; ++l) {
-        int in_dim = l == 0 ? d.E : d.H;
-        e = launch_concat_weights(c->stream, elem_bytes(c), w->w_ih[l], w->w_hh[l], c->wcat[l], 4 * d.H, in_dim,
-                                  d.H);
+    for (int l = 1; l < d.L; ++l) {
+        e = launch_concat_weights(c->stream, elem_bytes(c), w->w_ih[l], w->w_hh[l], c->wcat[l], 4 * d.H, d.H, d.H);
         if (e != hipSuccess) {
             c->last_hip = (int)e;
             tbs_free(c);
