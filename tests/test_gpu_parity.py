@@ -358,6 +358,22 @@ def test_decode_fp32_fixed_places(d, hidden, layers, V, U, N, S, debug):
     _check_decode(shape, model, offsets, enc, N, S, debug=debug)
 
 
+@pytest.mark.parametrize("U,N,S,V,xcd", [(3, 9, 3, 64, False), (2, 15, 5, 1000, False), (15, 5, 3, 100, True), (50, 5, 2, 33, True),
+                                         (20, 12, 1, 1024, True)])
+def test_decode_fp32_fixed_places_beams_and_row_ranges(U, N, S, V, xcd):
+    """fp32 models in the slot layout with beams of 9 to 15 (more candidates than lanes) and, from 225 joiner rows
+    on, with a range of rows per XCD in the joiner GEMM and the round kernel; the row ranges can be left out (debug
+    4096) and change nothing."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=U, vocab=V, d=64, hidden=64), dtype="f32")
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=(np.arange(U) * 5) % 11 + 2)
+    got, st = _gpu_decode(shape, model, offsets, enc, N, S)
+    assert st["path"]["fixed_places"] and xcd == (U * N * S >= 225)
+    if xcd:
+        assert _gpu_decode(shape, model, offsets, enc, N, S, debug=4096)[0] == got
+    _check_decode(shape, model, offsets, enc, N, S)
+
+
 @pytest.mark.parametrize("dtype,V,S", [("f32", 64, 3), ("bf16", 64, 3), ("bf16", 63, 3), ("bf16", 63, 1)])
 def test_counters_of_steps_driven_by_the_caller(dtype, V, S):
     """tbs_stats, and the trie nodes of TBS_BUF_COUNTS, say the same whether the step functions or tbs_decode ran the
@@ -937,6 +953,27 @@ def test_decode_long_segments(S):
     # (with blank probabilities of a few percent the blank products over such segments span ~1e-85:
     # this is the case that needs the forward variable and d carried with extended range)
     _check_decode(shape, model, offsets, enc, 5, S, rounds_capacity=4 * S, report=f"S={S}")
+
+
+@pytest.mark.parametrize("V,S,blank", [(1024, 6, 0), (1024, 7, 5), (500, 8, 0), (200, 8, 199), (257, 9, 0), (511, 32, 17), (512, 33, 0),
+                                       (500, 64, 0), (1000, 9, 999), (1023, 33, 0), (1021, 64, 1020), (1024, 32, 1023)])
+def test_joiner_expand_long_segments(V, S, blank):
+    """k_expand_long over what it serves: one, two and four 16-byte pieces a lane, two and four rows a wave, each at the
+    edges of its range of frames, vocabularies that leave lanes without a piece or a piece partly beyond the vocabulary,
+    a blank that is not token 0; full and ragged segments (the utterances' lengths differ), then every score equal."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=5, vocab=V, d=64, hidden=64), blank_id=blank, len_lo=2, len_hi=S + 3)
+    _check_joiner_expand(shape, U=5, N=5, S=S, seg=0, sample_pairs=8, rounds_capacity=4 * S)
+    if blank == 0:
+        _check_joiner_expand(shape, U=3, N=6, S=S, seg=0, sample_pairs=3, flat=True, rounds_capacity=4 * S)
+
+
+@pytest.mark.parametrize("V,S,N", [(1000, 7, 3), (400, 8, 10), (257, 12, 4), (1023, 40, 3)])
+def test_decode_long_segments_other_vocabularies(V, S, N):
+    """Whole decodes whose expansions run in k_expand_long, on vocabularies that are no power of two."""
+    shape = small_bf16_shape(n_utts=3, vocab=V, d=128, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=3, lengths=np.array([S + 3, 2 * S, 1]))
+    _check_decode(shape, model, offsets, enc, N, S, rounds_capacity=4 * S)
 
 
 def test_decode_largest_segment_and_smallest_vocabulary():
