@@ -153,7 +153,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool pre_h = on && fx.xh && H4 <= TT * HP;
     float4 hpar[HP];
     if (own_wave && sel_wave) {
-        select_merge_utt(1, d, round, drop, u, sel_lane, logits, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
+        select_merge_utt(1, d, round, drop, u, sel_lane, logits, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         if constexpr (S1NP == 0) {
 #pragma unroll
             for (int b = 0; b < EXPAND_PAIR_BARRIERS; ++b) __syncthreads();
@@ -267,13 +267,13 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const float *lg = S1NP > 0 ? nullptr : logits;   // (no logits: d of a new hypothesis over one frame is (1))
     if (own_wave) {
         if (sel_wave)
-            select_merge_utt(4, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
+            select_merge_utt(4, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         else if ((int)threadIdx.x < WAVE)
-            select_merge_utt(3, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
+            select_merge_utt(3, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         __syncthreads();
     }
     if (sel_wave) {
-        select_merge_utt(own_wave ? 5 : 0, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW);
+        select_merge_utt(own_wave ? 5 : 0, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         if (on) {
             // Slot layout: what a row list kernel would do for this utterance.  The new hypotheses
             // take trie nodes from the utterance's own range, their pairs get their descriptors, the

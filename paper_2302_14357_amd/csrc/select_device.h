@@ -129,7 +129,8 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
     return f;
 }
 
-// FEW (a constant): at most a wave's width of candidates and SEL_PRE_FRAMES frames, known when the code is made.
+// Constants, known when the code is made: SHORT: at most SEL_PRE_FRAMES frames; FEW: that, and at most a wave's width of
+// candidates.
 // s_dyn: LDS for the utterance's B list, BCAP * (8 + 8 + 3 * 4) bytes, 16-byte aligned.
 // phase 0: the whole step.  phase 1: only what does not depend on the expansion (B and A staged in
 // LDS); phase 2: the rest, by the same wave: a caller whose expansion runs in the same kernel does
@@ -141,7 +142,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                                                  const float *logits, SelectIn in, const SelectFigs &fg, AView A,
                                                  AView An, BView B, RowView rv, const int2 *nodes,
                                                  unsigned char *s_dyn, SelectOut *out = nullptr,
-                                                 const bool FEW = false) {
+                                                 const bool FEW = false, const bool SHORT = false) {
     double *s_blogs = reinterpret_cast<double *>(s_dyn);
     u64 *s_bhash = reinterpret_cast<u64 *>(s_blogs + d.BCAP);
     int *s_bnode = reinterpret_cast<int *>(s_bhash + d.BCAP);
@@ -335,10 +336,11 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                 An.count[u] = total;
                 if (out) out->total = total;
             }
-            // Longer segments, or more candidates: a lane takes (hypothesis, frame) pairs, then the frames of one
-            // hypothesis after the other.  (A lane per hypothesis that walks its frames alone took three
-            // passes of up to S' dependent steps.)
-            const bool by_frame = !FEW && logits != nullptr && !pre_x && sp <= WAVE;
+            // Longer segments: a lane takes (hypothesis, frame) pairs, then the frames of one hypothesis after the
+            // other.  (A lane per hypothesis that walks its frames alone takes three passes of up to S' dependent
+            // steps; up to SEL_PRE_FRAMES frames those are fewer than the reductions of N hypotheses: 16 utterances of
+            // the Librispeech-like widths N = 16 S = 3 18.4 ms per decode, by frame 19.6, N = 12 S = 8 12.4 and 13.8.)
+            const bool by_frame = !FEW && !SHORT && logits != nullptr && sp > SEL_PRE_FRAMES && sp <= WAVE;
             if (keep) {
                 const int c = s_sel[lane];
                 const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)N));   // c / N for c < 256
