@@ -503,6 +503,8 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
     if (first) select_merge_utt(5, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
 }
 
+extern "C" int select_dist_form(int candidates, int frames) { return sel_dist_form(candidates, frames); }
+
 hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int drop, const float *logits,
                                const float *row_lc, const float *dphi, const float *cand_score,
                                const int *cand_tok, AView A, AView An, BView B, RowView rv, const int2 *nodes) {

@@ -107,6 +107,18 @@ __device__ __forceinline__ void sel_rank(const double *v, int n, int lane, F fn)
 #define SEL_PRE_FRAMES 8   // segments up to this long have their candidates' logits asked for ahead of the ranking
 #define SEL_PRE_CANDS (2 * WAVE)   // ... where there are at most this many candidates (N <= 11)
 
+// How the frame distributions of the new hypotheses are made, by the number of candidates and of frames.
+// Ahead: from logits asked for ahead of the ranking, one or two candidates a lane.  By lane: a lane per hypothesis walks its
+// frames.  By frame: a lane takes (hypothesis, frame) pairs, then the frames of one hypothesis after the other are
+// normalised across the wave.  (By lane takes three passes of up to S' dependent steps; up to SEL_PRE_FRAMES frames
+// those are fewer than the reductions of N hypotheses: 16 utterances of the Librispeech-like widths N = 16 S = 3 18.4
+// ms per decode, by frame 19.6, N = 12 S = 8 12.4 and 13.8; 64 utterances N = 5 S = 20 by frame 21.1, by lane 22.3.)
+enum { SEL_AHEAD = 0, SEL_BY_LANE = 1, SEL_BY_FRAME = 2 };
+__host__ __device__ inline int sel_dist_form(int candidates, int frames) {
+    if (frames <= SEL_PRE_FRAMES) return candidates <= SEL_PRE_CANDS ? SEL_AHEAD : SEL_BY_LANE;
+    return frames <= WAVE ? SEL_BY_FRAME : SEL_BY_LANE;
+}
+
 struct SelectIn {
     const float *cand_score;
     const int *cand_tok;
@@ -203,7 +215,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
         if (PHASE == 0) sel_sync();   // (A's scores, staged just above, are read by other lanes below)
         const int nc = H * N;
         const float rcp_n = __builtin_amdgcn_rcpf((float)N);   // c / N as (c + 0.5) * (1 / N): exact for c < 1024
-        const bool pre_x = FEW ? logits != nullptr && !drop : logits != nullptr && nc <= SEL_PRE_CANDS && sp <= SEL_PRE_FRAMES && !drop;
+        const bool pre_x = logits != nullptr && !drop && (FEW || sel_dist_form(nc, sp) == SEL_AHEAD);
         float xpre[2][SEL_PRE_FRAMES];
         if (do_cand) {
             int tok_mine = -1, tok_mine2 = -1;   // (tokens of the candidates `lane` and `lane + 64`)
@@ -336,11 +348,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                 An.count[u] = total;
                 if (out) out->total = total;
             }
-            // Longer segments: a lane takes (hypothesis, frame) pairs, then the frames of one hypothesis after the
-            // other.  (A lane per hypothesis that walks its frames alone takes three passes of up to S' dependent
-            // steps; up to SEL_PRE_FRAMES frames those are fewer than the reductions of N hypotheses: 16 utterances of
-            // the Librispeech-like widths N = 16 S = 3 18.4 ms per decode, by frame 19.6, N = 12 S = 8 12.4 and 13.8.)
-            const bool by_frame = !FEW && !SHORT && logits != nullptr && sp > SEL_PRE_FRAMES && sp <= WAVE;
+            const bool by_frame = !FEW && !SHORT && logits != nullptr && sel_dist_form(nc, sp) == SEL_BY_FRAME;
             if (keep) {
                 const int c = s_sel[lane];
                 const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)N));   // c / N for c < 256

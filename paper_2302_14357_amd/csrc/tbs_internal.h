@@ -235,6 +235,8 @@ extern "C" int expand_form(int Vl, int S);
 hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                          float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
                          float *delta_nb, int force_generic, const int *pairs_dev = nullptr, int pair_base = 0);
+// how the select step makes the frame distributions of new hypotheses: 0 ahead of the ranking, 1 by lane, 2 by frame
+extern "C" int select_dist_form(int candidates, int frames);
 hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int drop, const float *logits,
                                const float *row_lc, const float *dphi, const float *cand_score,
                                const int *cand_tok, AView A, AView An, BView B, RowView rv, const int2 *nodes);

@@ -73,6 +73,15 @@ def test_expansion_kernel_by_size(V, S, form):
         assert code == (100 * a + b if kind == "reg" else 1000 + 10 * a + b)
 
 
+@pytest.mark.parametrize("N,frames,form", [(1, 1, 0), (8, 8, 0), (11, 8, 0), (12, 1, 1), (12, 8, 1), (16, 3, 1), (32, 8, 1),
+                                           (1, 9, 2), (11, 9, 2), (32, 64, 2), (1, 65, 1), (32, 128, 1)])
+def test_distributions_of_new_hypotheses_by_size(N, frames, form):
+    """How the select step makes them, on both sides of every line: ahead of the ranking (0) to 8 frames and 128
+    candidates, by (hypothesis, frame) pairs (2) from 9 to 64 frames only, by a lane per hypothesis (1) otherwise."""
+    L, _ = _lib()
+    assert L.select_dist_form(N * N, frames) == form
+
+
 def test_binding_has_no_oracle_or_cpu_path():
     """The product package must not import the oracle."""
     import paper_2302_14357_amd
