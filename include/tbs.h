@@ -67,7 +67,9 @@ typedef struct tbs_config {
                                        and left out, Section 3.2); 0: no such limit, but more than
                                        rounds_capacity rounds is TBS_EOVERFLOW */
     int32_t rounds_capacity;  /* sizes the per-segment workspaces; 0 = 32 */
-    int32_t max_nodes;        /* capacity of the token trie; 0 = 4*N*(max_frames_total+max_utts*S) */
+    int32_t max_nodes;        /* capacity of the token trie; 0 = 4*N*(max_frames_total+max_utts*S).  Where every hypothesis
+                                 has a fixed place (tbs_path) each utterance has a share of it in proportion to its
+                                 length, in a stream an equal one; otherwise all utterances share it as they need */
     int32_t debug;            /* bit 0: also keep per-row softmax statistics and the full non-blank
                                  expansion scores for tbs_debug_read; bit 1: always use the
                                  generic two-pass expansion kernel; bit 3: keep the LSTM cell update a
@@ -127,7 +129,11 @@ typedef struct tbs_weights {          /* DEVICE pointers, borrowed */
 /* Create a context: validates the configuration, allocates every workspace
  * once (no later call of the decode or streaming path allocates; the inspection
  * and timing calls below make temporaries of their own), and prepares the
- * predictor weights.  N * rounds capacity (the longest list B) may not exceed 2048.
+ * predictor weights: for both dtypes the embedding's share of the first layer's gates
+ * becomes two float32 tables [V, 4H], and the LSTM weights are copied in the order the
+ * kernels read them.  embed, w_ih, w_hh and b_lstm may therefore not change while the
+ * context lives (a change may go unseen, in part); nor may the other weights during a decode.
+ * N * rounds capacity (the longest list B) may not exceed 2048.
  * Algorithm 1 inputs N and S are fixed per context. */
 int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out);
 void tbs_free(tbs_ctx *ctx);

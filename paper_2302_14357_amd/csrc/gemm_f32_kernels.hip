@@ -13,8 +13,9 @@
 // input rows 8.9 us, joiner 7.4 us) a round is four launches instead of nine.
 // K tiles of 128 floats go from global memory straight into LDS, as many requested at once as there are
 // stages; rows are 512 bytes, chunk c (16 bytes) of row r sits at position c ^ (r & 15), so that the
-// 16-byte fragment reads of 16 neighbouring rows fall into different banks.  A lane takes 4 consecutive K elements per read and the MFMA steps take them in the
-// order in which they lie (any order of K that A and B share is the same sum).
+// 16-byte fragment reads of 16 neighbouring rows fall into different banks.  A lane takes 4 consecutive K
+// elements per read and the MFMA steps take them in the order in which they lie (any order of K that A and B
+// share is the same sum).  Products of every size run in these tiles; larger ones were not measured.
 #include "tbs_internal.h"
 #include <climits>
 

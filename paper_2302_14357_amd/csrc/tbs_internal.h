@@ -193,7 +193,12 @@ hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, 
                                 int K, const int *out_row, long ldc, const JoinEp &jp, const int *m_dev,
                                 const int *any_dev);
 #define GF_TILE 32            // fp32: edge of a tile
-#define GF_TILES 1024         // fp32: tiles of 32 x 32 up to which the fused forms serve the row lists
+#define GF_TILES 1024         // fp32: tiles of 32 x 32 up to which the fused forms serve the row lists: ms per decode fused /
+                              // separate by the most tiles of a round's products, Librispeech-like widths N = 5 S = 3
+                              // 256: 6.4 / 6.9, 736: 7.9 / 8.1, 1024: 8.6 / 9.0, 1152: 9.0 / 9.3, 1440: 10.0 / 10.1, 1920:
+                              // 11.7 / 11.6, 4512: 20.8 / 19.9; large widths N = 8 1024: 10.6 / 10.8, 1536: 11.9 / 12.3,
+                              // 3072: 17.6 / 16.9; widths of 256 2400: 11.5 / 11.9, 4000: 16.6 / 16.6.  Fused is no slower
+                              // anywhere up to here; the two cross between 1440 and 4000, by the widths.
 #define GF_TILES_FIXED 1280   // ... and the slot layout: measured at N = 5 on the Librispeech-like widths (most tiles of
                               // a round's products: ms per decode with slots / row lists) 640: 12.5 / 16.0, 800: 10.6 /
                               // 11.4, 960: 12.5 / 13.5, 1200: 20.8 / 22.1, 1440: 15.4 / 15.2, 1600: 13.9 / 13.4 and

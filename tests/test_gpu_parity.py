@@ -407,7 +407,7 @@ def test_counters_of_steps_driven_by_the_caller(dtype, V, S):
 
 @pytest.mark.parametrize("dtype,V", [("f32", 64), ("bf16", 63)])
 def test_small_trie_that_one_list_of_nodes_fits(dtype, V):
-    """A trie just large enough for all utterances together, too small for an even share of each: fp32 models
+    """A trie just large enough for all utterances together, too small for a share of each: fp32 models
     and vocabularies that are no whole 16-byte pieces then decode with row lists, to the same result; a stream of theirs
     runs with row lists from the start."""
     import dataclasses
