@@ -414,7 +414,9 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
         if (SMAX * TW > 8) __builtin_amdgcn_sched_barrier(0);   // one row at a time: the partial results of many rows at once cost registers
         mrow[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));   // uniform: a scalar register
     }
-    // ---- e = exp(l - m_t), once per logit; row sums across the workgroup
+    // ---- e = exp(l - m_t), once per logit; row sums across the workgroup.  (The exponent is one fused multiply-add, so
+    // every e of a row carries the rounding of m_t log2(e) as a common factor, up to 1e-6 for m_t = 20.  What is
+    // set against the row sum therefore takes the same factor: the blank probability below and log(alpha_t / Z_t).)
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) {
         const float nm = -mrow[t] * 1.44269504088896341f;
@@ -452,14 +454,15 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
                 for (int w = 1; w < TW; ++w) z += sm.pz[t][w];
                 __builtin_amdgcn_sched_barrier(0);
                 const float lz = __logf(z);
-                const float lb = (pi.lblank[t] - mrow[t]) - lz;       // log of the blank probability of frame t
+                const float nm = -mrow[t] * 1.44269504088896341f;     // (as in e)
+                const float lb = fmaf(fmaf(pi.lblank[t], 1.44269504088896341f, nm), 0.69314718055994531f, -lz);   // log of the blank probability of frame t
                 const float x = la + lbprev, ld = pi.dold[t];
                 const float mx = fmaxf(x, ld), mn = fminf(x, ld);
                 la = mx > -INFINITY ? mx + __logf(1.f + __expf(mn - mx)) : -INFINITY;
                 lbprev = lb;
                 const float lc = la - lz;                              // log(alpha_t / Z_t)
                 cf[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(__expf(lc))));
-                lcrow[t] = lc - mrow[t];
+                lcrow[t] = fmaf(nm, 0.69314718055994531f, lc);
                 if (t == pi.sp - 1) lphi = la + lb;                    // Eq. 7
                 if (row_stats && tid == 0 && live) {
                     row_stats[(long)(pi.row0 + t) * 3 + 0] = mrow[t];

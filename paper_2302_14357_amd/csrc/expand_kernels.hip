@@ -189,10 +189,10 @@ __device__ __forceinline__ ScanPart scan_up(ScanPart a, int by) { return {__shfl
 __device__ __forceinline__ float scan_log(ScanPart a) {
     return a.m > 0.f ? __logf(a.m) + (float)a.e * 0.69314718055994531f : -INFINITY;
 }
-// exp(x) / z (z = 1: exp(x)); zero for x = -inf
-__device__ __forceinline__ ScanPart scan_exp(float x, float z) {
-    if (!(x > -INFINITY)) return {0.f, 0};
-    const float l2 = x * 1.44269504088896341f, fl = floorf(l2);
+// 2^l2 / z; zero for l2 = -inf
+__device__ __forceinline__ ScanPart scan_exp2(float l2, float z) {
+    if (!(l2 > -INFINITY)) return {0.f, 0};
+    const float fl = floorf(l2);
     return scan_norm(__builtin_amdgcn_exp2f(l2 - fl) / z, (int)fl);
 }
 
@@ -249,7 +249,7 @@ k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, flo
         if (lane == 0) {
             s_m[t] = m;
             s_z[t] = z;
-            s_lb[t] = lblank[i] - m;
+            s_lb[t] = fmaf(lblank[i], 1.44269504088896341f, nm);   // (log2 of the blank's e: with the row's common factor, see expand_pair)
         }
     }
     __syncthreads();
@@ -257,8 +257,8 @@ k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, flo
         const bool have = lane < sp;
         const int t = min(lane, sp - 1);
         const float m = s_m[t], z = s_z[t];
-        const ScanPart b = scan_exp(s_lb[t], z);              // blank probability of the frame
-        ScanPart a = scan_exp(have ? ld : -INFINITY, 1.f), f = scan_up(b, 1);   // alpha_t = alpha_{t-1} f + a
+        const ScanPart b = scan_exp2(s_lb[t], z);             // blank probability of the frame
+        ScanPart a = scan_exp2(have ? ld * 1.44269504088896341f : -INFINITY, 1.f), f = scan_up(b, 1);   // alpha_t = alpha_{t-1} f + a
         for (int by = 1; by < sp; by <<= 1) {
             const ScanPart a2 = scan_up(a, by), f2 = scan_up(f, by);
             if (lane >= by) {
@@ -269,7 +269,7 @@ k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, flo
         const float lc = scan_log(a) - __logf(z);             // log(alpha_t / Z_t)
         if (have) {
             s_cf[t] = __expf(lc);
-            row_lc[row0 + t] = lc - m;
+            row_lc[row0 + t] = fmaf(-m * 1.44269504088896341f, 0.69314718055994531f, lc);
             if (lane == sp - 1) dphi[pair] = scan_log(scan_mul(a, b));   // Eq. 7
             if (row_stats) {
                 row_stats[(long)(row0 + t) * 3 + 0] = m;

@@ -189,6 +189,44 @@ def test_vocabularies_that_are_no_whole_pieces(V, N, S):
     _check_decode(shape, model, offsets, enc, N, S)
 
 
+@pytest.mark.parametrize("V,S,scale", [(1021, 5, 8), (64, 5, 8), (2049, 3, 8), (1024, 8, 8), (1024, 17, 8), (1023, 50, 4), (200, 64, 4)])
+def test_blank_expansion_error_of_peaked_models(V, S, scale):
+    """log delta_blank (Eq. 7) against fp64 on the kernel's own logits, for peaked distributions with large logits: the
+    rounding of a row's maximum must not enter the blank probabilities, whose errors add up over the segment.  Bound on
+    the rms over hypotheses: a frame's log blank probability has three roundings (the blank's exponential, the row
+    sum, its logarithm) of values about one, at most 2^-23 each and evenly spread, so 3^0.5 2^-23 / 3^0.5 = 2^-23 rms;
+    S of them are independent; the result is rounded once more to its own last place."""
+    import dataclasses
+    from paper_2302_14357_amd import BUF
+    U, N, Dj = 16, 5, 128
+    shape = dataclasses.replace(small_bf16_shape(n_utts=U, vocab=V, d=Dj, hidden=64), len_lo=S, len_hi=S, logit_scale=float(scale),
+                                blank_bias=3.0 * scale)
+    model, offsets, enc = build_case(shape, n_utts=U)
+    tbs = make_tbs(shape, model, offsets, N, S, debug=1, rounds_capacity=4 * S)
+    rng = np.random.default_rng(4)
+    pred = (rng.standard_normal((U, N, Dj)) * 0.5).astype(np.float32)
+    dhat = rng.random((U, N, S)).astype(np.float32)
+    dhat[rng.random((U, N, S)) < 0.3] = 0.0
+    dhat[:, :, 0] += 0.05
+    tbs.begin(tbs.upload_frames(enc), offsets)
+    tbs.debug_write(BUF.A_COUNT, np.full(U, N, np.int32))
+    tbs.debug_write(BUF.A_LOGS, -rng.random((U, N)))
+    tbs.debug_write(BUF.A_PRED, pred)
+    tbs.debug_write(BUF.A_DHAT, dhat)
+    tbs.debug_rebuild(0)
+    tbs.joiner_segment()
+    tbs.expand()
+    logits, dphi = tbs.debug_read(BUF.LOGITS).astype(np.float64), tbs.debug_read(BUF.DELTA_BLANK)
+    pu, ph, row0 = tbs.debug_read(BUF.PAIR_UTT), tbs.debug_read(BUF.PAIR_HYP), tbs.debug_read(BUF.PAIR_ROW0)
+    tbs.close()
+    want = np.array([math.log(oracle.expansion_scores(logits[r:r + S][None], dhat[u, h].astype(np.float64)[None], shape.blank_id)[4][0])
+                     for u, h, r in zip(pu, ph, row0)])
+    err = math.sqrt(np.mean((dphi - want) ** 2))
+    bound = math.sqrt(S) * 2.0 ** -23 + 2.0 ** -24 * math.sqrt(np.mean(want ** 2))
+    print(f"V={V} S={S} scale={scale}: rms error {err:.2e}, bound {bound:.2e}")
+    assert err <= bound
+
+
 def test_joiner_expand_odd_vocab():
     shape = small_bf16_shape(n_utts=3, vocab=77, d=64, hidden=64)
     _check_joiner_expand(shape, U=3, N=4, S=3, seg=0)
