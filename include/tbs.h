@@ -100,7 +100,10 @@ typedef struct tbs_config {
                                  16-column pieces itself, also where it would hand them to the round kernel
                                  as they are; bit 15: seg_s = 1 without logits also where the form with
                                  logits would run (beams above 4 with a vocabulary it can hold, where it was
-                                 measured faster; tests cover each pair of variants) */
+                                 measured faster; tests cover each pair of variants); bit 16: four kernels a round also
+                                 where whole segments would run inside one launch (tbs_path bit 2; so does any
+                                 other bit but 17); bit 17: that launch waits for a workgroup that does not exist, so that it
+                                 gives up as where the GPU is not free for it */
     int32_t stream_buffer_frames; /* per-utterance capacity, in frames, of the buffer tbs_push_segment
                                  collects encoder frames in; 0 = no streaming.  At least seg_s; one
                                  push may bring an utterance up to this many minus seg_s - 1 frames */
@@ -213,7 +216,10 @@ int tbs_stats(const tbs_ctx *ctx, int64_t *joiner_calls, int64_t *joined_frames,
 /* Which forms of the kernels the batch begun last runs in (they give the same results; tests and
  * benchmarks use this to say which one they exercised): bit 0 = every hypothesis in a fixed place,
  * four kernels a round; bit 1 = seg_s = 1 without logits (the standard search of Eq. 1 with the
- * row softmax sums and best tokens made in the joiner GEMM).  Negative: an error code. */
+ * row softmax sums and best tokens made in the joiner GEMM); bit 2 (with bit 0) = tbs_decode and tbs_push_segment run whole
+ * segments in one launch that takes every CU (bf16 models of one LSTM layer whose weights fit the LDS of an XCD's CUs; while
+ * another context's launch is under way on the GPU, or where its workgroups do not get onto the CUs together within
+ * 5 ms, four kernels a round instead).  Negative: an error code. */
 int tbs_path(const tbs_ctx *ctx);
 
 /* ---- inspection, for tests ---- */

@@ -484,6 +484,7 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
                const float *dphi, const float *cand_score, const int *cand_tok, AView A, AView An, BView B,
                RowView rv, const int2 *nodes) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // B list of this utterance
+    __shared__ SelectShared<> s_select;
     const int u = blockIdx.x;
     const int pair0 = rv.utt_pair0[u];
     const SelectFigs fg = select_figs(u, A, B, rv);
@@ -495,12 +496,12 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
     in.slot_rows = 0;
     const int lane = (int)threadIdx.x & (WAVE - 1);
     const bool first = __builtin_amdgcn_readfirstlane((int)threadIdx.x) < WAVE;
-    if (first) select_merge_utt(1, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    if (first) select_merge_utt(s_select, 1, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
     __syncthreads();
-    if (first) select_merge_utt(4, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
-    else select_merge_utt(3, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    if (first) select_merge_utt(s_select, 4, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
+    else select_merge_utt(s_select, 3, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
     __syncthreads();
-    if (first) select_merge_utt(5, d, round, drop, u, lane, logits, in, fg, A, An, B, rv, nodes, s_dyn);
+    if (first) select_merge_utt(s_select, 5, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
 }
 
 extern "C" int select_dist_form(int candidates, int frames) { return sel_dist_form(candidates, frames); }

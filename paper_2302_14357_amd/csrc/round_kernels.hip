@@ -79,6 +79,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool sel_wave = own_wave ? (int)threadIdx.x >= N * TT : (int)threadIdx.x < WAVE;
     const int sel_lane = (int)threadIdx.x & 63;
     __shared__ SelectOut s_out;
+    __shared__ SelectShared<> s_select;
     // Slot layout: everything the round has to know of the utterance lies side by side and comes
     // with one request.  What the kernel before this one wrote is asked for by the vector unit, a lane
     // per value, and handed to the scalar registers by lane reads: a request of the scalar unit for
@@ -153,7 +154,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool pre_h = on && fx.xh && H4 <= TT * HP;
     float4 hpar[HP];
     if (own_wave && sel_wave) {
-        select_merge_utt(1, d, round, drop, u, sel_lane, logits, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
+        select_merge_utt(s_select, 1, d, round, drop, u, sel_lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         if constexpr (S1NP == 0) {
 #pragma unroll
             for (int b = 0; b < EXPAND_PAIR_BARRIERS; ++b) __syncthreads();
@@ -267,13 +268,13 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const float *lg = S1NP > 0 ? nullptr : logits;   // (no logits: d of a new hypothesis over one frame is (1))
     if (own_wave) {
         if (sel_wave)
-            select_merge_utt(4, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
+            select_merge_utt(s_select, 4, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         else if ((int)threadIdx.x < WAVE)
-            select_merge_utt(3, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
+            select_merge_utt(s_select, 3, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         __syncthreads();
     }
     if (sel_wave) {
-        select_merge_utt(own_wave ? 5 : 0, d, round, drop, u, sel_lane, lg, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
+        select_merge_utt(s_select, own_wave ? 5 : 0, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         if (on) {
             // Slot layout: what a row list kernel would do for this utterance.  The new hypotheses
             // take trie nodes from the utterance's own range, their pairs get their descriptors, the

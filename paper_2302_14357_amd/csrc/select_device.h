@@ -119,6 +119,14 @@ __host__ __device__ inline int sel_dist_form(int candidates, int frames) {
     return frames <= WAVE ? SEL_BY_FRAME : SEL_BY_LANE;
 }
 
+// Where the select step reads single logits from (row of the utterance's lists, column): plain memory that an earlier kernel
+// wrote, or none at all (segments of one frame whose joiner kept no logits).
+struct LogitsPlain {
+    const float *p;
+    __device__ __forceinline__ bool none() const { return p == nullptr; }
+    __device__ __forceinline__ float at(long i) const { return p[i]; }
+};
+
 struct SelectIn {
     const float *cand_score;
     const int *cand_tok;
@@ -141,6 +149,27 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
     return f;
 }
 
+// LDS of the select step.  CANDS: candidates there is room for; DNEW: values of the frame distributions made by lane or by
+// frame (1 where every caller makes them ahead); PF: frames of a segment whose candidates' logits are asked for ahead, PC: such
+// candidates.
+template <int CANDS = CAND_MAX, int DNEW = TBS_MAX_SEG * TBS_MAX_BEAM, int PF = SEL_PRE_FRAMES, int PC = SEL_PRE_CANDS>
+struct SelectShared {
+    static constexpr int dnew = DNEW, pf = PF, pc = PC;
+    double s_key[CANDS];
+    int s_ctok[CANDS];
+    double s_alogs[TBS_MAX_BEAM];
+    u64 s_ahash[TBS_MAX_BEAM];
+    int s_anode[TBS_MAX_BEAM], s_alen[TBS_MAX_BEAM], s_aslot[TBS_MAX_BEAM];
+    double s_bkey[TBS_MAX_BEAM];
+    int s_match[TBS_MAX_BEAM];
+    int s_sel[TBS_MAX_BEAM];      // candidate index by rank
+    double s_thr;
+    int s_have_thr;
+    float s_dnew[DNEW];           // frame distributions of the new hypotheses, [frame][hypothesis]
+    float s_xpre[PF * PC];        // logits of the candidates' tokens, [frame][candidate]
+    int s_kh[TBS_MAX_BEAM], s_ktok[TBS_MAX_BEAM];   // kept candidates, by place: hypothesis they extend, token
+};
+
 // Constants, known when the code is made: SHORT: at most SEL_PRE_FRAMES frames; FEW: that, and at most a wave's width of
 // candidates.
 // s_dyn: LDS for the utterance's B list, BCAP * (8 + 8 + 3 * 4) bytes, 16-byte aligned.
@@ -148,10 +177,10 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
 // LDS); phase 2: the rest, by the same wave: a caller whose expansion runs in the same kernel does
 // phase 1 beside it.  Phases 3, 4 and 5 are the parts of phase 2 (see below), for a caller that has two
 // waves for them; the wave of phase 5 is the one that did phase 1 and 4 (`out->nB` is its).  (The phase is
-// an argument, not a template parameter: the LDS arrays below belong to the function, and each
-// instantiation of a template would have a set of its own.)
-__device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d, int round, int drop, int u, int lane,
-                                                 const float *logits, SelectIn in, const SelectFigs &fg, AView A,
+// an argument, not a template parameter: the code is inlined, and the phase known there.)
+template <class SM, class LG>
+__device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const Dims &d, int round, int drop, int u, int lane,
+                                                 const LG logits, SelectIn in, const SelectFigs &fg, AView A,
                                                  AView An, BView B, RowView rv, const int2 *nodes,
                                                  unsigned char *s_dyn, SelectOut *out = nullptr,
                                                  const bool FEW = false, const bool SHORT = false) {
@@ -160,19 +189,14 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
     int *s_bnode = reinterpret_cast<int *>(s_bhash + d.BCAP);
     int *s_blen = s_bnode + d.BCAP;
     int *s_bslot = s_blen + d.BCAP;
-    __shared__ double s_key[CAND_MAX];
-    __shared__ int s_ctok[CAND_MAX];
-    __shared__ double s_alogs[TBS_MAX_BEAM];
-    __shared__ u64 s_ahash[TBS_MAX_BEAM];
-    __shared__ int s_anode[TBS_MAX_BEAM], s_alen[TBS_MAX_BEAM], s_aslot[TBS_MAX_BEAM];
-    __shared__ double s_bkey[TBS_MAX_BEAM];
-    __shared__ int s_match[TBS_MAX_BEAM];
-    __shared__ int s_sel[TBS_MAX_BEAM];      // candidate index by rank
-    __shared__ double s_thr;
-    __shared__ int s_have_thr;
-    __shared__ float s_dnew[TBS_MAX_SEG * TBS_MAX_BEAM];   // frame distributions of the new hypotheses, [frame][hypothesis]
-    __shared__ float s_xpre[SEL_PRE_FRAMES * SEL_PRE_CANDS];   // logits of the candidates' tokens, [frame][candidate]
-    __shared__ int s_kh[TBS_MAX_BEAM], s_ktok[TBS_MAX_BEAM];   // kept candidates, by place: hypothesis they extend, token
+    constexpr int DNEW = SM::dnew, PF = SM::pf, PC = SM::pc;
+    double *const s_key = sm.s_key, *const s_alogs = sm.s_alogs, *const s_bkey = sm.s_bkey;
+    u64 *const s_ahash = sm.s_ahash;
+    int *const s_ctok = sm.s_ctok, *const s_anode = sm.s_anode, *const s_alen = sm.s_alen, *const s_aslot = sm.s_aslot;
+    int *const s_match = sm.s_match, *const s_sel = sm.s_sel, *const s_kh = sm.s_kh, *const s_ktok = sm.s_ktok;
+    float *const s_dnew = sm.s_dnew, *const s_xpre = sm.s_xpre;
+    double &s_thr = sm.s_thr;
+    int &s_have_thr = sm.s_have_thr;
     const int N = d.N;
     const int sp = fg.sp, cntA = fg.cntA, urow0 = fg.urow0, nB0 = fg.nB0, parity = fg.parity;
     const int H = sp > 0 ? cntA : 0;
@@ -215,8 +239,8 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
         if (PHASE == 0) sel_sync();   // (A's scores, staged just above, are read by other lanes below)
         const int nc = H * N;
         const float rcp_n = __builtin_amdgcn_rcpf((float)N);   // c / N as (c + 0.5) * (1 / N): exact for c < 1024
-        const bool pre_x = logits != nullptr && !drop && (FEW || sel_dist_form(nc, sp) == SEL_AHEAD);
-        float xpre[2][SEL_PRE_FRAMES];
+        const bool pre_x = !logits.none() && !drop && (FEW || sel_dist_form(nc, sp) == SEL_AHEAD);
+        float xpre[2][PF];
         if (do_cand) {
             int tok_mine = -1, tok_mine2 = -1;   // (tokens of the candidates `lane` and `lane + 64`)
             for (int c = lane; c < nc; c += WAVE) {
@@ -231,11 +255,10 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
             // suffice the logits of every candidate's token are asked for now and wait in registers: their
             // round trip runs beside the merge and the ranking instead of behind them.
             if (pre_x) {
-                auto ask = [&](float (&x)[SEL_PRE_FRAMES], int c, int tok) {
-                    const float *lrow = logits + (long)(urow0 + (int)(((float)c + 0.5f) * rcp_n) * (in.slot_rows ? d.S : sp)) * d.Vl +
-                                        max(tok, 0);
+                auto ask = [&](float (&x)[PF], int c, int tok) {
+                    const long at = (long)(urow0 + (int)(((float)c + 0.5f) * rcp_n) * (in.slot_rows ? d.S : sp)) * d.Vl + max(tok, 0);
 #pragma unroll
-                    for (int q = 0; q < SEL_PRE_FRAMES; ++q) x[q] = lrow[(long)min(q, sp - 1) * d.Vl];
+                    for (int q = 0; q < PF; ++q) x[q] = logits.at(at + (long)min(q, sp - 1) * d.Vl);
                 };
                 ask(xpre[0], min(lane, nc - 1), tok_mine);
                 if (!FEW && nc > WAVE) ask(xpre[1], min(lane + WAVE, nc - 1), tok_mine2);
@@ -319,9 +342,9 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
             });
             if (pre_x) {
 #pragma unroll
-                for (int q = 0; q < SEL_PRE_FRAMES; ++q) {
-                    s_xpre[q * SEL_PRE_CANDS + lane] = xpre[0][q];
-                    if (!FEW && nc > WAVE) s_xpre[q * SEL_PRE_CANDS + WAVE + lane] = xpre[1][q];
+                for (int q = 0; q < PF; ++q) {
+                    s_xpre[q * PC + lane] = xpre[0][q];
+                    if (!FEW && nc > WAVE) s_xpre[q * PC + WAVE + lane] = xpre[1][q];
                 }
             }
         }
@@ -348,7 +371,7 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                 An.count[u] = total;
                 if (out) out->total = total;
             }
-            const bool by_frame = !FEW && !SHORT && logits != nullptr && sel_dist_form(nc, sp) == SEL_BY_FRAME;
+            const bool by_frame = !FEW && !SHORT && !logits.none() && sel_dist_form(nc, sp) == SEL_BY_FRAME;
             if (keep) {
                 const int c = s_sel[lane];
                 const int h = (int)(((float)c + 0.5f) * __builtin_amdgcn_rcpf((float)N));   // c / N for c < 256
@@ -384,29 +407,29 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                     s_ktok[pos] = tok;
                 } else if (pre_x) {
                     // (the S' <= 8 values stay in registers)
-                    float x[SEL_PRE_FRAMES];
+                    float x[PF];
                     float mx = -INFINITY;
 #pragma unroll
-                    for (int q = 0; q < SEL_PRE_FRAMES; ++q) {
-                        x[q] = s_xpre[q * SEL_PRE_CANDS + c] + in.lc[h * sp + min(q, sp - 1)];
+                    for (int q = 0; q < PF; ++q) {
+                        x[q] = s_xpre[q * PC + c] + in.lc[h * sp + min(q, sp - 1)];
                         if (q < sp) mx = fmaxf(mx, x[q]);
                     }
                     float sum = 0.f;
 #pragma unroll
-                    for (int q = 0; q < SEL_PRE_FRAMES; ++q)
+                    for (int q = 0; q < PF; ++q)
                         if (q < sp) sum += __expf(x[q] - mx);
                     const float lz = mx + __logf(sum);
 #pragma unroll
-                    for (int q = 0; q < SEL_PRE_FRAMES; ++q)
+                    for (int q = 0; q < PF; ++q)
                         if (q < d.S) dh[q] = q < sp ? x[q] - lz : -INFINITY;
-                    for (int t = SEL_PRE_FRAMES; t < d.S; ++t) dh[t] = -INFINITY;
-                } else if (!FEW && logits) {
+                    for (int t = PF; t < d.S; ++t) dh[t] = -INFINITY;
+                } else if (DNEW > 1 && !FEW && !logits.none()) {
                     float *sd = s_dnew + lane;
                     float mx = -INFINITY;
                     for (int t0 = 0; t0 < sp; t0 += 8) {   // (eight logits asked for before the first is used)
                         float xv[8];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) xv[q] = logits[(long)(row0 + min(t0 + q, sp - 1)) * d.Vl + tok];
+                        for (int q = 0; q < 8; ++q) xv[q] = logits.at((long)(row0 + min(t0 + q, sp - 1)) * d.Vl + tok);
 #pragma unroll
                         for (int q = 0; q < 8; ++q)
                             if (t0 + q < sp) {
@@ -426,13 +449,13 @@ __device__ __forceinline__ void select_merge_utt(const int PHASE, const Dims &d,
                     for (int t = 1; t < d.S; ++t) dh[t] = -INFINITY;
                 }
             }
-            if (by_frame && total > 0) {   // (uniform)
+            if (DNEW > 1 && by_frame && total > 0) {   // (uniform)
                 sel_sync();
                 const float rcp_sp = __builtin_amdgcn_rcpf((float)sp);   // (exact quotients up to 32 x 64 items)
 #pragma unroll 4
                 for (int it = lane; it < total * sp; it += WAVE) {
                     const int k = (int)(((float)it + 0.5f) * rcp_sp), t = it - k * sp, h = s_kh[k];
-                    s_dnew[t * TBS_MAX_BEAM + k] = logits[(long)(urow0 + h * (in.slot_rows ? d.S : sp) + t) * d.Vl + s_ktok[k]] +
+                    s_dnew[t * TBS_MAX_BEAM + k] = logits.at((long)(urow0 + h * (in.slot_rows ? d.S : sp) + t) * d.Vl + s_ktok[k]) +
                                                    in.lc[h * sp + t];
                 }
                 sel_sync();

@@ -75,6 +75,17 @@ struct tbs_ctx {
     std::vector<int> live_u;   // hypotheses each utterance takes into the coming round
     int64_t fx_calls, fx_joined;   // joiner invocations and frames joined, counted on the host in this layout
     int fx_nodes;                  // and trie nodes taken
+    // whole segments as one launch (see xcd_kernels.hip); what it needs beside the slot layout's memory
+    bool xcd_ready;     // the context's shapes and device can run it
+    bool xcd;           // the current batch does
+    XcdCtl *x_ctl;      // [2], used in turn: a launch clears the next one's
+    int *x_order;       // [U] the XCDs' utterances (behind utt_fig)
+    int x_first[XR_XCDS + 1];
+    bf16_t *x_hb, *x_amat;
+    int4 *x_desc;
+    int *h_xcd;         // pinned: [XCDs * workgroups, 4] how each workgroup ended, then [XCDs, XR_SEGS] rounds
+    int *h_xcd_dev;
+    int x_seq;
     int2 *nodes;
     long pool_rows;
     float *pool_p, *pool_h, *pool_c;
@@ -262,6 +273,7 @@ void tbs_free(tbs_ctx *c) {
     for (void *p : c->allocs) (void)hipFree(p);
     if (c->h_counts) (void)hipHostFree(c->h_counts);
     if (c->h_live) (void)hipHostFree(c->h_live);
+    if (c->h_xcd) (void)hipHostFree(c->h_xcd);
     if (c->h_desc) (void)hipHostFree(c->h_desc);
     for (auto &e : c->events) {
         (void)hipEventDestroy(e.a);
@@ -301,6 +313,9 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->last_hip = 0;
     c->h_counts = nullptr;
     c->h_live = nullptr;
+    c->h_xcd = nullptr;
+    c->xcd_ready = c->xcd = false;
+    c->x_seq = 0;
     c->fixed = c->trie_full = false;
     c->trie_share = c->full_share = 0.0;
     c->h_desc = nullptr;
@@ -369,7 +384,8 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     rc |= dev_alloc(c, &c->rv.row_enc, M);
     rc |= dev_alloc(c, &c->rv.row_slot, M);
     rc |= dev_alloc(c, &c->rv.counts, TBS_CNT_SIZE);
-    rc |= dev_alloc(c, &c->utt_fig, U * TBS_FIG_SIZE);
+    rc |= dev_alloc(c, &c->utt_fig, U * TBS_FIG_SIZE + U);   // (and the order of the utterances, see xcd_kernels.hip)
+    if (rc == 0) c->x_order = c->utt_fig + U * TBS_FIG_SIZE;
     rc |= dev_alloc(c, &c->live_sum, 2);
     // (utterance lengths, first frames and the frame-copy descriptors of a push side by side, so that
     // one copy from pinned memory brings all a push has to tell the kernels)
@@ -436,6 +452,18 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         c->bperm[l] = nullptr;
         if (l > 0) rc |= dev_alloc(c, &c->bperm[l], (size_t)4 * d.H);
     }
+    {
+        int cus = 0;
+        c->xcd_ready = cfg->dtype == 1 && (cfg->debug & ~131072) == 0 && cfg->joiner_chunk_rows == 0 && xcd_fits(d) &&
+                       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device_id) == hipSuccess &&
+                       cus == XR_XCDS * XR_WGS;
+    }
+    if (c->xcd_ready) {
+        rc |= dev_alloc(c, &c->x_ctl, 2);
+        rc |= dev_alloc(c, &c->x_desc, UN);
+        rc |= dev_alloc(c, &c->x_hb, (size_t)c->pool_rows * d.H);
+        rc |= dev_alloc(c, &c->x_amat, (size_t)(M + 16 * XR_XCDS) * d.Dj);   // (every XCD's rows in whole tiles of 16)
+    }
     rc |= dev_alloc(c, &c->res_count, U);
     rc |= dev_alloc(c, &c->res_len, UN);
     rc |= dev_alloc(c, &c->res_logs, UN);
@@ -473,6 +501,18 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         return TBS_ENOMEM;
     }
     memset(c->h_live, 0, 2 * (size_t)U * sizeof(int));
+    if (c->xcd_ready) {
+        const size_t ints = 4 * XR_XCDS * XR_WGS + XR_XCDS * XR_SEGS;
+        e = hipHostMalloc((void **)&c->h_xcd, ints * sizeof(int), hipHostMallocMapped);
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&c->h_xcd_dev, c->h_xcd, 0);
+        if (e == hipSuccess) e = hipMemsetAsync(c->x_ctl, 0, 2 * sizeof(XcdCtl), c->stream);
+        if (e != hipSuccess) {
+            c->last_hip = (int)e;
+            tbs_free(c);
+            return TBS_ENOMEM;
+        }
+        memset(c->h_xcd, 0, ints * sizeof(int));
+    }
     e = hipHostGetDevicePointer((void **)&c->h_counts_dev, c->h_counts, 0);
     if (e != hipSuccess) {
         c->last_hip = (int)e;
@@ -632,7 +672,23 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
         }
         c->trie_share = (double)pool / weight_all;
     }
-    HIPCHK(c, hipMemcpyAsync(c->utt_fig, fig.data(), sizeof(int) * fig.size(), hipMemcpyHostToDevice, c->stream));
+    // The utterances of each XCD, in falling length and dealt out back and forth, so that the XCDs get the same work
+    // and an XCD's utterances that still have frames come first.
+    {
+        std::vector<int> by_length(U);
+        for (int u = 0; u < U; ++u) by_length[u] = u;
+        std::stable_sort(by_length.begin(), by_length.end(), [&](int a, int b) { return c->h_T[a] > c->h_T[b]; });
+        for (int x = 0; x < XR_XCDS; ++x) {
+            c->x_first[x] = (int)fig.size() - U * TBS_FIG_SIZE;
+            for (int k = 0; k < U; ++k) {
+                const int j = k % XR_XCDS;
+                if (((k / XR_XCDS) % 2 ? XR_XCDS - 1 - j : j) == x) fig.push_back(by_length[k]);
+            }
+        }
+        c->x_first[XR_XCDS] = U;
+    }
+    HIPCHK(c, hipMemcpyAsync(c->utt_fig, fig.data(), sizeof(int) * (size_t)U * TBS_FIG_SIZE, hipMemcpyHostToDevice, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->x_order, fig.data() + (size_t)U * TBS_FIG_SIZE, sizeof(int) * (size_t)U, hipMemcpyHostToDevice, c->stream));
     // the host arrays above are read by the copies: finish them before returning
     HIPCHK(c, hipStreamSynchronize(c->stream));
     c->seg = -1;
@@ -651,6 +707,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->trie_full = false;
     c->fixed = fixed_layout_ok(c);
     c->s1 = c->fixed && one_frame_ok(c);
+    c->xcd = c->xcd_ready && c->fixed && !c->s1 && U <= XR_XCDS * XR_POS;
     return TBS_OK;
 }
 
@@ -1287,6 +1344,137 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
     return TBS_OK;
 }
 
+// Only one launch of the kernel that decodes whole segments can be on a GPU at a time (its workgroups take every CU and wait
+// for each other): a call that finds another one's under way runs its batch in the slot layout.
+static std::mutex g_xcd_mutex[TBS_MAX_DEVICES];
+
+// Segments [seg0, seg1) in one launch or several.  *ran is the number of segments that were decoded: fewer, with TBS_OK,
+// where the GPU was not free for it; the rest has to run in the slot layout, which finds everything in its place.
+static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
+    *ran = 0;
+    std::unique_lock<std::mutex> alone(g_xcd_mutex[c->cfg.device_id], std::try_to_lock);
+    if (!alone.owns_lock()) return TBS_OK;
+    const Dims &d = c->cur;
+    XcdArgs g{};
+    g.d = d;
+    g.max_rounds = c->cfg.max_rounds_per_segment;
+    g.act = c->cfg.act;
+    g.expect = XR_XCDS * XR_WGS + (c->cfg.debug & 131072 ? 1 : 0);
+    int tiles = 0;
+    for (int x = 0; x <= XR_XCDS; ++x) g.first[x] = c->x_first[x];
+    for (int x = 0; x < XR_XCDS; ++x) {
+        g.tile0[x] = tiles;
+        tiles += ((g.first[x + 1] - g.first[x]) * d.N * d.S + 15) / 16;
+    }
+    g.order = c->x_order;
+    g.utt_T = c->utt_T;
+    g.utt_off = c->utt_off;
+    g.enc = (const bf16_t *)c->enc;
+    g.w_out = (const bf16_t *)c->w.w_out;
+    g.w_gate = (const bf16_t *)c->wperm[0];
+    g.w_proj = (const bf16_t *)c->w.w_proj;
+    g.b_out = c->w.b_out;
+    g.b_proj = c->w.b_proj;
+    g.emb_gates = c->emb_gates_perm;
+    g.A[0] = c->A[0];
+    g.A[1] = c->A[1];
+    g.B = c->B;
+    g.rv = c->rv;
+    g.fig = c->utt_fig;
+    g.nodes = c->nodes;
+    g.pool_p = c->pool_p;
+    g.pool_h = c->pool_h;
+    g.pool_c = c->pool_c;
+    g.hb = c->x_hb;
+    g.hb_bytes = c->pool_rows * d.H * 2;
+    g.amat = c->x_amat;
+    g.logits = c->logits;
+    g.desc = c->x_desc;
+    g.host = c->h_xcd_dev;
+    g.host_rounds = c->h_xcd_dev + 4 * XR_XCDS * XR_WGS;
+    const int *ends = c->h_xcd, *rounds = c->h_xcd + 4 * XR_XCDS * XR_WGS;
+    c->prep_ahead = false;
+    for (int s0 = seg0; s0 < seg1; s0 += XR_SEGS) {
+        const int s1 = std::min(seg1, s0 + XR_SEGS);
+        g.seg0 = s0;
+        g.seg1 = s1;
+        g.seq = ++c->x_seq & 0x7FFFFF;
+        g.ctl = c->x_ctl + (c->x_seq & 1);
+        g.ctl_next = c->x_ctl + ((c->x_seq + 1) & 1);
+        memset(c->h_xcd + 4 * XR_XCDS * XR_WGS, 0, sizeof(int) * XR_XCDS * XR_SEGS);
+        HIPCHK(c, launch_xcd_decode(c->stream, g));
+        // every workgroup says how it ended; the wait is bounded as that for a round's words
+        bool absent = false, full = false, over = false, stuck = false;
+        int64_t calls = 0, joined = 0, nodes = 0;
+        std::chrono::steady_clock::time_point t0;
+        bool timing = false;
+        int w = 0;
+        for (unsigned spin = 1; w < XR_XCDS * XR_WGS; ++spin) {
+            const int v = __atomic_load_n(&ends[4 * w + 3], __ATOMIC_ACQUIRE);
+            if ((v >> 8) == g.seq) {
+                const int how = v & 255;
+                absent = absent || how == XR_ABSENT;
+                full = full || how == XR_TRIE;
+                over = over || how == XR_ROUNDS;
+                stuck = stuck || how == XR_STUCK;
+                if (how != XR_ABSENT) {
+                    calls += ends[4 * w];
+                    joined += ends[4 * w + 1];
+                    nodes += ends[4 * w + 2];
+                }
+                ++w;
+                continue;
+            }
+            if ((spin & 0x3FFFFF) == 0) {
+                const hipError_t e = hipStreamQuery(c->stream);
+                if (e == hipSuccess) {
+                    if ((__atomic_load_n(&ends[4 * w + 3], __ATOMIC_ACQUIRE) >> 8) == g.seq) continue;
+                    c->last_hip = (int)hipErrorUnknown;
+                    return TBS_EHIP;
+                }
+                if (e != hipErrorNotReady) {
+                    c->last_hip = (int)e;
+                    return TBS_EHIP;
+                }
+                const auto now = std::chrono::steady_clock::now();
+                if (!timing) {
+                    t0 = now;
+                    timing = true;
+                } else if (now - t0 > std::chrono::seconds(3 * TBS_WAIT_LIMIT_S)) {
+                    c->last_hip = (int)hipErrorLaunchTimeOut;
+                    return TBS_EHIP;
+                }
+            }
+        }
+        if (absent || stuck) HIPCHK(c, hipMemsetAsync(c->x_ctl, 0, 2 * sizeof(XcdCtl), c->stream));
+        if (absent) return TBS_OK;   // (all ended like this, with nothing changed but the counts of those that came)
+        c->fx_calls += calls;
+        c->fx_joined += joined;
+        for (int s = s0; s < s1; ++s) {   // the batch's joiner calls in lock-step
+            int most = 0;
+            for (int x = 0; x < XR_XCDS; ++x) most = std::max(most, rounds[x * XR_SEGS + s - s0]);
+            c->n_launches += most;
+        }
+        if (stuck) {
+            c->last_hip = (int)hipErrorLaunchTimeOut;
+            return TBS_EHIP;
+        }
+        if (full) {
+            c->trie_full = true;
+            return TBS_EOVERFLOW;
+        }
+        if (over) return TBS_EOVERFLOW;
+        c->fx_nodes += (int)nodes;
+        *ran = s1 - seg0;
+        c->seg = s1 - 1;
+        c->a_cur = 0;
+        c->h_counts[TBS_CNT_PAIRS] = 0;
+        c->h_counts[TBS_CNT_ROWS] = 0;
+        c->state = ST_SELECTED;
+    }
+    return TBS_OK;
+}
+
 // one segment: the head of the outer loop of Algorithm 1 and its inner loop (while Length(A) > 0)
 static int run_segment(tbs_ctx *c, int32_t seg_index) {
     if (c->fixed) return run_segment_fixed(c, seg_index);
@@ -1361,7 +1549,9 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
         }
         if (!any) break;
         for (int u = 0; u < U; ++u) c->h_T[u] = take[u];   // (the slot layout's host bookkeeping reads the step sizes)
-        const int rc = run_segment(c, 0);   // (waits for counts: the copy above is done by then)
+        int ran = 0, rc = TBS_OK;   // (both forms wait for the device: the copy above is done by then)
+        if (c->xcd && c->prof_kernel < 0) rc = run_segments_xcd(c, 0, 1, &ran);
+        if (rc == TBS_OK && ran == 0) rc = run_segment(c, 0);
         if (rc) return rc;
         for (int u = 0; u < U; ++u) pos[u] += take[u];
     }
@@ -1391,7 +1581,9 @@ static int decode_all(tbs_ctx *c, const void *enc_proj, const int32_t *frame_off
     if (rc) return rc;
     const int S = c->cur.S;
     const int nseg = (c->max_T + S - 1) / S;
-    for (int seg = 0; seg < nseg; ++seg) {          // while t <= Length(enc)
+    int seg = 0;
+    if (c->xcd && c->prof_kernel < 0 && nseg > 0 && (rc = run_segments_xcd(c, 0, nseg, &seg))) return rc;
+    for (; seg < nseg; ++seg) {          // while t <= Length(enc)
         if ((rc = run_segment(c, seg))) return rc;
     }
     return TBS_OK;
@@ -1427,7 +1619,7 @@ int tbs_stats(const tbs_ctx *c, int64_t *joiner_calls, int64_t *joined_frames, i
 int tbs_path(const tbs_ctx *c) {
     if (!c) return TBS_EINVAL;
     if (c->state == ST_INIT) return TBS_ESTATE;
-    return (c->fixed ? 1 : 0) | (c->s1 ? 2 : 0);
+    return (c->fixed ? 1 : 0) | (c->s1 ? 2 : 0) | (c->xcd ? 4 : 0);
 }
 
 // ------------------------------------------------------------------ inspection

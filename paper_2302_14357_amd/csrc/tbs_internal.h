@@ -161,6 +161,49 @@ struct PartEp {
 };
 __host__ __device__ inline int part_width(int np) { return (4 + 2 * np + 3) & ~3; }   // (whole 16-byte pieces)
 
+// Whole segments of a batch as one launch, every XCD decoding utterances of its own (xcd_kernels.hip).
+#define XR_XCDS 8
+#define XR_WGS 32      // workgroups per XCD, one on each of its CUs
+#define XR_POS 64      // most utterances an XCD decodes
+#define XR_KMAX 640    // widest joint space and LSTM
+#define XR_SEGS 4096   // most segments of a launch
+struct XcdCtl {        // device memory, zero when the launch begins
+    u64 bar[XR_XCDS * 16];            // an XCD's barriers (a line each)
+    unsigned place[XR_XCDS * 32];     // workgroups that came on each XCD
+    unsigned arrived, state;          // all of them; 1: all came, 2: given up
+    unsigned pad[30];
+};
+enum { XR_DONE = 1, XR_ABSENT = 2, XR_TRIE = 3, XR_ROUNDS = 4, XR_STUCK = 5 };   // how a workgroup ended
+#define XR_FULL_TRIE (1 << 20)
+struct XcdArgs {
+    Dims d;
+    int seg0, seg1;         // segments of this launch
+    int max_rounds;         // limit on the rounds of a segment (0: none)
+    int act, seq;
+    int expect;             // workgroups that have to come before anything is done
+    int first[XR_XCDS + 1]; // the XCDs' parts of `order` [U]: utterances in falling length
+    int tile0[XR_XCDS];     // and of amat, in tiles of 16 rows
+    const int *order, *utt_T, *utt_off;
+    const bf16_t *enc, *w_out, *w_gate, *w_proj;   // (gate rows interleaved, see LstmEp)
+    const float *b_out, *b_proj, *emb_gates;
+    AView A[2];
+    BView B;
+    RowView rv;
+    int *fig;
+    int2 *nodes;
+    float *pool_p, *pool_h, *pool_c;
+    bf16_t *hb;             // [slots, H] h as bf16, the rows of the products
+    long hb_bytes;
+    bf16_t *amat;           // joiner input rows, in pieces of 16 rows x 32 columns
+    float *logits;
+    int4 *desc;             // [U*N] state slot (-1: no hypothesis), parent's slot, last token
+    XcdCtl *ctl, *ctl_next;
+    int *host;              // pinned [workgroups, 4]: joiner calls, frames joined, nodes taken, (seq << 8) | how it ended
+    int *host_rounds;       // pinned [XCDs, XR_SEGS]: rounds of each segment
+};
+bool xcd_fits(const Dims &d);
+hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g);
+
 // ---- launchers (each enqueues on `st` and returns the HIP status) ----
 hipError_t launch_init_batch(hipStream_t st, const Dims &d, BView B, AView A0, AView A1, RowView rv, int2 *nodes,
                              float *pool_p, float *pool_h, float *pool_c, const float *pred_init,

@@ -1239,3 +1239,97 @@ def test_errors_are_codes_not_crashes():
     assert e.value.code == -5
     tbs.close()
     _check_decode(shape, model, offsets, enc, 2, 2)
+
+
+def _one_launch(tbs):
+    return bool(tbs.L.tbs_path(tbs.ctx) & 4)
+
+
+@pytest.mark.parametrize("d,hidden,V,N,S,lengths,peaked", [
+    (128, 128, 17, 1, 2, [5], False), (128, 256, 96, 5, 3, [0, 1, 7, 12, 23, 31], True), (256, 128, 200, 5, 1, [3] * 9, False),
+    (384, 384, 257, 7, 5, list(range(1, 18)), True), (512, 640, 1024, 5, 3, [8] * 3 + [40] * 6, False), (640, 512, 1023, 3, 2, [9, 30], False),
+    (512, 640, 1000, 10, 3, [17] * 5, False), (512, 640, 500, 10, 5, [21, 20, 19, 5], True), (128, 128, 512, 8, 4, [6, 33], True),
+    (128, 128, 33, 11, 5, [11, 12], True), (256, 384, 40, 4, 3, [3 + i % 7 for i in range(300)], False), (128, 128, 64, 6, 1, [9, 2, 31], True)])
+def test_segments_in_one_launch_equal_four_kernels_a_round(d, hidden, V, N, S, lengths, peaked):
+    """Whole segments inside one launch, every XCD with utterances of its own: the same bits as the four kernels a round (debug
+    bit 16), whose arithmetic and order of sums it keeps, and the same counters; every width of K, ragged tiles of rows,
+    columns and utterances (none, fewer than XCDs, more than workgroups), beams on both sides of the workgroup sizes."""
+    shape = small_bf16_shape(n_utts=len(lengths), vocab=V, d=d, hidden=hidden)
+    cap = 0
+    if peaked:
+        shape, cap = _peaked(shape, 8.0, 8.0), 5
+    model, offsets, enc = build_case(shape, n_utts=len(lengths), lengths=np.array(lengths))
+    kw = dict(max_rounds_per_segment=cap) if cap else {}
+    seen = []
+    for debug in (0, 65536, 131072):
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
+        frames = tbs.upload_frames(enc)
+        got = [tbs.decode(frames, offsets), tbs.decode(frames, offsets)]
+        assert _one_launch(tbs) == (debug != 65536) and tbs.path()["fixed_places"]
+        assert got[0] == got[1]
+        seen.append((got[0], tbs.stats(), tbs.counts()["nodes"]))
+        tbs.close()
+    assert seen[0] == seen[1] == seen[2]   # (131072: the launch gives up and the batch runs with four kernels a round)
+    if len(lengths) < 20:
+        _check_decode(shape, model, offsets, enc, N, S, max_rounds=cap)
+
+
+@pytest.mark.parametrize("debug", [0, 131072])
+def test_streams_in_one_launch_a_step(debug):
+    """A stream pushed in uneven pieces, utterances starting and ending segments at different steps, gives what the four
+    kernels a round give for the whole batch; tries, lists and states are left as those kernels go on from them."""
+    N, S = 5, 3
+    shape = _peaked(small_bf16_shape(n_utts=11, vocab=120, d=256, hidden=128), 8.0, 8.0)
+    model, offsets, enc = build_case(shape, n_utts=11, lengths=np.array([0, 1, 3, 4, 9, 10, 14, 21, 22, 5, 30]))
+    want, _ = _gpu_decode(shape, model, offsets, enc, N, S, debug=65536, max_rounds_per_segment=5)
+    tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=12, max_rounds_per_segment=5, debug=debug)
+    _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: (u + 2 * c) % 5)
+    assert _one_launch(tbs)
+    assert tbs.result() == want
+    tbs.close()
+
+
+def test_contexts_that_decode_at_the_same_time():
+    """Two threads, each with a context on a stream of its own: whoever finds the other's launch under way takes four kernels a
+    round; both get the results they get alone."""
+    import threading
+    import torch
+    N, S = 5, 3
+    shape = small_bf16_shape(n_utts=9, vocab=200, d=256, hidden=256)
+    model, offsets, enc = build_case(shape, n_utts=9, lengths=np.arange(20, 29))
+    want, _ = _gpu_decode(shape, model, offsets, enc, N, S)
+    out, streams = [None, None], [torch.cuda.Stream(), torch.cuda.Stream()]
+    ctx = []
+    for st in streams:
+        with torch.cuda.stream(st):
+            ctx.append(make_tbs(shape, model, offsets, N, S))
+    frames = [t.upload_frames(enc) for t in ctx]
+    torch.cuda.synchronize()
+
+    def work(i):
+        out[i] = [ctx[i].decode(frames[i], offsets) for _ in range(8)]
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert out[i] is not None and all(g == want for g in out[i])
+        ctx[i].close()
+
+
+def test_codes_of_segments_in_one_launch():
+    """Rounds beyond the capacity and a full share of the trie are the same codes as with four kernels a round."""
+    from paper_2302_14357_amd.tbs import TbsError
+    shape = small_bf16_shape(n_utts=5, vocab=64, d=128, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=5, lengths=np.array([3, 40, 8, 21, 13]))
+    for kw in (dict(rounds_capacity=2), dict(max_nodes=60)):
+        for debug in (0, 65536):
+            tbs = make_tbs(shape, model, offsets, 4, 3, debug=debug, **kw)
+            frames = tbs.upload_frames(enc)
+            for _ in range(2):
+                with pytest.raises(TbsError) as e:
+                    tbs.decode(frames, offsets)
+                assert e.value.code == -5
+            tbs.close()
