@@ -132,11 +132,24 @@ struct ExpandBest {
     float jv[TW * EXP_CAND_CAP];  // ... and all of them in one list, in any order
     int jk[TW * EXP_CAND_CAP];
     int jn;                              // entries of the joint list (cleared by the caller, a barrier ahead)
+    __device__ __forceinline__ int joint(int) const { return jn; }
+    __device__ __forceinline__ const float *joint_v() const { return jv; }
+    __device__ __forceinline__ const int *joint_k() const { return jk; }
+};
+template <>
+struct ExpandBest<1> {            // (one wave: its list is the joint list)
+    float cv[1][EXP_CAND_CAP];
+    int ck[1][EXP_CAND_CAP];
+    __device__ __forceinline__ int joint(int total) const { return total; }
+    __device__ __forceinline__ const float *joint_v() const { return cv[0]; }
+    __device__ __forceinline__ const int *joint_k() const { return ck[0]; }
 };
 template <int SMAX, int TW>
 struct ExpandShared : ExpandBest<TW> {
     float pm[SMAX][TW], pz[SMAX][TW];   // per-wave row maxima and row sums
 };
+template <int SMAX>
+struct ExpandShared<SMAX, 1> : ExpandBest<1> {};
 
 // What a workgroup needs to know of one (utterance, hypothesis) pair besides its logits.
 template <int SMAX>
@@ -222,8 +235,21 @@ __device__ __forceinline__ float wave_max_ord(float f) {
                      max(__builtin_amdgcn_readlane(v, 32), __builtin_amdgcn_readlane(v, 48))));
 }
 
+// What a team's threads left in LDS is there for all of them: a workgroup-wide barrier, or, for a team that is one wave, no
+// more than the order of its own accesses.
+template <int TW>
+__device__ __forceinline__ void team_sync() {
+    if constexpr (TW > 1) {
+        __syncthreads();
+    } else {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    }
+}
+
 // The N best of the scores v (thread tid holds columns 4 * (tid + TT * q) + c, zero where there is none),
-// by a team of TT threads, one workgroup-wide barrier inside.  cs / ct: logarithms and tokens in order
+// by a team of TT threads, one team_sync inside (sm.jn is zero, a team_sync ahead, for a team of several waves).  cs / ct: logarithms and tokens in order
 // (-inf / -1 where there are fewer).  live = false: the team only keeps the barrier company.
 template <int NV4, int TT>
 __device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT / 64> &sm, const Dims &d, int tid, bool live,
@@ -311,9 +337,9 @@ __device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT /
                     if (4 * (tid + TT * q) + c == bk) v[4 * q + c] = -1.f;
         }
     }
-    // append this wave's list to the joint list (the order of waves there does not matter: the
-    // merge below orders by score and token)
-    {
+    if constexpr (TW > 1) {
+        // append this wave's list to the joint list (the order of waves there does not matter: the
+        // merge below orders by score and token)
         int base = 0;
         if (lane == 0) base = atomicAdd(&sm.jn, total);
         base = __builtin_amdgcn_readfirstlane(base);
@@ -322,16 +348,18 @@ __device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT /
             sm.jk[base + lane] = sm.ck[wave][lane];
         }
     }
-    __syncthreads();
+    team_sync<TW>();
     // ---- merge (first wave): larger score first, smaller token on equal scores
     if (wave == 0 && live) {
-        const int all = sm.jn;
-        if (all <= 64) {
+        const int all = sm.joint(total);
+        const float *jv = sm.joint_v();
+        const int *jk = sm.joint_k();
+        if (TW == 1 || all <= 64) {
             // one candidate per lane, as a 64-bit key (score bits, inverted token) that orders like
             // the rule above; the rank of a candidate is the number of keys above its own
             const bool have = lane < all;
-            const float x = have ? sm.jv[lane] : 0.f;
-            const int k = have ? sm.jk[lane] : 0x7fffffff;
+            const float x = have ? jv[lane] : 0.f;
+            const int k = have ? jk[lane] : 0x7fffffff;
             const u64 key = ((u64)__float_as_uint(x) << 32) | (unsigned)(0x7fffffff - k);
             int rank = 0;
             for (int j = 0; j < all; ++j) {
@@ -347,8 +375,8 @@ __device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT /
 #pragma unroll
             for (int i = 0; i < TW; ++i) {
                 const bool have = lane + 64 * i < all;
-                cv[i] = have ? sm.jv[lane + 64 * i] : -1.f;
-                ck[i] = have ? sm.jk[lane + 64 * i] : 0x7fffffff;
+                cv[i] = have ? jv[lane + 64 * i] : -1.f;
+                ck[i] = have ? jk[lane + 64 * i] : 0x7fffffff;
             }
             for (int n = 0; n < d.N; ++n) {
                 float bv = -1.f;
@@ -370,24 +398,20 @@ __device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT /
     }
 }
 
-// (expand_pair meets the other teams of its workgroup at this many barriers; a wave of the workgroup
-// that does something else meanwhile must meet them too)
-#define EXPAND_PAIR_BARRIERS 3
-
-// Everything after the load for one pair, by a team of TT threads (tid = 0 .. TT-1 within the team).
+// Everything after the load for one pair, by a team of TT threads (tid = 0 .. TT-1 within the team), in two parts: up to the
+// blank expansion and the row coefficients cf, then the N best.
 // Results: lc_out[t] = log(alpha_t / Z_t) - m_t for the pair's frames, *dphi_out = log of the blank
 // expansion relative to the hypothesis score, cs / ct = logarithms and tokens of the N best
 // expansions in order (-inf / -1 where there are fewer); any of them may point into LDS.
-// live = false: a team with no hypothesis; it only keeps the workgroup's barriers company.
+// live = false: a team with no hypothesis; it only keeps the workgroup's barriers company (a team of one wave has none).
 template <int NV4, int SMAX, int TT>
-__device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const ExpandPair<SMAX> &pi,
-                                            ExpandShared<SMAX, TT / 64> &sm, const Dims &d, int tid, bool live,
-                                            float *lc_out, float *dphi_out, float *cs, int *ct,
-                                            float *__restrict__ row_stats, float *__restrict__ delta_nb) {
+__device__ __forceinline__ void expand_front(float (&e)[SMAX][NV4 * 4], float (&cf)[SMAX], const ExpandPair<SMAX> &pi,
+                                             ExpandShared<SMAX, TT / 64> &sm, const Dims &d, int tid, bool live,
+                                             float *lc_out, float *dphi_out, float *__restrict__ row_stats) {
     constexpr int NC = NV4 * 4;  // columns per thread
     constexpr int TW = TT / 64;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int V = d.V, V4 = d.Vl >> 2;
+    const int V4 = d.Vl >> 2;
     // Rows past S' and columns past V hold copies of real logits (see expand_load): copies leave a
     // row maximum unchanged, the row sums skip the copied columns, the copied rows get coefficient
     // zero and the copied columns score zero below.  (The columns between V and Vl hold -inf: e = 0.)
@@ -398,25 +422,31 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
 #pragma unroll
         for (int c = 0; c < NC; ++c) mrow[t] = fmaxf(mrow[t], e[t][c]);
     }
-    // ---- row maxima across the workgroup (waves by DPP, then through LDS)
+    // ---- row maxima across the team (waves by DPP, then through LDS)
+    if constexpr (TW == 1) {
 #pragma unroll
-    for (int t = 0; t < SMAX; ++t) {
-        const float m = wave_max_ord(mrow[t]);
-        if (lane == 0) sm.pm[t][wave] = m;
-    }
-    if (tid == 0) sm.jn = 0;
-    __syncthreads();
+        for (int t = 0; t < SMAX; ++t) mrow[t] = wave_max_ord(mrow[t]);   // (uniform)
+    } else {
 #pragma unroll
-    for (int t = 0; t < SMAX; ++t) {
-        float m = sm.pm[t][0];
+        for (int t = 0; t < SMAX; ++t) {
+            const float m = wave_max_ord(mrow[t]);
+            if (lane == 0) sm.pm[t][wave] = m;
+        }
+        if (tid == 0) sm.jn = 0;
+        __syncthreads();
 #pragma unroll
-        for (int w = 1; w < TW; ++w) m = fmaxf(m, sm.pm[t][w]);
-        if (SMAX * TW > 8) __builtin_amdgcn_sched_barrier(0);   // one row at a time: the partial results of many rows at once cost registers
-        mrow[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));   // uniform: a scalar register
+        for (int t = 0; t < SMAX; ++t) {
+            float m = sm.pm[t][0];
+#pragma unroll
+            for (int w = 1; w < TW; ++w) m = fmaxf(m, sm.pm[t][w]);
+            if (SMAX * TW > 8) __builtin_amdgcn_sched_barrier(0);   // one row at a time: the partial results of many rows at once cost registers
+            mrow[t] = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(m)));   // uniform: a scalar register
+        }
     }
     // ---- e = exp(l - m_t), once per logit; row sums across the workgroup.  (The exponent is one fused multiply-add, so
     // every e of a row carries the rounding of m_t log2(e) as a common factor, up to 1e-6 for m_t = 20.  What is
     // set against the row sum therefore takes the same factor: the blank probability below and log(alpha_t / Z_t).)
+    float zrow[SMAX];
 #pragma unroll
     for (int t = 0; t < SMAX; ++t) {
         const float nm = -mrow[t] * 1.44269504088896341f;
@@ -431,16 +461,17 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
             }
             z += (tid + TT * q < V4) ? zq : 0.f;
         }
-        z = wave_sum(z);
-        if (lane == 0) sm.pz[t][wave] = z;
+        zrow[t] = wave_sum(z);
+        if constexpr (TW > 1)
+            if (lane == 0) sm.pz[t][wave] = zrow[t];
     }
-    __syncthreads();
+    if constexpr (TW > 1) __syncthreads();
     // ---- every thread: row sums, forward variable (Eq. 3 as a scan), Eq. 7, the row coefficients.
     // The scan runs on logarithms: la_t = log alpha_t = logaddexp(la_{t-1} + log b_{t-1}, log d_old[t]),
     // which has the range the products of Eq. 3 need (see ScanAlpha) at four transcendentals and a
     // dozen plain operations per frame; the values are the same in every lane.  What goes to memory
     // is kept in registers until the scan is over and then stored by one thread in one go.
-    float cf[SMAX], lcrow[SMAX];
+    float lcrow[SMAX];
     float lphi = -INFINITY;
     {
         float la = -INFINITY, lbprev = 0.f;
@@ -449,10 +480,13 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
             cf[t] = 0.f;
             lcrow[t] = 0.f;
             if (t < pi.sp) {   // (uniform)
-                float z = sm.pz[t][0];
+                float z = zrow[t];
+                if constexpr (TW > 1) {
+                    z = sm.pz[t][0];
 #pragma unroll
-                for (int w = 1; w < TW; ++w) z += sm.pz[t][w];
-                __builtin_amdgcn_sched_barrier(0);
+                    for (int w = 1; w < TW; ++w) z += sm.pz[t][w];
+                    __builtin_amdgcn_sched_barrier(0);
+                }
                 const float lz = __logf(z);
                 const float nm = -mrow[t] * 1.44269504088896341f;     // (as in e)
                 const float lb = fmaf(fmaf(pi.lblank[t], 1.44269504088896341f, nm), 0.69314718055994531f, -lz);   // log of the blank probability of frame t
@@ -478,6 +512,14 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
             if (t < pi.sp) lc_out[t] = lcrow[t];   // log(alpha_t / Z_t) - m_t
         *dphi_out = lphi;
     }
+}
+
+template <int NV4, int SMAX, int TT>
+__device__ __forceinline__ void expand_back(float (&e)[SMAX][NV4 * 4], const float (&cf)[SMAX], const ExpandPair<SMAX> &pi,
+                                            ExpandShared<SMAX, TT / 64> &sm, const Dims &d, int tid, bool live, float *cs, int *ct,
+                                            float *__restrict__ delta_nb) {
+    constexpr int NC = NV4 * 4;  // columns per thread
+    const int V = d.V, V4 = d.Vl >> 2;
     // ---- Eq. 4-6 from registers
     float v[NC];
 #pragma unroll
@@ -513,4 +555,14 @@ __device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const Exp
         }
     }
     expand_best<NV4, TT>(v, sm, d, tid, live, cs, ct);
+}
+
+template <int NV4, int SMAX, int TT>
+__device__ __forceinline__ void expand_pair(float (&e)[SMAX][NV4 * 4], const ExpandPair<SMAX> &pi,
+                                            ExpandShared<SMAX, TT / 64> &sm, const Dims &d, int tid, bool live,
+                                            float *lc_out, float *dphi_out, float *cs, int *ct,
+                                            float *__restrict__ row_stats, float *__restrict__ delta_nb) {
+    float cf[SMAX];
+    expand_front<NV4, SMAX, TT>(e, cf, pi, sm, d, tid, live, lc_out, dphi_out, row_stats);
+    expand_back<NV4, SMAX, TT>(e, cf, pi, sm, d, tid, live, cs, ct, delta_nb);
 }

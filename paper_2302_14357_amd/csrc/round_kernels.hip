@@ -32,7 +32,7 @@ __device__ __forceinline__ typename RoundPiece<F32>::type round_piece(const floa
 
 // S1NP > 0: segments of one frame (the standard breadth-first search, Eq. 1) in the slot layout.  The
 // joiner GEMM kept no logits: `logits` points at its row partials (see PartEp), tiles_n per row, and
-// the expansion of a hypothesis is the merge of its row's partials by one wave (TW = 1, SMAX = 1),
+// the expansion of a hypothesis is the merge of its row's partials by one wave (SMAX = 1),
 // lane l taking tile l with a list of up to S1NP candidates in registers.
 // SLOTS: the slot layout with a wave for the select step and no debug output, known when the code is made.
 // A launch runs through its code once, so what other callers need stands in its way: with everything in one
@@ -40,16 +40,16 @@ __device__ __forceinline__ typename RoundPiece<F32>::type round_piece(const floa
 // the 64 KB instruction cache (per launch: 64 utterances S = 3 13.1 -> 11.3-12.1 us, one utterance 11.2 ->
 // 10.4, 37 utterances N = 10 S = 5 21.3 -> 19.8).  SLOTS = 2: beams up to 8 besides, whose candidates are at most
 // one a lane (with the forms for more of them in the body, one utterance decoded in 10.26 instead of 9.74 ms).
-template <int TW, int NV4, int SMAX, int S1NP, bool F32, int SLOTS>
+template <int NV4, int SMAX, int S1NP, bool F32, int SLOTS>
 __global__ void __launch_bounds__(1024)
 k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, AView An, BView B, RowView rv,
         int2 *nodes, float *__restrict__ row_stats_arg, float *__restrict__ delta_nb_arg, FixedView fx, int tiles_n) {
     const bool on = SLOTS || fx.on;
     constexpr bool FEW = SLOTS == 2;
     float *row_stats = SLOTS ? nullptr : row_stats_arg, *delta_nb = SLOTS ? nullptr : delta_nb_arg;
-    constexpr int TT = TW * 64;
+    constexpr int TT = 64;
     typedef typename RoundPiece<F32>::type XP;
-    typedef ExpandShared<SMAX, TW> TeamShared;
+    typedef ExpandShared<SMAX, 1> TeamShared;
     extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
     // LDS: the utterance's B list for the select step, one TeamShared per team, then what the teams
     // hand to the select step
@@ -156,8 +156,9 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     if (own_wave && sel_wave) {
         select_merge_utt(s_select, 1, d, round, drop, u, sel_lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         if constexpr (S1NP == 0) {
-#pragma unroll
-            for (int b = 0; b < EXPAND_PAIR_BARRIERS; ++b) __syncthreads();
+            // the blank expansions are there long before the N best are: they are merged meanwhile
+            __syncthreads();
+            select_merge_utt(s_select, 4, d, round, drop, u, sel_lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         }
     } else if constexpr (S1NP > 0) {
         if (pre_h && live) {
@@ -249,8 +250,10 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
                     for (int c = 0; c < NV4 * 4; ++c) e[t][c] = 0.f;
                 }
         }
-        expand_pair<NV4, SMAX, TT>(e, pi, teams[team], d, tid, live, s_lc + team * sp, s_dphi + team, s_cs + team * N,
-                                   s_ct + team * N, row_stats, delta_nb);
+        float cf[SMAX];
+        expand_front<NV4, SMAX, 64>(e, cf, pi, teams[team], d, tid, live, s_lc + team * sp, s_dphi + team, row_stats);
+        __syncthreads();
+        expand_back<NV4, SMAX, 64>(e, cf, pi, teams[team], d, tid, live, s_cs + team * N, s_ct + team * N, delta_nb);
     }
     __syncthreads();
     // (the parent's h is asked for only now, by the state slot asked for at the start: requests made
@@ -262,12 +265,11 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
         for (int q = 0; q < HP; ++q)
             hpar[q] = reinterpret_cast<const float4 *>(fx.pool_h + slot * d.H)[min(tid + TT * q, H4 - 1)];
     }
-    // Behind the expansion the select step has two parts that need nothing of each other: the select
-    // wave merges the blank expansions into B and finds the threshold while the workgroup's first wave,
-    // idle by now, ranks the candidates; the select wave goes on when both are done.
+    // Behind the expansion the workgroup's first wave, idle by now, ranks the candidates; the select wave, which has merged the
+    // blank expansions into B and found the threshold (it needs nothing else of the expansion), goes on when that is done.
     const float *lg = S1NP > 0 ? nullptr : logits;   // (no logits: d of a new hypothesis over one frame is (1))
     if (own_wave) {
-        if (sel_wave)
+        if (S1NP > 0 && sel_wave)
             select_merge_utt(s_select, 4, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         else if ((int)threadIdx.x < WAVE)
             select_merge_utt(s_select, 3, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
@@ -346,7 +348,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
 // Librispeech-like batch at S = 3 with teams of 4 / 2 / 1 waves: N = 2: 16.6 / 16.9 / 16.6, N = 4:
 // 19.1 / 17.6 / 17.4, N = 5: - / 18.2 / 18.0, N = 8: - / 28.3 / 26.4): what a wave more per hypothesis saves in
 // values per thread it costs in reductions, candidate lists and their merge, and the waves of a
-// workgroup share four SIMDs.  The template keeps teams of several waves.
+// workgroup share four SIMDs; and a team that is one wave needs none of the workgroup's barriers.
 static int round_variant(const Dims &d) {
     if (d.S > 5 || d.N > 16) return 0;
     const int v4 = d.Vl / 4;
@@ -357,36 +359,36 @@ static int round_variant(const Dims &d) {
 
 bool round_fits(const Dims &d) { return round_variant(d) != 0; }
 
-template <int TW, int NV4, int SMAX, int S1NP, bool F32, int SLOTS>
+template <int NV4, int SMAX, int S1NP, bool F32, int SLOTS>
 static hipError_t round_launch_t(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
                                AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
                                const FixedView &fx, int tiles_n) {
     const size_t b_list = ((size_t)d.BCAP * (sizeof(double) + sizeof(u64) + 3 * sizeof(int)) + 15) & ~(size_t)15;
-    const size_t shm = b_list + (S1NP > 0 ? 0 : (size_t)d.N * sizeof(ExpandShared<SMAX, TW>)) +
+    const size_t shm = b_list + (S1NP > 0 ? 0 : (size_t)d.N * sizeof(ExpandShared<SMAX, 1>)) +
                        sizeof(float) * ((size_t)d.N * SMAX + d.N + 2 * (size_t)d.N * d.N);
     static size_t attr_for = 0;
     if (shm > attr_for) {   // (static LDS of the select step comes on top: raise the limit to what the launch needs)
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_round<TW, NV4, SMAX, S1NP, F32, SLOTS>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_round<NV4, SMAX, S1NP, F32, SLOTS>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_for = shm;
     }
     // (one wave more for the select step where 1024 threads allow it)
-    const int threads = d.N * TW * 64 + (d.N * TW * 64 + 64 <= 1024 ? 64 : 0);
+    const int threads = d.N * 64 + (d.N * 64 + 64 <= 1024 ? 64 : 0);
     // (with a row range per XCD: eight workgroups, one per XCD, for each place in the longest XCD's list)
     const int grid = fx.on && fx.xcd_rows > 0 ? 8 * (fx.xcd_rows / (d.N * d.S) + 1) : d.U;
-    hipLaunchKernelGGL((k_round<TW, NV4, SMAX, S1NP, F32, SLOTS>), dim3(grid), dim3(threads), shm, st, d, round, drop, logits, A, An,
+    hipLaunchKernelGGL((k_round<NV4, SMAX, S1NP, F32, SLOTS>), dim3(grid), dim3(threads), shm, st, d, round, drop, logits, A, An,
                        B, rv, nodes, row_stats, delta_nb, fx, tiles_n);
     return hipGetLastError();
 }
 
-template <int TW, int NV4, int SMAX, int S1NP = 0>
+template <int NV4, int SMAX, int S1NP = 0>
 static hipError_t round_launch(hipStream_t st, const Dims &d, int round, int drop, const float *logits, AView A,
                                AView An, BView B, RowView rv, int2 *nodes, float *row_stats, float *delta_nb,
                                const FixedView &fx, int tiles_n = 0) {
-    const bool slots = fx.on && (d.N * TW + 1) * 64 <= 1024 && !row_stats && !delta_nb;
+    const bool slots = fx.on && (d.N + 1) * 64 <= 1024 && !row_stats && !delta_nb;
 #define TBS_ROUND_LAUNCH(F32, SLOTS)                                                                                     \
-    return round_launch_t<TW, NV4, SMAX, S1NP, F32, SLOTS>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats,    \
+    return round_launch_t<NV4, SMAX, S1NP, F32, SLOTS>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats,    \
                                                            delta_nb, fx, tiles_n)
     if constexpr (S1NP == 0) {   // (only bf16 models run without logits)
         if (fx.f32) {
@@ -407,12 +409,12 @@ hipError_t launch_round(hipStream_t st, const Dims &d, int round, int drop, cons
     if (fxp) fx = *fxp;
     if (fx.on && fx.xh && (d.H & 3)) return hipErrorInvalidValue;
     switch (round_variant(d)) {
-        case 13: return round_launch<1, 1, 3>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
-        case 15: return round_launch<1, 1, 5>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
-        case 23: return round_launch<1, 2, 3>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
-        case 25: return round_launch<1, 2, 5>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
-        case 43: return round_launch<1, 4, 3>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
-        case 45: return round_launch<1, 4, 5>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
+        case 13: return round_launch<1, 3>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
+        case 15: return round_launch<1, 5>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
+        case 23: return round_launch<2, 3>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
+        case 25: return round_launch<2, 5>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
+        case 43: return round_launch<4, 3>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
+        case 45: return round_launch<4, 5>(st, d, round, drop, logits, A, An, B, rv, nodes, row_stats, delta_nb, fx);
         default: return hipErrorInvalidValue;
     }
 }
@@ -422,7 +424,7 @@ bool round_s1_fits(const Dims &d) { return d.S == 1 && d.N >= 1 && d.N <= 16 && 
 hipError_t launch_round_s1(hipStream_t st, const Dims &d, int round, int drop, const float *part, int tiles_n, AView A,
                            AView An, BView B, RowView rv, int2 *nodes, const FixedView *fxp) {
     if (!fxp || !fxp->on || !part || !round_s1_fits(d) || tiles_n < 1 || tiles_n > 64) return hipErrorInvalidValue;
-    if (d.N <= 4) return round_launch<1, 1, 1, 4>(st, d, round, drop, part, A, An, B, rv, nodes, nullptr, nullptr, *fxp, tiles_n);
-    if (d.N <= 8) return round_launch<1, 1, 1, 8>(st, d, round, drop, part, A, An, B, rv, nodes, nullptr, nullptr, *fxp, tiles_n);
-    return round_launch<1, 1, 1, 16>(st, d, round, drop, part, A, An, B, rv, nodes, nullptr, nullptr, *fxp, tiles_n);
+    if (d.N <= 4) return round_launch<1, 1, 4>(st, d, round, drop, part, A, An, B, rv, nodes, nullptr, nullptr, *fxp, tiles_n);
+    if (d.N <= 8) return round_launch<1, 1, 8>(st, d, round, drop, part, A, An, B, rv, nodes, nullptr, nullptr, *fxp, tiles_n);
+    return round_launch<1, 1, 16>(st, d, round, drop, part, A, An, B, rv, nodes, nullptr, nullptr, *fxp, tiles_n);
 }

@@ -397,8 +397,9 @@ __device__ __forceinline__ void xcd_joiner(const XcdPlace &w, const unsigned cha
 }
 
 // Eq. 3-7, the N best expansions, AddAndMerge, the new list A: a workgroup per utterance, a wave per hypothesis and one for
-// the select step, which stages the lists while the others expand.  Behind the expansion the select wave merges the blank
-// expansions and finds the threshold while all the others rank the candidates, 16 a wave, four lanes sharing one.
+// the select step, which stages the lists while the others expand, and merges the blank expansions and finds the threshold while
+// they pick their N best.  Then all the others rank the candidates, 16 a wave, four lanes sharing one, and the select wave
+// makes the new list.
 // (Each role reads the arguments it needs for itself and asks for what it waits for longest before all else.)
 // Returns the hypotheses made (and XR_FULL_TRIE where an utterance's share of the trie was full).
 template <int NT, int NV4, int SMAX, bool FEW, class SM>
@@ -440,8 +441,10 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
 #pragma unroll
                         for (int c = 0; c < NV4 * 4; ++c) e[q][c] = 0.f;
                     }
-                expand_pair<NV4, SMAX, 64>(e, pi, sc.teams[wave], d, lane, live_team, sc.lc + wave * sp, sc.dphi + wave, sc.cs + wave * N,
-                                           sc.ct + wave * N, nullptr, nullptr);
+                float cf[SMAX];
+                expand_front<NV4, SMAX, 64>(e, cf, pi, sc.teams[wave], d, lane, live_team, sc.lc + wave * sp, sc.dphi + wave, nullptr);
+                __syncthreads();
+                expand_back<NV4, SMAX, 64>(e, cf, pi, sc.teams[wave], d, lane, live_team, sc.cs + wave * N, sc.ct + wave * N, nullptr);
                 if (live_team) {
                     // the team's candidates as keys of the joint ranking; the logits of their tokens at the segment's frames,
                     // a lane each (N S <= 64), wait in a register until the ranking is done
@@ -463,12 +466,18 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
                 if (wave == N) {
                     const XcdArgs &g = xcd_args();
                     const XcdScratch<SMAX> sc(scratch, g.d);
+                    const int u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
+                    SelectIn in{};
+                    in.dphi = sc.dphi;
                     const SelectFigs fg{sp, H, i * N * g.d.S, __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_NB]), 0};
-                    select_merge_utt(sm, 1, g.d, round, 0, __builtin_amdgcn_readfirstlane(sh.utt[i]), lane, LogitsPlain{nullptr}, SelectIn{}, fg,
-                                     g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes, sc.b_list, &s_out, FEW, true);
+                    select_merge_utt(sm, 1, g.d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes,
+                                     sc.b_list, &s_out, FEW, true);
+                    __syncthreads();
+                    select_merge_utt(sm, 4, g.d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes,
+                                     sc.b_list, &s_out, FEW, true);
+                } else {
+                    __syncthreads();
                 }
-#pragma unroll
-                for (int b = 0; b < EXPAND_PAIR_BARRIERS; ++b) __syncthreads();
             }
         }
         const int sp = __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_SP]);
@@ -479,15 +488,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
             continue;
         }
         __syncthreads();
-        if (wave == N) {
-            const XcdArgs &g = xcd_args();
-            const XcdScratch<SMAX> sc(scratch, g.d);
-            SelectIn in{};
-            in.dphi = sc.dphi;
-            const SelectFigs fg{sp, H, i * N * g.d.S, __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_NB]), 0};
-            select_merge_utt(sm, 4, g.d, round, 0, __builtin_amdgcn_readfirstlane(sh.utt[i]), lane, LogitsPlain{nullptr}, in, fg, g.A[a],
-                             g.A[a ^ 1], g.B, g.rv, g.nodes, sc.b_list, &s_out, FEW, true);
-        } else {
+        if (wave != N) {
             // ChooseNBestExpansions: the rank of a candidate is the number of those that beat it (larger score, or equal score
             // and earlier place; a place without a candidate holds NaN and beats nothing)
             const int nc = H * N, per = (nc + 3) >> 2, j0 = (lane >> 4) * per, j1 = min(j0 + per, nc);
