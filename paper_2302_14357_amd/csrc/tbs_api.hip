@@ -81,7 +81,8 @@ struct tbs_ctx {
     XcdCtl *x_ctl;      // [2], used in turn: a launch clears the next one's
     int *x_order;       // [U] the XCDs' utterances (behind utt_fig)
     int x_first[XR_XCDS + 1];
-    bf16_t *x_hb, *x_amat;
+    void *x_hb, *x_amat;
+    float *x_frags[3];  // fp32: the output, gate and projection weights in the pieces the products read
     int4 *x_desc;
     int *h_xcd;         // pinned: [XCDs * workgroups, 4] how each workgroup ended, then [XCDs, XR_SEGS] rounds
     int *h_xcd_dev;
@@ -454,15 +455,24 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     }
     {
         int cus = 0;
-        c->xcd_ready = cfg->dtype == 1 && (cfg->debug & ~131072) == 0 && cfg->joiner_chunk_rows == 0 && xcd_fits(d) &&
+        c->xcd_ready = (cfg->debug & ~131072) == 0 && cfg->joiner_chunk_rows == 0 && (cfg->dtype == 1 ? xcd_fits(d) : xcd_f32_fits(d)) &&
                        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device_id) == hipSuccess &&
                        cus == XR_XCDS * XR_WGS;
     }
     if (c->xcd_ready) {
         rc |= dev_alloc(c, &c->x_ctl, 2);
         rc |= dev_alloc(c, &c->x_desc, UN);
-        rc |= dev_alloc(c, &c->x_hb, (size_t)c->pool_rows * d.H);
-        rc |= dev_alloc(c, &c->x_amat, (size_t)(M + 16 * XR_XCDS) * d.Dj);   // (every XCD's rows in whole tiles of 16)
+        const bool f32 = cfg->dtype == 0;
+        char *p = nullptr, *q = nullptr;
+        rc |= dev_alloc(c, &p, (size_t)c->pool_rows * (f32 ? 4 * xcd_f32_row(d.H) : 2 * d.H));
+        rc |= dev_alloc(c, &q, (size_t)(M + 16 * XR_XCDS) * (f32 ? 4 * xcd_f32_row(d.Dj) : 2 * d.Dj));   // (every XCD's rows in whole tiles of 16)
+        c->x_hb = p;
+        c->x_amat = q;
+        if (f32) {
+            rc |= dev_alloc(c, &c->x_frags[0], (size_t)xcd_f32_frags(d.V, d.Dj));
+            rc |= dev_alloc(c, &c->x_frags[1], (size_t)xcd_f32_frags(4 * d.H, d.H));
+            rc |= dev_alloc(c, &c->x_frags[2], (size_t)xcd_f32_frags(d.Dj, d.H));
+        }
     }
     rc |= dev_alloc(c, &c->res_count, U);
     rc |= dev_alloc(c, &c->res_len, UN);
@@ -544,6 +554,16 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         }
         if (e == hipSuccess)
             e = gemm(c, w->embed, w->w_ih[0], w->b_lstm[0], c->emb_gates, d.V, 4 * d.H, d.E, nullptr, 4L * d.H);
+        if (e != hipSuccess) {
+            c->last_hip = (int)e;
+            tbs_free(c);
+            return TBS_EHIP;
+        }
+    }
+    if (c->xcd_ready && cfg->dtype == 0) {
+        e = launch_xcd_frags(c->stream, (const float *)w->w_out, c->x_frags[0], d.V, d.Dj);
+        if (e == hipSuccess) e = launch_xcd_frags(c->stream, (const float *)c->wperm[0], c->x_frags[1], 4 * d.H, d.H);
+        if (e == hipSuccess) e = launch_xcd_frags(c->stream, (const float *)w->w_proj, c->x_frags[2], d.Dj, d.H);
         if (e != hipSuccess) {
             c->last_hip = (int)e;
             tbs_free(c);
@@ -1369,10 +1389,11 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.order = c->x_order;
     g.utt_T = c->utt_T;
     g.utt_off = c->utt_off;
-    g.enc = (const bf16_t *)c->enc;
-    g.w_out = (const bf16_t *)c->w.w_out;
-    g.w_gate = (const bf16_t *)c->wperm[0];
-    g.w_proj = (const bf16_t *)c->w.w_proj;
+    const bool f32 = c->cfg.dtype == 0;
+    g.enc = c->enc;
+    g.w_out = f32 ? c->x_frags[0] : c->w.w_out;
+    g.w_gate = f32 ? c->x_frags[1] : c->wperm[0];
+    g.w_proj = f32 ? c->x_frags[2] : c->w.w_proj;
     g.b_out = c->w.b_out;
     g.b_proj = c->w.b_proj;
     g.emb_gates = c->emb_gates_perm;
@@ -1386,7 +1407,7 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.pool_h = c->pool_h;
     g.pool_c = c->pool_c;
     g.hb = c->x_hb;
-    g.hb_bytes = c->pool_rows * d.H * 2;
+    g.hb_bytes = c->pool_rows * (f32 ? 4 * xcd_f32_row(d.H) : 2 * d.H);
     g.amat = c->x_amat;
     g.logits = c->logits;
     g.desc = c->x_desc;
@@ -1401,8 +1422,8 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
         g.seq = ++c->x_seq & 0x7FFFFF;
         g.ctl = c->x_ctl + (c->x_seq & 1);
         g.ctl_next = c->x_ctl + ((c->x_seq + 1) & 1);
-        memset(c->h_xcd + 4 * XR_XCDS * XR_WGS, 0, sizeof(int) * XR_XCDS * XR_SEGS);
-        HIPCHK(c, launch_xcd_decode(c->stream, g));
+        for (int x = 0; x < XR_XCDS; ++x) memset(c->h_xcd + 4 * XR_XCDS * XR_WGS + x * XR_SEGS, 0, sizeof(int) * (size_t)(s1 - s0));
+        HIPCHK(c, f32 ? launch_xcd_decode_f32(c->stream, g) : launch_xcd_decode(c->stream, g));
         // every workgroup says how it ended; the wait is bounded as that for a round's words
         bool absent = false, full = false, over = false, stuck = false;
         int64_t calls = 0, joined = 0, nodes = 0;

@@ -184,7 +184,8 @@ struct XcdArgs {
     int first[XR_XCDS + 1]; // the XCDs' parts of `order` [U]: utterances in falling length
     int tile0[XR_XCDS];     // and of amat, in tiles of 16 rows
     const int *order, *utt_T, *utt_off;
-    const bf16_t *enc, *w_out, *w_gate, *w_proj;   // (gate rows interleaved, see LstmEp)
+    const void *enc;        // frames, and weights as bf16 rows or fp32 pieces (launch_xcd_frags); gate rows interleaved, see LstmEp
+    const void *w_out, *w_gate, *w_proj;
     const float *b_out, *b_proj, *emb_gates;
     AView A[2];
     BView B;
@@ -192,9 +193,9 @@ struct XcdArgs {
     int *fig;
     int2 *nodes;
     float *pool_p, *pool_h, *pool_c;
-    bf16_t *hb;             // [slots, H] h as bf16, the rows of the products
+    void *hb;               // [slots, H] h as the products read it: bf16, or fp32 rows of xcd_f32_row(H)
     long hb_bytes;
-    bf16_t *amat;           // joiner input rows, in pieces of 16 rows x 32 columns
+    void *amat;             // joiner input rows, in pieces of 16 rows x 32 columns (fp32: 16)
     float *logits;
     int4 *desc;             // [U*N] state slot (-1: no hypothesis), parent's slot, last token
     XcdCtl *ctl, *ctl_next;
@@ -203,6 +204,11 @@ struct XcdArgs {
 };
 bool xcd_fits(const Dims &d);
 hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g);
+bool xcd_f32_fits(const Dims &d);
+hipError_t launch_xcd_decode_f32(hipStream_t st, const XcdArgs &g);
+int xcd_f32_row(int K);                    // floats of a row of K columns in the order the products read
+long xcd_f32_frags(int rows, int K);       // floats of a weight matrix in pieces
+hipError_t launch_xcd_frags(hipStream_t st, const float *w, float *frags, int rows, int K);
 
 // ---- launchers (each enqueues on `st` and returns the HIP status) ----
 hipError_t launch_init_batch(hipStream_t st, const Dims &d, BView B, AView A0, AView A1, RowView rv, int2 *nodes,

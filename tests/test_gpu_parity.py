@@ -1245,16 +1245,21 @@ def _one_launch(tbs):
     return bool(tbs.L.tbs_path(tbs.ctx) & 4)
 
 
-@pytest.mark.parametrize("d,hidden,V,N,S,lengths,peaked", [
+@pytest.mark.parametrize("dtype,d,hidden,V,N,S,lengths,peaked", [
+    ("f32", 64, 64, 32, 2, 3, [50], False), ("f32", 72, 72, 37, 8, 5, [9, 12, 33, 1, 0, 31], True), ("f32", 96, 136, 97, 3, 1, [9, 2, 31], False),
+    ("f32", 256, 200, 500, 10, 4, [7, 30, 12], False), ("f32", 512, 640, 1001, 5, 3, [6, 40, 11], False),
+    ("f32", 520, 384, 1024, 11, 5, [4, 9], True), ("f32", 64, 128, 60, 5, 2, [2 + i % 9 for i in range(50)], False)] + [("bf16",) + c for c in [
     (128, 128, 17, 1, 2, [5], False), (128, 256, 96, 5, 3, [0, 1, 7, 12, 23, 31], True), (256, 128, 200, 5, 1, [3] * 9, False),
     (384, 384, 257, 7, 5, list(range(1, 18)), True), (512, 640, 1024, 5, 3, [8] * 3 + [40] * 6, False), (640, 512, 1023, 3, 2, [9, 30], False),
     (512, 640, 1000, 10, 3, [17] * 5, False), (512, 640, 500, 10, 5, [21, 20, 19, 5], True), (128, 128, 512, 8, 4, [6, 33], True),
-    (128, 128, 33, 11, 5, [11, 12], True), (256, 384, 40, 4, 3, [3 + i % 7 for i in range(300)], False), (128, 128, 64, 6, 1, [9, 2, 31], True)])
-def test_segments_in_one_launch_equal_four_kernels_a_round(d, hidden, V, N, S, lengths, peaked):
+    (128, 128, 33, 11, 5, [11, 12], True), (256, 384, 40, 4, 3, [3 + i % 7 for i in range(300)], False), (128, 128, 64, 6, 1, [9, 2, 31], True)]])
+def test_segments_in_one_launch_equal_four_kernels_a_round(dtype, d, hidden, V, N, S, lengths, peaked):
     """Whole segments inside one launch, every XCD with utterances of its own: the same bits as the four kernels a round (debug
     bit 16), whose arithmetic and order of sums it keeps, and the same counters; every width of K, ragged tiles of rows,
-    columns and utterances (none, fewer than XCDs, more than workgroups), beams on both sides of the workgroup sizes."""
-    shape = small_bf16_shape(n_utts=len(lengths), vocab=V, d=d, hidden=hidden)
+    columns and utterances (none, fewer than XCDs, more than workgroups), beams on both sides of the workgroup sizes; fp32
+    with K of no whole chunks and with gate weights that do not fit the LDS."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=len(lengths), vocab=V, d=d, hidden=hidden), dtype=dtype)
     cap = 0
     if peaked:
         shape, cap = _peaked(shape, 8.0, 8.0), 5
