@@ -162,42 +162,6 @@ k_expand_reg(Dims d, const float *__restrict__ logits, AView A, RowView rv, floa
 }
 
 // ------------------------------------------------------------------ long segments
-// Segments too long for the registers of four waves: a wave takes whole rows (up to RPW of them, NQ
-// 16-byte pieces a lane and row), so a row's maximum and sum never leave its wave and every logit is
-// read from memory and exponentiated once.  The forward variable of Eq. 3 is a chain of S' steps; here it is
-// a prefix scan over the lanes of one wave, alpha_t = alpha_{t-1} b_{t-1} + d_old[t] as the composition
-// of the maps x -> x B + A, which takes log2(S') steps instead.  A and B are kept as mantissa * 2^exponent
-// (see ScanAlpha: the products leave the range of float).  The waves' shares of delta_nb (Eq. 6) meet in LDS,
-// and the first four waves take the N best.
-struct ScanPart {
-    float m;   // mantissa in [0.5, 1), or 0
-    int e;
-};
-__device__ __forceinline__ ScanPart scan_norm(float m, int e) {
-    int k;
-    m = frexpf(m, &k);
-    return {m, m != 0.f ? e + k : 0};
-}
-__device__ __forceinline__ ScanPart scan_mul(ScanPart a, ScanPart b) { return scan_norm(a.m * b.m, a.e + b.e); }
-__device__ __forceinline__ ScanPart scan_add(ScanPart a, ScanPart b) {
-    if (a.m == 0.f) return b;
-    if (b.m == 0.f) return a;
-    const int e = max(a.e, b.e);
-    return scan_norm(ldexpf(a.m, a.e - e) + ldexpf(b.m, b.e - e), e);
-}
-__device__ __forceinline__ ScanPart scan_up(ScanPart a, int by) { return {__shfl_up(a.m, by), __shfl_up(a.e, by)}; }
-__device__ __forceinline__ float scan_log(ScanPart a) {
-    return a.m > 0.f ? __logf(a.m) + (float)a.e * 0.69314718055994531f : -INFINITY;
-}
-// 2^l2 / z; zero for l2 = -inf
-__device__ __forceinline__ ScanPart scan_exp2(float l2, float z) {
-    if (!(l2 > -INFINITY)) return {0.f, 0};
-    const float fl = floorf(l2);
-    return scan_norm(__builtin_amdgcn_exp2f(l2 - fl) / z, (int)fl);
-}
-
-#define LONG_FRAMES 64     // a lane per frame in the scan
-#define LONG_MIN_WAVES 4   // the N best are taken by the first four waves
 template <int NQ, int RPW>
 __global__ void __launch_bounds__(1024)
 k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *__restrict__ row_lc,
@@ -205,121 +169,18 @@ k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, flo
               float *__restrict__ row_stats, float *__restrict__ delta_nb, const int *__restrict__ pairs_dev,
               int pair_base) {
     extern __shared__ __attribute__((aligned(16))) float4 s_part[];   // [waves][Vl / 4]
-    __shared__ ExpandBest<EXP_WAVES> sm;
-    __shared__ float s_m[LONG_FRAMES], s_z[LONG_FRAMES], s_lb[LONG_FRAMES], s_cf[LONG_FRAMES];
-    const int pair = pair_base + blockIdx.x, tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = (int)blockDim.x >> 6;
+    __shared__ LongShared sm;
+    const int pair = pair_base + blockIdx.x, tid = threadIdx.x;
+    const int waves = (int)blockDim.x >> 6;
     if (pairs_dev && pair >= *pairs_dev) return;   // (enqueued on an upper-bound grid, see k_expand_reg)
     const int u = ((cint_p)rv.pair_u)[pair], h = ((cint_p)rv.pair_h)[pair];
     const int row0 = ((cint_p)rv.pair_row0)[pair], sp = ((cint_p)rv.pair_len)[pair];
-    const int V = d.V, Vl = d.Vl, V4 = Vl >> 2;
-    const float *L = logits + (long)row0 * Vl;
-    // this wave's rows: wave, wave + waves, ... (rows past S' repeat the last one, pieces past V the last piece)
-    float4 e[RPW][NQ];
-    float lblank[RPW];
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const float *row = L + (long)min(wave + i * waves, sp - 1) * Vl;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) e[i][q] = reinterpret_cast<const float4 *>(row)[min(lane + 64 * q, V4 - 1)];
-        lblank[i] = row[d.blank];
-    }
-    const float ld = wave == 0 ? A.dhat[((long)u * d.N + h) * d.S + min(lane, d.S - 1)] : 0.f;
-    if (tid == 0) sm.jn = 0;
-#pragma unroll
-    for (int i = 0; i < RPW; ++i) {
-        const int t = wave + i * waves;
-        if (t >= sp) continue;   // (uniform)
-        float m = -INFINITY;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) m = fmaxf(m, fmaxf(fmaxf(e[i][q].x, e[i][q].y), fmaxf(e[i][q].z, e[i][q].w)));
-        m = wave_max_ord(m);
-        const float nm = -m * 1.44269504088896341f;
-        float z = 0.f;
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) {
-            float4 &x = e[i][q];
-            x.x = __builtin_amdgcn_exp2f(fmaf(x.x, 1.44269504088896341f, nm));
-            x.y = __builtin_amdgcn_exp2f(fmaf(x.y, 1.44269504088896341f, nm));
-            x.z = __builtin_amdgcn_exp2f(fmaf(x.z, 1.44269504088896341f, nm));
-            x.w = __builtin_amdgcn_exp2f(fmaf(x.w, 1.44269504088896341f, nm));
-            if (lane + 64 * q < V4) z += (x.x + x.y) + (x.z + x.w);
-        }
-        z = wave_sum(z);
-        if (lane == 0) {
-            s_m[t] = m;
-            s_z[t] = z;
-            s_lb[t] = fmaf(lblank[i], 1.44269504088896341f, nm);   // (log2 of the blank's e: with the row's common factor, see expand_pair)
-        }
-    }
-    __syncthreads();
-    if (wave == 0) {   // lane t: frame t
-        const bool have = lane < sp;
-        const int t = min(lane, sp - 1);
-        const float m = s_m[t], z = s_z[t];
-        const ScanPart b = scan_exp2(s_lb[t], z);             // blank probability of the frame
-        ScanPart a = scan_exp2(have ? ld * 1.44269504088896341f : -INFINITY, 1.f), f = scan_up(b, 1);   // alpha_t = alpha_{t-1} f + a
-        for (int by = 1; by < sp; by <<= 1) {
-            const ScanPart a2 = scan_up(a, by), f2 = scan_up(f, by);
-            if (lane >= by) {
-                a = scan_add(scan_mul(a2, f), a);
-                f = scan_mul(f2, f);
-            }
-        }
-        const float lc = scan_log(a) - __logf(z);             // log(alpha_t / Z_t)
-        if (have) {
-            s_cf[t] = __expf(lc);
-            row_lc[row0 + t] = fmaf(-m * 1.44269504088896341f, 0.69314718055994531f, lc);
-            if (lane == sp - 1) dphi[pair] = scan_log(scan_mul(a, b));   // Eq. 7
-            if (row_stats) {
-                row_stats[(long)(row0 + t) * 3 + 0] = m;
-                row_stats[(long)(row0 + t) * 3 + 1] = z;
-                row_stats[(long)(row0 + t) * 3 + 2] = ldexpf(b.m, b.e);
-            }
-        }
-    }
-    __syncthreads();
-    {   // this wave's share of Eq. 4-6
-        float4 acc[NQ];
-#pragma unroll
-        for (int q = 0; q < NQ; ++q) acc[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int i = 0; i < RPW; ++i) {
-            const int t = wave + i * waves;
-            if (t >= sp) continue;   // (uniform)
-            const float cf = s_cf[t];
-#pragma unroll
-            for (int q = 0; q < NQ; ++q) {
-                acc[q].x += cf * e[i][q].x;
-                acc[q].y += cf * e[i][q].y;
-                acc[q].z += cf * e[i][q].z;
-                acc[q].w += cf * e[i][q].w;
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-            if (lane + 64 * q < V4) s_part[wave * V4 + lane + 64 * q] = acc[q];
-    }
-    __syncthreads();
-    if (wave >= EXP_WAVES) {
-        __syncthreads();   // (the barrier inside expand_best)
-        return;
-    }
-    float v[4] = {0.f, 0.f, 0.f, 0.f};
-    if (tid < V4) {
-        const int shares = min(waves, sp);   // (a wave beyond S' had no row)
-        for (int w = 0; w < shares; ++w) {
-            const float4 x = s_part[w * V4 + tid];
-            v[0] += x.x; v[1] += x.y; v[2] += x.z; v[3] += x.w;
-        }
-    }
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        const int col = 4 * tid + c;
-        if (col == d.blank || col >= V) v[c] = 0.f;   // blank is not a non-blank expansion
-        if (delta_nb && col < V) delta_nb[(long)pair * V + col] = v[c];
-    }
-    expand_best<1, EXP_THREADS>(v, sm, d, tid, true, cand_score + (long)pair * d.N, cand_tok + (long)pair * d.N);
+    const float *L = logits + (long)row0 * d.Vl;
+    expand_long<NQ, RPW, false>(
+        d, sp, waves, waves, tid, sm, s_part, [&](int t) { return A.dhat[((long)u * d.N + h) * d.S + t]; },
+        [&](int t, int piece) { return reinterpret_cast<const float4 *>(L + (long)t * d.Vl)[piece]; },
+        [&](int t, int col) { return L[(long)t * d.Vl + col]; }, row_lc + row0, dphi + pair, cand_score + (long)pair * d.N,
+        cand_tok + (long)pair * d.N, row_stats ? row_stats + (long)row0 * 3 : nullptr, delta_nb ? delta_nb + (long)pair * d.V : nullptr);
 }
 
 template <int NQ, int RPW>

@@ -150,8 +150,8 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
 }
 
 // LDS of the select step.  CANDS: candidates there is room for; DNEW: values of the frame distributions made by lane or by
-// frame (1 where every caller makes them ahead); PF: frames of a segment whose candidates' logits are asked for ahead, PC: such
-// candidates.
+// frame (1 where every caller makes them ahead; 0: the caller makes them behind the step, from s_kh and s_ktok); PF: frames of a
+// segment whose candidates' logits are asked for ahead, PC: such candidates.
 template <int CANDS = CAND_MAX, int DNEW = TBS_MAX_SEG * TBS_MAX_BEAM, int PF = SEL_PRE_FRAMES, int PC = SEL_PRE_CANDS>
 struct SelectShared {
     static constexpr int dnew = DNEW, pf = PF, pc = PC;
@@ -165,7 +165,7 @@ struct SelectShared {
     int s_sel[TBS_MAX_BEAM];      // candidate index by rank
     double s_thr;
     int s_have_thr;
-    float s_dnew[DNEW];           // frame distributions of the new hypotheses, [frame][hypothesis]
+    float s_dnew[DNEW > 0 ? DNEW : 1];   // frame distributions of the new hypotheses, [frame][hypothesis]
     float s_xpre[PF * PC];        // logits of the candidates' tokens, [frame][candidate]
     int s_kh[TBS_MAX_BEAM], s_ktok[TBS_MAX_BEAM];   // kept candidates, by place: hypothesis they extend, token
 };
@@ -176,7 +176,8 @@ struct SelectShared {
 // phase 0: the whole step.  phase 1: only what does not depend on the expansion (B and A staged in
 // LDS); phase 2: the rest, by the same wave: a caller whose expansion runs in the same kernel does
 // phase 1 beside it.  Phases 3, 4 and 5 are the parts of phase 2 (see below), for a caller that has two
-// waves for them; the wave of phase 5 is the one that did phase 1 and 4 (`out->nB` is its).  (The phase is
+// waves for them; the wave of phase 5 is the one that did phase 1 and 4 (`out->nB` is its).  Phase 6 is phase 4 without the
+// threshold, for a caller that ranks B by several waves.  (The phase is
 // an argument, not a template parameter: the code is inlined, and the phase known there.)
 template <class SM, class LG>
 __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const Dims &d, int round, int drop, int u, int lane,
@@ -234,7 +235,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
         // candidates only, phase 4: merge only, phase 5: finish only: a caller with a second wave to
         // spare runs 3 and 4 side by side and 5 behind a barrier.
         const bool do_cand = PHASE == 0 || PHASE == 2 || PHASE == 3;
-        const bool do_merge = PHASE == 0 || PHASE == 2 || PHASE == 4;
+        const bool do_merge = PHASE == 0 || PHASE == 2 || PHASE == 4 || PHASE == 6;
         const bool do_finish = PHASE == 0 || PHASE == 2 || PHASE == 5;
         if (PHASE == 0) sel_sync();   // (A's scores, staged just above, are read by other lanes below)
         const int nc = H * N;
@@ -327,7 +328,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
             // overlaps.)
             const bool have_thr_m = nB >= N;
             if (lane == 0) s_have_thr = have_thr_m;
-            if (have_thr_m) sel_rank(s_blogs, nB, lane, [&](int i, int rank, double si) {
+            if (have_thr_m && PHASE != 6) sel_rank(s_blogs, nB, lane, [&](int i, int rank, double si) {
                 if (rank == N - 1) s_thr = si;
             });
         }
@@ -402,7 +403,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
                 // banks) between the pass that reads the logits and the one that writes the normalised
                 // result: going through the result array itself cost two more memory round trips.
                 float *dh = An.dhat + an * d.S;
-                if (by_frame) {
+                if (DNEW == 0 || by_frame) {
                     s_kh[pos] = h;
                     s_ktok[pos] = tok;
                 } else if (pre_x) {

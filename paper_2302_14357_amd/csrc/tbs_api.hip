@@ -727,7 +727,10 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->trie_full = false;
     c->fixed = fixed_layout_ok(c);
     c->s1 = c->fixed && one_frame_ok(c);
-    c->xcd = c->xcd_ready && c->fixed && !c->s1 && U <= XR_XCDS * XR_POS;
+    // (Beyond the slot layout the batch would have row lists, whose one trie serves all: where its shares may not hold what
+    // that holds it goes without this form, and a decode whose share was full all the same is run again, see tbs_decode.)
+    const bool shares = !c->streaming && c->trie_share >= 4.0 * c->cur.N && c->trie_share > c->full_share;
+    c->xcd = c->xcd_ready && (c->fixed ? !c->s1 : shares) && U <= XR_XCDS * XR_POS;
     return TBS_OK;
 }
 
@@ -1410,6 +1413,11 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.hb_bytes = c->pool_rows * (f32 ? 4 * xcd_f32_row(d.H) : 2 * d.H);
     g.amat = c->x_amat;
     g.logits = c->logits;
+    g.row_lc = c->row_lc;
+    g.dphi = c->dphi;
+    g.cand_score = c->cand_score;
+    g.cand_tok = c->cand_tok;
+    g.all_utts = c->d.U;
     g.desc = c->x_desc;
     g.host = c->h_xcd_dev;
     g.host_rounds = c->h_xcd_dev + 4 * XR_XCDS * XR_WGS;
@@ -1603,7 +1611,13 @@ static int decode_all(tbs_ctx *c, const void *enc_proj, const int32_t *frame_off
     const int S = c->cur.S;
     const int nseg = (c->max_T + S - 1) / S;
     int seg = 0;
-    if (c->xcd && c->prof_kernel < 0 && nseg > 0 && (rc = run_segments_xcd(c, 0, nseg, &seg))) return rc;
+    if (c->xcd && c->prof_kernel < 0 && nseg > 0) {
+        if ((rc = run_segments_xcd(c, 0, nseg, &seg))) return rc;
+        if (seg > 0 && seg < nseg && !c->fixed) {   // (row lists do not go on from there: their trie is another)
+            if ((rc = tbs_begin(c, enc_proj, frame_offsets, U))) return rc;
+            seg = 0;
+        }
+    }
     for (; seg < nseg; ++seg) {          // while t <= Length(enc)
         if ((rc = run_segment(c, seg))) return rc;
     }
@@ -1616,7 +1630,7 @@ int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, i
     const int64_t units0 = c->prof_units;
     const size_t ev0 = c->ev_used;
     int rc = decode_all(c, enc_proj, frame_offsets, U);
-    if (rc == TBS_EOVERFLOW && c->trie_full && slots_by_choice(c)) {   // one trie for all utterances may hold them
+    if (rc == TBS_EOVERFLOW && c->trie_full && (slots_by_choice(c) || !c->fixed)) {   // one trie for all utterances may hold them
         c->full_share = std::max(c->full_share, c->trie_share);        // (this batch and its like: row lists from here on)
         c->prof_units = units0;
         c->ev_used = ev0;

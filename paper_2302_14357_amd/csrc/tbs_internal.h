@@ -197,6 +197,9 @@ struct XcdArgs {
     long hb_bytes;
     void *amat;             // joiner input rows, in pieces of 16 rows x 32 columns (fp32: 16)
     float *logits;
+    float *row_lc, *dphi, *cand_score;   // long segments: what the expansion leaves [U*N, S], [U*N], [U*N, N] ...
+    int *cand_tok;                       // ... for the select step
+    int all_utts;           // utterances there is room for in A and B
     int4 *desc;             // [U*N] state slot (-1: no hypothesis), parent's slot, last token
     XcdCtl *ctl, *ctl_next;
     int *host;              // pinned [workgroups, 4]: joiner calls, frames joined, nodes taken, (seq << 8) | how it ended
@@ -204,6 +207,7 @@ struct XcdArgs {
 };
 bool xcd_fits(const Dims &d);
 hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g);
+hipError_t launch_xcd_decode_long(hipStream_t st, const XcdArgs &g);   // (its segments of more than five frames)
 bool xcd_f32_fits(const Dims &d);
 hipError_t launch_xcd_decode_f32(hipStream_t st, const XcdArgs &g);
 int xcd_f32_row(int K);                    // floats of a row of K columns in the order the products read

@@ -46,6 +46,9 @@ __device__ __forceinline__ uintx4 fresh16(rsrc_t r, unsigned voff, unsigned soff
 __device__ __forceinline__ float fresh4(rsrc_t r, unsigned voff, unsigned soff) {
     return __int_as_float((int)__builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, XR_DEVICE_SCOPE));
 }
+__device__ __forceinline__ float4 as_float4(const uintx4 &v) {
+    return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
+}
 #define XR_TICKS 100000ull   // wall_clock64 ticks per millisecond
 
 // Barrier of the XCD's workgroups, in two halves: every wave waits for its stores (they are in the L2 then) and one thread
@@ -244,15 +247,16 @@ struct XcdShared {   // LDS
 // LDS behind the weights
 template <int SMAX>
 struct XcdScratch {
+    static constexpr bool LONG = SMAX > 5;   // (long segments: a hypothesis by a workgroup, in a step of its own)
     unsigned char *b_list;             // B of an utterance (head of a segment: its scores)
-    ExpandShared<SMAX, 1> *teams;
+    ExpandShared<SMAX, 1> *teams;      // (not for long segments)
     float *lc, *dphi, *cs;             // what the teams hand to the select step: [H, S'], [H], [H, N]
     int *ct;                           // [H, N]
     __device__ __forceinline__ XcdScratch(unsigned char *at, const Dims &d) {
         const size_t list = ((size_t)d.BCAP * (sizeof(double) + sizeof(u64) + 3 * sizeof(int)) + 15) & ~(size_t)15;
         b_list = at;
         teams = reinterpret_cast<ExpandShared<SMAX, 1> *>(at + list);
-        lc = reinterpret_cast<float *>(teams + d.N);
+        lc = reinterpret_cast<float *>(teams + (LONG ? 0 : d.N));
         dphi = lc + d.N * SMAX;
         cs = dphi + d.N;
         ct = reinterpret_cast<int *>(cs + d.N * d.N);
@@ -283,13 +287,16 @@ struct XcdLds {
 template <int SMAX>
 __host__ __device__ inline size_t scratch_bytes(int N, int BCAP) {
     const size_t b_list = ((size_t)BCAP * (sizeof(double) + sizeof(u64) + 3 * sizeof(int)) + 15) & ~(size_t)15;
-    return b_list + (size_t)N * sizeof(ExpandShared<SMAX, 1>) + sizeof(float) * ((size_t)N * SMAX + N + 2 * (size_t)N * N);
+    return b_list + (SMAX > 5 ? 0 : (size_t)N * sizeof(ExpandShared<SMAX, 1>)) + sizeof(float) * ((size_t)N * SMAX + N + 2 * (size_t)N * N);
 }
+#define XR_LONG_SHARES 4   // long segments: arrays of shares of Eq. 6 (see expand_long)
+__host__ __device__ __forceinline__ int long_bytes(int Vl) { return (int)((sizeof(LongShared) + 15) & ~(size_t)15) + XR_LONG_SHARES * Vl * 4; }
 __host__ __device__ __forceinline__ int slice_bytes_f32(int tiles, int K) { return (tiles + XR_WGS - 1) / XR_WGS * f32_pieces(K) * 1024; }
 template <int SMAX, bool F32>
 __host__ __device__ inline XcdLds xcd_lds(const Dims &d, int nw, int limit) {
     XcdLds l{};
-    const int round = ((int)scratch_bytes<SMAX>(d.N, d.BCAP) + 15) & ~15;
+    int round = ((int)scratch_bytes<SMAX>(d.N, d.BCAP) + 15) & ~15;
+    if (SMAX > 5 && long_bytes(d.Vl) > round) round = long_bytes(d.Vl);
     if (!F32) {
         l.wJ = gate_bytes(d, nw);
         l.wP = l.scratch = l.wJ + joiner_bytes(d);
@@ -414,13 +421,16 @@ __device__ __forceinline__ void xcd_carry(const XcdPlace &w, XcdShared &sh) {
             const int i = (int)(((float)p + 0.5f) * rcp_n), sp = sh.sp[i];
             const float4 v = *reinterpret_cast<const float4 *>(g.pool_p + src * d.Dj + c0);
             const quad *ef = enc_of<F32>(g, sh.f0[i], c0);
-            quad ev[SMAX];
+            constexpr int FR = SMAX > 5 ? 4 : SMAX;   // frames asked for at a time
+            for (int t0 = 0; t0 < (SMAX > 5 ? sp : 1); t0 += FR) {
+                quad ev[FR];
 #pragma unroll
-            for (int t = 0; t < SMAX; ++t) ev[t] = ef[(long)min(t, sp - 1) * (d.Dj >> 2)];
-            *reinterpret_cast<float4 *>(g.pool_p + dst * d.Dj + c0) = v;
+                for (int t = 0; t < FR; ++t) ev[t] = ef[(long)min(t0 + t, sp - 1) * (d.Dj >> 2)];
+                if (t0 == 0) *reinterpret_cast<float4 *>(g.pool_p + dst * d.Dj + c0) = v;
 #pragma unroll
-            for (int t = 0; t < SMAX; ++t)
-                if (t < sp) put_joiner_quad(amat, p * S + t, c0, d.Dj, ev[t], v, g.act);
+                for (int t = 0; t < FR; ++t)
+                    if (t0 + t < sp) put_joiner_quad(amat, p * S + t0 + t, c0, d.Dj, ev[t], v, g.act);
+            }
         } else {
             const int c0 = (w.r + (j - nP) * XR_WGS) * 4;
             const float4 h = *reinterpret_cast<const float4 *>(g.pool_h + src * d.H + c0);
@@ -480,6 +490,77 @@ __device__ __forceinline__ void xcd_joiner(const XcdPlace &w, const unsigned cha
                 }
             }
         }
+    }
+}
+
+// ChooseNBestExpansions and ChooseNthScore, by all waves but the select wave (wave N), 16 entries of a list a wave, four lanes
+// sharing one: the rank of an entry is the number of those that beat it (larger score, or equal score and earlier place; a
+// place without a candidate holds NaN and beats nothing).  (By the select wave alone, ranking a B of 85 entries was 2 us.)
+template <int NW, class SM>
+__device__ __forceinline__ void xcd_rank(SM &sm, const double *blogs, int nB, int nc, int N, int wave, int lane) {
+    const int gc = (nc + 15) >> 4, groups = gc + (nB >= N ? (nB + 15) >> 4 : 0);
+    for (int gr = wave < N ? wave : wave - 1; gr < groups; gr += NW - 1) {
+        const bool cands = gr < gc;   // (uniform)
+        const double *v = cands ? sm.s_key : blogs;
+        const int n = cands ? nc : nB, c = 16 * (cands ? gr : gr - gc) + (lane & 15);
+        const int per = (n + 3) >> 2, j0 = (lane >> 4) * per, j1 = min(j0 + per, n);
+        const double mine = v[min(c, n - 1)];
+        int rank = 0;
+#pragma unroll 4
+        for (int j = j0; j < j1; ++j) {
+            const double o = v[j];
+            rank += (o > mine) || (o == mine && j < c);
+        }
+        rank += __shfl_xor(rank, 32);
+        rank += __shfl_xor(rank, 16);
+        if (lane < 16 && c < n) {
+            if (cands) {
+                if (mine == mine && rank < N) sm.s_sel[rank] = c;
+            } else if (rank == N - 1) {
+                sm.s_thr = mine;
+            }
+        }
+    }
+}
+
+// Threshold test, the new list A and what depends on it (trie nodes, descriptors, the figures), by the select wave.
+template <int SMAX, bool FEW, class SM>
+__device__ __forceinline__ void xcd_finish(const XcdPlace &w, XcdShared &sh, SM &sm, SelectOut &s_out, unsigned char *scratch, int round,
+                                           int a, int i, int k, int sp, int H) {
+    const int lane = w.lane, N = w.N;
+    const XcdArgs &g = xcd_args();
+    const XcdScratch<SMAX> sc(scratch, g.d);
+    const int drop = g.max_rounds > 0 && round >= g.max_rounds, u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
+    const AView An = g.A[a ^ 1];
+    SelectIn in{};
+    in.lc = sc.lc;
+    in.slot_rows = 1;
+    const SelectFigs fg{sp, H, i * N * g.d.S, 0, __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_PAR])};
+    // (its logits are in LDS already; that it has some is all it needs to know)
+    select_merge_utt(sm, 5, g.d, round, drop, u, lane, LogitsPlain{g.logits}, in, fg, An, An, g.B, g.rv, g.nodes, sc.b_list, &s_out,
+                     FEW, true);
+    sel_sync();
+    const int used0 = sh.fig[k][TBS_FIG_USED], ncap = sh.fig[k][TBS_FIG_CAP], nbase = sh.fig[k][TBS_FIG_BASE];
+    const int total = s_out.total;
+    bool full = false;
+    if (lane < N) {
+        int4 ds = make_int4(-1, 0, 0, 0);
+        if (lane < total) {
+            const int tok = s_out.tok[lane];
+            full = used0 + lane >= ncap;
+            const int node = full ? 0 : nbase + used0 + lane;
+            if (!full) g.nodes[node] = make_int2(s_out.pnode[lane], tok);
+            An.node[(long)u * N + lane] = node;
+            ds = make_int4(s_out.slot[lane], s_out.pslot[lane], tok, 0);
+        }
+        g.desc[((long)w.u_base + i) * N + lane] = ds;
+    }
+    const bool any_full = __ballot(full) != 0;
+    if (lane == 0) {
+        sh.fig[k][TBS_FIG_CNT] = total;
+        sh.fig[k][TBS_FIG_NB] = s_out.nB;
+        sh.fig[k][TBS_FIG_USED] = min(used0 + total, ncap);
+        sh.made = total | (any_full ? XR_FULL_TRIE : 0);
     }
 }
 
@@ -560,7 +641,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
                     select_merge_utt(sm, 1, g.d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes,
                                      sc.b_list, &s_out, FEW, true);
                     __syncthreads();
-                    select_merge_utt(sm, 4, g.d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes,
+                    select_merge_utt(sm, 6, g.d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes,
                                      sc.b_list, &s_out, FEW, true);
                 } else {
                     __syncthreads();
@@ -576,70 +657,125 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
         }
         __syncthreads();
         if (wave != N) {
-            // ChooseNBestExpansions: the rank of a candidate is the number of those that beat it (larger score, or equal score
-            // and earlier place; a place without a candidate holds NaN and beats nothing)
-            const int nc = H * N, per = (nc + 3) >> 2, j0 = (lane >> 4) * per, j1 = min(j0 + per, nc);
-            for (int base = 16 * (wave < N ? wave : wave - 1); base < nc; base += 16 * (NW - 1)) {
-                const int c = base + (lane & 15);
-                const double mine = sm.s_key[min(c, nc - 1)];
-                int rank = 0;
-#pragma unroll 4
-                for (int j = j0; j < j1; ++j) {
-                    const double o = sm.s_key[j];
-                    rank += (o > mine) || (o == mine && j < c);
-                }
-                rank += __shfl_xor(rank, 32);
-                rank += __shfl_xor(rank, 16);
-                if (lane < 16 && c < nc && mine == mine && rank < N) sm.s_sel[rank] = c;
-            }
+            xcd_rank<NW>(sm, reinterpret_cast<const double *>(scratch), s_out.nB, H * N, N, wave, lane);
             if (wave < H) {
                 const int q = lane / SMAX, tq = lane - q * SMAX;
                 if (q < N) sm.s_xpre[tq * SM::pc + wave * N + q] = xpre;
             }
         }
         __syncthreads();
-        if (wave == N) {
-            const XcdArgs &g = xcd_args();
-            const XcdScratch<SMAX> sc(scratch, g.d);
-            const int drop = g.max_rounds > 0 && round >= g.max_rounds, u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
-            const AView An = g.A[a ^ 1];
-            SelectIn in{};
-            in.lc = sc.lc;
-            in.slot_rows = 1;
-            const SelectFigs fg{sp, H, i * N * g.d.S, 0, __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_PAR])};
-            // (its logits are in LDS already; that it has some is all it needs to know)
-            select_merge_utt(sm, 5, g.d, round, drop, u, lane, LogitsPlain{g.logits}, in, fg, An, An, g.B, g.rv, g.nodes, sc.b_list, &s_out,
-                             FEW, true);
-            sel_sync();
-            const int used0 = sh.fig[k][TBS_FIG_USED], ncap = sh.fig[k][TBS_FIG_CAP], nbase = sh.fig[k][TBS_FIG_BASE];
-            const int total = s_out.total;
-            bool full = false;
-            if (lane < N) {
-                int4 ds = make_int4(-1, 0, 0, 0);
-                if (lane < total) {
-                    const int tok = s_out.tok[lane];
-                    full = used0 + lane >= ncap;
-                    const int node = full ? 0 : nbase + used0 + lane;
-                    if (!full) g.nodes[node] = make_int2(s_out.pnode[lane], tok);
-                    An.node[(long)u * N + lane] = node;
-                    ds = make_int4(s_out.slot[lane], s_out.pslot[lane], tok, 0);
-                }
-                g.desc[((long)w.u_base + i) * N + lane] = ds;
-            }
-            const bool any_full = __ballot(full) != 0;
-            if (lane == 0) {
-                sh.fig[k][TBS_FIG_CNT] = total;
-                sh.fig[k][TBS_FIG_NB] = s_out.nB;
-                sh.fig[k][TBS_FIG_USED] = min(used0 + total, ncap);
-                sh.made = total | (any_full ? XR_FULL_TRIE : 0);
-            }
-        }
+        if (wave == N) xcd_finish<SMAX, FEW>(w, sh, sm, s_out, scratch, round, a, i, k, sp, H);
         __syncthreads();
         const int made = __builtin_amdgcn_readfirstlane(sh.made);
         live += made;
         calls += 1;
         joined += sp;
         nodes_made += made & (XR_FULL_TRIE - 1);
+    }
+    return live;
+}
+
+// Long segments: the hypotheses of the XCD's utterances by its workgroups in turn (a hypothesis has up to 64 rows of logits;
+// the utterance's own workgroup would be alone with all of them).
+template <int NT, int NQ, int SMAX>
+__device__ __forceinline__ void xcd_expand_long(const XcdPlace &w, XcdShared &sh, unsigned char *scratch, int a) {
+    static_assert(SMAX <= LONG_FRAMES && SMAX % (NT / 64) == 0, "rows of a wave");
+    const XcdArgs &g = xcd_args();
+    const Dims &d = g.d;
+    const int N = w.N, S = d.S, P = w.n_act * N;
+    const long pair0 = (long)w.u_base * N;
+    const rsrc_t r_desc = rsrc_of(g.desc + pair0, (long)w.nu * N * 16);
+    const rsrc_t r_logits = rsrc_of(g.logits + pair0 * S * d.Vl, (long)w.nu * N * S * d.Vl * 4);
+    const rsrc_t r_dhat = rsrc_of(g.A[a].dhat, (long)g.all_utts * N * S * 4);
+    LongShared &sm = *reinterpret_cast<LongShared *>(scratch);
+    float4 *s_part = reinterpret_cast<float4 *>(scratch + ((sizeof(LongShared) + 15) & ~(size_t)15));
+    for (int p = w.r; p < P; p += XR_WGS) {
+        const int i = p / N, h = p - i * N;
+        const int slot = __builtin_amdgcn_readfirstlane((int)fresh16(r_desc, (unsigned)p * 16u, 0u)[0]);
+        const int sp = __builtin_amdgcn_readfirstlane(sh.sp[i]), u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
+        if (slot < 0 || sp == 0) continue;   // (the same for the whole workgroup)
+        expand_long<NQ, SMAX / (NT / 64), true>(
+            d, sp, NT / 64, XR_LONG_SHARES, w.tid, sm, s_part,
+            [&](int t) { return fresh4(r_dhat, (unsigned)((u * N + h) * S + t) * 4u, 0u); },
+            [&](int t, int piece) { return as_float4(fresh16(r_logits, (unsigned)piece * 16u, (unsigned)(p * S + t) * (unsigned)d.Vl * 4u)); },
+            [&](int t, int col) { return fresh4(r_logits, (unsigned)((p * S + t) * d.Vl + col) * 4u, 0u); }, g.row_lc + (pair0 + p) * S,
+            g.dphi + pair0 + p, g.cand_score + (pair0 + p) * N, g.cand_tok + (pair0 + p) * N, nullptr, nullptr);
+        __syncthreads();
+    }
+}
+
+// ... and the select step of an utterance by its own workgroup, whose waves then make the frame distributions of the new
+// hypotheses, one each.
+template <int NT, int SMAX, class SM>
+__device__ __forceinline__ int xcd_select_long(const XcdPlace &w, XcdShared &sh, SM &sm, SelectOut &s_out, unsigned char *scratch, int round,
+                                               int a, int &calls, int &joined, int &nodes_made) {
+    constexpr int NW = NT / 64;
+    int live = 0;
+    for (int i = w.r, k = 0; i < w.n_act; i += XR_WGS, ++k) {
+        const int tid = w.tid, lane = w.lane, wave = w.wave, N = w.N;
+        const int sp = __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_SP]);
+        const int H = sp > 0 ? __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_CNT]) : 0;
+        const XcdArgs &g = xcd_args();
+        const Dims &d = g.d;
+        const long pair = (long)w.u_base * N + (long)i * N;
+        if (H == 0) {   // (the same for the whole workgroup)
+            if (tid < N) g.desc[pair + tid] = make_int4(-1, 0, 0, 0);
+            continue;
+        }
+        const XcdScratch<SMAX> sc(scratch, d);
+        const int u = __builtin_amdgcn_readfirstlane(sh.utt[i]), nc = H * N;
+        SelectIn in{};
+        in.dphi = sc.dphi;
+        const SelectFigs fg{sp, H, i * N * d.S, __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_NB]), 0};
+        if (wave == N) {
+            select_merge_utt(sm, 1, d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes, sc.b_list,
+                             &s_out, true, false);
+        } else {   // what the expansion left, from the L2
+            const rsrc_t r_cs = rsrc_of(g.cand_score + pair * N, N * N * 4), r_ct = rsrc_of(g.cand_tok + pair * N, N * N * 4);
+            const rsrc_t r_dphi = rsrc_of(g.dphi + pair, N * 4), r_lc = rsrc_of(g.row_lc + pair * d.S, (long)N * d.S * 4);
+            const int tt = (wave < N ? wave : wave - 1) * 64 + lane, n = (NW - 1) * 64;
+            if (tt < nc) {
+                sc.cs[tt] = fresh4(r_cs, (unsigned)tt * 4u, 0u);
+                sc.ct[tt] = __float_as_int(fresh4(r_ct, (unsigned)tt * 4u, 0u));
+            }
+            if (tt < H) sc.dphi[tt] = fresh4(r_dphi, (unsigned)tt * 4u, 0u);
+            const float rcp_sp = __builtin_amdgcn_rcpf((float)sp);   // (exact quotients of up to 7 x 64 rows)
+            for (int e = tt; e < H * sp; e += n) {
+                const int h = (int)(((float)e + 0.5f) * rcp_sp);
+                sc.lc[e] = fresh4(r_lc, (unsigned)(h * d.S + e - h * sp) * 4u, 0u);
+            }
+        }
+        __syncthreads();
+        if (wave == N) {
+            select_merge_utt(sm, 6, d, round, 0, u, lane, LogitsPlain{nullptr}, in, fg, g.A[a], g.A[a ^ 1], g.B, g.rv, g.nodes, sc.b_list,
+                             &s_out, true, false);
+        } else if (wave < H && lane < N) {
+            const int c = wave * N + lane, tok = sc.ct[c];
+            sm.s_ctok[c] = tok;
+            sm.s_key[c] = tok >= 0 ? sm.s_alogs[wave] + (double)sc.cs[c] : nan("");
+        }
+        __syncthreads();
+        if (wave != N) xcd_rank<NW>(sm, reinterpret_cast<const double *>(scratch), s_out.nB, nc, N, wave, lane);
+        __syncthreads();
+        if (wave == N) xcd_finish<SMAX, true>(w, sh, sm, s_out, scratch, round, a, i, k, sp, H);
+        __syncthreads();
+        const int made = __builtin_amdgcn_readfirstlane(sh.made), total = made & (XR_FULL_TRIE - 1);
+        if (wave < total) {   // (at most N < NW)
+            const rsrc_t r_logits = rsrc_of(g.logits + pair * d.S * d.Vl, (long)N * d.S * d.Vl * 4);
+            const int h = __builtin_amdgcn_readfirstlane(sm.s_kh[wave]), tok = __builtin_amdgcn_readfirstlane(sm.s_ktok[wave]);
+            const int t = min(lane, sp - 1);
+            const float xv = fresh4(r_logits, (unsigned)((h * d.S + t) * d.Vl + tok) * 4u, 0u) + sc.lc[h * sp + t];
+            const float xx = lane < sp ? xv : -INFINITY;
+            const float mx = wave_max(xx);
+            const float lz = mx + __logf(wave_sum(lane < sp ? __expf(xx - mx) : 0.f));
+            float *dh = g.A[a ^ 1].dhat + ((long)u * N + wave) * d.S;
+            if (lane < d.S) dh[lane] = lane < sp ? xx - lz : -INFINITY;
+        }
+        __syncthreads();
+        live += made;
+        calls += 1;
+        joined += sp;
+        nodes_made += total;
     }
     return live;
 }
@@ -700,7 +836,7 @@ __device__ __forceinline__ void xcd_gates(const XcdPlace &w, const unsigned char
 // 16 columns, as many at a time as there are waves, and leaves it in LDS; then all threads form the rows, four
 // columns of one frame each (the few waves that have tiles would take longer over the activations than over the products).
 // The first frames are asked for between the halves of the barrier ahead.
-template <int NT, int C>
+template <int NT, int C, int FR>
 __device__ __forceinline__ int xcd_project(const XcdPlace &w, XcdShared &sh, XcdBarrier &bar, const unsigned char *wP, unsigned char *scratch) {
     constexpr int NW = NT / 64, steps = 4 * C;
     const XcdArgs &g = xcd_args();
@@ -713,28 +849,29 @@ __device__ __forceinline__ int xcd_project(const XcdPlace &w, XcdShared &sh, Xcd
     const float rcp_n = __builtin_amdgcn_rcpf((float)w.N);
     float *s_p = reinterpret_cast<float *>(scratch);         // [per * 16 hypotheses][own * 16]
     int *s_on = reinterpret_cast<int *>(s_p + NW * 256);     // [per * 16]
-    // item of the second half: columns 4 q .. of hypothesis p0 + h at frame f
-    const int q_n = own * 4;
-    int q = 0, h = 0, f = 0, p0 = 0, n = 0;
-    uint2 ev;
+    // item of the second half: columns 4 q .. of hypothesis p0 + h at frames f .. f + FR - 1
+    const int q_n = own * 4, fg_n = (S + FR - 1) / FR;
+    int q = 0, h = 0, f = 0, p0 = 0, n = 0, left = 0;
+    uint2 ev[FR];
     auto item = [&](int it) {
         const float rq = __builtin_amdgcn_rcpf((float)q_n), rn = __builtin_amdgcn_rcpf((float)n);
-        const int hf = (int)(((float)it + 0.5f) * rq);       // (exact: fewer than 2^14 items)
+        const int hf = (int)(((float)it + 0.5f) * rq);       // (exact: fewer than 2^16 items)
         q = it - hf * q_n;
         f = (int)(((float)hf + 0.5f) * rn);
         h = hf - f * n;
+        f *= FR;
     };
-    auto frame = [&]() {
+    auto frames = [&]() {   // asks for them, and how many there are
         const int i = (int)(((float)(p0 + h) + 0.5f) * rcp_n), sp = sh.sp[i], c0 = (w.r + (q >> 2) * XR_WGS) * 16 + (q & 3) * 4;
         // (beyond the utterance's frames any frame that exists will do)
-        ev = *enc_of<false>(g, sp > 0 ? sh.f0[i] + min(f, sp - 1) : 0, c0);
-        return f < sp;
+#pragma unroll
+        for (int t = 0; t < FR; ++t) ev[t] = *enc_of<false>(g, sp > 0 ? sh.f0[i] + min(f + t, sp - 1) : 0, c0);
+        return sp - f;
     };
-    bool there = false;
     n = min(P, per * 16);
-    if (w.tid < n * q_n * S) {
+    if (w.tid < n * q_n * fg_n) {
         item(w.tid);
-        there = frame();
+        left = frames();
     }
     const int sum = xcd_wait(bar, sh.sum);
     if (sum < 0) return sum;
@@ -761,14 +898,17 @@ __device__ __forceinline__ int xcd_project(const XcdPlace &w, XcdShared &sh, Xcd
             if (on) *reinterpret_cast<float4 *>(g.pool_p + slot * d.Dj + c0) = pv;
         }
         __syncthreads();
-        for (int it = w.tid; it < n * q_n * S; it += NT) {
+        for (int it = w.tid; it < n * q_n * fg_n; it += NT) {
             if (rt0 > 0 || it >= NT) {
                 item(it);
-                there = frame();
+                left = frames();
             }
-            if (there && s_on[h]) {
+            if (left > 0 && s_on[h]) {
                 const float4 v = *reinterpret_cast<const float4 *>(s_p + h * own * 16 + q * 4);
-                put_joiner_quad(amat, (p0 + h) * S + f, (w.r + (q >> 2) * XR_WGS) * 16 + (q & 3) * 4, d.Dj, ev, v, g.act);
+#pragma unroll
+                for (int t = 0; t < FR; ++t)
+                    if (t < left)
+                        put_joiner_quad(amat, (p0 + h) * S + f + t, (w.r + (q >> 2) * XR_WGS) * 16 + (q & 3) * 4, d.Dj, ev[t], v, g.act);
             }
         }
         if (rt0 + per < ptiles) __syncthreads();
@@ -817,10 +957,6 @@ __device__ __forceinline__ float4 f32_sum(const float4 *part, int tile, int lane
 }
 template <class F>
 __device__ __forceinline__ void by_chunks_f32(int K, F fn) { by_chunks((K + 127) & ~127, fn); }
-
-__device__ __forceinline__ float4 as_float4(const uintx4 &v) {
-    return make_float4(__uint_as_float(v[0]), __uint_as_float(v[1]), __uint_as_float(v[2]), __uint_as_float(v[3]));
-}
 
 template <int NT, int C>
 __device__ __forceinline__ void xcd_joiner_f32(const XcdPlace &w, const float4 *wJ, float4 *part, int at_once) {
@@ -953,7 +1089,7 @@ k_xcd_decode(XcdArgs args) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     __shared__ XcdShared sh;
     __shared__ SelectOut s_out;
-    __shared__ SelectShared<XR_CANDS, 1, SMAX, FEW ? 64 : XR_CANDS> s_select;
+    __shared__ SelectShared<(SMAX > 5 ? 64 : XR_CANDS), (SMAX > 5 ? 0 : 1), (SMAX > 5 ? 1 : SMAX), FEW ? 64 : XR_CANDS> s_select;
     XcdPlace w;
     w.tid = threadIdx.x;
     w.lane = w.tid & 63;
@@ -1064,10 +1200,17 @@ k_xcd_decode(XcdArgs args) {
                 else
                     by_chunks(Dj, [&](auto c) { xcd_joiner<NT, c.value>(w, wJ); });
                 if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
-                const int live = xcd_round<NT, NV4, SMAX, FEW>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
+                int live;
+                if constexpr (SMAX > 5) {
+                    xcd_expand_long<NT, NV4, SMAX>(w, sh, scratch, a);
+                    if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+                    live = xcd_select_long<NT, SMAX>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
+                } else {
+                    live = xcd_round<NT, NV4, SMAX, FEW>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
+                }
                 a ^= 1;
                 xcd_arrive(bar, live);
-                if (!F32 && (w.r < w.n_act || round == 1)) {   // (only who has utterances of its own writes over the slice)
+                if (!F32 && (SMAX > 5 || w.r < w.n_act || round == 1)) {   // (only who has utterances of its own, or hypotheses, writes over the slice)
                     const XcdArgs &g = xcd_args();
                     const int own = own_tiles(g.d.Dj >> 4, w.r);
                     load_pieces(wP, static_cast<const bf16_t *>(g.w_proj), g.d.Dj, g.d.H, w.r, 0, own * (g.d.H >> 5), w.wave, NW, lane);
@@ -1089,7 +1232,7 @@ k_xcd_decode(XcdArgs args) {
                     by_chunks(Hh, [&](auto c) { xcd_gates<NT, c.value>(w, wG); });
                     xcd_arrive(bar, 0);
                     int there = 0;
-                    by_chunks(Hh, [&](auto c) { there = xcd_project<NT, c.value>(w, sh, bar, wP, wG); });
+                    by_chunks(Hh, [&](auto c) { there = xcd_project<NT, c.value, (SMAX > 5 ? 4 : 1)>(w, sh, bar, wP, wG); });
                     if (there < 0) { status = XR_STUCK; break; }
                     xcd_arrive(bar, 0);
                     {
@@ -1135,6 +1278,7 @@ static int nv4_of(const Dims &d) {   // (as the round kernel of the slot layout:
 template <bool F32>
 static XcdLds lds_of(const Dims &d) {
     const int nw = d.N <= 7 ? 8 : 12, limit = XR_LDS(F32 || d.N > 7);
+    if (d.S > 5) return d.S <= 16 ? xcd_lds<16, F32>(d, nw, limit) : d.S <= 32 ? xcd_lds<32, F32>(d, nw, limit) : xcd_lds<64, F32>(d, nw, limit);
     return d.S == 1 ? xcd_lds<1, F32>(d, nw, limit) : d.S <= 3 ? xcd_lds<3, F32>(d, nw, limit) : xcd_lds<5, F32>(d, nw, limit);
 }
 
@@ -1167,10 +1311,10 @@ static hipError_t xcd_launch(hipStream_t st, const XcdArgs &g) {
 }
 
 // the shapes both types have in common
-static bool xcd_shape_fits(const Dims &d) {
-    return d.L == 1 && d.N <= 11 && d.S <= 5 && d.V <= 1024 && d.Dj <= XR_KMAX && d.H <= XR_KMAX && d.BCAP <= 2048;
+[[maybe_unused]] static bool xcd_shape_fits(const Dims &d) {
+    return d.L == 1 && (d.S <= 5 ? d.N <= 11 : d.S <= LONG_FRAMES && d.N <= 7) && d.V <= 1024 && d.Dj <= XR_KMAX && d.H <= XR_KMAX && d.BCAP <= 2048;
 }
-static bool xcd_batch_fits(const XcdArgs &g) {
+[[maybe_unused]] static bool xcd_batch_fits(const XcdArgs &g) {
     if (g.d.U > XR_XCDS * XR_POS) return false;
     for (int x = 0; x < XR_XCDS; ++x)
         if (g.first[x + 1] - g.first[x] > XR_POS) return false;

@@ -5,7 +5,7 @@ int xcd_f32_row(int K) { return f32_row(K); }
 long xcd_f32_frags(int rows, int K) { return (long)((rows + 15) / 16) * f32_pieces(K) * 256; }
 
 bool xcd_f32_fits(const Dims &d) {
-    if (!xcd_shape_fits(d) || d.Dj % 8 || d.H % 8) return false;
+    if (!xcd_shape_fits(d) || d.S > 5 || d.Dj % 8 || d.H % 8) return false;
     const long hb = (long)d.U * 2 * (d.R + 1) * d.N * f32_row(d.H) * 4;
     return hb < (1l << 31) && lds_of<true>(d).bytes <= XR_LDS(true);
 }

@@ -9,5 +9,6 @@ bool xcd_fits(const Dims &d) {
 
 hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g) {
     if (!xcd_fits(g.d) || !xcd_batch_fits(g)) return hipErrorInvalidValue;
+    if (g.d.S > 5) return launch_xcd_decode_long(st, g);
     return g.d.N <= 7 ? xcd_launch<512, true, false>(st, g) : xcd_launch<768, false, false>(st, g);
 }

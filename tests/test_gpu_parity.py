@@ -1338,3 +1338,72 @@ def test_codes_of_segments_in_one_launch():
                     tbs.decode(frames, offsets)
                 assert e.value.code == -5
             tbs.close()
+
+
+@pytest.mark.parametrize("d,hidden,V,N,S,lengths,peaked", [
+    (128, 128, 96, 4, 7, [0, 2, 7, 12, 23, 31], False), (128, 256, 200, 7, 16, [5, 16, 17, 40], True), (256, 128, 1023, 2, 17, [34, 3, 18], False),
+    (384, 128, 500, 5, 33, [33, 70, 1], False), (128, 128, 64, 3, 64, [64, 65, 130, 20], False), (512, 640, 1024, 5, 20, [25] * 9, False),
+    (128, 128, 40, 5, 6, [3 + i % 10 for i in range(270)], False), (128, 128, 700, 10, 5, [4 + i % 5 for i in range(140)], False),
+    (128, 128, 1000, 5, 3, [2 + i % 5 for i in range(300)], False)])
+def test_one_launch_beyond_the_fixed_places(d, hidden, V, N, S, lengths, peaked):
+    """Segments of 6 to 64 frames (a wave's rows one to eight, hypotheses spread over the XCD's workgroups, more of them than
+    those) and batches too large for the layout with fixed places: what row lists give (debug bit 16), and the oracle."""
+    shape = small_bf16_shape(n_utts=len(lengths), vocab=V, d=d, hidden=hidden)
+    kw, cap = {}, 0
+    if peaked:
+        shape, cap = _peaked(shape, 8.0, 8.0), 5
+        kw = dict(max_rounds_per_segment=cap)
+    elif S > 16:
+        kw = dict(rounds_capacity=4 * S)
+    model, offsets, enc = build_case(shape, n_utts=len(lengths), lengths=np.array(lengths))
+    seen = []
+    for debug in (0, 65536, 131072):
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
+        got = tbs.decode(tbs.upload_frames(enc), offsets)
+        assert _one_launch(tbs) == (debug != 65536) and not tbs.path()["fixed_places"]
+        seen.append((got, tbs.stats(), tbs.counts()["nodes"]))
+        tbs.close()
+    for other in seen[1:]:
+        for a, b in zip(seen[0][0], other[0]):
+            assert [h[0] for h in a] == [h[0] for h in b]
+            np.testing.assert_allclose([h[1] for h in a], [h[1] for h in b], rtol=1e-6, atol=1e-5)
+        assert seen[0][1:] == other[1:]
+    n = min(len(lengths), 6)
+    okw = {k: v for k, v in kw.items() if k != "max_rounds_per_segment"}
+    _check_decode(shape, model, offsets[:n + 1], enc[:offsets[n]], N, S, max_rounds=cap, **okw)
+
+
+def test_one_launch_with_a_trie_that_one_list_of_nodes_fits():
+    """A trie just large enough for all utterances together, too small for a share of each: decodes of long segments and of
+    batches beyond the fixed places run with row lists then, with the same result; nothing that was accepted is refused."""
+    N, S = 4, 7
+    shape = small_bf16_shape(n_utts=5, vocab=64, d=128, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=5, lengths=np.array([3, 40, 8, 21, 13]))
+
+    def run(**kw):
+        try:
+            got, _ = _gpu_decode(shape, model, offsets, enc, N, S, **kw)
+        except RuntimeError:
+            return None
+        return [[y for y, _ in u] for u in got]
+
+    want = run()
+    lo, hi = 16, 4 * N * (85 + 5 * S) + 16
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        lo, hi = (mid, hi) if run(max_nodes=mid, debug=65536) is None else (lo, mid)
+    assert run(max_nodes=hi) == want
+    assert run(max_nodes=lo) is None
+    # (one utterance that emits more than its share of a trie of the default size: decoded again with row lists)
+    cap = 24
+    model["w_out"] = np.zeros_like(model["w_out"])
+    model["w_out"][0, :] = 0.5
+    model["b_out"] = np.linspace(0.0, 0.3, 64).astype(np.float32)
+    model["b_out"][0] = -60.0
+    enc = np.full_like(enc, 8.0)
+    enc[offsets[1]:offsets[2]] = -64.0
+    import dataclasses
+    shape = dataclasses.replace(shape, act="relu")
+    one, two = (_gpu_decode(shape, model, offsets, enc, 2, 6, max_rounds_per_segment=cap, debug=dbg) for dbg in (0, 65536))
+    assert [[h[0] for h in u] for u in one[0]] == [[h[0] for h in u] for u in two[0]]
+    assert one[1]["joiner_calls"] == two[1]["joiner_calls"]
