@@ -82,7 +82,7 @@ struct tbs_ctx {
     int *x_order;       // [U] the XCDs' utterances (behind utt_fig)
     int x_first[XR_XCDS + 1];
     void *x_hb, *x_amat;
-    float *x_frags[3];  // fp32: the output, gate and projection weights in the pieces the products read
+    void *x_frags;      // the gate weights in the pieces the products read
     int4 *x_desc;
     int *h_xcd;         // pinned: [XCDs * workgroups, 4] how each workgroup ended, then [XCDs, XR_SEGS] rounds
     int *h_xcd_dev;
@@ -456,22 +456,24 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     {
         int cus = 0;
         c->xcd_ready = (cfg->debug & ~131072) == 0 && cfg->joiner_chunk_rows == 0 && (cfg->dtype == 1 ? xcd_fits(d) : xcd_f32_fits(d)) &&
+                       ((reinterpret_cast<uintptr_t>(w->w_out) | reinterpret_cast<uintptr_t>(w->w_proj)) & 15) == 0 &&   // (16 B to the LDS at once)
                        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device_id) == hipSuccess &&
                        cus == XR_XCDS * XR_WGS;
     }
     if (c->xcd_ready) {
         rc |= dev_alloc(c, &c->x_ctl, 2);
         rc |= dev_alloc(c, &c->x_desc, UN);
-        const bool f32 = cfg->dtype == 0;
-        char *p = nullptr, *q = nullptr;
-        rc |= dev_alloc(c, &p, (size_t)c->pool_rows * (f32 ? 4 * xcd_f32_row(d.H) : 2 * d.H));
-        rc |= dev_alloc(c, &q, (size_t)(M + 16 * XR_XCDS) * (f32 ? 4 * xcd_f32_row(d.Dj) : 2 * d.Dj));   // (every XCD's rows in whole tiles of 16)
-        c->x_hb = p;
-        c->x_amat = q;
-        if (f32) {
-            rc |= dev_alloc(c, &c->x_frags[0], (size_t)xcd_f32_frags(d.V, d.Dj));
-            rc |= dev_alloc(c, &c->x_frags[1], (size_t)xcd_f32_frags(4 * d.H, d.H));
-            rc |= dev_alloc(c, &c->x_frags[2], (size_t)xcd_f32_frags(d.Dj, d.H));
+        const long n[3] = {c->pool_rows * xcd_row_bytes(cfg->dtype, d.H),
+                           (M + 16 * XR_XCDS) * xcd_row_bytes(cfg->dtype, d.Dj),   // (every XCD's rows in whole tiles of 16)
+                           xcd_frag_bytes(cfg->dtype, 4 * d.H, d.H)};
+        void **to[3] = {&c->x_hb, &c->x_amat, &c->x_frags};
+        long all = 0;
+        for (int i = 0; i < 3; ++i) all += (n[i] + 255) & ~255l;
+        char *p = nullptr;
+        rc |= dev_alloc(c, &p, (size_t)all);
+        for (int i = 0; i < 3; ++i) {
+            *to[i] = p;
+            p += (n[i] + 255) & ~255l;
         }
     }
     rc |= dev_alloc(c, &c->res_count, U);
@@ -560,10 +562,8 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
             return TBS_EHIP;
         }
     }
-    if (c->xcd_ready && cfg->dtype == 0) {
-        e = launch_xcd_frags(c->stream, (const float *)w->w_out, c->x_frags[0], d.V, d.Dj);
-        if (e == hipSuccess) e = launch_xcd_frags(c->stream, (const float *)c->wperm[0], c->x_frags[1], 4 * d.H, d.H);
-        if (e == hipSuccess) e = launch_xcd_frags(c->stream, (const float *)w->w_proj, c->x_frags[2], d.Dj, d.H);
+    if (c->xcd_ready) {
+        e = launch_xcd_frags(c->stream, cfg->dtype, c->wperm[0], c->x_frags, 4 * d.H, d.H);
         if (e != hipSuccess) {
             c->last_hip = (int)e;
             tbs_free(c);
@@ -1382,7 +1382,7 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.d = d;
     g.max_rounds = c->cfg.max_rounds_per_segment;
     g.act = c->cfg.act;
-    g.expect = XR_XCDS * XR_WGS + (c->cfg.debug & 131072 ? 1 : 0);
+    g.expect = XR_XCDS + (c->cfg.debug & 131072 ? 1 : 0);
     int tiles = 0;
     for (int x = 0; x <= XR_XCDS; ++x) g.first[x] = c->x_first[x];
     for (int x = 0; x < XR_XCDS; ++x) {
@@ -1394,9 +1394,9 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.utt_off = c->utt_off;
     const bool f32 = c->cfg.dtype == 0;
     g.enc = c->enc;
-    g.w_out = f32 ? c->x_frags[0] : c->w.w_out;
-    g.w_gate = f32 ? c->x_frags[1] : c->wperm[0];
-    g.w_proj = f32 ? c->x_frags[2] : c->w.w_proj;
+    g.w_out = c->w.w_out;
+    g.w_gate = c->x_frags;
+    g.w_proj = c->w.w_proj;
     g.b_out = c->w.b_out;
     g.b_proj = c->w.b_proj;
     g.emb_gates = c->emb_gates_perm;
@@ -1410,7 +1410,7 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.pool_h = c->pool_h;
     g.pool_c = c->pool_c;
     g.hb = c->x_hb;
-    g.hb_bytes = c->pool_rows * (f32 ? 4 * xcd_f32_row(d.H) : 2 * d.H);
+    g.hb_bytes = c->pool_rows * xcd_row_bytes(c->cfg.dtype, d.H);
     g.amat = c->x_amat;
     g.logits = c->logits;
     g.row_lc = c->row_lc;

@@ -170,7 +170,8 @@ __host__ __device__ inline int part_width(int np) { return (4 + 2 * np + 3) & ~3
 struct XcdCtl {        // device memory, zero when the launch begins
     u64 bar[XR_XCDS * 16];            // an XCD's barriers (a line each)
     unsigned place[XR_XCDS * 32];     // workgroups that came on each XCD
-    unsigned arrived, state;          // all of them; 1: all came, 2: given up
+    unsigned told[XR_XCDS * 32];      // what became of it, as `state`
+    unsigned arrived, state;          // XCDs that are complete; 1: all are, 2: given up
     unsigned pad[30];
 };
 enum { XR_DONE = 1, XR_ABSENT = 2, XR_TRIE = 3, XR_ROUNDS = 4, XR_STUCK = 5 };   // how a workgroup ended
@@ -180,11 +181,12 @@ struct XcdArgs {
     int seg0, seg1;         // segments of this launch
     int max_rounds;         // limit on the rounds of a segment (0: none)
     int act, seq;
-    int expect;             // workgroups that have to come before anything is done
+    int expect;             // XCDs that have to be complete before anything is done
     int first[XR_XCDS + 1]; // the XCDs' parts of `order` [U]: utterances in falling length
     int tile0[XR_XCDS];     // and of amat, in tiles of 16 rows
     const int *order, *utt_T, *utt_off;
-    const void *enc;        // frames, and weights as bf16 rows or fp32 pieces (launch_xcd_frags); gate rows interleaved, see LstmEp
+    const void *enc;        // frames; the caller's output and projection weights, and the recurrent gate weights
+                            // (rows interleaved, see LstmEp) in the pieces the products read (launch_xcd_frags)
     const void *w_out, *w_gate, *w_proj;
     const float *b_out, *b_proj, *emb_gates;
     AView A[2];
@@ -193,7 +195,7 @@ struct XcdArgs {
     int *fig;
     int2 *nodes;
     float *pool_p, *pool_h, *pool_c;
-    void *hb;               // [slots, H] h as the products read it: bf16, or fp32 rows of xcd_f32_row(H)
+    void *hb;               // [slots] rows of h as the products read it (xcd_row_bytes)
     long hb_bytes;
     void *amat;             // joiner input rows, in pieces of 16 rows x 32 columns (fp32: 16)
     float *logits;
@@ -210,9 +212,9 @@ hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g);
 hipError_t launch_xcd_decode_long(hipStream_t st, const XcdArgs &g);   // (its segments of more than five frames)
 bool xcd_f32_fits(const Dims &d);
 hipError_t launch_xcd_decode_f32(hipStream_t st, const XcdArgs &g);
-int xcd_f32_row(int K);                    // floats of a row of K columns in the order the products read
-long xcd_f32_frags(int rows, int K);       // floats of a weight matrix in pieces
-hipError_t launch_xcd_frags(hipStream_t st, const float *w, float *frags, int rows, int K);
+long xcd_row_bytes(int dtype, int K);                // bytes of a row of K columns as the products read it
+long xcd_frag_bytes(int dtype, int rows, int K);     // and of a weight matrix in pieces
+hipError_t launch_xcd_frags(hipStream_t st, int dtype, const void *w, void *frags, int rows, int K);
 
 // ---- launchers (each enqueues on `st` and returns the HIP status) ----
 hipError_t launch_init_batch(hipStream_t st, const Dims &d, BView B, AView A0, AView A1, RowView rv, int2 *nodes,

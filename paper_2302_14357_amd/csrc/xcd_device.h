@@ -170,30 +170,40 @@ __device__ __forceinline__ void by_chunks(int K, F fn) {
     }
 }
 
-// This workgroup's slice of a weight matrix [rows, K] in LDS: tiles r, r + 32, ... of 16 rows, each as K / 32 pieces of 1 KB.
-// Pieces [from, to) of it, straight from memory; they are there behind the next barrier that has waited for them.
-__device__ __forceinline__ void load_pieces(unsigned char *lds, const bf16_t *w, int rows, int K, int r, int from, int to, int wave, int nw,
-                                            int lane) {
-    const int steps = K >> 5;
-    const float rcp_s = __builtin_amdgcn_rcpf((float)steps);   // (exact quotients of fewer than 2^12 pieces)
+// This workgroup's slice of a weight matrix [rows, K] in LDS: tiles r, r + 32, ... of 16 rows, each in pieces of 1 KB as the
+// matrix instructions read them (see amat_at, f32_at).  Pieces [from, to) of it; they are there behind the next barrier that has
+// waited for them.  The gates' lie in memory in that order; the output matrix and the projection, which may change from one
+// decode to the next, come from their rows.
+__device__ __forceinline__ void load_frags(unsigned char *lds, const void *frags, int pieces, int from, int to, int r, int wave, int nw, int lane) {
+    const float rcp_p = __builtin_amdgcn_rcpf((float)pieces);   // (exact quotients of fewer than 2^12 pieces)
 #pragma unroll 4
     for (int i = from + wave; i < to; i += nw) {
-        const int t = (int)(((float)i + 0.5f) * rcp_s), s = i - t * steps;
-        const int row = min((r + t * XR_WGS) * 16 + (lane & 15), rows - 1);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(w + (long)row * K + s * 32 + (lane >> 4) * 8),
-                                         (__attribute__((address_space(3))) void *)(lds + (size_t)i * 1024), 16, 0, 0);
-    }
-}
-
-// (fp32: the pieces lie in memory as in LDS)
-__device__ __forceinline__ void load_frags(unsigned char *lds, const void *frags, int pieces, int own, int r, int wave, int nw, int lane) {
-    const float rcp_p = __builtin_amdgcn_rcpf((float)pieces);
-#pragma unroll 4
-    for (int i = wave; i < own * pieces; i += nw) {
         const int t = (int)(((float)i + 0.5f) * rcp_p), m = i - t * pieces;
         __builtin_amdgcn_global_load_lds(
             (const __attribute__((address_space(1))) void *)(static_cast<const float4 *>(frags) + ((long)(r + t * XR_WGS) * pieces + m) * 64 + lane),
             (__attribute__((address_space(3))) void *)(lds + (size_t)i * 1024), 16, 0, 0);
+    }
+}
+template <bool F32>
+__device__ __forceinline__ void load_rows(unsigned char *lds, const void *w, int rows, int K, int own, int r, int wave, int nw, int lane) {
+    const int pieces = F32 ? f32_pieces(K) : K >> 5;
+    const float rcp_p = __builtin_amdgcn_rcpf((float)pieces);
+#pragma unroll 4
+    for (int i = wave; i < own * pieces; i += nw) {
+        const int t = (int)(((float)i + 0.5f) * rcp_p), m = i - t * pieces;
+        const long row = min((r + t * XR_WGS) * 16 + (lane & 15), rows - 1);
+        if constexpr (F32) {   // (K is a multiple of 8: a piece's second half may lie beyond it)
+            const int q = lane >> 4, k = m * 16 + (q & 1) * 4 + (q & 2);
+            const float *src = static_cast<const float *>(w) + row * K + k;
+            const float2 lo = *reinterpret_cast<const float2 *>(src);
+            float2 hi = *reinterpret_cast<const float2 *>(k + 8 < K ? src + 8 : src);
+            if (k + 8 >= K) hi = make_float2(0.f, 0.f);
+            *reinterpret_cast<float4 *>(lds + (size_t)i * 1024 + lane * 16) = make_float4(lo.x, lo.y, hi.x, hi.y);
+        } else {
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void *)(static_cast<const bf16_t *>(w) + row * K + m * 32 + (lane >> 4) * 8),
+                (__attribute__((address_space(3))) void *)(lds + (size_t)i * 1024), 16, 0, 0);
+        }
     }
 }
 
@@ -1102,24 +1112,28 @@ k_xcd_decode(XcdArgs args) {
         XcdCtl *ctl = args.ctl;
         const int x = (int)(__builtin_amdgcn_s_getreg(20 | (3 << 11)) & 15u);   // (the number of this CU's XCD: hwreg 20, 4 bits)
         const int xc = min(x, XR_XCDS - 1);
+        // (Places are counted per XCD; the last of an XCD's workgroups counts the XCD, waits for the others' and tells its own.
+        // A word that all 256 count in takes them one after the other: 10.5 -> 4.7 us a launch until the first segment with the
+        // small fp32 configuration, 12.4 -> 8.5 with 64 utterances.)
         const unsigned r = __hip_atomic_fetch_add(&ctl->place[xc * 32], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        // (the sum below depends on the answer above: nobody is counted in before its place is taken)
-        const unsigned t = __hip_atomic_fetch_add(&ctl->arrived, r < 0x40000000u ? 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        unsigned none = 0;
-        if (t == (unsigned)args.expect - 1)
+        const bool leads = r == XR_WGS - 1;
+        unsigned st = 0;
+        if (leads && __hip_atomic_fetch_add(&ctl->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)args.expect - 1) {
+            unsigned none = 0;
             __hip_atomic_compare_exchange_strong(&ctl->state, &none, 1u, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        unsigned *word = leads ? &ctl->state : &ctl->told[xc * 32];
         const u64 t0 = wall_clock64();
-        unsigned st;
-        while ((st = __hip_atomic_load(&ctl->state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
+        while ((st = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
             if (wall_clock64() - t0 > 5ull * XR_TICKS) {   // (who decides first decides for all)
-                none = 0;
+                unsigned none = 0;
                 __hip_atomic_compare_exchange_strong(&ctl->state, &none, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);
+                word = &ctl->state;
             }
         }
-        bool ok = st == 1 && x < XR_XCDS;
-        for (int i = 0; i < XR_XCDS; ++i)
-            ok = ok && __hip_atomic_load(&ctl->place[i * 32], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == XR_WGS;
+        if (leads) __hip_atomic_store(&ctl->told[xc * 32], st, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const bool ok = st == 1 && x < XR_XCDS && r < XR_WGS;
         sh.where[0] = xc;
         sh.where[1] = (int)r;
         sh.where[2] = ok;
@@ -1151,16 +1165,11 @@ k_xcd_decode(XcdArgs args) {
             wP = s_dyn + l.wP;
             scratch = s_dyn + l.scratch;
             at_once = l.tiles;
-            if constexpr (F32) {
-                const int pH = f32_pieces(d.H), pJ = f32_pieces(d.Dj);
-                if (l.wG < 0) wG = nullptr;
-                else load_frags(wG, g.w_gate, pH, own_tiles(tiles_gate(d), w.r), w.r, w.wave, NW, lane);
-                load_frags(wJ, g.w_out, pJ, own_tiles(tiles_joiner(d), w.r), w.r, w.wave, NW, lane);
-                load_frags(wP, g.w_proj, pH, own_tiles(tiles_proj(d), w.r), w.r, w.wave, NW, lane);
-            } else {
-                load_pieces(wG, static_cast<const bf16_t *>(g.w_gate), 4 * d.H, d.H, w.r, 0, own_tiles(tiles_gate(d), w.r) * (d.H >> 5), w.wave, NW, lane);
-                load_pieces(wJ, static_cast<const bf16_t *>(g.w_out), d.V, d.Dj, w.r, 0, own_tiles(tiles_joiner(d), w.r) * (d.Dj >> 5), w.wave, NW, lane);
-            }
+            const int pH = F32 ? f32_pieces(d.H) : d.H >> 5;
+            if (l.wG < 0) wG = nullptr;
+            else load_frags(wG, g.w_gate, pH, 0, own_tiles(tiles_gate(d), w.r) * pH, w.r, w.wave, NW, lane);
+            load_rows<F32>(wJ, g.w_out, d.V, d.Dj, own_tiles(tiles_joiner(d), w.r), w.r, w.wave, NW, lane);
+            if (F32) load_rows<F32>(wP, g.w_proj, d.Dj, d.H, own_tiles(tiles_proj(d), w.r), w.r, w.wave, NW, lane);
             if (tid < w.nu) sh.utt[tid] = g.order[w.u_base + tid];
             __syncthreads();
             for (int i = w.r, k = 0; i < w.nu; i += XR_WGS, ++k)
@@ -1212,8 +1221,7 @@ k_xcd_decode(XcdArgs args) {
                 xcd_arrive(bar, live);
                 if (!F32 && (SMAX > 5 || w.r < w.n_act || round == 1)) {   // (only who has utterances of its own, or hypotheses, writes over the slice)
                     const XcdArgs &g = xcd_args();
-                    const int own = own_tiles(g.d.Dj >> 4, w.r);
-                    load_pieces(wP, static_cast<const bf16_t *>(g.w_proj), g.d.Dj, g.d.H, w.r, 0, own * (g.d.H >> 5), w.wave, NW, lane);
+                    load_rows<false>(wP, g.w_proj, g.d.Dj, g.d.H, own_tiles(g.d.Dj >> 4, w.r), w.r, w.wave, NW, lane);
                 }
                 const int sum = xcd_wait(bar, sh.sum);
                 if (sum < 0) { status = XR_STUCK; break; }
@@ -1238,8 +1246,7 @@ k_xcd_decode(XcdArgs args) {
                     {
                         const XcdArgs &g = xcd_args();
                         const int all = own_tiles(tiles_gate(g.d), w.r) * (g.d.H >> 5);
-                        load_pieces(wG, static_cast<const bf16_t *>(g.w_gate), 4 * g.d.H, g.d.H, w.r, 0, min(all, (XR_PROJ_BYTES(NW) + 1023) / 1024),
-                                    w.wave, NW, lane);
+                        load_frags(wG, g.w_gate, g.d.H >> 5, 0, min(all, (XR_PROJ_BYTES(NW) + 1023) / 1024), w.r, w.wave, NW, lane);
                     }
                     if (xcd_wait(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                 }

@@ -1407,3 +1407,25 @@ def test_one_launch_with_a_trie_that_one_list_of_nodes_fits():
     one, two = (_gpu_decode(shape, model, offsets, enc, 2, 6, max_rounds_per_segment=cap, debug=dbg) for dbg in (0, 65536))
     assert [[h[0] for h in u] for u in one[0]] == [[h[0] for h in u] for u in two[0]]
     assert one[1]["joiner_calls"] == two[1]["joiner_calls"]
+
+
+@pytest.mark.parametrize("dtype,S", [("bf16", 3), ("f32", 3), ("bf16", 8)])
+def test_output_and_projection_weights_may_change_between_decodes(dtype, S):
+    """The output matrix and the projection are read when a batch is decoded: a change in place is seen by the next decode."""
+    import dataclasses
+    import torch
+    shape = dataclasses.replace(small_bf16_shape(n_utts=3, vocab=96, d=128, hidden=128), dtype=dtype)
+    model, offsets, enc = build_case(shape, lengths=np.array([9, 17, 4]))
+    other = make_model(dataclasses.replace(shape, index=8))
+    changed = dict(model, w_out=other["w_out"], w_proj=other["w_proj"])
+    want, _ = _gpu_decode(shape, changed, offsets, enc, 4, S)
+    tbs = make_tbs(shape, model, offsets, 4, S)
+    frames = tbs.upload_frames(enc)
+    before = tbs.decode(frames, offsets)
+    assert _one_launch(tbs)
+    for name in ("w_out", "w_proj"):
+        tbs.t[name].copy_(torch.from_numpy(changed[name]))
+    torch.cuda.synchronize()
+    after = tbs.decode(frames, offsets)
+    tbs.close()
+    assert after == want and after != before
