@@ -13,9 +13,18 @@
 
 // ------------------------------------------------------------------ batch init
 __global__ void k_init_batch(Dims d, BView B, AView A0, AView A1, RowView rv, int2 *nodes, float *pool_p,
-                             float *pool_h, float *pool_c, const float *pred_init, long pool_rows) {
+                             float *pool_h, float *pool_c, const float *pred_init, long pool_rows, const int *told, int *fig,
+                             int *order, int *utt_T, int *utt_off, int *live_sum) {
     int u = blockIdx.x;
     int tid = threadIdx.x;
+    // the batch's figures, order of utterances, lengths and first frames from the host's memory
+    if (tid < TBS_FIG_SIZE) fig[u * TBS_FIG_SIZE + tid] = told[u * TBS_FIG_SIZE + tid];
+    const int *rest = told + d.U * TBS_FIG_SIZE;
+    if (tid == 64) order[u] = rest[u];
+    if (tid == 65) utt_T[u] = rest[d.U + u];
+    if (tid == 66) utt_off[u] = rest[2 * d.U + u];
+    if (tid == 67 && u == d.U - 1) utt_off[d.U] = rest[3 * d.U];
+    if (tid < 2 && u == 0) live_sum[tid] = 0;
     // B = [([], 1, InitPredictor(), Null)]: the empty sequence is trie node 0;
     // its predictor state sits in the "previous segment" arena (parity 1).
     int slot = tbs_slot_id(u, 1, 0, 0, d.R, d.N);
@@ -55,9 +64,9 @@ __global__ void k_init_batch(Dims d, BView B, AView A0, AView A1, RowView rv, in
 
 hipError_t launch_init_batch(hipStream_t st, const Dims &d, BView B, AView A0, AView A1, RowView rv, int2 *nodes,
                              float *pool_p, float *pool_h, float *pool_c, const float *pred_init,
-                             long pool_rows) {
+                             long pool_rows, const int *told, int *fig, int *order, int *utt_T, int *utt_off, int *live_sum) {
     hipLaunchKernelGGL(k_init_batch, dim3(d.U), dim3(256), 0, st, d, B, A0, A1, rv, nodes, pool_p, pool_h, pool_c,
-                       pred_init, pool_rows);
+                       pred_init, pool_rows, told, fig, order, utt_T, utt_off, live_sum);
     return hipGetLastError();
 }
 

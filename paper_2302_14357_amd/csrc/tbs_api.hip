@@ -18,6 +18,11 @@
 
 namespace {
 
+// Results up to this many bytes are written straight into pinned memory (four copies into pageable memory behind the kernel:
+// tbs_result 63 -> 20 us for the small fp32 configuration, 93 -> 42 for 64 utterances, 330 KB).  Larger ones keep to the copies,
+// so that a context's pinned memory stays small.
+#define TBS_RES_PINNED (512 * 1024)
+
 enum State { ST_INIT = 0, ST_BEGUN, ST_READY, ST_JOINED, ST_EXPANDED, ST_SELECTED };
 
 struct EventPair {
@@ -53,6 +58,7 @@ struct tbs_ctx {
     bool streaming;
     std::vector<int> s_fill;   // frames buffered per utterance (they start at the front of its buffer)
     int *h_desc;               // pinned: descriptors of the frame copies and of a decode step
+    char *pinned;              // all of the context's pinned memory (see tbs_init)
     int *d_desc;
     int *h_counts;      // pinned host mirror of rv.counts
     int *h_counts_dev;  // device view of the same memory
@@ -106,10 +112,13 @@ struct tbs_ctx {
     void *htop;
     float *gates;
 
-    // results
+    int *h_begin, *h_begin_dev;   // pinned: what tbs_begin tells the kernels of a batch's utterances (see launch_init_batch)
+
+    // results; small ones straight in pinned memory (h_res: the host's view, else null)
     int *res_count, *res_len, *res_tok;
     double *res_logs;
     int res_max_len;
+    char *h_res, *h_res_dev;
 
     // counters
     int64_t n_frames, n_launches;   // (joiner invocations and frames joined are counted on the device)
@@ -272,10 +281,7 @@ void tbs_free(tbs_ctx *c) {
     (void)hipSetDevice(c->cfg.device_id);
     (void)hipStreamSynchronize(c->stream);
     for (void *p : c->allocs) (void)hipFree(p);
-    if (c->h_counts) (void)hipHostFree(c->h_counts);
-    if (c->h_live) (void)hipHostFree(c->h_live);
-    if (c->h_xcd) (void)hipHostFree(c->h_xcd);
-    if (c->h_desc) (void)hipHostFree(c->h_desc);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     for (auto &e : c->events) {
         (void)hipEventDestroy(e.a);
         (void)hipEventDestroy(e.b);
@@ -312,9 +318,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->stream = (hipStream_t)cfg->stream;
     c->state = ST_INIT;
     c->last_hip = 0;
-    c->h_counts = nullptr;
-    c->h_live = nullptr;
-    c->h_xcd = nullptr;
+    c->pinned = c->h_res = c->h_res_dev = nullptr;
     c->xcd_ready = c->xcd = false;
     c->x_seq = 0;
     c->fixed = c->trie_full = false;
@@ -476,11 +480,15 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
             p += (n[i] + 255) & ~255l;
         }
     }
-    rc |= dev_alloc(c, &c->res_count, U);
-    rc |= dev_alloc(c, &c->res_len, UN);
-    rc |= dev_alloc(c, &c->res_logs, UN);
     c->res_max_len = cfg->max_result_len > 0 ? cfg->max_result_len : 256;
-    rc |= dev_alloc(c, &c->res_tok, (size_t)UN * c->res_max_len);
+    const size_t res_bytes = (size_t)UN * (sizeof(double) + sizeof(int) * (1 + (size_t)c->res_max_len)) + sizeof(int) * U;
+    const bool res_pinned = res_bytes <= TBS_RES_PINNED;
+    if (!res_pinned) {
+        rc |= dev_alloc(c, &c->res_count, U);
+        rc |= dev_alloc(c, &c->res_len, UN);
+        rc |= dev_alloc(c, &c->res_logs, UN);
+        rc |= dev_alloc(c, &c->res_tok, (size_t)UN * c->res_max_len);
+    }
     if (rc) {
         tbs_free(c);
         return TBS_ENOMEM;
@@ -492,44 +500,39 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         rc |= dev_alloc(c, &q, (size_t)U * d.S * d.Dj * elem_bytes(c));
         c->stream_enc = p;
         c->stream_tmp = q;
-        if (rc == 0 && hipHostMalloc((void **)&c->h_desc, (11 * (size_t)U + 1) * sizeof(int), hipHostMallocDefault) != hipSuccess) rc = 1;
         if (rc) {
             tbs_free(c);
             return TBS_ENOMEM;
         }
     }
-    e = hipHostMalloc((void **)&c->h_counts, TBS_CNT_SIZE * sizeof(int), hipHostMallocMapped);
-    if (e != hipSuccess) {
-        c->last_hip = (int)e;
-        tbs_free(c);
-        return TBS_ENOMEM;
-    }
-    memset(c->h_counts, 0, TBS_CNT_SIZE * sizeof(int));
-    e = hipHostMalloc((void **)&c->h_live, 2 * (size_t)U * sizeof(int), hipHostMallocMapped);
-    if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&c->h_live_dev, c->h_live, 0);
-    if (e != hipSuccess) {
-        c->last_hip = (int)e;
-        tbs_free(c);
-        return TBS_ENOMEM;
-    }
-    memset(c->h_live, 0, 2 * (size_t)U * sizeof(int));
-    if (c->xcd_ready) {
-        const size_t ints = 4 * XR_XCDS * XR_WGS + XR_XCDS * XR_SEGS;
-        e = hipHostMalloc((void **)&c->h_xcd, ints * sizeof(int), hipHostMallocMapped);
-        if (e == hipSuccess) e = hipHostGetDevicePointer((void **)&c->h_xcd_dev, c->h_xcd, 0);
-        if (e == hipSuccess) e = hipMemsetAsync(c->x_ctl, 0, 2 * sizeof(XcdCtl), c->stream);
+    // Pinned memory, in one allocation: the row lists' counts, the slot layout's words, a batch's figures, a push's
+    // descriptors, the ends of a launch over whole segments, small results.
+    {
+        const size_t ints[5] = {TBS_CNT_SIZE, 2 * (size_t)U, (3 + TBS_FIG_SIZE) * (size_t)U + 1,
+                                cfg->stream_buffer_frames > 0 ? 11 * (size_t)U + 1 : 0,
+                                c->xcd_ready ? (size_t)(4 * XR_XCDS * XR_WGS + XR_XCDS * XR_SEGS) : 0};
+        int **host[5] = {&c->h_counts, &c->h_live, &c->h_begin, &c->h_desc, &c->h_xcd};
+        int *none = nullptr, **dev[5] = {&c->h_counts_dev, &c->h_live_dev, &c->h_begin_dev, &none, &c->h_xcd_dev};
+        size_t at[6] = {0};
+        for (int i = 0; i < 5; ++i) at[i + 1] = at[i] + (ints[i] * sizeof(int) + 255) / 256 * 256;
+        void *view = nullptr;
+        e = hipHostMalloc((void **)&c->pinned, at[5] + (res_pinned ? res_bytes : 0), hipHostMallocMapped);
+        if (e == hipSuccess) e = hipHostGetDevicePointer(&view, c->pinned, 0);
+        if (e == hipSuccess && c->xcd_ready) e = hipMemsetAsync(c->x_ctl, 0, 2 * sizeof(XcdCtl), c->stream);
         if (e != hipSuccess) {
             c->last_hip = (int)e;
             tbs_free(c);
             return TBS_ENOMEM;
         }
-        memset(c->h_xcd, 0, ints * sizeof(int));
-    }
-    e = hipHostGetDevicePointer((void **)&c->h_counts_dev, c->h_counts, 0);
-    if (e != hipSuccess) {
-        c->last_hip = (int)e;
-        tbs_free(c);
-        return TBS_EHIP;
+        memset(c->pinned, 0, at[5]);
+        for (int i = 0; i < 5; ++i) {
+            *host[i] = reinterpret_cast<int *>(c->pinned + at[i]);
+            *dev[i] = reinterpret_cast<int *>(static_cast<char *>(view) + at[i]);
+        }
+        if (res_pinned) {
+            c->h_res = c->pinned + at[5];
+            c->h_res_dev = static_cast<char *>(view) + at[5];
+        }
     }
     for (int l = 1; l < d.L; ++l) {
         e = launch_concat_weights(c->stream, elem_bytes(c), w->w_ih[l], w->w_hh[l], c->wcat[l], 4 * d.H, d.H, d.H);
@@ -665,17 +668,17 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->cur.U = U;
     c->enc = enc;
     c->max_T = max_T;
-    HIPCHK(c, hipMemcpyAsync(c->utt_T, c->h_T.data(), sizeof(int) * U, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->utt_off, offsets, sizeof(int) * (U + 1), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, launch_init_batch(c->stream, c->cur, c->B, c->A[0], c->A[1], c->rv, c->nodes, c->pool_p, c->pool_h,
-                                c->pool_c, c->w.pred_init, c->pool_rows));
-    HIPCHK(c, hipMemsetAsync(c->live_sum, 0, sizeof(int) * 2, c->stream));
+    // (what an earlier batch left in the stream may still write the words below, or read its figures)
+    HIPCHK(c, hipStreamSynchronize(c->stream));
     memset(c->h_live, 0, 2 * sizeof(int) * (size_t)c->d.U);
     c->fx_calls = c->fx_joined = 0;
     c->fx_nodes = 0;
     // Slot layout: every utterance takes trie nodes from a range of its own, sized in proportion to
     // its length (a stream's utterances, whose lengths are not known, share equally); node 0 is the root.
-    std::vector<int> fig((size_t)U * TBS_FIG_SIZE, 0);
+    int *fig = c->h_begin, *order = fig + (size_t)U * TBS_FIG_SIZE, *T = order + U, *off = T + U;
+    memset(fig, 0, sizeof(int) * (size_t)U * TBS_FIG_SIZE);
+    memcpy(T, c->h_T.data(), sizeof(int) * U);
+    memcpy(off, offsets, sizeof(int) * (U + 1));
     {
         const int S = c->cur.S;
         double weight_all = 0.0;
@@ -698,19 +701,22 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
         std::vector<int> by_length(U);
         for (int u = 0; u < U; ++u) by_length[u] = u;
         std::stable_sort(by_length.begin(), by_length.end(), [&](int a, int b) { return c->h_T[a] > c->h_T[b]; });
+        int n = 0;
         for (int x = 0; x < XR_XCDS; ++x) {
-            c->x_first[x] = (int)fig.size() - U * TBS_FIG_SIZE;
+            c->x_first[x] = n;
             for (int k = 0; k < U; ++k) {
                 const int j = k % XR_XCDS;
-                if (((k / XR_XCDS) % 2 ? XR_XCDS - 1 - j : j) == x) fig.push_back(by_length[k]);
+                if (((k / XR_XCDS) % 2 ? XR_XCDS - 1 - j : j) == x) order[n++] = by_length[k];
             }
         }
         c->x_first[XR_XCDS] = U;
     }
-    HIPCHK(c, hipMemcpyAsync(c->utt_fig, fig.data(), sizeof(int) * (size_t)U * TBS_FIG_SIZE, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipMemcpyAsync(c->x_order, fig.data() + (size_t)U * TBS_FIG_SIZE, sizeof(int) * (size_t)U, hipMemcpyHostToDevice, c->stream));
-    // the host arrays above are read by the copies: finish them before returning
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    // One launch, and no wait behind it: its kernel reads the figures where they are and puts them into device memory.  (Four
+    // copies from pageable memory, a fill and a wait: tbs_begin until the device was idle 35 -> 21 us for the small fp32
+    // configuration.)
+    HIPCHK(c, launch_init_batch(c->stream, c->cur, c->B, c->A[0], c->A[1], c->rv, c->nodes, c->pool_p, c->pool_h,
+                                c->pool_c, c->w.pred_init, c->pool_rows, c->h_begin_dev, c->utt_fig, c->x_order, c->utt_T,
+                                c->utt_off, c->live_sum));
     c->seg = -1;
     c->round = 0;
     c->a_cur = 0;
@@ -1094,13 +1100,24 @@ int tbs_result(tbs_ctx *c, int32_t *tokens, int32_t *lens, double *logscores, in
     const long UN = (long)d.U * d.N;
     if (max_len > c->res_max_len) return TBS_EINVAL;   // the result buffer was sized at tbs_init (max_result_len)
     // (the kernel writes every entry of the four outputs: nothing is cleared beforehand)
-    HIPCHK(c, launch_finalize(c->stream, d, c->B, c->nodes, c->res_count, c->res_len, c->res_logs, c->res_tok,
-                              max_len));
-    HIPCHK(c, hipMemcpyAsync(tokens, c->res_tok, sizeof(int) * UN * max_len, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(lens, c->res_len, sizeof(int) * UN, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(logscores, c->res_logs, sizeof(double) * UN, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipMemcpyAsync(nbest_count, c->res_count, sizeof(int) * d.U, hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (c->h_res) {
+        const size_t at[4] = {0, sizeof(double) * UN, (sizeof(double) + sizeof(int)) * UN, (sizeof(double) + sizeof(int)) * UN + sizeof(int) * d.U};
+        char *v = c->h_res_dev;
+        const char *h = c->h_res;
+        HIPCHK(c, launch_finalize(c->stream, d, c->B, c->nodes, (int *)(v + at[2]), (int *)(v + at[1]), (double *)v, (int *)(v + at[3]), max_len));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+        memcpy(tokens, h + at[3], sizeof(int) * UN * max_len);
+        memcpy(lens, h + at[1], sizeof(int) * UN);
+        memcpy(logscores, h, sizeof(double) * UN);
+        memcpy(nbest_count, h + at[2], sizeof(int) * d.U);
+    } else {
+        HIPCHK(c, launch_finalize(c->stream, d, c->B, c->nodes, c->res_count, c->res_len, c->res_logs, c->res_tok, max_len));
+        HIPCHK(c, hipMemcpyAsync(tokens, c->res_tok, sizeof(int) * UN * max_len, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipMemcpyAsync(lens, c->res_len, sizeof(int) * UN, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipMemcpyAsync(logscores, c->res_logs, sizeof(double) * UN, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipMemcpyAsync(nbest_count, c->res_count, sizeof(int) * d.U, hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipStreamSynchronize(c->stream));
+    }
     for (long i = 0; i < UN; ++i)
         if (lens[i] > max_len) return TBS_EOVERFLOW;   // truncated to max_len tokens; lens keeps the true length
     return TBS_OK;
@@ -1561,6 +1578,7 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
     // decode: every utterance with a whole segment buffered (or, at a flush, with anything
     // buffered) takes one step; utterances advance independently of each other
     std::vector<int> pos(U, 0);
+    bool drained = false;   // the stream holds nothing that reads the caller's frames or the descriptors any more
     for (int step = 0;; ++step) {
         bool any = false;
         for (int u = 0; u < U; ++u) {
@@ -1580,6 +1598,7 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
         for (int u = 0; u < U; ++u) c->h_T[u] = take[u];   // (the slot layout's host bookkeeping reads the step sizes)
         int ran = 0, rc = TBS_OK;   // (both forms wait for the device: the copy above is done by then)
         if (c->xcd && c->prof_kernel < 0) rc = run_segments_xcd(c, 0, 1, &ran);
+        drained = ran > 0;   // (every workgroup of the launch has told its end)
         if (rc == TBS_OK && ran == 0) rc = run_segment(c, 0);
         if (rc) return rc;
         for (int u = 0; u < U; ++u) pos[u] += take[u];
@@ -1601,7 +1620,7 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
         HIPCHK(c, hipMemcpyAsync(c->d_desc, src2, sizeof(int) * 3 * U, hipMemcpyHostToDevice, c->stream));
         HIPCHK(c, launch_stream_copy(c->stream, U, c->stream_tmp, c->stream_enc, c->d_desc, row_bytes));
     }
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (!drained || left) HIPCHK(c, hipStreamSynchronize(c->stream));
     return check_err_flags(c);
 }
 

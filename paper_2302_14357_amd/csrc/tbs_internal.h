@@ -217,9 +217,11 @@ long xcd_frag_bytes(int dtype, int rows, int K);     // and of a weight matrix i
 hipError_t launch_xcd_frags(hipStream_t st, int dtype, const void *w, void *frags, int rows, int K);
 
 // ---- launchers (each enqueues on `st` and returns the HIP status) ----
+// told: pinned, as a batch's [U, TBS_FIG_SIZE] figures, [U] order, [U] lengths and [U + 1] first frames; they go to the others
 hipError_t launch_init_batch(hipStream_t st, const Dims &d, BView B, AView A0, AView A1, RowView rv, int2 *nodes,
                              float *pool_p, float *pool_h, float *pool_c, const float *pred_init,
-                             long pool_rows);
+                             long pool_rows,
+                             const int *told, int *fig, int *order, int *utt_T, int *utt_off, int *live_sum);
 hipError_t launch_segment_begin(hipStream_t st, const Dims &d, int seg, const int *utt_T, BView B,
                                 AView A, RowView rv, float *pool_p, float *pool_h, float *pool_c, long pool_rows,
                                 const FixedView *fx = nullptr);
