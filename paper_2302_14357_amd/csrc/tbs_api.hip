@@ -57,7 +57,7 @@ struct tbs_ctx {
     int stream_cap;
     bool streaming;
     std::vector<int> s_fill;   // frames buffered per utterance (they start at the front of its buffer)
-    int *h_desc;               // pinned: descriptors of the frame copies and of a decode step
+    int *h_desc, *h_desc_dev;  // pinned: descriptors of the frame copies and of a decode step
     char *pinned;              // all of the context's pinned memory (see tbs_init)
     int *d_desc;
     int *h_counts;      // pinned host mirror of rv.counts
@@ -509,10 +509,10 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     // descriptors, the ends of a launch over whole segments, small results.
     {
         const size_t ints[5] = {TBS_CNT_SIZE, 2 * (size_t)U, (3 + TBS_FIG_SIZE) * (size_t)U + 1,
-                                cfg->stream_buffer_frames > 0 ? 11 * (size_t)U + 1 : 0,
+                                cfg->stream_buffer_frames > 0 ? 17 * (size_t)U + 1 : 0,
                                 c->xcd_ready ? (size_t)(4 * XR_XCDS * XR_WGS + XR_XCDS * XR_SEGS) : 0};
         int **host[5] = {&c->h_counts, &c->h_live, &c->h_begin, &c->h_desc, &c->h_xcd};
-        int *none = nullptr, **dev[5] = {&c->h_counts_dev, &c->h_live_dev, &c->h_begin_dev, &none, &c->h_xcd_dev};
+        int **dev[5] = {&c->h_counts_dev, &c->h_live_dev, &c->h_begin_dev, &c->h_desc_dev, &c->h_xcd_dev};
         size_t at[6] = {0};
         for (int i = 0; i < 5; ++i) at[i + 1] = at[i] + (ints[i] * sizeof(int) + 255) / 256 * 256;
         void *view = nullptr;
@@ -1390,7 +1390,8 @@ static std::mutex g_xcd_mutex[TBS_MAX_DEVICES];
 
 // Segments [seg0, seg1) in one launch or several.  *ran is the number of segments that were decoded: fewer, with TBS_OK,
 // where the GPU was not free for it; the rest has to run in the slot layout, which finds everything in its place.
-static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
+// push (or null): its figures and frames go with the launch (segment 0 alone, see XcdArgs).
+static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void *push = nullptr, long row_bytes = 0) {
     *ran = 0;
     std::unique_lock<std::mutex> alone(g_xcd_mutex[c->cfg.device_id], std::try_to_lock);
     if (!alone.owns_lock()) return TBS_OK;
@@ -1409,6 +1410,13 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran) {
     g.order = c->x_order;
     g.utt_T = c->utt_T;
     g.utt_off = c->utt_off;
+    if (push) {
+        g.push_rows = reinterpret_cast<const int4 *>(c->h_desc_dev);
+        g.push_step = reinterpret_cast<const int2 *>(c->h_desc_dev + 4 * c->d.U);
+        g.push_from = static_cast<const uint4 *>(push);
+        g.push_to = static_cast<uint4 *>(c->stream_enc);
+        g.push_units = (int)(row_bytes / 16);
+    }
     const bool f32 = c->cfg.dtype == 0;
     g.enc = c->enc;
     g.w_out = c->w.w_out;
@@ -1541,6 +1549,12 @@ static int run_segment(tbs_ctx *c, int32_t seg_index) {
     }
 }
 
+// May the frames of a push go with the launch?  Its copies are 16 bytes wide (rows are in whole pieces of that), and one workgroup appends an utterance's: beyond
+// 64 KB (a few us of one CU) the whole chip does it sooner.
+static bool push_fused_ok(const void *enc, long row_bytes, int most) {
+    return (reinterpret_cast<uintptr_t>(enc) & 15) == 0 && most * row_bytes <= 64 * 1024;
+}
+
 int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, int32_t flush) {
     if (!c || !frame_offsets) return TBS_EINVAL;
     if (!c->streaming || c->state == ST_INIT) return TBS_ESTATE;
@@ -1561,17 +1575,20 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
     // The first area mirrors the device's: step sizes, first frames, then the descriptors of the copy that
     // appends the new frames, so that the first decode step of a push needs one copy for all three.
     const int Um = c->d.U;
-    int *take = c->h_desc, *first = take + Um;                           // a decode step
+    // (What goes with a launch over the whole segment lies in front of them.)
+    int *take = c->h_desc + 6 * Um, *first = take + Um;                  // a decode step
     int *src = first + Um + 1, *dst = src + U, *cnt = src + 2 * U;       // appending the new frames
-    int *src1 = c->h_desc + 5 * Um + 1, *dst1 = src1 + U, *cnt1 = src1 + 2 * U;   // leftovers to the spare area
-    int *src2 = c->h_desc + 8 * Um + 1, *dst2 = src2 + U, *cnt2 = src2 + 2 * U;   // and back to the front
+    int *src1 = take + 5 * Um + 1, *dst1 = src1 + U, *cnt1 = src1 + 2 * U;   // leftovers to the spare area
+    int *src2 = take + 8 * Um + 1, *dst2 = src2 + U, *cnt2 = src2 + 2 * U;   // and back to the front
     const bool append = frame_offsets[U] > 0;
+    int most = 0;
     if (append) {
         for (int u = 0; u < U; ++u) {
             src[u] = frame_offsets[u];
             dst[u] = u * cap + c->s_fill[u];
             cnt[u] = frame_offsets[u + 1] - frame_offsets[u];
             c->s_fill[u] += cnt[u];
+            most = std::max(most, cnt[u]);
         }
         c->n_frames += frame_offsets[U];
     }
@@ -1587,17 +1604,30 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
             first[u] = u * cap + pos[u];
             any = any || take[u] > 0;
         }
-        if (step == 0 && append) {
+        int ran = 0, rc = TBS_OK;   // (both forms wait for the device: what the host wrote has been read by then)
+        const bool fused = step == 0 && append && any && c->xcd && c->prof_kernel < 0 && push_fused_ok(enc_proj, row_bytes, most);
+        if (fused) {
+            const int *order = c->h_begin + (size_t)U * TBS_FIG_SIZE;
+            int4 *rows = reinterpret_cast<int4 *>(c->h_desc);
+            int2 *steps = reinterpret_cast<int2 *>(c->h_desc + 4 * Um);
+            for (int i = 0; i < U; ++i) {
+                const int u = order[i];
+                rows[i] = make_int4(src[u], dst[u], cnt[u], 0);
+                steps[i] = make_int2(take[u], first[u]);
+            }
+            for (int u = 0; u < U; ++u) c->h_T[u] = take[u];
+            if ((rc = run_segments_xcd(c, 0, 1, &ran, enc_proj, row_bytes))) return rc;
+        }
+        if (step == 0 && append && ran == 0) {
             HIPCHK(c, hipMemcpyAsync(c->utt_T, take, sizeof(int) * (2 * (size_t)Um + 1 + 3 * (size_t)U), hipMemcpyHostToDevice,
                                      c->stream));
             HIPCHK(c, launch_stream_copy(c->stream, U, enc_proj, c->stream_enc, c->d_desc, row_bytes));
-        } else if (any) {
+        } else if (any && ran == 0) {
             HIPCHK(c, hipMemcpyAsync(c->utt_T, take, sizeof(int) * (2 * (size_t)Um), hipMemcpyHostToDevice, c->stream));
         }
         if (!any) break;
         for (int u = 0; u < U; ++u) c->h_T[u] = take[u];   // (the slot layout's host bookkeeping reads the step sizes)
-        int ran = 0, rc = TBS_OK;   // (both forms wait for the device: the copy above is done by then)
-        if (c->xcd && c->prof_kernel < 0) rc = run_segments_xcd(c, 0, 1, &ran);
+        if (!fused && c->xcd && c->prof_kernel < 0) rc = run_segments_xcd(c, 0, 1, &ran);
         drained = ran > 0;   // (every workgroup of the launch has told its end)
         if (rc == TBS_OK && ran == 0) rc = run_segment(c, 0);
         if (rc) return rc;

@@ -184,7 +184,15 @@ struct XcdArgs {
     int expect;             // XCDs that have to be complete before anything is done
     int first[XR_XCDS + 1]; // the XCDs' parts of `order` [U]: utterances in falling length
     int tile0[XR_XCDS];     // and of amat, in tiles of 16 rows
-    const int *order, *utt_T, *utt_off;
+    const int *order;
+    int *utt_T, *utt_off;
+    // a push of a stream (pinned, by place in `order`; null: none): frames to decode and the first of them, and rows to append
+    // first: source row, destination row, how many, of push_units pieces of 16 bytes each
+    const int2 *push_step;
+    const int4 *push_rows;
+    const uint4 *push_from;
+    uint4 *push_to;
+    int push_units;
     const void *enc;        // frames; the caller's output and projection weights, and the recurrent gate weights
                             // (rows interleaved, see LstmEp) in the pieces the products read (launch_xcd_frags)
     const void *w_out, *w_gate, *w_proj;

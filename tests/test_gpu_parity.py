@@ -1294,6 +1294,32 @@ def test_streams_in_one_launch_a_step(debug):
     tbs.close()
 
 
+@pytest.mark.parametrize("U,piece,offset,debug", [(300, 4, 0, 0), (20, 130, 0, 0), (20, 7, 2, 0), (9, 5, 0, 0), (20, 7, 0, 131072)])
+def test_pushes_whose_frames_go_with_the_launch(U, piece, offset, debug):
+    """Frames appended inside the launch (two utterances of a workgroup too), or by a kernel in front of it: pieces of more
+    than 64 KB, frames that begin off 16 bytes, a launch that gives up.  Every utterance brings another number of frames."""
+    import torch
+    N, S = 3, 3
+    shape = small_bf16_shape(n_utts=U, vocab=40, d=256, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=np.array([piece + 2 + (i * 7) % 11 for i in range(U)]))
+    want, _ = _gpu_decode(shape, model, offsets, enc, N, S, debug=65536)
+    tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=piece + S, debug=debug)
+    tbs.stream_begin(U)
+    at, c = offsets[:-1].copy(), 0
+    while (at < offsets[1:]).any():
+        n = np.minimum([piece - (u + c) % 3 for u in range(U)], offsets[1:] - at)
+        rows = tbs.upload_frames(np.concatenate([enc[at[u]:at[u] + n[u]] for u in range(U)]))
+        space = torch.empty(rows.numel() + offset, dtype=rows.dtype, device=rows.device)
+        space[offset:].copy_(rows.reshape(-1))
+        torch.cuda.synchronize()
+        at, c = at + n, c + 1
+        tbs.push_segment(space[offset:], np.concatenate([[0], np.cumsum(n)]), flush=bool((at == offsets[1:]).all()))
+    assert _one_launch(tbs)
+    got = tbs.result()
+    tbs.close()
+    assert got == want
+
+
 def test_contexts_that_decode_at_the_same_time():
     """Two threads, each with a context on a stream of its own: whoever finds the other's launch under way takes four kernels a
     round; both get the results they get alone."""
