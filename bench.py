@@ -82,7 +82,8 @@ def quick_decode(workload, steps=2, warmup=1, seg=0, beam=0, debug=0):
         path = t.path()
         return {"workload": f"{shape.name}-like: {U} utterances, {frames} frames, Dj={shape.d_joint}, V={shape.vocab}, "
                             f"LSTM {shape.pred_layers}x{shape.pred_hidden}, N={N}, S={S}",
-                "kernels": ("four kernels a round, hypotheses in fixed places" if path["fixed_places"] else
+                "kernels": ("whole segments in one launch" if t.L.tbs_path(t.ctx) & 4 else
+                            "four kernels a round, hypotheses in fixed places" if path["fixed_places"] else
                             "row lists, kernels sized by the round's rows") +
                            ("; joiner GEMM keeps row softmax sums and best tokens, no logits" if path["one_frame_no_logits"] else ""),
                 "frames_per_sec": frames / (ms / 1e3), "ms_per_step": ms, "steps": steps,
@@ -247,6 +248,7 @@ def main():
     ms_per_step = dt / args.steps * 1e3
     value = frames / (ms_per_step / 1e3)
     stats = tbs.stats()
+    one_launch = bool(tbs.L.tbs_path(tbs.ctx) & 4)
 
     # ---- per-kernel timing with HIP events on the library's stream (separate, untimed passes)
     kernels = {}
@@ -293,7 +295,10 @@ def main():
                     "bound": d["bound"], "achieved": d["achieved"], "peak": d["peak"], "unit": d["unit"],
                     "frac": d["frac"], "traffic": read_traffic(dom, args.workload), "avg_us": d["avg_us"],
                     "launches": d["launches"],
-                    "note": "achieved = summed algorithmic work / summed HIP-event durations over every launch of "
+                    "note": ("the timed decodes run whole segments in one launch; while a kernel family is timed the same "
+                             "arithmetic runs as four kernels a round or more, and these figures are theirs; "
+                             if one_launch else "") +
+                            "achieved = summed algorithmic work / summed HIP-event durations over every launch of "
                             "the kernel in one decode; an event pair reads event_pair_around_empty_kernel_us around "
                             "a kernel that does nothing, so microsecond kernels read long (profiles/ has the "
                             "kernels' own durations); a problem of at most 1 GFLOP per launch is latency-bound: "

@@ -216,10 +216,11 @@ int tbs_stats(const tbs_ctx *ctx, int64_t *joiner_calls, int64_t *joined_frames,
 /* Which forms of the kernels the batch begun last runs in (they give the same results; tests and
  * benchmarks use this to say which one they exercised): bit 0 = every hypothesis in a fixed place,
  * four kernels a round; bit 1 = seg_s = 1 without logits (the standard search of Eq. 1 with the
- * row softmax sums and best tokens made in the joiner GEMM); bit 2 (with bit 0) = tbs_decode and tbs_push_segment run whole
- * segments in one launch that takes every CU (bf16 models of one LSTM layer whose weights fit the LDS of an XCD's CUs; while
- * another context's launch is under way on the GPU, or where its workgroups do not get onto the CUs together within
- * 5 ms, four kernels a round instead).  Negative: an error code. */
+ * row softmax sums and best tokens made in the joiner GEMM); bit 2 = tbs_decode and tbs_push_segment run whole
+ * segments in one launch that takes every CU (models of one LSTM layer whose weights fit the LDS of an XCD's CUs, up to 512
+ * utterances; bf16 with segments of up to 64 frames, fp32 up to 5; without bit 0 not streams.  While another context's launch is
+ * under way on the GPU, where its workgroups do not get onto the CUs together within 5 ms, and while a kernel family is
+ * timed, the form of bits 0 and 1 instead).  Negative: an error code. */
 int tbs_path(const tbs_ctx *ctx);
 
 /* ---- inspection, for tests ---- */

@@ -8,7 +8,11 @@
 // (640 x 2560 and 512 x 1024 bf16 are 132 KB a CU); activations, logits and descriptors travel
 // through the L2 that the XCD's CUs share, and a step ends with a barrier of those 32 workgroups alone,
 // a counter in that L2: 0.7-1.0 us, where a barrier of the whole chip took 10 us (its release writes the L2
-// back to memory) and a kernel boundary takes 3.5 us.
+// back to memory) and a kernel boundary takes 3.5 us.  Measured, ms per decode, four kernels a round (row lists for S > 5) and
+// in one launch: one utterance 10.2 and 4.9, 64 utterances 17.4 and 10.2 (S = 1 28.3 and 12.9, S = 20 21.2 and 14.5), 200
+// utterances 24.6 and 15.3, 16 utterances fp32 20.4 and 12.5.  What bounds a round now is the expansion and the select step (one
+// wave's chain of instructions per hypothesis, 6.5 of 19 us), the barriers (5 us with the wait for the last CU) and what the
+// products read from LDS and L2.
 //
 // What one CU writes and another of the XCD reads goes out by ordinary stores (they go through the L1 to the L2; the
 // barrier waits for their acknowledgement) and comes in by loads of device scope (`fresh` below), which
