@@ -26,6 +26,7 @@
 #pragma once
 #include "expand_device.h"
 #include "select_device.h"
+#include "xcd_barrier.h"
 #include <algorithm>
 #include <type_traits>
 
@@ -57,12 +58,12 @@ __device__ __forceinline__ float4 as_float4(const uintx4 &v) {
 
 // Barrier of the XCD's workgroups, in two halves: every wave waits for its stores (they are in the L2 then) and one thread
 // counts the workgroup in; later that thread waits for the others.  What is asked for between the halves is on its way
-// meanwhile.  `live` is added up over the workgroups: the result is the sum over those of this barrier, or -1 if
-// the others did not come (bounded: nobody here takes anywhere near that long).
+// meanwhile.  At the barrier that ends a round (LIVE) `live` is added up over the workgroups and the wait returns the sum; at the
+// others it returns 0; -1 if the others did not come (bounded: nobody here takes anywhere near that long).
 struct XcdBarrier {
     u64 *word;        // low half: arrivals, high half: sum of live, both since the launch began
     unsigned due;     // arrivals that end the coming barrier
-    unsigned seen;    // sum of live up to the last one
+    unsigned seen;    // sum of live up to the last one that ended a round
 };
 __device__ __forceinline__ void xcd_arrive(XcdBarrier &b, int live) {
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -71,19 +72,14 @@ __device__ __forceinline__ void xcd_arrive(XcdBarrier &b, int live) {
     if (threadIdx.x == 0)
         __hip_atomic_fetch_add(b.word, 1ull | ((u64)(unsigned)live << 32), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
+template <bool LIVE>
 __device__ __forceinline__ int xcd_wait(XcdBarrier &b, int &s_sum) {
     if (threadIdx.x == 0) {
         unsigned spin = 0;
         u64 t0 = 0;
         int sum = 0;
-        while (true) {
-            const u64 v = __hip_atomic_load(b.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((int)((unsigned)v - b.due) >= 0) {
-                // (a workgroup that is past this barrier already may have counted itself into the next one, but adds to
-                // `live` only in the barrier behind a round, which no one passes without this workgroup)
-                sum = (int)((unsigned)(v >> 32) - b.seen);
-                break;
-            }
+        while ((sum = xcd_barrier_read(__hip_atomic_load(b.word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), b.due, b.seen, LIVE)) ==
+               XR_NOT_YET) {
             if ((++spin & 1023u) == 0) {
                 const u64 t = wall_clock64();
                 if (t0 == 0) t0 = t;
@@ -98,12 +94,12 @@ __device__ __forceinline__ int xcd_wait(XcdBarrier &b, int &s_sum) {
     __syncthreads();
     const int sum = __builtin_amdgcn_readfirstlane(s_sum);
     asm volatile("" ::: "memory");
-    if (sum > 0) b.seen += (unsigned)sum;
+    if (LIVE && sum > 0) b.seen += (unsigned)sum;
     return sum;
 }
-__device__ __forceinline__ int xcd_barrier(XcdBarrier &b, int live, int &s_sum) {
-    xcd_arrive(b, live);
-    return xcd_wait(b, s_sum);
+__device__ __forceinline__ int xcd_barrier(XcdBarrier &b, int &s_sum) {
+    xcd_arrive(b, 0);
+    return xcd_wait<false>(b, s_sum);
 }
 
 // ------------------------------------------------------------------ arithmetic shared with the kernels of the slot layout
@@ -887,7 +883,7 @@ __device__ __forceinline__ int xcd_project(const XcdPlace &w, XcdShared &sh, Xcd
         item(w.tid);
         left = frames();
     }
-    const int sum = xcd_wait(bar, sh.sum);
+    const int sum = xcd_wait<false>(bar, sh.sum);
     if (sum < 0) return sum;
     if (own == 0) return 0;
     for (int rt0 = 0; rt0 < ptiles; rt0 += per) {
@@ -1222,9 +1218,9 @@ k_xcd_decode(XcdArgs args) {
                 if (w.n_act == 0) break;   // (the same for the whole XCD; utterances come in falling length, or there is one step)
             }
             xcd_head<NT>(w, sh, reinterpret_cast<double *>(scratch));
-            if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+            if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
             xcd_carry<NT, SMAX, F32>(w, sh);
-            if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+            if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
             int a = 0, round = 0;
             while (true) {   // while Length(A) > 0
                 if (round + 1 > R) { status = XR_ROUNDS; break; }
@@ -1235,11 +1231,11 @@ k_xcd_decode(XcdArgs args) {
                     });
                 else
                     by_chunks(Dj, [&](auto c) { xcd_joiner<NT, c.value>(w, wJ); });
-                if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+                if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                 int live;
                 if constexpr (SMAX > 5) {
                     xcd_expand_long<NT, NV4, SMAX>(w, sh, scratch, a);
-                    if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+                    if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                     live = xcd_select_long<NT, SMAX>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
                 } else {
                     live = xcd_round<NT, NV4, SMAX, FEW>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
@@ -1250,7 +1246,7 @@ k_xcd_decode(XcdArgs args) {
                     const XcdArgs &g = xcd_args();
                     load_rows<false>(wP, g.w_proj, g.d.Dj, g.d.H, own_tiles(g.d.Dj >> 4, w.r), w.r, w.wave, NW, lane);
                 }
-                const int sum = xcd_wait(bar, sh.sum);
+                const int sum = xcd_wait<true>(bar, sh.sum);
                 if (sum < 0) { status = XR_STUCK; break; }
                 if (sum >= XR_FULL_TRIE) { status = XR_TRIE; break; }
                 if (sum == 0) break;
@@ -1258,11 +1254,11 @@ k_xcd_decode(XcdArgs args) {
                     by_chunks_f32(Hh, [&](auto c) {
                         xcd_gates_f32<NT, c.value>(w, reinterpret_cast<const float4 *>(wG), reinterpret_cast<float4 *>(scratch), at_once);
                     });
-                    if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+                    if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                     by_chunks_f32(Hh, [&](auto c) {
                         xcd_project_f32<NT, c.value>(w, sh, reinterpret_cast<const float4 *>(wP), reinterpret_cast<float4 *>(scratch), at_once);
                     });
-                    if (xcd_barrier(bar, 0, sh.sum) < 0) { status = XR_STUCK; break; }
+                    if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                 } else {
                     by_chunks(Hh, [&](auto c) { xcd_gates<NT, c.value>(w, wG); });
                     xcd_arrive(bar, 0);
@@ -1275,7 +1271,7 @@ k_xcd_decode(XcdArgs args) {
                         const int all = own_tiles(tiles_gate(g.d), w.r) * (g.d.H >> 5);
                         load_frags(wG, g.w_gate, g.d.H >> 5, 0, min(all, (XR_PROJ_BYTES(NW) + 1023) / 1024), w.r, w.wave, NW, lane);
                     }
-                    if (xcd_wait(bar, sh.sum) < 0) { status = XR_STUCK; break; }
+                    if (xcd_wait<false>(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                 }
             }
             if (w.r == 0 && tid == 0) store_host(args.host_rounds + w.x * XR_SEGS + (seg - seg0), round);

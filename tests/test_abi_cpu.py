@@ -91,3 +91,51 @@ def test_binding_has_no_oracle_or_cpu_path():
             if f.endswith((".py", ".hip", ".h", ".cpp")):
                 text = open(os.path.join(dirpath, f)).read()
                 assert "import oracle" not in text and "from oracle" not in text and "liborc" not in text, f
+
+
+def _barrier_runs(read, groups, live, ahead, behind):
+    """All interleavings of `groups` workgroups on one XCD that run rounds of barriers: `ahead` of them, the one that ends the
+    round and carries live[round][workgroup], `behind` more; a round whose sum is 0 is the last.  read(word, due, seen, ends):
+    what the kernel makes of the word.  Yields what each workgroup got, by round, at every end of a run."""
+    per = ahead + 1 + behind
+    # a workgroup: barriers passed, has it arrived at the coming one, sum seen, sums by round (or None: it has left)
+    first = (0, 0, tuple((0, False, 0, ()) for _ in range(groups)))
+    stack, known, ends = [first], {first}, set()
+    while stack:
+        low, high, wgs = stack.pop()
+        moved = False
+        for i, (passed, there, seen, sums) in enumerate(wgs):
+            rnd, step = divmod(passed, per)
+            if rnd == len(live) or (sums and sums[-1] == 0):
+                continue
+            if not there:
+                add = live[rnd][i] if step == ahead else 0
+                after = (low + 1, (high + add) & 0xffffffff, (passed, True, seen, sums))
+            else:
+                got = read(low | high << 32, groups * (passed + 1), seen, step == ahead)
+                if got == -2:
+                    continue
+                after = (low, high, (passed + 1, False, (seen + got) & 0xffffffff if got > 0 else seen,
+                                     sums + (got,) if step == ahead else sums))
+            moved = True
+            state = (after[0], after[1], wgs[:i] + (after[2],) + wgs[i + 1:])
+            if state not in known:
+                known.add(state)
+                stack.append(state)
+        if not moved:
+            ends.add(tuple(w[3] for w in wgs))
+    return ends
+
+
+@pytest.mark.parametrize("ahead,behind", [(1, 2), (2, 2), (1, 1)])
+@pytest.mark.parametrize("live", [[(5, 0), (0, 0)], [(5, 3), (2, 0), (0, 0)], [(5 + (1 << 20), 0, 3), (0, 0, 0)], [(0, 7, 0), (0, 4, 0), (0, 0, 0)]])
+def test_barrier_of_an_xcd_in_every_order(ahead, behind, live):
+    """Every workgroup of an XCD gets every round's sum, whoever is late to look at the word (the barrier of the joiner, or of the
+    joiner and a long segment's expansion, in front of the round's; the predictor's behind it)."""
+    L, _ = _lib()
+    L.xcd_barrier_reads.argtypes = [C.c_uint64, C.c_uint32, C.c_uint32, C.c_int]
+    groups = len(live[0])
+    want = {tuple(tuple(sum(r) for r in live) for _ in range(groups))}
+    assert _barrier_runs(L.xcd_barrier_reads, groups, live, ahead, behind) == want
+    # (the model sees the mistake it is here for: a sum taken at every barrier)
+    assert _barrier_runs(lambda w, due, seen, ends: L.xcd_barrier_reads(w, due, seen, 1), groups, live, ahead, behind) != want
