@@ -82,7 +82,7 @@ def quick_decode(workload, steps=2, warmup=1, seg=0, beam=0, debug=0):
         path = t.path()
         return {"workload": f"{shape.name}-like: {U} utterances, {frames} frames, Dj={shape.d_joint}, V={shape.vocab}, "
                             f"LSTM {shape.pred_layers}x{shape.pred_hidden}, N={N}, S={S}",
-                "kernels": ("whole segments in one launch" if t.L.tbs_path(t.ctx) & 4 else
+                "kernels": ("whole segments in one launch" if t.one_launch()["segments"] > 0 else
                             "four kernels a round, hypotheses in fixed places" if path["fixed_places"] else
                             "row lists, kernels sized by the round's rows") +
                            ("; joiner GEMM keeps row softmax sums and best tokens, no logits" if path["one_frame_no_logits"] else ""),
@@ -248,7 +248,7 @@ def main():
     ms_per_step = dt / args.steps * 1e3
     value = frames / (ms_per_step / 1e3)
     stats = tbs.stats()
-    one_launch = bool(tbs.L.tbs_path(tbs.ctx) & 4)
+    one_launch = tbs.one_launch()["segments"] > 0
 
     # ---- per-kernel timing with HIP events on the library's stream (separate, untimed passes)
     kernels = {}

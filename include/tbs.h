@@ -213,8 +213,7 @@ int tbs_result(tbs_ctx *ctx, int32_t *tokens, int32_t *lens, double *logscores,
 int tbs_stats(const tbs_ctx *ctx, int64_t *joiner_calls, int64_t *joined_frames, int64_t *frames,
               int64_t *launches);
 
-/* Which forms of the kernels the batch begun last runs in (they give the same results; tests and
- * benchmarks use this to say which one they exercised): bit 0 = every hypothesis in a fixed place,
+/* Which forms of the kernels the batch begun last runs in (they give the same results): bit 0 = every hypothesis in a fixed place,
  * four kernels a round; bit 1 = seg_s = 1 without logits (the standard search of Eq. 1 with the
  * row softmax sums and best tokens made in the joiner GEMM); bit 2 = tbs_decode and tbs_push_segment run whole
  * segments in one launch that takes every CU (models of one LSTM layer whose weights fit the LDS of an XCD's CUs, up to 512
@@ -222,6 +221,10 @@ int tbs_stats(const tbs_ctx *ctx, int64_t *joiner_calls, int64_t *joined_frames,
  * under way on the GPU, where its workgroups do not get onto the CUs together within 5 ms, and while a kernel family is
  * timed, the form of bits 0 and 1 instead).  Negative: an error code. */
 int tbs_path(const tbs_ctx *ctx);
+
+/* What came of tbs_path's bit 2 in the batch begun last: segments (of a stream: steps) that were decoded inside one launch, and
+ * launches that gave up because the GPU was not free for them.  Either pointer may be NULL. */
+int tbs_one_launch(const tbs_ctx *ctx, int64_t *segments, int64_t *gave_up);
 
 /* ---- inspection, for tests ---- */
 enum tbs_buffer {

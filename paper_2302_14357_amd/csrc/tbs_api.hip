@@ -93,6 +93,7 @@ struct tbs_ctx {
     int *h_xcd;         // pinned: [XCDs * workgroups, 4] how each workgroup ended, then [XCDs, XR_SEGS] rounds
     int *h_xcd_dev;
     int x_seq;
+    int64_t x_segments, x_gave_up;   // of the current batch: segments decoded in such a launch, launches that gave up
     int2 *nodes;
     long pool_rows;
     float *pool_p, *pool_h, *pool_c;
@@ -321,6 +322,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->pinned = c->h_res = c->h_res_dev = nullptr;
     c->xcd_ready = c->xcd = false;
     c->x_seq = 0;
+    c->x_segments = c->x_gave_up = 0;
     c->fixed = c->trie_full = false;
     c->trie_share = c->full_share = 0.0;
     c->h_desc = nullptr;
@@ -673,6 +675,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     memset(c->h_live, 0, 2 * sizeof(int) * (size_t)c->d.U);
     c->fx_calls = c->fx_joined = 0;
     c->fx_nodes = 0;
+    c->x_segments = c->x_gave_up = 0;
     // Slot layout: every utterance takes trie nodes from a range of its own, sized in proportion to
     // its length (a stream's utterances, whose lengths are not known, share equally); node 0 is the root.
     int *fig = c->h_begin, *order = fig + (size_t)U * TBS_FIG_SIZE, *T = order + U, *off = T + U;
@@ -1501,7 +1504,10 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
             }
         }
         if (absent || stuck) HIPCHK(c, hipMemsetAsync(c->x_ctl, 0, 2 * sizeof(XcdCtl), c->stream));
-        if (absent) return TBS_OK;   // (all ended like this, with nothing changed but the counts of those that came)
+        if (absent) {   // (all ended like this, with nothing changed but the counts of those that came)
+            c->x_gave_up += 1;
+            return TBS_OK;
+        }
         c->fx_calls += calls;
         c->fx_joined += joined;
         for (int s = s0; s < s1; ++s) {   // the batch's joiner calls in lock-step
@@ -1520,6 +1526,7 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
         if (over) return TBS_EOVERFLOW;
         c->fx_nodes += (int)nodes;
         *ran = s1 - seg0;
+        c->x_segments += s1 - s0;
         c->seg = s1 - 1;
         c->a_cur = 0;
         c->h_counts[TBS_CNT_PAIRS] = 0;
@@ -1663,7 +1670,9 @@ static int decode_all(tbs_ctx *c, const void *enc_proj, const int32_t *frame_off
     if (c->xcd && c->prof_kernel < 0 && nseg > 0) {
         if ((rc = run_segments_xcd(c, 0, nseg, &seg))) return rc;
         if (seg > 0 && seg < nseg && !c->fixed) {   // (row lists do not go on from there: their trie is another)
+            const int64_t gave_up = c->x_gave_up;
             if ((rc = tbs_begin(c, enc_proj, frame_offsets, U))) return rc;
+            c->x_gave_up = gave_up;
             seg = 0;
         }
     }
@@ -1704,6 +1713,14 @@ int tbs_path(const tbs_ctx *c) {
     if (!c) return TBS_EINVAL;
     if (c->state == ST_INIT) return TBS_ESTATE;
     return (c->fixed ? 1 : 0) | (c->s1 ? 2 : 0) | (c->xcd ? 4 : 0);
+}
+
+int tbs_one_launch(const tbs_ctx *c, int64_t *segments, int64_t *gave_up) {
+    if (!c) return TBS_EINVAL;
+    if (c->state == ST_INIT) return TBS_ESTATE;
+    if (segments) *segments = c->x_segments;
+    if (gave_up) *gave_up = c->x_gave_up;
+    return TBS_OK;
 }
 
 // ------------------------------------------------------------------ inspection

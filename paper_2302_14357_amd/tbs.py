@@ -15,7 +15,7 @@ EXPORTED_SYMBOLS = [
     "tbs_select_merge", "tbs_predictor_step", "tbs_decode", "tbs_result", "tbs_stats", "tbs_debug_read",
     "tbs_debug_write", "tbs_debug_rebuild", "tbs_debug_hyps", "tbs_profile_select", "tbs_profile_read",
     "tbs_strerror", "tbs_last_hip_error", "tbs_gemm_bf16", "tbs_stream_begin", "tbs_push_segment",
-    "tbs_profile_overhead", "tbs_debug_hyps_noalloc", "tbs_path",
+    "tbs_profile_overhead", "tbs_debug_hyps_noalloc", "tbs_path", "tbs_one_launch",
 ]
 
 TBS_MAX_LAYERS = 4
@@ -83,6 +83,7 @@ def load_library():
     L.tbs_push_segment.argtypes = [vp, vp, vp, i32]
     L.tbs_stats.argtypes = [vp, i64p, i64p, i64p, i64p]
     L.tbs_path.argtypes = [vp]
+    L.tbs_one_launch.argtypes = [vp, i64p, i64p]
     L.tbs_debug_read.argtypes = [vp, i32, vp, C.c_size_t]
     L.tbs_debug_write.argtypes = [vp, i32, vp, C.c_size_t]
     L.tbs_debug_rebuild.argtypes = [vp, i32, C.POINTER(i32)]
@@ -264,6 +265,15 @@ class Tbs:
         if v < 0:
             _check(v, self.ctx)
         return {"fixed_places": bool(v & 1), "one_frame_no_logits": bool(v & 2)}
+
+    def one_launch(self):
+        """Whether the batch begun last may run whole segments in one launch, those it did, and launches that gave up."""
+        v = self.L.tbs_path(self.ctx)
+        if v < 0:
+            _check(v, self.ctx)
+        a, b = C.c_int64(), C.c_int64()
+        _check(self.L.tbs_one_launch(self.ctx, C.byref(a), C.byref(b)), self.ctx)
+        return {"may": bool(v & 4), "segments": a.value, "gave_up": b.value}
 
     # ---- inspection
     def counts(self):

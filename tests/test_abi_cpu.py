@@ -50,6 +50,7 @@ def test_strerror_and_invalid_configs():
     assert L.tbs_joiner_segment(None) == -1 and L.tbs_expand(None) == -1
     assert L.tbs_select_merge(None, None) == -1 and L.tbs_predictor_step(None) == -1
     assert L.tbs_gemm_bf16(None, None, None, None, 1, 1, 8, 0, None) == -1
+    assert L.tbs_path(None) == -1 and L.tbs_one_launch(None, None, None) == -1
     assert L.tbs_stream_begin(None, 1) == -1 and L.tbs_push_segment(None, None, None, 0) == -1
     L.tbs_free(None)
 

@@ -1241,8 +1241,16 @@ def test_errors_are_codes_not_crashes():
     _check_decode(shape, model, offsets, enc, 2, 2)
 
 
-def _one_launch(tbs):
-    return bool(tbs.L.tbs_path(tbs.ctx) & 4)
+def _assert_one_launch(tbs, segments, debug=0):
+    """The batch's segments ran inside one launch, every one of them, or (debug bit 16) in no launch, or (bit 17) in launches
+    that gave up: what ran, not what could have."""
+    ran = tbs.one_launch()
+    assert ran["may"] == (debug != 65536)
+    assert ran["segments"] == (segments if debug == 0 else 0) and (ran["gave_up"] > 0) == (debug == 131072), ran
+
+
+def _segments(offsets, S):
+    return -(-int(np.diff(offsets).max()) // S)
 
 
 @pytest.mark.parametrize("dtype,d,hidden,V,N,S,lengths,peaked", [
@@ -1270,8 +1278,8 @@ def test_segments_in_one_launch_equal_four_kernels_a_round(dtype, d, hidden, V, 
         tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
         frames = tbs.upload_frames(enc)
         got = [tbs.decode(frames, offsets), tbs.decode(frames, offsets)]
-        assert _one_launch(tbs) == (debug != 65536) and tbs.path()["fixed_places"]
-        assert got[0] == got[1]
+        _assert_one_launch(tbs, _segments(offsets, S), debug)
+        assert tbs.path()["fixed_places"] and got[0] == got[1]
         seen.append((got[0], tbs.stats(), tbs.counts()["nodes"]))
         tbs.close()
     assert seen[0] == seen[1] == seen[2]   # (131072: the launch gives up and the batch runs with four kernels a round)
@@ -1289,8 +1297,8 @@ def test_streams_in_one_launch_a_step(debug):
     want, _ = _gpu_decode(shape, model, offsets, enc, N, S, debug=65536, max_rounds_per_segment=5)
     tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=12, max_rounds_per_segment=5, debug=debug)
     _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: (u + 2 * c) % 5)
-    assert _one_launch(tbs)
     assert tbs.result() == want
+    _assert_one_launch(tbs, max(tbs.one_launch()["segments"], _segments(offsets, S)), debug)   # (at least: a step need not be all utterances')
     tbs.close()
 
 
@@ -1314,7 +1322,7 @@ def test_pushes_whose_frames_go_with_the_launch(U, piece, offset, debug):
         torch.cuda.synchronize()
         at, c = at + n, c + 1
         tbs.push_segment(space[offset:], np.concatenate([[0], np.cumsum(n)]), flush=bool((at == offsets[1:]).all()))
-    assert _one_launch(tbs)
+    _assert_one_launch(tbs, max(tbs.one_launch()["segments"], _segments(offsets, S)), debug)
     got = tbs.result()
     tbs.close()
     assert got == want
@@ -1386,7 +1394,8 @@ def test_one_launch_beyond_the_fixed_places(d, hidden, V, N, S, lengths, peaked)
     for debug in (0, 65536, 131072):
         tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
         got = tbs.decode(tbs.upload_frames(enc), offsets)
-        assert _one_launch(tbs) == (debug != 65536) and not tbs.path()["fixed_places"]
+        _assert_one_launch(tbs, _segments(offsets, S), debug)
+        assert not tbs.path()["fixed_places"]
         seen.append((got, tbs.stats(), tbs.counts()["nodes"]))
         tbs.close()
     for other in seen[1:]:
@@ -1448,7 +1457,7 @@ def test_output_and_projection_weights_may_change_between_decodes(dtype, S):
     tbs = make_tbs(shape, model, offsets, 4, S)
     frames = tbs.upload_frames(enc)
     before = tbs.decode(frames, offsets)
-    assert _one_launch(tbs)
+    _assert_one_launch(tbs, _segments(offsets, S))
     for name in ("w_out", "w_proj"):
         tbs.t[name].copy_(torch.from_numpy(changed[name]))
     torch.cuda.synchronize()
