@@ -95,6 +95,17 @@ __device__ __forceinline__ float wave_sum(float v) {
     v += dpp_f<DPP_MIRROR>(v);
     return (lane_f(v, 0) + lane_f(v, 16)) + (lane_f(v, 32) + lane_f(v, 48));
 }
+#define DPP_ROW_ROR(n) (0x120 + (n))
+// The sum of a butterfly from far to near, lane i and i ^ 32 first (another order than wave_sum's, so other last bits).  From the
+// third step on a rotation brings what the exchange would: lanes that have been added up hold the same value.
+__device__ __forceinline__ float wave_sum_far(float v) {
+    v += __shfl_xor(v, 32);
+    v += __shfl_xor(v, 16);
+    v += dpp_f<DPP_ROW_ROR(8)>(v);
+    v += dpp_f<DPP_ROW_ROR(4)>(v);
+    v += dpp_f<DPP_QUAD_SWAP2>(v);
+    return v + dpp_f<DPP_QUAD_SWAP1>(v);
+}
 __device__ __forceinline__ int wave_min_int(int v) {
     v = min(v, dpp_i<DPP_QUAD_SWAP1>(v));
     v = min(v, dpp_i<DPP_QUAD_SWAP2>(v));
@@ -604,6 +615,8 @@ __device__ __forceinline__ ScanPart scan_exp2(float l2, float z) {
 
 #define LONG_FRAMES 64     // a lane per frame in the scan
 #define LONG_MIN_WAVES 4   // the N best are taken by the first four waves
+#define LONG_FOLD_WAVES 8  // whole segments in one launch: waves of a workgroup, and the arrays their shares of Eq. 6 meet in
+#define LONG_FOLD_SHARES 4
 struct LongShared : ExpandBest<EXP_WAVES> {
     float m[LONG_FRAMES], z[LONG_FRAMES], lb[LONG_FRAMES], cf[LONG_FRAMES];
 };

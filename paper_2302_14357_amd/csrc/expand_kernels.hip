@@ -162,43 +162,45 @@ k_expand_reg(Dims d, const float *__restrict__ logits, AView A, RowView rv, floa
 }
 
 // ------------------------------------------------------------------ long segments
-template <int NQ, int RPW>
-__global__ void __launch_bounds__(1024)
+// (FOLD: as the launch over whole segments adds up, for batches that it may decode)
+template <int NQ, int RPW, bool FOLD>
+__global__ void __launch_bounds__(FOLD ? 64 * LONG_FOLD_WAVES : 1024)
 k_expand_long(Dims d, const float *__restrict__ logits, AView A, RowView rv, float *__restrict__ row_lc,
               float *__restrict__ dphi, float *__restrict__ cand_score, int *__restrict__ cand_tok,
               float *__restrict__ row_stats, float *__restrict__ delta_nb, const int *__restrict__ pairs_dev,
               int pair_base) {
-    extern __shared__ __attribute__((aligned(16))) float4 s_part[];   // [waves][Vl / 4]
+    extern __shared__ __attribute__((aligned(16))) float4 s_part[];   // [shares][Vl / 4]
     __shared__ LongShared sm;
     const int pair = pair_base + blockIdx.x, tid = threadIdx.x;
-    const int waves = (int)blockDim.x >> 6;
+    const int waves = FOLD ? LONG_FOLD_WAVES : (int)blockDim.x >> 6, shares = FOLD ? LONG_FOLD_SHARES : waves;
     if (pairs_dev && pair >= *pairs_dev) return;   // (enqueued on an upper-bound grid, see k_expand_reg)
     const int u = ((cint_p)rv.pair_u)[pair], h = ((cint_p)rv.pair_h)[pair];
     const int row0 = ((cint_p)rv.pair_row0)[pair], sp = ((cint_p)rv.pair_len)[pair];
     const float *L = logits + (long)row0 * d.Vl;
-    expand_long<NQ, RPW, false>(
-        d, sp, waves, waves, tid, sm, s_part, [&](int t) { return A.dhat[((long)u * d.N + h) * d.S + t]; },
+    expand_long<NQ, RPW, FOLD>(
+        d, sp, waves, shares, tid, sm, s_part, [&](int t) { return A.dhat[((long)u * d.N + h) * d.S + t]; },
         [&](int t, int piece) { return reinterpret_cast<const float4 *>(L + (long)t * d.Vl)[piece]; },
         [&](int t, int col) { return L[(long)t * d.Vl + col]; }, row_lc + row0, dphi + pair, cand_score + (long)pair * d.N,
         cand_tok + (long)pair * d.N, row_stats ? row_stats + (long)row0 * 3 : nullptr, delta_nb ? delta_nb + (long)pair * d.V : nullptr);
 }
 
-template <int NQ, int RPW>
+template <int NQ, int RPW, bool FOLD = false>
 static hipError_t expand_long_launch(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                                      float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
                                      float *delta_nb, const int *pairs_dev, int pair_base) {
     int waves = (d.S + RPW - 1) / RPW;
     if (waves < LONG_MIN_WAVES) waves = LONG_MIN_WAVES;
-    if (waves > 16) return hipErrorInvalidValue;
-    const size_t shm = (size_t)waves * d.Vl * sizeof(float);   // (at most 64 KB)
+    if (waves > (FOLD ? LONG_FOLD_WAVES : 16)) return hipErrorInvalidValue;
+    if (FOLD) waves = LONG_FOLD_WAVES;
+    const size_t shm = (size_t)(FOLD ? LONG_FOLD_SHARES : waves) * d.Vl * sizeof(float);   // (at most 64 KB)
     static size_t attr_for = 0;
     if (shm > attr_for) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_expand_long<NQ, RPW>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_expand_long<NQ, RPW, FOLD>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_for = shm;
     }
-    hipLaunchKernelGGL((k_expand_long<NQ, RPW>), dim3(pairs), dim3(64 * waves), shm, st, d, logits, A, rv, row_lc, dphi,
+    hipLaunchKernelGGL((k_expand_long<NQ, RPW, FOLD>), dim3(pairs), dim3(64 * waves), shm, st, d, logits, A, rv, row_lc, dphi,
                        cand_score, cand_tok, row_stats, delta_nb, pairs_dev, pair_base);
     return hipGetLastError();
 }
@@ -236,7 +238,7 @@ extern "C" int expand_form(int Vl, int S) {
 
 hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                          float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
-                         float *delta_nb, int force_generic, const int *pairs_dev, int pair_base) {
+                         float *delta_nb, int force_generic, const int *pairs_dev, int pair_base, bool fold) {
     if (pairs <= 0) return hipSuccess;
     if (pairs_dev && pair_base) return hipErrorInvalidValue;   // (a piece is launched with its size known)
     size_t shm = (size_t)d.Vl * sizeof(float);
@@ -250,7 +252,21 @@ hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *
     case EXPAND_LONG(NQ, RPW):                                                                                         \
         return expand_long_launch<NQ, RPW>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok, row_stats, \
                                            delta_nb, pairs_dev, pair_base);
-        switch (expand_form(d.Vl, d.S)) {
+        const int form = expand_form(d.Vl, d.S);
+        if (fold && form >= EXPAND_LONG(1, 0)) {   // (rows a wave: those of the launch's bodies for 16, 32 and 64 frames)
+#define TBS_EXPAND_FOLD(NQ, RPW)                                                                                        \
+    case EXPAND_LONG(NQ, RPW):                                                                                          \
+        return expand_long_launch<NQ, RPW, true>(st, d, pairs, logits, A, rv, row_lc, dphi, cand_score, cand_tok,       \
+                                                 row_stats, delta_nb, pairs_dev, pair_base);
+            switch (EXPAND_LONG((form - 1000) / 10, d.S <= 16 ? 2 : (d.S <= 32 ? 4 : 8))) {
+                TBS_EXPAND_FOLD(1, 2) TBS_EXPAND_FOLD(1, 4) TBS_EXPAND_FOLD(1, 8)
+                TBS_EXPAND_FOLD(2, 2) TBS_EXPAND_FOLD(2, 4) TBS_EXPAND_FOLD(2, 8)
+                TBS_EXPAND_FOLD(4, 2) TBS_EXPAND_FOLD(4, 4) TBS_EXPAND_FOLD(4, 8)
+                default: return hipErrorInvalidValue;
+            }
+#undef TBS_EXPAND_FOLD
+        }
+        switch (form) {
             TBS_EXPAND_REG(1, 3) TBS_EXPAND_REG(1, 5) TBS_EXPAND_REG(2, 8) TBS_EXPAND_REG(4, 3) TBS_EXPAND_REG(4, 5)
             TBS_EXPAND_LONG(1, 2) TBS_EXPAND_LONG(1, 4)
             TBS_EXPAND_LONG(2, 2) TBS_EXPAND_LONG(2, 4)

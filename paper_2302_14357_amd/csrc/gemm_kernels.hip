@@ -55,7 +55,7 @@ __device__ __forceinline__ bool gemm_tile_of(int xcd, int idx, int tiles_m, int 
 // is prefetched during the last K tile of the current one and the epilogue's
 // stores are left in flight, so neither the load latency at the head of a tile
 // nor the store traffic at its tail stalls the matrix cores.
-template <int TM, int TN, int WM, int WN, int BK, bool KGUARD>
+template <int TM, int TN, int WM, int WN, int BK, bool KGUARD, bool LATE>
 __global__ void __launch_bounds__(64 * WM * WN)
 k_gemm_bf16(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const float *__restrict__ bias,
             float *__restrict__ C, int M, int N, int K, const int *__restrict__ out_row, long ldc, int tiles_m,
@@ -152,11 +152,14 @@ k_gemm_bf16(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const fl
     __syncthreads();
     int buf = 0;
     for (;;) {
-        // accumulators start from the bias: a lane's column is the same for all 16 of its entries
+        // accumulators start from the bias (LATE: it is added to the sum, as k_gemm_small does): a lane's column is the same
+        // for all 16 of its entries
+        float bl[TN];
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             const int col = tile_n * BN + wn * 32 * TN + j * 32 + (lane & 31);
-            const float bv = (bias && col < N) ? bias[col] : 0.f;
+            bl[j] = (bias && col < N) ? bias[col] : 0.f;
+            const float bv = LATE ? 0.f : bl[j];
 #pragma unroll
             for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -247,7 +250,7 @@ k_gemm_bf16(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const fl
                 for (int r = 0; r < 16; ++r) {
                     float *tr = tb + (long)(i * 32 + (r >> 2) * 8 + (r & 3)) * ldc;   // uniform
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) tr[offl + j * 32] = acc[i][j][r];
+                    for (int j = 0; j < TN; ++j) tr[offl + j * 32] = LATE ? acc[i][j][r] + bl[j] : acc[i][j][r];
                 }
         } else {
             // edge tiles and scattered rows.  The destination rows of a 32-row block are requested
@@ -270,7 +273,7 @@ k_gemm_bf16(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const fl
                     for (int r = 0; r < 16; ++r) {
                         const int row = m0 + wm * 32 * TM + i * 32 + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
                         if (row < M && col < N) {
-                            C[orow[r] * ldc + col] = acc[i][j][r];
+                            C[orow[r] * ldc + col] = LATE ? acc[i][j][r] + bl[j] : acc[i][j][r];
                         }
                     }
                 }
@@ -287,7 +290,7 @@ k_gemm_bf16(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const fl
     }
 }
 
-template <int TM, int TN, int WM, int WN, int BK, int OCC>
+template <int TM, int TN, int WM, int WN, int BK, int OCC, bool LATE = false>
 static hipError_t gemm_launch(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                               int N, int K, const int *out_row, long ldc, const int *m_begin = nullptr,
                               const int *m_end = nullptr) {
@@ -296,10 +299,10 @@ static hipError_t gemm_launch(hipStream_t st, const bf16_t *A, const bf16_t *B, 
     const size_t shm = 2u * (BM + BN) * BK * sizeof(bf16_t);
     static bool attr_set = false;
     if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<TM, TN, WM, WN, BK, false>),
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<TM, TN, WM, WN, BK, false, LATE>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<TM, TN, WM, WN, BK, true>),
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_bf16<TM, TN, WM, WN, BK, true, LATE>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
         if (e != hipSuccess) return e;
         attr_set = true;
@@ -310,10 +313,10 @@ static hipError_t gemm_launch(hipStream_t st, const bf16_t *A, const bf16_t *B, 
     if (g > 256L * OCC) g = 256L * OCC;
     const dim3 grid((unsigned)g), block(64 * WM * WN);
     if (K % BK == 0)
-        hipLaunchKernelGGL((k_gemm_bf16<TM, TN, WM, WN, BK, false>), grid, block, shm, st, A, B, bias, C, M, N, K, out_row,
+        hipLaunchKernelGGL((k_gemm_bf16<TM, TN, WM, WN, BK, false, LATE>), grid, block, shm, st, A, B, bias, C, M, N, K, out_row,
                            ldc, tiles_m, tiles_n, GEMM_GROUP_M, m_begin, m_end);
     else
-        hipLaunchKernelGGL((k_gemm_bf16<TM, TN, WM, WN, BK, true>), grid, block, shm, st, A, B, bias, C, M, N, K, out_row,
+        hipLaunchKernelGGL((k_gemm_bf16<TM, TN, WM, WN, BK, true, LATE>), grid, block, shm, st, A, B, bias, C, M, N, K, out_row,
                            ldc, tiles_m, tiles_n, GEMM_GROUP_M, m_begin, m_end);
     return hipGetLastError();
 }
@@ -828,7 +831,8 @@ hipError_t launch_gemm_join(hipStream_t st, const bf16_t *A, const bf16_t *B, co
 // kernel: 0 = by size (what the decode uses); 1..4 force one (tests run every kernel on every shape):
 // 1 = 64x64 tiles, 2 = 128x128, 3 = 256x256 (all k_gemm_bf16), 4 = k_gemm_small
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
-                            int N, int K, const int *out_row, long ldc, int kernel, const int *m_dev, bool xcd_rows) {
+                            int N, int K, const int *out_row, long ldc, int kernel, const int *m_dev, bool xcd_rows,
+                            bool bias_late) {
     if (M <= 0) return hipSuccess;
     if (m_dev && !gemm_small_fits(M, N, K, INT_MAX)) return hipErrorInvalidValue;   // only k_gemm_small reads its row count
     if ((kernel == 0 || kernel == 4) && K % GS_BK == 0) {
@@ -852,6 +856,14 @@ hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, co
         long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
         long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
         kernel = t256 >= 384 ? 3 : (t128 >= 256 ? 2 : 1);
+    }
+    if (bias_late && bias) {   // (for the bits of k_gemm_small, whatever the size)
+        switch (kernel) {
+            case 1: return gemm_launch<1, 1, 2, 2, 64, 4, true>(st, A, B, bias, C, M, N, K, out_row, ldc);
+            case 2: return gemm_launch<2, 2, 2, 2, 64, 2, true>(st, A, B, bias, C, M, N, K, out_row, ldc);
+            case 3: return gemm_launch<4, 2, 2, 4, 64, 1, true>(st, A, B, bias, C, M, N, K, out_row, ldc);
+            default: return hipErrorInvalidValue;
+        }
     }
     switch (kernel) {
         case 1: return gemm_launch<1, 1, 2, 2, 64, 4>(st, A, B, bias, C, M, N, K, out_row, ldc);   // 64x64, 4 waves

@@ -82,8 +82,12 @@ struct tbs_ctx {
     int64_t fx_calls, fx_joined;   // joiner invocations and frames joined, counted on the host in this layout
     int fx_nodes;                  // and trie nodes taken
     // whole segments as one launch (see xcd_kernels.hip); what it needs beside the slot layout's memory
-    bool xcd_ready;     // the context's shapes and device can run it
-    bool xcd;           // the current batch does
+    bool xcd_shape;     // the context's shapes and device can run it
+    bool xcd_ready;     // ... and debug bit 16 does not keep it from it
+    bool xcd;           // the current batch does, where the GPU is free for it
+    // Batches of such contexts add up in the launch's order in every form (long segments' shares of Eq. 6, the bias of large
+    // products), so that results do not hang on what else the GPU is doing.
+    bool xcd_sums;
     XcdCtl *x_ctl;      // [2], used in turn: a launch clears the next one's
     int *x_order;       // [U] the XCDs' utterances (behind utt_fig)
     int x_first[XR_XCDS + 1];
@@ -254,7 +258,8 @@ hipError_t gemm(tbs_ctx *c, const void *A, const void *B, const float *bias, flo
                 const int *out_row, long ldc) {
     ProfScope ps(c, TBS_K_GEMM, (int64_t)M * N * K);
     if (c->cfg.dtype == 1)
-        return launch_gemm_bf16(c->stream, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc);
+        return launch_gemm_bf16(c->stream, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, 0, nullptr, false,
+                                c->xcd_sums);
     return launch_gemm_f32(c->stream, (const float *)A, (const float *)B, bias, C, M, N, K, out_row, ldc);
 }
 
@@ -320,7 +325,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->state = ST_INIT;
     c->last_hip = 0;
     c->pinned = c->h_res = c->h_res_dev = nullptr;
-    c->xcd_ready = c->xcd = false;
+    c->xcd_shape = c->xcd_ready = c->xcd = c->xcd_sums = false;
     c->x_seq = 0;
     c->x_segments = c->x_gave_up = 0;
     c->fixed = c->trie_full = false;
@@ -461,10 +466,11 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     }
     {
         int cus = 0;
-        c->xcd_ready = (cfg->debug & ~131072) == 0 && cfg->joiner_chunk_rows == 0 && (cfg->dtype == 1 ? xcd_fits(d) : xcd_f32_fits(d)) &&
+        c->xcd_shape = (cfg->debug & ~(65536 | 131072)) == 0 && cfg->joiner_chunk_rows == 0 && (cfg->dtype == 1 ? xcd_fits(d) : xcd_f32_fits(d)) &&
                        ((reinterpret_cast<uintptr_t>(w->w_out) | reinterpret_cast<uintptr_t>(w->w_proj)) & 15) == 0 &&   // (16 B to the LDS at once)
                        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device_id) == hipSuccess &&
                        cus == XR_XCDS * XR_WGS;
+        c->xcd_ready = c->xcd_shape && !(cfg->debug & 65536);
     }
     if (c->xcd_ready) {
         rc |= dev_alloc(c, &c->x_ctl, 2);
@@ -734,6 +740,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->n_frames = frames;
     c->state = ST_BEGUN;
     c->trie_full = false;
+    c->xcd_sums = c->xcd_shape && U <= XR_XCDS * XR_POS;
     c->fixed = fixed_layout_ok(c);
     c->s1 = c->fixed && one_frame_ok(c);
     // (Beyond the slot layout the batch would have row lists, whose one trie serves all: where its shares may not hold what
@@ -845,7 +852,7 @@ static int joiner_expand_pieces(tbs_ctx *c, int rows, int piece) {
             ProfScope ps(c, TBS_K_EXPAND, units);
             HIPCHK(c, launch_expand(c->stream, d, p1 - p0, c->logits, c->A[c->a_cur], c->rv, c->row_lc, c->dphi,
                                     c->cand_score, c->cand_tok, c->row_stats, c->delta_nb, (c->cfg.debug & 2) != 0,
-                                    nullptr, p0));
+                                    nullptr, p0, c->xcd_sums));
         }
     }
     c->prep_ahead = false;
@@ -902,7 +909,8 @@ int tbs_expand(tbs_ctx *c) {
     {
         ProfScope ps(c, TBS_K_EXPAND, c->h_counts[TBS_CNT_ROWS]);
         HIPCHK(c, launch_expand(c->stream, c->cur, pairs, c->logits, c->A[c->a_cur], c->rv, c->row_lc, c->dphi,
-                                c->cand_score, c->cand_tok, c->row_stats, c->delta_nb, (c->cfg.debug & 2) != 0));
+                                c->cand_score, c->cand_tok, c->row_stats, c->delta_nb, (c->cfg.debug & 2) != 0, nullptr, 0,
+                                c->xcd_sums));
     }
     c->state = ST_EXPANDED;
     return TBS_OK;
@@ -1171,7 +1179,7 @@ static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
                                c->delta_nb));
     } else {
         HIPCHK(c, launch_expand(c->stream, d, d.U * d.N, c->logits, A, c->rv, c->row_lc, c->dphi, c->cand_score,
-                                c->cand_tok, c->row_stats, c->delta_nb, (c->cfg.debug & 2) != 0, pairs_dev));
+                                c->cand_tok, c->row_stats, c->delta_nb, (c->cfg.debug & 2) != 0, pairs_dev, 0, c->xcd_sums));
         HIPCHK(c, launch_select_merge(c->stream, d, c->round, drop, c->logits, c->row_lc, c->dphi, c->cand_score,
                                       c->cand_tok, A, An, c->B, c->rv, c->nodes));
     }

@@ -272,7 +272,7 @@ hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, 
 // before the host knows the row count; M is an upper bound and the count is read from *m_dev
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel = 0, const int *m_dev = nullptr,
-                            bool xcd_rows = false);
+                            bool xcd_rows = false, bool bias_late = false);
 // rows per XCD when k_gemm_small gives every XCD a row range of its own (PartEp::xcd_rows)
 inline int gemm_small_xcd_rows(int M, int tile) { return tile * ((((M + tile - 1) / tile) + 7) / 8); }
 hipError_t launch_gemm_bf16_rows(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C,
@@ -304,7 +304,8 @@ hipError_t launch_permute_gate_rows(hipStream_t st, const void *src, void *dst, 
 extern "C" int expand_form(int Vl, int S);
 hipError_t launch_expand(hipStream_t st, const Dims &d, int pairs, const float *logits, AView A, RowView rv,
                          float *row_lc, float *dphi, float *cand_score, int *cand_tok, float *row_stats,
-                         float *delta_nb, int force_generic, const int *pairs_dev = nullptr, int pair_base = 0);
+                         float *delta_nb, int force_generic, const int *pairs_dev = nullptr, int pair_base = 0,
+                         bool fold = false);
 // how the select step makes the frame distributions of new hypotheses: 0 ahead of the ranking, 1 by lane, 2 by frame
 extern "C" int select_dist_form(int candidates, int frames);
 hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int drop, const float *logits,

@@ -299,8 +299,7 @@ __host__ __device__ inline size_t scratch_bytes(int N, int BCAP) {
     const size_t b_list = ((size_t)BCAP * (sizeof(double) + sizeof(u64) + 3 * sizeof(int)) + 15) & ~(size_t)15;
     return b_list + (SMAX > 5 ? 0 : (size_t)N * sizeof(ExpandShared<SMAX, 1>)) + sizeof(float) * ((size_t)N * SMAX + N + 2 * (size_t)N * N);
 }
-#define XR_LONG_SHARES 4   // long segments: arrays of shares of Eq. 6 (see expand_long)
-__host__ __device__ __forceinline__ int long_bytes(int Vl) { return (int)((sizeof(LongShared) + 15) & ~(size_t)15) + XR_LONG_SHARES * Vl * 4; }
+__host__ __device__ __forceinline__ int long_bytes(int Vl) { return (int)((sizeof(LongShared) + 15) & ~(size_t)15) + LONG_FOLD_SHARES * Vl * 4; }
 __host__ __device__ __forceinline__ int slice_bytes_f32(int tiles, int K) { return (tiles + XR_WGS - 1) / XR_WGS * f32_pieces(K) * 1024; }
 template <int SMAX, bool F32>
 __host__ __device__ inline XcdLds xcd_lds(const Dims &d, int nw, int limit) {
@@ -689,7 +688,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
 // the utterance's own workgroup would be alone with all of them).
 template <int NT, int NQ, int SMAX>
 __device__ __forceinline__ void xcd_expand_long(const XcdPlace &w, XcdShared &sh, unsigned char *scratch, int a) {
-    static_assert(SMAX <= LONG_FRAMES && SMAX % (NT / 64) == 0, "rows of a wave");
+    static_assert(SMAX <= LONG_FRAMES && SMAX % (NT / 64) == 0 && NT / 64 == LONG_FOLD_WAVES, "rows of a wave");
     const XcdArgs &g = xcd_args();
     const Dims &d = g.d;
     const int N = w.N, S = d.S, P = w.n_act * N;
@@ -705,7 +704,7 @@ __device__ __forceinline__ void xcd_expand_long(const XcdPlace &w, XcdShared &sh
         const int sp = __builtin_amdgcn_readfirstlane(sh.sp[i]), u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
         if (slot < 0 || sp == 0) continue;   // (the same for the whole workgroup)
         expand_long<NQ, SMAX / (NT / 64), true>(
-            d, sp, NT / 64, XR_LONG_SHARES, w.tid, sm, s_part,
+            d, sp, NT / 64, LONG_FOLD_SHARES, w.tid, sm, s_part,
             [&](int t) { return fresh4(r_dhat, (unsigned)((u * N + h) * S + t) * 4u, 0u); },
             [&](int t, int piece) { return as_float4(fresh16(r_logits, (unsigned)piece * 16u, (unsigned)(p * S + t) * (unsigned)d.Vl * 4u)); },
             [&](int t, int col) { return fresh4(r_logits, (unsigned)((p * S + t) * d.Vl + col) * 4u, 0u); }, g.row_lc + (pair0 + p) * S,
@@ -777,7 +776,15 @@ __device__ __forceinline__ int xcd_select_long(const XcdPlace &w, XcdShared &sh,
             const float xv = fresh4(r_logits, (unsigned)((h * d.S + t) * d.Vl + tok) * 4u, 0u) + sc.lc[h * sp + t];
             const float xx = lane < sp ? xv : -INFINITY;
             const float mx = wave_max(xx);
-            const float lz = mx + __logf(wave_sum(lane < sp ? __expf(xx - mx) : 0.f));
+            const float ex = lane < sp ? __expf(xx - mx) : 0.f;
+            float sum = 0.f;   // (in the order of the select step: one after the other, or by a butterfly over the frames)
+            if (sp <= SEL_PRE_FRAMES) {
+#pragma unroll
+                for (int q = 0; q < SEL_PRE_FRAMES; ++q) sum += lane_f(ex, q);   // (zero beyond S')
+            } else {
+                sum = wave_sum_far(ex);
+            }
+            const float lz = mx + __logf(sum);
             float *dh = g.A[a ^ 1].dhat + ((long)u * N + wave) * d.S;
             if (lane < d.S) dh[lane] = lane < sp ? xx - lz : -INFINITY;
         }

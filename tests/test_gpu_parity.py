@@ -1464,3 +1464,36 @@ def test_output_and_projection_weights_may_change_between_decodes(dtype, S):
     after = tbs.decode(frames, offsets)
     tbs.close()
     assert after == want and after != before
+
+
+@pytest.mark.parametrize("dtype,d,hidden,V,N,S,lengths,peaked", [
+    ("bf16", 128, 128, 96, 4, 7, [0, 2, 7, 12, 23, 31], False), ("bf16", 128, 256, 200, 7, 16, [5, 16, 17, 40], True),
+    ("bf16", 256, 128, 1023, 2, 17, [34, 3, 18, 24, 26], False), ("bf16", 384, 128, 500, 5, 33, [33, 70, 1, 42], False),
+    ("bf16", 128, 128, 64, 3, 64, [64, 65, 130, 20, 73], False), ("bf16", 512, 640, 1024, 5, 20, [9 + i for i in range(64)], False),
+    ("bf16", 512, 640, 1000, 5, 8, [9 + i for i in range(64)], True), ("bf16", 128, 128, 40, 5, 6, [3 + i % 10 for i in range(270)], False),
+    ("bf16", 128, 128, 700, 10, 5, [4 + i % 5 for i in range(140)], False), ("bf16", 128, 128, 1000, 5, 3, [2 + i % 5 for i in range(300)], True),
+    ("bf16", 512, 640, 1024, 10, 5, [4 + i % 5 for i in range(320)], False), ("bf16", 256, 128, 300, 5, 1, [1 + i % 3 for i in range(512)], False),
+    ("f32", 64, 64, 32, 4, 3, [2 + i % 5 for i in range(300)], False), ("f32", 128, 256, 500, 10, 5, [4 + i % 4 for i in range(200)], False)])
+def test_results_do_not_hang_on_what_the_gpu_is_doing(dtype, d, hidden, V, N, S, lengths, peaked):
+    """Where the slot layout does not reach (long segments, large batches), row lists take the place of a launch that gives up
+    (debug bit 17) or is not made (bit 16): the same bits, for products of every tile size, and as a stream, which has row lists
+    there in any case."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=len(lengths), vocab=V, d=d, hidden=hidden), dtype=dtype)
+    kw = dict(rounds_capacity=4 * S) if S > 16 else {}
+    if peaked:
+        shape = _peaked(shape, 8.0, 8.0)
+        kw = dict(max_rounds_per_segment=5)
+    model, offsets, enc = build_case(shape, n_utts=len(lengths), lengths=np.array(lengths))
+    seen = []
+    for debug in (0, 65536, 131072):
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
+        seen.append(tbs.decode(tbs.upload_frames(enc), offsets))
+        _assert_one_launch(tbs, _segments(offsets, S), debug)
+        tbs.close()
+    assert seen[0] == seen[1] == seen[2]
+    if S > 5:
+        tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=2 * S, **kw)
+        _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: 1 + (u + 3 * c) % S)
+        assert tbs.result() == seen[0]
+        tbs.close()
