@@ -4,6 +4,7 @@
 // the other files; this file only sizes buffers, orders launches and moves
 // counts and results between device and host.
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <cstdio>
 #include <cstdlib>
@@ -97,6 +98,7 @@ struct tbs_ctx {
     int *h_xcd;         // pinned: [XCDs * workgroups, 4] how each workgroup ended, then [XCDs, XR_SEGS] rounds
     int *h_xcd_dev;
     int x_seq;
+    int x_lds;          // LDS of the launch, per CU
     int64_t x_segments, x_gave_up;   // of the current batch: segments decoded in such a launch, launches that gave up
     int2 *nodes;
     long pool_rows;
@@ -156,6 +158,15 @@ static hipError_t scratch_resolve(int device) {
     g_scratch_ptr[device] = p;
     return hipSuccess;
 }
+
+// Calls that run rounds on a GPU and wait for them, from whatever contexts (see xcd_may_launch).
+static std::atomic<int> g_inside[TBS_MAX_DEVICES];
+struct Inside {
+    std::atomic<int> &n;
+    explicit Inside(const tbs_ctx *c) : n(g_inside[c->cfg.device_id]) { n.fetch_add(1); }
+    ~Inside() { n.fetch_sub(1); }
+    Inside(const Inside &) = delete;
+};
 
 #define HIPCHK(ctx, expr)                       \
     do {                                        \
@@ -328,6 +339,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->xcd_shape = c->xcd_ready = c->xcd = c->xcd_sums = false;
     c->x_seq = 0;
     c->x_segments = c->x_gave_up = 0;
+    c->x_lds = 0;
     c->fixed = c->trie_full = false;
     c->trie_share = c->full_share = 0.0;
     c->h_desc = nullptr;
@@ -473,6 +485,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         c->xcd_ready = c->xcd_shape && !(cfg->debug & 65536);
     }
     if (c->xcd_ready) {
+        c->x_lds = xcd_lds_bytes(cfg->dtype, d);
         rc |= dev_alloc(c, &c->x_ctl, 2);
         rc |= dev_alloc(c, &c->x_desc, UN);
         const long n[3] = {c->pool_rows * xcd_row_bytes(cfg->dtype, d.H),
@@ -782,6 +795,7 @@ static int segment_begin(tbs_ctx *c, int32_t seg_index, int32_t *rows_host);
 int tbs_segment_begin(tbs_ctx *c, int32_t seg_index, int32_t *rows_host) {
     if (!c || seg_index < 0) return TBS_EINVAL;
     if (c->streaming) return TBS_ESTATE;   // a stream's segments are started by tbs_push_segment
+    const Inside inside(c);
     return segment_begin(c, seg_index, rows_host);
 }
 
@@ -931,6 +945,7 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused);
 int tbs_select_merge(tbs_ctx *c, int32_t *live_host) {
     if (!c) return TBS_EINVAL;
     if (c->state != ST_EXPANDED) return TBS_ESTATE;
+    const Inside inside(c);
     return select_merge_impl(c, live_host, false);
 }
 
@@ -1396,16 +1411,26 @@ static int run_segment_fixed(tbs_ctx *c, int32_t seg_index) {
 }
 
 // Only one launch of the kernel that decodes whole segments can be on a GPU at a time (its workgroups take every CU and wait
-// for each other): a call that finds another one's under way runs its batch in the slot layout.
+// for each other).
 static std::mutex g_xcd_mutex[TBS_MAX_DEVICES];
+
+// May a call make such a launch while `inside` calls, it among them, run rounds on the GPU?  The kernels of the others find no LDS
+// until the launch ends.  Two threads that decode in a loop would share nothing: who has the launch once has it every time
+// (64 utterances N = 5 S = 3, ten decodes each: done after 109 and 222 ms; a stream beside such a thread 54 ms instead of 22).  With four
+// kernels a round both are done after 220 ms, and more contexts or longer segments fill the chip better than launches one after
+// the other (four threads S = 20 9.3 ms a decode against 14.2, fp32 9.6 against 12.8; eight with one utterance each 5.1 both).  So a call
+// launches where it is alone; a launch that leaves the others half of every CU's LDS does them no harm (small fp32
+// configuration, two threads 0.37 ms a decode, 0.54 without).
+extern "C" int xcd_may_launch(int inside, int lds) { return inside <= 1 || lds <= 80 * 1024; }
 
 // Segments [seg0, seg1) in one launch or several.  *ran is the number of segments that were decoded: fewer, with TBS_OK,
 // where the GPU was not free for it; the rest has to run in the slot layout, which finds everything in its place.
 // push (or null): its figures and frames go with the launch (segment 0 alone, see XcdArgs).
 static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void *push = nullptr, long row_bytes = 0) {
     *ran = 0;
-    std::unique_lock<std::mutex> alone(g_xcd_mutex[c->cfg.device_id], std::try_to_lock);
-    if (!alone.owns_lock()) return TBS_OK;
+    if (!xcd_may_launch(g_inside[c->cfg.device_id].load(), c->x_lds)) return TBS_OK;
+    std::unique_lock<std::mutex> only(g_xcd_mutex[c->cfg.device_id], std::try_to_lock);
+    if (!only.owns_lock()) return TBS_OK;
     const Dims &d = c->cur;
     XcdArgs g{};
     g.d = d;
@@ -1460,6 +1485,8 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
     const int *ends = c->h_xcd, *rounds = c->h_xcd + 4 * XR_XCDS * XR_WGS;
     c->prep_ahead = false;
     for (int s0 = seg0; s0 < seg1; s0 += XR_SEGS) {
+        // (others have come: they get their turn between two launches, where the rest of the batch can go on beside them)
+        if (s0 > seg0 && c->fixed && !xcd_may_launch(g_inside[c->cfg.device_id].load(), c->x_lds)) return TBS_OK;
         const int s1 = std::min(seg1, s0 + XR_SEGS);
         g.seg0 = s0;
         g.seg1 = s1;
@@ -1584,6 +1611,7 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
     if (c->n_frames + frame_offsets[U] > c->cfg.max_frames_total) return TBS_EINVAL;
     if (frame_offsets[U] > 0 && !enc_proj) return TBS_EINVAL;
     HIPCHK(c, hipSetDevice(c->cfg.device_id));
+    const Inside inside(c);
     const long row_bytes = (long)d.Dj * elem_bytes(c);
     // Pinned descriptor areas, one per use within a call (the stream reads them later than the host
     // writes them); the call ends with the stream drained, so the next call may write them again.
@@ -1693,6 +1721,7 @@ static int decode_all(tbs_ctx *c, const void *enc_proj, const int32_t *frame_off
 int tbs_decode(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offsets, int32_t U, int32_t *tokens,
                int32_t *lens, double *logscores, int32_t *nbest_count, int32_t max_len) {
     if (!c) return TBS_EINVAL;
+    const Inside inside(c);
     const int64_t units0 = c->prof_units;
     const size_t ev0 = c->ev_used;
     int rc = decode_all(c, enc_proj, frame_offsets, U);

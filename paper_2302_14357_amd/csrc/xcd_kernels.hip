@@ -17,6 +17,7 @@ hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g) {
 // (asked by a CPU test that runs the barrier in every order)
 extern "C" int xcd_barrier_reads(u64 word, unsigned due, unsigned seen, int live) { return xcd_barrier_read(word, due, seen, live != 0); }
 
+int xcd_lds_bytes(int dtype, const Dims &d) { return dtype == 1 ? lds_of<false>(d).bytes + XR_STATIC_LDS(d.N > 7) : xcd_f32_lds_bytes(d); }
 long xcd_row_bytes(int dtype, int K) { return dtype == 1 ? 2l * K : 4l * f32_row(K); }
 long xcd_frag_bytes(int dtype, int rows, int K) { return (long)((rows + 15) / 16) * 16 * xcd_row_bytes(dtype, K); }
 

@@ -83,6 +83,13 @@ def test_distributions_of_new_hypotheses_by_size(N, frames, form):
     assert L.select_dist_form(N * N, frames) == form
 
 
+@pytest.mark.parametrize("inside,lds,may", [(1, 160 * 1024, 1), (2, 160 * 1024, 0), (8, 81921, 0), (2, 81920, 1), (8, 20000, 1)])
+def test_when_a_call_may_take_every_cu(inside, lds, may):
+    """A launch over whole segments where no other call runs rounds on the GPU, or where it leaves those half of every CU's LDS."""
+    L, _ = _lib()
+    assert L.xcd_may_launch(inside, lds) == may
+
+
 def test_binding_has_no_oracle_or_cpu_path():
     """The product package must not import the oracle."""
     import paper_2302_14357_amd

@@ -1277,8 +1277,9 @@ def test_segments_in_one_launch_equal_four_kernels_a_round(dtype, d, hidden, V, 
     for debug in (0, 65536, 131072):
         tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
         frames = tbs.upload_frames(enc)
-        got = [tbs.decode(frames, offsets), tbs.decode(frames, offsets)]
+        got = [tbs.decode(frames, offsets)]
         _assert_one_launch(tbs, _segments(offsets, S), debug)
+        got.append(tbs.decode(frames, offsets))
         assert tbs.path()["fixed_places"] and got[0] == got[1]
         seen.append((got[0], tbs.stats(), tbs.counts()["nodes"]))
         tbs.close()
@@ -1497,3 +1498,40 @@ def test_results_do_not_hang_on_what_the_gpu_is_doing(dtype, d, hidden, V, N, S,
         _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: 1 + (u + 3 * c) % S)
         assert tbs.result() == seen[0]
         tbs.close()
+
+
+@pytest.mark.parametrize("dtype,S", [("bf16", 3), ("bf16", 8), ("f32", 3)])
+def test_contexts_at_the_same_time_share_the_gpu(dtype, S):
+    """Two threads that decode in a loop at widths whose launch takes all of the CUs' LDS: when one is done the other has come
+    nearly as far (it stood still when the launch went to whoever asked first), and both get the results they get alone."""
+    import dataclasses
+    import threading
+    import torch
+    N, rounds = 5, 12
+    shape = dataclasses.replace(small_bf16_shape(n_utts=9, vocab=1024, d=512, hidden=640), dtype=dtype)
+    model, offsets, enc = build_case(shape, n_utts=9, lengths=np.arange(60, 69))
+    want, _ = _gpu_decode(shape, model, offsets, enc, N, S)
+    ctx = []
+    for st in [torch.cuda.Stream(), torch.cuda.Stream()]:
+        with torch.cuda.stream(st):
+            ctx.append(make_tbs(shape, model, offsets, N, S))
+    frames = [t.upload_frames(enc) for t in ctx]
+    assert all(t.decode(f, offsets) == want for t, f in zip(ctx, frames))
+    _assert_one_launch(ctx[0], _segments(offsets, S))
+    done, at_end, ok, start = [0, 0], [], [True, True], threading.Barrier(2)
+
+    def work(i):
+        start.wait()
+        for _ in range(rounds):
+            ok[i] = ok[i] and ctx[i].decode(frames[i], offsets) == want
+            done[i] += 1
+        at_end.append(min(done))
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for t in ctx:
+        t.close()
+    assert ok == [True, True] and at_end[0] >= rounds // 2, at_end
