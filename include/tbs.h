@@ -219,7 +219,7 @@ int tbs_stats(const tbs_ctx *ctx, int64_t *joiner_calls, int64_t *joined_frames,
  * segments in one launch that takes every CU (models of one LSTM layer whose weights fit the LDS of an XCD's CUs, up to 512
  * utterances; bf16 with segments of up to 64 frames, fp32 up to 5; without bit 0 not streams.  While other contexts run rounds on
  * the GPU (a launch that takes little LDS: while another's launch is under way), where its workgroups do not get onto the CUs
- * together within 5 ms, and while a kernel family is timed, the form of bits 0 and 1 instead, with the
+ * together within 5 ms and for 100 ms after that, and while a kernel family is timed, the form of bits 0 and 1 instead, with the
  * same results).  Negative: an error code. */
 int tbs_path(const tbs_ctx *ctx);
 

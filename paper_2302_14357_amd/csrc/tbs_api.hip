@@ -99,6 +99,8 @@ struct tbs_ctx {
     int *h_xcd_dev;
     int x_seq;
     int x_lds;          // LDS of the launch, per CU
+    bool x_waits;       // a launch gave up: none before x_retry
+    std::chrono::steady_clock::time_point x_retry;
     int64_t x_segments, x_gave_up;   // of the current batch: segments decoded in such a launch, launches that gave up
     int2 *nodes;
     long pool_rows;
@@ -340,6 +342,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->x_seq = 0;
     c->x_segments = c->x_gave_up = 0;
     c->x_lds = 0;
+    c->x_waits = false;
     c->fixed = c->trie_full = false;
     c->trie_share = c->full_share = 0.0;
     c->h_desc = nullptr;
@@ -1423,11 +1426,20 @@ static std::mutex g_xcd_mutex[TBS_MAX_DEVICES];
 // configuration, two threads 0.37 ms a decode, 0.54 without).
 extern "C" int xcd_may_launch(int inside, int lds) { return inside <= 1 || lds <= 80 * 1024; }
 
+// A launch that gave up has cost its 5 ms (XR_PATIENCE_MS): none is tried for twenty times as long, a twentieth of the time at most.  (5 ms
+// is not too long to wait beside another stream's kernels: a launch gets onto the CUs as they end, where four kernels a round wait for
+// them every time.  Beside matrix products of 0.9 ms: 64 utterances 13.4 ms a decode against 863, a push 0.8 ms against 6.4.)
+#define TBS_RETRY_MS (20 * XR_PATIENCE_MS)
+
 // Segments [seg0, seg1) in one launch or several.  *ran is the number of segments that were decoded: fewer, with TBS_OK,
 // where the GPU was not free for it; the rest has to run in the slot layout, which finds everything in its place.
 // push (or null): its figures and frames go with the launch (segment 0 alone, see XcdArgs).
 static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void *push = nullptr, long row_bytes = 0) {
     *ran = 0;
+    if (c->x_waits) {
+        if (std::chrono::steady_clock::now() < c->x_retry) return TBS_OK;
+        c->x_waits = false;
+    }
     if (!xcd_may_launch(g_inside[c->cfg.device_id].load(), c->x_lds)) return TBS_OK;
     std::unique_lock<std::mutex> only(g_xcd_mutex[c->cfg.device_id], std::try_to_lock);
     if (!only.owns_lock()) return TBS_OK;
@@ -1541,6 +1553,8 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
         if (absent || stuck) HIPCHK(c, hipMemsetAsync(c->x_ctl, 0, 2 * sizeof(XcdCtl), c->stream));
         if (absent) {   // (all ended like this, with nothing changed but the counts of those that came)
             c->x_gave_up += 1;
+            c->x_waits = true;
+            c->x_retry = std::chrono::steady_clock::now() + std::chrono::milliseconds(TBS_RETRY_MS);
             return TBS_OK;
         }
         c->fx_calls += calls;

@@ -167,6 +167,7 @@ __host__ __device__ inline int part_width(int np) { return (4 + 2 * np + 3) & ~3
 #define XR_POS 64      // most utterances an XCD decodes
 #define XR_KMAX 640    // widest joint space and LSTM
 #define XR_SEGS 4096   // most segments of a launch
+#define XR_PATIENCE_MS 5   // how long a launch's workgroups wait for each other to come
 struct XcdCtl {        // device memory, zero when the launch begins
     u64 bar[XR_XCDS * 16];            // an XCD's barriers (a line each)
     unsigned place[XR_XCDS * 32];     // workgroups that came on each XCD

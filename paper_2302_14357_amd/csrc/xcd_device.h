@@ -1132,7 +1132,7 @@ k_xcd_decode(XcdArgs args) {
         unsigned *word = leads ? &ctl->state : &ctl->told[xc * 32];
         const u64 t0 = wall_clock64();
         while ((st = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0) {
-            if (wall_clock64() - t0 > 5ull * XR_TICKS) {   // (who decides first decides for all)
+            if (wall_clock64() - t0 > XR_PATIENCE_MS * XR_TICKS) {   // (who decides first decides for all)
                 unsigned none = 0;
                 __hip_atomic_compare_exchange_strong(&ctl->state, &none, 2u, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                      __HIP_MEMORY_SCOPE_AGENT);

@@ -1535,3 +1535,19 @@ def test_contexts_at_the_same_time_share_the_gpu(dtype, S):
     for t in ctx:
         t.close()
     assert ok == [True, True] and at_end[0] >= rounds // 2, at_end
+
+
+def test_a_launch_that_gave_up_is_not_tried_at_every_push():
+    """Where the GPU is not free for the launch (debug bit 17) a stream waits for it once in 100 ms, not at every push."""
+    import time
+    N, S = 3, 3
+    shape = small_bf16_shape(n_utts=4, vocab=40, d=256, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=4, lengths=np.full(4, 120))
+    want, _ = _gpu_decode(shape, model, offsets, enc, N, S)
+    tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=6, debug=131072)
+    t0 = time.monotonic()
+    _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: 3)   # (40 pushes)
+    most = 1 + int((time.monotonic() - t0) / 0.1)
+    _assert_one_launch(tbs, 0, 131072)
+    assert tbs.one_launch()["gave_up"] <= most and tbs.result() == want
+    tbs.close()
