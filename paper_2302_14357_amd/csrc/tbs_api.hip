@@ -1426,6 +1426,11 @@ static std::mutex g_xcd_mutex[TBS_MAX_DEVICES];
 // configuration, two threads 0.37 ms a decode, 0.54 without).
 extern "C" int xcd_may_launch(int inside, int lds) { return inside <= 1 || lds <= 80 * 1024; }
 
+// Segments of one launch, where the XCD with most utterances has `utts`.  A launch keeps the others' kernels from the GPU and the host waits for
+// it under one time limit, so its work is bounded: 65536 frames an XCD, 0.4 s at the 6 us a frame of the Librispeech-like widths (S = 1 and 3, 64
+// utterances); 4096 segments are those of 8 utterances of 6 frames or shorter, and a launch more costs 15 us.
+extern "C" int xcd_launch_segments(int utts, int S) { return std::max(1, std::min(XR_SEGS, 65536 / std::max(1, utts * S))); }
+
 // A launch that gave up has cost its 5 ms (XR_PATIENCE_MS): none is tried for twenty times as long, a twentieth of the time at most.  (5 ms
 // is not too long to wait beside another stream's kernels: a launch gets onto the CUs as they end, where four kernels a round wait for
 // them every time.  Beside matrix products of 0.9 ms: 64 utterances 13.4 ms a decode against 863, a push 0.8 ms against 6.4.)
@@ -1496,10 +1501,13 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
     g.host_rounds = c->h_xcd_dev + 4 * XR_XCDS * XR_WGS;
     const int *ends = c->h_xcd, *rounds = c->h_xcd + 4 * XR_XCDS * XR_WGS;
     c->prep_ahead = false;
-    for (int s0 = seg0; s0 < seg1; s0 += XR_SEGS) {
+    int most = 0;
+    for (int x = 0; x < XR_XCDS; ++x) most = std::max(most, g.first[x + 1] - g.first[x]);
+    const int per = xcd_launch_segments(most, d.S);
+    for (int s0 = seg0; s0 < seg1; s0 += per) {
         // (others have come: they get their turn between two launches, where the rest of the batch can go on beside them)
         if (s0 > seg0 && c->fixed && !xcd_may_launch(g_inside[c->cfg.device_id].load(), c->x_lds)) return TBS_OK;
-        const int s1 = std::min(seg1, s0 + XR_SEGS);
+        const int s1 = std::min(seg1, s0 + per);
         g.seg0 = s0;
         g.seg1 = s1;
         g.seq = ++c->x_seq & 0x7FFFFF;

@@ -90,6 +90,13 @@ def test_when_a_call_may_take_every_cu(inside, lds, may):
     assert L.xcd_may_launch(inside, lds) == may
 
 
+@pytest.mark.parametrize("utts,S,segments", [(1, 1, 4096), (1, 16, 4096), (8, 2, 4096), (1, 17, 3855), (8, 3, 2730), (25, 3, 873), (64, 64, 16)])
+def test_segments_of_a_launch(utts, S, segments):
+    """A launch holds the GPU, so its work is bounded: 4096 segments, 65536 frames of an XCD's utterances."""
+    L, _ = _lib()
+    assert L.xcd_launch_segments(utts, S) == segments
+
+
 def test_binding_has_no_oracle_or_cpu_path():
     """The product package must not import the oracle."""
     import paper_2302_14357_amd
