@@ -1577,3 +1577,34 @@ def test_decodes_of_several_launches(dtype, S, lengths):
         _assert_one_launch(tbs, _segments(offsets, S), debug)
         tbs.close()
     assert seen[0] == seen[1]
+
+
+@pytest.mark.parametrize("S,peaked", [(3, True), (1, False), (5, False)])
+def test_streams_that_change_form_between_pushes(S, peaked):
+    """Pushes in a launch, with four kernels a round (a timed kernel family is not there in a launch) and back, as where another
+    context comes and goes: the stream's result, and its counters, are those of the batch."""
+    N = 5
+    shape = small_bf16_shape(n_utts=11, vocab=120, d=256, hidden=128)
+    kw = {}
+    if peaked:
+        shape, kw = _peaked(shape, 8.0, 8.0), dict(max_rounds_per_segment=5)
+    model, offsets, enc = build_case(shape, n_utts=11, lengths=np.array([0, 1, 3, 4, 9, 10, 14, 21, 22, 5, 30]))
+    want, st = _gpu_decode(shape, model, offsets, enc, N, S, debug=65536, **kw)
+    steps = None
+    for turn in (1000, 1, 2, 3):
+        tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=12, **kw)
+        push, calls = tbs.push_segment, []
+
+        def one(*a, **k):
+            tbs.profile_select(0 if len(calls) // turn % 2 else -1)
+            calls.append(0)
+            push(*a, **k)
+
+        tbs.push_segment = one
+        _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: (u + 2 * c) % 5)
+        ran = tbs.one_launch()
+        steps = steps or ran["segments"]   # (all of them in a launch)
+        assert ran["gave_up"] == 0 and (turn == 1000 or 0 < ran["segments"] < steps)
+        assert tbs.result() == want
+        assert {k: tbs.stats()[k] for k in ("joiner_calls", "joined_frames", "frames")} == {k: st[k] for k in ("joiner_calls", "joined_frames", "frames")}
+        tbs.close()
