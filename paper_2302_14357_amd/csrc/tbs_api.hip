@@ -99,6 +99,7 @@ struct tbs_ctx {
     int *h_xcd_dev;
     int x_seq;
     int x_lds;          // LDS of the launch, per CU
+    long x_hb_bytes;
     bool x_waits;       // a launch gave up: none before x_retry
     std::chrono::steady_clock::time_point x_retry;
     int64_t x_segments, x_gave_up;   // of the current batch: segments decoded in such a launch, launches that gave up
@@ -342,6 +343,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->x_seq = 0;
     c->x_segments = c->x_gave_up = 0;
     c->x_lds = 0;
+    c->x_hb_bytes = 0;
     c->x_waits = false;
     c->fixed = c->trie_full = false;
     c->trie_share = c->full_share = 0.0;
@@ -487,19 +489,24 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
                        cus == XR_XCDS * XR_WGS;
         c->xcd_ready = c->xcd_shape && !(cfg->debug & 65536);
     }
-    if (c->xcd_ready) {
+    if (c->xcd_ready && rc == 0) {
+        // (for as many utterances as it decodes, however many a batch of row lists may have; a context that gets no memory for it
+        // goes without)
+        const long xu = std::min(U, (long)XR_XCDS * XR_POS);
         c->x_lds = xcd_lds_bytes(cfg->dtype, d);
-        rc |= dev_alloc(c, &c->x_ctl, 2);
-        rc |= dev_alloc(c, &c->x_desc, UN);
-        const long n[3] = {c->pool_rows * xcd_row_bytes(cfg->dtype, d.H),
-                           (M + 16 * XR_XCDS) * xcd_row_bytes(cfg->dtype, d.Dj),   // (every XCD's rows in whole tiles of 16)
+        c->x_hb_bytes = xu * 2 * (d.R + 1) * d.N * xcd_row_bytes(cfg->dtype, d.H);
+        int none = dev_alloc(c, &c->x_ctl, 2);
+        none |= dev_alloc(c, &c->x_desc, xu * d.N);
+        const long n[3] = {c->x_hb_bytes,
+                           (xu * d.N * d.S + 16 * XR_XCDS) * xcd_row_bytes(cfg->dtype, d.Dj),   // (every XCD's rows in whole tiles of 16)
                            xcd_frag_bytes(cfg->dtype, 4 * d.H, d.H)};
         void **to[3] = {&c->x_hb, &c->x_amat, &c->x_frags};
         long all = 0;
         for (int i = 0; i < 3; ++i) all += (n[i] + 255) & ~255l;
         char *p = nullptr;
-        rc |= dev_alloc(c, &p, (size_t)all);
-        for (int i = 0; i < 3; ++i) {
+        none |= dev_alloc(c, &p, (size_t)all);
+        if (none) c->xcd_ready = false;
+        for (int i = 0; i < 3 && !none; ++i) {
             *to[i] = p;
             p += (n[i] + 255) & ~255l;
         }
@@ -1488,7 +1495,7 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
     g.pool_h = c->pool_h;
     g.pool_c = c->pool_c;
     g.hb = c->x_hb;
-    g.hb_bytes = c->pool_rows * xcd_row_bytes(c->cfg.dtype, d.H);
+    g.hb_bytes = c->x_hb_bytes;
     g.amat = c->x_amat;
     g.logits = c->logits;
     g.row_lc = c->row_lc;

@@ -1608,3 +1608,26 @@ def test_streams_that_change_form_between_pushes(S, peaked):
         assert tbs.result() == want
         assert {k: tbs.stats()[k] for k in ("joiner_calls", "joined_frames", "frames")} == {k: st[k] for k in ("joiner_calls", "joined_frames", "frames")}
         tbs.close()
+
+
+def test_memory_of_the_launch_ends_with_its_utterances():
+    """A context for 1500 utterances takes no more for the launch, which decodes up to 512, than those need (state rows of
+    4 x 2 x 33 places of 256 bytes an utterance, input rows of 12 x 256), and batches on both sides of the limit decode."""
+    import torch
+    N, S = 4, 3
+    shape = small_bf16_shape(n_utts=520, vocab=40, d=128, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=520, lengths=np.array([1 + i % 4 for i in range(520)]))
+    taken, got = [], []
+    for debug in (0, 65536, 0):   # (the first for what a process takes once)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        tbs = make_tbs(shape, model, offsets, N, S, max_utts=1500, debug=debug)
+        taken.append(free - torch.cuda.mem_get_info()[0])
+        out = []
+        for U in (512, 513):
+            out.append(tbs.decode(tbs.upload_frames(enc[:offsets[U]]), offsets[:U + 1]))
+            assert tbs.one_launch()["segments"] == (2 if debug == 0 and U == 512 else 0)
+        got.append(out)
+        tbs.close()
+    assert got[0] == got[1] == got[2] and got[0][0] == got[0][1][:512]
+    assert taken[2] - taken[1] <= 512 * (N * 2 * 33 + N * S) * 256 + (8 << 20), taken
