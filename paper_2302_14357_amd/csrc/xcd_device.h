@@ -1103,6 +1103,7 @@ __device__ __forceinline__ void xcd_project_f32(const XcdPlace &w, XcdShared &sh
 template <int NT, int NV4, int SMAX, bool FEW, bool F32>
 __global__ void __launch_bounds__(NT)
 k_xcd_decode(XcdArgs args) {
+    constexpr bool PUSH = !F32 && SMAX <= 5;   // (other models' streams have row lists)
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     __shared__ XcdShared sh;
     __shared__ SelectOut s_out;
@@ -1175,8 +1176,8 @@ k_xcd_decode(XcdArgs args) {
             const int pH = F32 ? f32_pieces(d.H) : d.H >> 5;
             int2 step = make_int2(0, 0);
             int4 rows = make_int4(0, 0, 0, 0);
-            if (g.push_step && tid < w.nu) step = g.push_step[w.u_base + tid];
-            if (g.push_step && w.r < w.nu) rows = g.push_rows[w.u_base + w.r];
+            if (PUSH && g.push_step && tid < w.nu) step = g.push_step[w.u_base + tid];
+            if (PUSH && g.push_step && w.r < w.nu) rows = g.push_rows[w.u_base + w.r];
             if (l.wG < 0) wG = nullptr;
             else load_frags(wG, g.w_gate, pH, 0, own_tiles(tiles_gate(d), w.r) * pH, w.r, w.wave, NW, lane);
             load_rows<F32>(wJ, g.w_out, d.V, d.Dj, own_tiles(tiles_joiner(d), w.r), w.r, w.wave, NW, lane);
@@ -1185,7 +1186,7 @@ k_xcd_decode(XcdArgs args) {
             // A push brings its frames and figures with it: who has the utterance appends the frames to its buffer, while the
             // weights come (the first that reads them does so behind a barrier).  With a copy of the figures and a kernel that
             // appends in front of the launch a push of one segment of 64 streams took 116 us, now 107.
-            if (g.push_step) {
+            if (PUSH && g.push_step) {
                 if (tid < w.nu) {
                     sh.sp[tid] = step.x;
                     sh.f0[tid] = step.y;
@@ -1214,7 +1215,7 @@ k_xcd_decode(XcdArgs args) {
             // frames of the XCD's utterances in this segment; utterances beyond the last that has any are left out
             {
                 const XcdArgs &g = xcd_args();
-                if (tid < w.nu && !g.push_step) {
+                if (tid < w.nu && !(PUSH && g.push_step)) {
                     const int u = sh.utt[tid], left = g.utt_T[u] - seg * g.d.S;
                     sh.sp[tid] = left < 0 ? 0 : min(left, g.d.S);
                     sh.f0[tid] = g.utt_off[u] + seg * g.d.S;

@@ -9,6 +9,7 @@ static hipError_t xcd_launch_long(hipStream_t st, const XcdArgs &g, int shm) {
 }
 
 hipError_t launch_xcd_decode_long(hipStream_t st, const XcdArgs &g) {
+    if (g.push_step) return hipErrorInvalidValue;
     const int nv4 = nv4_of(g.d), shm = lds_of<false>(g.d).bytes;
     if (nv4 == 1) return xcd_launch_long<1>(st, g, shm);
     if (nv4 == 2) return xcd_launch_long<2>(st, g, shm);
