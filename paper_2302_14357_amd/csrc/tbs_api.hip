@@ -646,9 +646,10 @@ static bool proj_small(const tbs_ctx *c, int M, bool slots) {
 // keep the row lists.
 // Segments of one frame: the joiner GEMM can keep row partials instead of logits (unless debug output
 // that needs the logits, or debug bit 9, asks for them), and the round kernel then has no limit on
-// the vocabulary from its registers.  Measured on the Librispeech-like batch (ms per decode, with
-// logits / without): N = 2: 25.7 / 24.6, N = 3: 26.7 / 25.6, N = 4: 27.2 / 26.7, N = 5: 28.4 / 29.0, N = 8:
-// 34.0 / 37.0, N = 10: 47.0 / 47.3.  The logits of a small batch never leave the cache, and picking the N
+// the vocabulary from its registers.  Measured on the Librispeech-like batch, four kernels a round each (ms per
+// decode, with logits / without): N = 2: 25.7 / 24.6, N = 3: 26.7 / 25.6, N = 4: 27.2 / 26.7, N = 5: 28.4 / 29.0, N = 8:
+// 34.0 / 37.0, N = 10: 47.0 / 47.3.  (The launch over whole segments, which keeps logits, takes 13.2 for N = 5; beams up to
+// 4 keep to the form without them, whose scores differ from it in the last digits.)  The logits of a small batch never leave the cache, and picking the N
 // best of every 16 logits costs the GEMM N rounds of a 16-way arg-max: the partials serve beams up to 4,
 // the vocabularies the form with logits cannot hold, and debug bit 15.
 static bool one_frame_fits(const tbs_ctx *c) {
@@ -1620,8 +1621,8 @@ static int run_segment(tbs_ctx *c, int32_t seg_index) {
     }
 }
 
-// May the frames of a push go with the launch?  Its copies are 16 bytes wide (rows are in whole pieces of that), and one workgroup appends an utterance's: beyond
-// 64 KB (a few us of one CU) the whole chip does it sooner.
+// May the frames of a push go with the launch?  Its copies are 16 bytes wide (rows are in whole pieces of that), and one
+// workgroup appends an utterance's: beyond 64 KB (a few us of one CU) the whole chip does it sooner.
 static bool push_fused_ok(const void *enc, long row_bytes, int most) {
     return (reinterpret_cast<uintptr_t>(enc) & 15) == 0 && most * row_bytes <= 64 * 1024;
 }
@@ -1642,8 +1643,10 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
     HIPCHK(c, hipSetDevice(c->cfg.device_id));
     const Inside inside(c);
     const long row_bytes = (long)d.Dj * elem_bytes(c);
-    // Pinned descriptor areas, one per use within a call (the stream reads them later than the host
-    // writes them); the call ends with the stream drained, so the next call may write them again.
+    // Pinned descriptor areas, one per use within a call (the stream reads them later than the host writes them).  The next call
+    // may write them again, and the caller its frames: this one ends with the stream drained, or behind a launch all of whose
+    // workgroups have told their ends, which they do after their last read of either.  (What that launch then still stores for
+    // the device, figures and counts of lists, is ordered by the stream alone.)
     // The first area mirrors the device's: step sizes, first frames, then the descriptors of the copy that
     // appends the new frames, so that the first decode step of a push needs one copy for all three.
     const int Um = c->d.U;
