@@ -217,7 +217,8 @@ int tbs_stats(const tbs_ctx *ctx, int64_t *joiner_calls, int64_t *joined_frames,
  * four kernels a round; bit 1 = seg_s = 1 without logits (the standard search of Eq. 1 with the
  * row softmax sums and best tokens made in the joiner GEMM); bit 2 = tbs_decode and tbs_push_segment run whole
  * segments in one launch that takes every CU (models of one LSTM layer whose weights fit the LDS of an XCD's CUs, up to 512
- * utterances; bf16 with segments of up to 64 frames, fp32 up to 5; without bit 0 not streams.  While other contexts run rounds on
+ * utterances; bf16 with segments of up to 64 frames, fp32 up to 5; not where long segments or an fp32 model give an eighth of the
+ * utterances so many hypotheses that the other forms are faster; without bit 0 not streams.  While other contexts run rounds on
  * the GPU (a launch that takes little LDS: while another's launch is under way), where its workgroups do not get onto the CUs
  * together within 5 ms and for 100 ms after that, and while a kernel family is timed, the form of bits 0 and 1 instead, with the
  * same results).  Negative: an error code. */

@@ -99,6 +99,7 @@ struct tbs_ctx {
     int *h_xcd_dev;
     int x_seq;
     int x_lds;          // LDS of the launch, per CU
+    bool x_gates_stay;  // the gates' weights among it
     long x_hb_bytes;
     bool x_waits;       // a launch gave up: none before x_retry
     std::chrono::steady_clock::time_point x_retry;
@@ -343,6 +344,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     c->x_seq = 0;
     c->x_segments = c->x_gave_up = 0;
     c->x_lds = 0;
+    c->x_gates_stay = false;
     c->x_hb_bytes = 0;
     c->x_waits = false;
     c->fixed = c->trie_full = false;
@@ -494,6 +496,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         // goes without)
         const long xu = std::min(U, (long)XR_XCDS * XR_POS);
         c->x_lds = xcd_lds_bytes(cfg->dtype, d);
+        c->x_gates_stay = cfg->dtype == 1 || xcd_f32_gates_stay(d);
         c->x_hb_bytes = xu * 2 * (d.R + 1) * d.N * xcd_row_bytes(cfg->dtype, d.H);
         int none = dev_alloc(c, &c->x_ctl, 2);
         none |= dev_alloc(c, &c->x_desc, xu * d.N);
@@ -693,6 +696,29 @@ static hipError_t joiner_rows(tbs_ctx *c, int rows, const int *rows_dev) {
                               rows_dev);
 }
 
+// Is the launch over whole segments the faster form for batches with `utts` utterances on an XCD?  Measured against the slot
+// layout and the row lists (times of theirs / times of its own, utterances of 24 to 36 frames, beyond 20 frames a segment 66 to 99;
+// widths 512/640/1024, 256/256/500, 128/128/64):
+// bf16, up to 5 frames: 2.2 for one utterance, 1.0 to 1.5 for 512.  Longer segments expand in turns of an XCD's 32 workgroups, as the row lists
+// do on all 256: with hypotheses an XCD, S = 6 N = 5 1.02 1.13 1.22 at 160, 0.98 1.08 1.03 at 180; S = 8 N = 7 1.00 1.07 1.13 at 140,
+// 0.95 1.07 1.13 at 168, 0.90 0.96 1.01 at 196; S = 12 N = 5 1.00 1.03 1.06 at 120, 0.97 0.97 0.98 at 140; S = 16 N = 7 1.03 1.07 1.06 at 112, 0.95
+// 0.99 0.91 at 168; S = 20 N = 5 1.11 1.05 1.11 at 80, 0.92 0.88 0.91 at 140; S = 32 N = 5 1.08 1.01 1.14 at 80, 0.98 0.87 0.94 at 120; S = 64
+// N = 3 1.16 1.06 1.31 at 36, 0.94 0.93 0.99 at 60.
+// fp32 is bound by its products, which the chip shares better than its XCDs.  Gates' weights that do not stay in LDS come through the
+// L2 every round (widths 512/640/1024, rows an XCD): S = 3 N = 5 1.09 at 240, 0.97 at 300, 0.85 at 720; S = 5 N = 5 1.02 at 250, 0.90 at
+// 350, 0.74 at 1200; S = 1 N = 5 1.06 at 160, 0.95 at 180; with twelve waves a workgroup (N > 7) S = 3 1.02 at 480, 0.97 at 600, S = 1 1.08 at 200, 0.99
+// at 240.  Those that stay (256/256/500, 64/64/32): S = 5 N = 5 1.18 1.12 at 800, 0.95 0.90 at 1200; N = 10 1.22 1.00 at 1400, 1.13 0.98 at 1600.
+extern "C" int xcd_pays(int f32, int gates_stay, int N, int S, int utts) {
+    const int hyps = utts * N, rows = hyps * S;
+    if (f32) {
+        if (gates_stay) return rows <= (N <= 7 ? 800 : 1400);
+        return rows <= (N <= 7 ? 240 : 480) && hyps <= (N <= 7 ? 160 : 200);
+    }
+    if (S <= 5) return 1;
+    if (S <= 8) return rows <= 1120;
+    return hyps <= (S <= 16 ? 120 : (S <= 32 ? 80 : 40));
+}
+
 // B = [([], 1, InitPredictor(), Null)] for U utterances whose lengths and first frames are h_T / offsets
 static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int32_t U, int max_T, long frames) {
     HIPCHK(c, hipSetDevice(c->cfg.device_id));
@@ -770,7 +796,8 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     // (Beyond the slot layout the batch would have row lists, whose one trie serves all: where its shares may not hold what
     // that holds it goes without this form, and a decode whose share was full all the same is run again, see tbs_decode.)
     const bool shares = !c->streaming && c->trie_share >= 4.0 * c->cur.N && c->trie_share > c->full_share;
-    c->xcd = c->xcd_ready && (c->fixed ? !c->s1 : shares) && U <= XR_XCDS * XR_POS;
+    c->xcd = c->xcd_ready && (c->fixed ? !c->s1 : shares) && U <= XR_XCDS * XR_POS &&
+             xcd_pays(c->cfg.dtype == 0, c->x_gates_stay, c->cur.N, c->cur.S, (U + XR_XCDS - 1) / XR_XCDS);
     return TBS_OK;
 }
 

@@ -221,6 +221,7 @@ hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g);
 hipError_t launch_xcd_decode_long(hipStream_t st, const XcdArgs &g);   // (its segments of more than five frames)
 bool xcd_f32_fits(const Dims &d);
 int xcd_f32_lds_bytes(const Dims &d);
+bool xcd_f32_gates_stay(const Dims &d);
 int xcd_lds_bytes(int dtype, const Dims &d);   // LDS a workgroup takes
 hipError_t launch_xcd_decode_f32(hipStream_t st, const XcdArgs &g);
 long xcd_row_bytes(int dtype, int K);                // bytes of a row of K columns as the products read it

@@ -9,6 +9,8 @@ bool xcd_f32_fits(const Dims &d) {
 
 int xcd_f32_lds_bytes(const Dims &d) { return lds_of<true>(d).bytes + XR_STATIC_LDS(true); }
 
+bool xcd_f32_gates_stay(const Dims &d) { return lds_of<true>(d).wG >= 0; }
+
 hipError_t launch_xcd_decode_f32(hipStream_t st, const XcdArgs &g) {
     if (!xcd_f32_fits(g.d) || !xcd_batch_fits(g) || g.push_step) return hipErrorInvalidValue;
     return g.d.N <= 7 ? xcd_launch<512, true, true>(st, g) : xcd_launch<768, false, true>(st, g);

@@ -97,6 +97,17 @@ def test_segments_of_a_launch(utts, S, segments):
     assert L.xcd_launch_segments(utts, S) == segments
 
 
+@pytest.mark.parametrize("f32,stay,N,S,most", [
+    (0, 1, 11, 5, 64), (0, 1, 1, 1, 64), (0, 1, 5, 6, 37), (0, 1, 7, 8, 20), (0, 1, 5, 9, 24), (0, 1, 7, 16, 17), (0, 1, 5, 17, 16), (0, 1, 5, 32, 16),
+    (0, 1, 5, 33, 8), (0, 1, 1, 64, 40), (1, 0, 5, 3, 16), (1, 0, 7, 1, 22), (1, 0, 2, 5, 24), (1, 0, 8, 1, 25), (1, 0, 10, 5, 9),
+    (1, 1, 5, 5, 32), (1, 1, 2, 1, 64), (1, 1, 8, 5, 35), (1, 1, 11, 5, 25)])
+def test_batches_the_launch_is_faster_for(f32, stay, N, S, most):
+    """Utterances an XCD up to which whole segments run in one launch: bf16 of up to 5 frames all (64 are its limit anyway),
+    longer segments by hypotheses, fp32 by rows, fewer where the gates' weights do not stay in LDS."""
+    L, _ = _lib()
+    assert [u for u in range(1, 65) if L.xcd_pays(f32, stay, N, S, u)] == list(range(1, most + 1))
+
+
 def test_binding_has_no_oracle_or_cpu_path():
     """The product package must not import the oracle."""
     import paper_2302_14357_amd

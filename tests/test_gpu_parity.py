@@ -1631,3 +1631,19 @@ def test_memory_of_the_launch_ends_with_its_utterances():
         tbs.close()
     assert got[0] == got[1] == got[2] and got[0][0] == got[0][1][:512]
     assert taken[2] - taken[1] <= 512 * (N * 2 * 33 + N * S) * 256 + (8 << 20), taken
+
+
+@pytest.mark.parametrize("dtype,N,S,few,many", [("bf16", 5, 20, 128, 129), ("f32", 7, 5, 176, 177)])
+def test_large_batches_keep_to_the_other_forms(dtype, N, S, few, many):
+    """Batches on both sides of the line up to which the launch is faster: one runs in it and one does not, with the same results."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=many, vocab=32, d=128, hidden=128), dtype=dtype)
+    model, offsets, enc = build_case(shape, n_utts=many, lengths=np.array([1 + i % 23 for i in range(many)]))
+    kw = dict(rounds_capacity=4 * S) if S > 16 else {}
+    tbs = make_tbs(shape, model, offsets, N, S, **kw)
+    got = []
+    for U in (few, many):
+        got.append(tbs.decode(tbs.upload_frames(enc[:offsets[U]]), offsets[:U + 1]))
+        assert tbs.one_launch()["may"] == (U == few) and (tbs.one_launch()["segments"] > 0) == (U == few)
+    tbs.close()
+    assert got[0] == got[1][:few]
