@@ -415,7 +415,9 @@ __device__ __forceinline__ void expand_best(float (&v)[NV4 * 4], ExpandBest<TT /
 // expansion relative to the hypothesis score, cs / ct = logarithms and tokens of the N best
 // expansions in order (-inf / -1 where there are fewer); any of them may point into LDS.
 // live = false: a team with no hypothesis; it only keeps the workgroup's barriers company (a team of one wave has none).
-template <int NV4, int SMAX, int TT>
+// TIGHT: one row after the other also for a team of one wave, where no barrier keeps the compiler from it: the partial results of
+// many rows at once cost registers, and those the waves in flight where several workgroups share a CU.
+template <int NV4, int SMAX, int TT, bool TIGHT = false>
 __device__ __forceinline__ void expand_front(float (&e)[SMAX][NV4 * 4], float (&cf)[SMAX], const ExpandPair<SMAX> &pi,
                                              ExpandShared<SMAX, TT / 64> &sm, const Dims &d, int tid, bool live,
                                              float *lc_out, float *dphi_out, float *__restrict__ row_stats) {
@@ -437,6 +439,7 @@ __device__ __forceinline__ void expand_front(float (&e)[SMAX][NV4 * 4], float (&
     if constexpr (TW == 1) {
 #pragma unroll
         for (int t = 0; t < SMAX; ++t) mrow[t] = wave_max_ord(mrow[t]);   // (uniform)
+        if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     } else {
 #pragma unroll
         for (int t = 0; t < SMAX; ++t) {
@@ -473,10 +476,12 @@ __device__ __forceinline__ void expand_front(float (&e)[SMAX][NV4 * 4], float (&
             z += (tid + TT * q < V4) ? zq : 0.f;
         }
         zrow[t] = wave_sum(z);
+        if (TIGHT) __builtin_amdgcn_sched_barrier(0);
         if constexpr (TW > 1)
             if (lane == 0) sm.pz[t][wave] = zrow[t];
     }
     if constexpr (TW > 1) __syncthreads();
+    else if (TIGHT) __builtin_amdgcn_sched_barrier(0);
     // ---- every thread: row sums, forward variable (Eq. 3 as a scan), Eq. 7, the row coefficients.
     // The scan runs on logarithms: la_t = log alpha_t = logaddexp(la_{t-1} + log b_{t-1}, log d_old[t]),
     // which has the range the products of Eq. 3 need (see ScanAlpha) at four transcendentals and a
@@ -496,8 +501,8 @@ __device__ __forceinline__ void expand_front(float (&e)[SMAX][NV4 * 4], float (&
                     z = sm.pz[t][0];
 #pragma unroll
                     for (int w = 1; w < TW; ++w) z += sm.pz[t][w];
-                    __builtin_amdgcn_sched_barrier(0);
                 }
+                if (TW > 1 || TIGHT) __builtin_amdgcn_sched_barrier(0);
                 const float lz = __logf(z);
                 const float nm = -mrow[t] * 1.44269504088896341f;     // (as in e)
                 const float lb = fmaf(fmaf(pi.lblank[t], 1.44269504088896341f, nm), 0.69314718055994531f, -lz);   // log of the blank probability of frame t

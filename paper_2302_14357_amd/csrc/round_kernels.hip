@@ -79,7 +79,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool sel_wave = own_wave ? (int)threadIdx.x >= N * TT : (int)threadIdx.x < WAVE;
     const int sel_lane = (int)threadIdx.x & 63;
     __shared__ SelectOut s_out;
-    __shared__ SelectShared<> s_select;
+    TBS_SELECT_ARRAYS(s_select);
     // Slot layout: everything the round has to know of the utterance lies side by side and comes
     // with one request.  What the kernel before this one wrote is asked for by the vector unit, a lane
     // per value, and handed to the scalar registers by lane reads: a request of the scalar unit for
@@ -155,7 +155,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     float4 hpar[HP];
     if (own_wave && sel_wave) {
         select_merge_utt(s_select, 1, d, round, drop, u, sel_lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
-        if constexpr (S1NP == 0) {
+        if constexpr (S1NP == 0 && SLOTS != 0) {
             // the blank expansions are there long before the N best are: they are merged meanwhile
             __syncthreads();
             select_merge_utt(s_select, 4, d, round, drop, u, sel_lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
@@ -251,8 +251,8 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
                 }
         }
         float cf[SMAX];
-        expand_front<NV4, SMAX, 64>(e, cf, pi, teams[team], d, tid, live, s_lc + team * sp, s_dphi + team, row_stats);
-        __syncthreads();
+        expand_front<NV4, SMAX, 64, SLOTS == 0>(e, cf, pi, teams[team], d, tid, live, s_lc + team * sp, s_dphi + team, row_stats);
+        if (SLOTS) __syncthreads();
         expand_back<NV4, SMAX, 64>(e, cf, pi, teams[team], d, tid, live, s_cs + team * N, s_ct + team * N, delta_nb);
     }
     __syncthreads();
@@ -267,9 +267,12 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     }
     // Behind the expansion the workgroup's first wave, idle by now, ranks the candidates; the select wave, which has merged the
     // blank expansions into B and found the threshold (it needs nothing else of the expansion), goes on when that is done.
+    // (Row lists, where workgroups share a CU and the waves of one need no barrier to stay together: merged only now.  With the barrier
+    // and without TIGHT above, 89 registers instead of 76, 600 utterances N = 11 S = 3 took 53 us a launch instead of 38, N = 9 S = 2 36
+    // instead of 26, 300 of N = 8 S = 5 21 instead of 16.)
     const float *lg = S1NP > 0 ? nullptr : logits;   // (no logits: d of a new hypothesis over one frame is (1))
     if (own_wave) {
-        if (S1NP > 0 && sel_wave)
+        if ((S1NP > 0 || SLOTS == 0) && sel_wave)
             select_merge_utt(s_select, 4, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
         else if ((int)threadIdx.x < WAVE)
             select_merge_utt(s_select, 3, d, round, drop, u, sel_lane, LogitsPlain{lg}, in, fg, A, An, B, rv, nodes, s_raw, &s_out, FEW, true);
