@@ -86,7 +86,7 @@ struct tbs_ctx {
     bool xcd_shape;     // the context's shapes and device can run it
     bool xcd_ready;     // ... and debug bit 16 does not keep it from it
     bool xcd;           // the current batch does, where the GPU is free for it
-    // Batches of such contexts add up in the launch's order in every form (long segments' shares of Eq. 6, the bias of large
+    // Batches that the launch may decode add up in its order in every form (long segments' shares of Eq. 6, the bias of large
     // products), so that results do not hang on what else the GPU is doing.
     bool xcd_sums;
     XcdCtl *x_ctl;      // [2], used in turn: a launch clears the next one's
@@ -490,13 +490,13 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
                        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg->device_id) == hipSuccess &&
                        cus == XR_XCDS * XR_WGS;
         c->xcd_ready = c->xcd_shape && !(cfg->debug & 65536);
+        if (c->xcd_shape) c->x_gates_stay = cfg->dtype == 1 || xcd_f32_gates_stay(d);
     }
     if (c->xcd_ready && rc == 0) {
         // (for as many utterances as it decodes, however many a batch of row lists may have; a context that gets no memory for it
         // goes without)
         const long xu = std::min(U, (long)XR_XCDS * XR_POS);
         c->x_lds = xcd_lds_bytes(cfg->dtype, d);
-        c->x_gates_stay = cfg->dtype == 1 || xcd_f32_gates_stay(d);
         c->x_hb_bytes = xu * 2 * (d.R + 1) * d.N * xcd_row_bytes(cfg->dtype, d.H);
         int none = dev_alloc(c, &c->x_ctl, 2);
         none |= dev_alloc(c, &c->x_desc, xu * d.N);
@@ -790,14 +790,14 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->n_frames = frames;
     c->state = ST_BEGUN;
     c->trie_full = false;
-    c->xcd_sums = c->xcd_shape && U <= XR_XCDS * XR_POS;
+    const bool pays = U <= XR_XCDS * XR_POS && xcd_pays(c->cfg.dtype == 0, c->x_gates_stay, c->cur.N, c->cur.S, (U + XR_XCDS - 1) / XR_XCDS);
+    c->xcd_sums = c->xcd_shape && pays;
     c->fixed = fixed_layout_ok(c);
     c->s1 = c->fixed && one_frame_ok(c);
     // (Beyond the slot layout the batch would have row lists, whose one trie serves all: where its shares may not hold what
     // that holds it goes without this form, and a decode whose share was full all the same is run again, see tbs_decode.)
     const bool shares = !c->streaming && c->trie_share >= 4.0 * c->cur.N && c->trie_share > c->full_share;
-    c->xcd = c->xcd_ready && (c->fixed ? !c->s1 : shares) && U <= XR_XCDS * XR_POS &&
-             xcd_pays(c->cfg.dtype == 0, c->x_gates_stay, c->cur.N, c->cur.S, (U + XR_XCDS - 1) / XR_XCDS);
+    c->xcd = c->xcd_ready && (c->fixed ? !c->s1 : shares) && pays;
     return TBS_OK;
 }
 

@@ -1635,7 +1635,8 @@ def test_memory_of_the_launch_ends_with_its_utterances():
 
 @pytest.mark.parametrize("dtype,N,S,few,many", [("bf16", 5, 20, 128, 129), ("f32", 7, 5, 176, 177)])
 def test_large_batches_keep_to_the_other_forms(dtype, N, S, few, many):
-    """Batches on both sides of the line up to which the launch is faster: one runs in it and one does not, with the same results."""
+    """Batches on both sides of the line up to which the launch is faster: one runs in it and one does not.  (A batch beyond the line
+    adds up in the order of its own forms, whoever else is on the GPU: the same hypotheses, scores to the last digits.)"""
     import dataclasses
     shape = dataclasses.replace(small_bf16_shape(n_utts=many, vocab=32, d=128, hidden=128), dtype=dtype)
     model, offsets, enc = build_case(shape, n_utts=many, lengths=np.array([1 + i % 23 for i in range(many)]))
@@ -1646,4 +1647,6 @@ def test_large_batches_keep_to_the_other_forms(dtype, N, S, few, many):
         got.append(tbs.decode(tbs.upload_frames(enc[:offsets[U]]), offsets[:U + 1]))
         assert tbs.one_launch()["may"] == (U == few) and (tbs.one_launch()["segments"] > 0) == (U == few)
     tbs.close()
-    assert got[0] == got[1][:few]
+    for a, b in zip(got[0], got[1]):
+        assert [h[0] for h in a] == [h[0] for h in b]
+        np.testing.assert_allclose([h[1] for h in a], [h[1] for h in b], rtol=1e-6, atol=1e-5)
