@@ -492,28 +492,6 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         c->xcd_ready = c->xcd_shape && !(cfg->debug & 65536);
         if (c->xcd_shape) c->x_gates_stay = cfg->dtype == 1 || xcd_f32_gates_stay(d);
     }
-    if (c->xcd_ready && rc == 0) {
-        // (for as many utterances as it decodes, however many a batch of row lists may have; a context that gets no memory for it
-        // goes without)
-        const long xu = std::min(U, (long)XR_XCDS * XR_POS);
-        c->x_lds = xcd_lds_bytes(cfg->dtype, d);
-        c->x_hb_bytes = xu * 2 * (d.R + 1) * d.N * xcd_row_bytes(cfg->dtype, d.H);
-        int none = dev_alloc(c, &c->x_ctl, 2);
-        none |= dev_alloc(c, &c->x_desc, xu * d.N);
-        const long n[3] = {c->x_hb_bytes,
-                           (xu * d.N * d.S + 16 * XR_XCDS) * xcd_row_bytes(cfg->dtype, d.Dj),   // (every XCD's rows in whole tiles of 16)
-                           xcd_frag_bytes(cfg->dtype, 4 * d.H, d.H)};
-        void **to[3] = {&c->x_hb, &c->x_amat, &c->x_frags};
-        long all = 0;
-        for (int i = 0; i < 3; ++i) all += (n[i] + 255) & ~255l;
-        char *p = nullptr;
-        none |= dev_alloc(c, &p, (size_t)all);
-        if (none) c->xcd_ready = false;
-        for (int i = 0; i < 3 && !none; ++i) {
-            *to[i] = p;
-            p += (n[i] + 255) & ~255l;
-        }
-    }
     c->res_max_len = cfg->max_result_len > 0 ? cfg->max_result_len : 256;
     const size_t res_bytes = (size_t)UN * (sizeof(double) + sizeof(int) * (1 + (size_t)c->res_max_len)) + sizeof(int) * U;
     const bool res_pinned = res_bytes <= TBS_RES_PINNED;
@@ -537,6 +515,28 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         if (rc) {
             tbs_free(c);
             return TBS_ENOMEM;
+        }
+    }
+    if (c->xcd_ready) {
+        // (last, and for as many utterances as it decodes, however many a batch of row lists may have; a context that gets no memory for
+        // it goes without)
+        const long xu = std::min(U, (long)XR_XCDS * XR_POS);
+        c->x_lds = xcd_lds_bytes(cfg->dtype, d);
+        c->x_hb_bytes = xu * 2 * (d.R + 1) * d.N * xcd_row_bytes(cfg->dtype, d.H);
+        int none = dev_alloc(c, &c->x_ctl, 2);
+        none |= dev_alloc(c, &c->x_desc, xu * d.N);
+        const long n[3] = {c->x_hb_bytes,
+                           (xu * d.N * d.S + 16 * XR_XCDS) * xcd_row_bytes(cfg->dtype, d.Dj),   // (every XCD's rows in whole tiles of 16)
+                           xcd_frag_bytes(cfg->dtype, 4 * d.H, d.H)};
+        void **to[3] = {&c->x_hb, &c->x_amat, &c->x_frags};
+        long all = 0;
+        for (int i = 0; i < 3; ++i) all += (n[i] + 255) & ~255l;
+        char *p = nullptr;
+        none |= dev_alloc(c, &p, (size_t)all);
+        if (none) c->xcd_ready = false;
+        for (int i = 0; i < 3 && !none; ++i) {
+            *to[i] = p;
+            p += (n[i] + 255) & ~255l;
         }
     }
     // Pinned memory, in one allocation: the row lists' counts, the slot layout's words, a batch's figures, a push's
