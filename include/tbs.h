@@ -103,7 +103,9 @@ typedef struct tbs_config {
                                  measured faster; tests cover each pair of variants); bit 16: four kernels a round also
                                  where whole segments would run inside one launch (tbs_path bit 2; so does any
                                  other bit but 17); bit 17: that launch waits for a workgroup that does not exist, so that it
-                                 gives up as where the GPU is not free for it */
+                                 gives up as where the GPU is not free for it; bit 18: the predictor step
+                                 multiplies the recurrent weights by the state of every new hypothesis' parent,
+                                 also where it would do so once for every parent */
     int32_t stream_buffer_frames; /* per-utterance capacity, in frames, of the buffer tbs_push_segment
                                  collects encoder frames in; 0 = no streaming.  At least seg_s; one
                                  push may bring an utterance up to this many minus seg_s - 1 frames */

@@ -52,6 +52,7 @@ __global__ void k_init_batch(Dims d, BView B, AView A0, AView A1, RowView rv, in
             rv.counts[TBS_CNT_NODE_BASE] = 1;
             rv.counts[TBS_CNT_ACC_CALLS] = 0;
             rv.counts[TBS_CNT_ACC_JOINED] = 0;
+            rv.counts[TBS_CNT_PARS] = 0;
         }
     }
     for (int j = tid; j < d.Dj; j += blockDim.x) pool_p[(long)slot * d.Dj + j] = pred_init[j];
@@ -319,27 +320,33 @@ __device__ __forceinline__ int wave_sum_int(int v) {
 
 __device__ __forceinline__ void rowfill_lists(const Dims &d, int seg, const int *utt_off, AView A, RowView rv, int2 *nodes,
                                               int assign_nodes, int *host_counts, int seq, int u, int lane, bool share,
-                                              int *s_pslot, int *s_pair0, int *s_cnt) {
+                                              bool by_parent, int *s_pslot, int *s_pair0, int *s_cnt) {
     // trie nodes handed out so far: launches alternate between two slots, so that the first
     // workgroup can store the new figure while others still read the old one
     const int slot_old = (seq & 1) ? TBS_CNT_NODE_BASE : TBS_CNT_NODES;
     const int slot_new = (seq & 1) ? TBS_CNT_NODES : TBS_CNT_NODE_BASE;
+    const bool by_list = A.parents != nullptr;   // (the parents of the new hypotheses are wanted)
     const int node_base = rv.counts[slot_old];
     const int frame0 = utt_off[u] + seg * d.S;
     // what the fill below needs of this utterance's hypotheses, lane h holding hypothesis h:
     // requested together with the counts, so the kernel costs one memory round trip, not two
     const long ah = (long)u * d.N + min(lane, d.N - 1);
     const int h_slot = A.slot[ah], h_pslot = A.pslot[ah], h_tok = A.token[ah], h_pnode = A.pnode[ah];
-    int before_p = 0, before_r = 0, tot_p = 0, tot_r = 0, utts = 0, frames = 0, my_sp = 0, my_cnt = 0;
+    int before_p = 0, before_r = 0, tot_p = 0, tot_r = 0, utts = 0, frames = 0, my_sp = 0, my_cnt = 0, before_q = 0, tot_q = 0;
+    // (every request is made whatever the others bring, four turns at a time: 1024 utterances 12.7 -> 6.8 us a launch)
+    const int *parents = by_list ? A.parents : A.count;
+#pragma unroll 4
     for (int base = 0; base < d.U; base += WAVE) {
-        const int v = base + lane;
-        const int sp = v < d.U ? rv.utt_sp[v] : 0;
-        const int c = (v < d.U && sp > 0) ? A.count[v] : 0;
-        const int r = c * sp;
-        if (v < u) { before_p += c; before_r += r; }
+        const int v = base + lane, vc = min(v, d.U - 1);
+        const int v_sp = rv.utt_sp[vc], v_cnt = A.count[vc], v_par = parents[vc];
+        const int sp = v < d.U ? v_sp : 0;
+        const int c = sp > 0 ? v_cnt : 0;
+        const int r = c * sp, q = c > 0 ? v_par : 0;
+        if (v < u) { before_p += c; before_r += r; before_q += q; }
         if (v == u) { my_sp = sp; my_cnt = c; }
         tot_p += c;
         tot_r += r;
+        tot_q += q;
         utts += c > 0;
         frames += c > 0 ? sp : 0;
     }
@@ -350,6 +357,7 @@ __device__ __forceinline__ void rowfill_lists(const Dims &d, int seg, const int 
         tot_r = wave_sum_int(tot_r);
         utts = wave_sum_int(utts);
         frames = wave_sum_int(frames);
+        tot_q = by_list ? wave_sum_int(tot_q) : 0;
         if (lane == 0) {
             int err = rv.counts[TBS_CNT_ERR];
             int nodes_used = node_base;
@@ -366,6 +374,7 @@ __device__ __forceinline__ void rowfill_lists(const Dims &d, int seg, const int 
             if (host_counts) {
                 store_host(host_counts + TBS_CNT_ACC_CALLS, acc_calls);
                 store_host(host_counts + TBS_CNT_ACC_JOINED, acc_joined);
+                store_host(host_counts + TBS_CNT_PARS, tot_q);
                 store_host(host_counts + TBS_CNT_PAIRS, tot_p);
                 store_host(host_counts + TBS_CNT_ROWS, tot_r);
                 store_host(host_counts + TBS_CNT_NODES, nodes_used);
@@ -375,6 +384,7 @@ __device__ __forceinline__ void rowfill_lists(const Dims &d, int seg, const int 
                 __builtin_amdgcn_s_waitcnt(0);   // the figures are acknowledged before their number goes out
                 store_host(host_counts + TBS_CNT_SEQ, seq);
             }
+            rv.counts[TBS_CNT_PARS] = tot_q;
             rv.counts[TBS_CNT_PAIRS] = tot_p;
             rv.counts[TBS_CNT_ROWS] = tot_r;
             rv.counts[slot_new] = nodes_used;
@@ -386,6 +396,22 @@ __device__ __forceinline__ void rowfill_lists(const Dims &d, int seg, const int 
     if (lane == 0) {
         rv.utt_pair0[u] = pair0;
         rv.utt_row0[u] = row0;
+    }
+    // the hypotheses that this utterance's new ones were made from, in the order of their first ones
+    int par0 = 0, n_par = 0, par_of = -1;
+    if (by_list) {
+        par0 = wave_sum_int(before_q);
+        int first_of = lane;   // the first new hypothesis with this one's parent
+        for (int g = cnt - 1; g >= 0; --g)
+            if (__builtin_amdgcn_readlane(h_pslot, g) == h_pslot) first_of = g;
+        const u64 firsts = __ballot(lane < cnt && first_of == lane);
+        n_par = __popcll(firsts);
+        par_of = __popcll(firsts & ((1ull << first_of) - 1ull));
+        if (lane < cnt) {
+            rv.pair_par[pair0 + lane] = par0 + par_of;
+            if (first_of == lane) rv.par_slot[par0 + par_of] = h_pslot;
+        }
+        if (share && by_parent && lane < cnt && first_of == lane) s_pslot[par_of] = h_pslot;
     }
     for (int base = 0; base < cnt * sp; base += WAVE) {   // (cnt and sp are the same in every lane)
         const int idx = base + lane;
@@ -420,18 +446,17 @@ __device__ __forceinline__ void rowfill_lists(const Dims &d, int seg, const int 
         }
     }
     if (share) {   // for the other waves of the workgroup
-        if (lane < d.N) s_pslot[lane] = h_pslot;
+        if (!by_parent && lane < d.N) s_pslot[lane] = h_pslot;
         if (lane == 0) {
-            *s_pair0 = pair0;
-            *s_cnt = cnt;
+            *s_pair0 = by_parent ? par0 : pair0;
+            *s_cnt = by_parent ? n_par : cnt;
         }
     }
 }
 
-// With gather_h not null the workgroup has four waves: the first does all of the above, then all
-// four write the first LSTM layer's input rows of this utterance's new hypotheses,
-// gather_xh[pair, :] = bf16(h of the parent), which would otherwise take a kernel of its own between
-// this one and the gate GEMM.
+// With `gather` the workgroup has four waves: the first does all of the above, then all
+// four write the rows of h that the gate products of this utterance's new hypotheses read (see HidRows), which would otherwise
+// take a kernel of its own between this one and the gate GEMM.
 __device__ __forceinline__ unsigned rowfill_bf16(float f) {
     unsigned v = __float_as_uint(f);
     v += 0x7FFFu + ((v >> 16) & 1u);   // round to nearest, ties to even
@@ -440,40 +465,42 @@ __device__ __forceinline__ unsigned rowfill_bf16(float f) {
 
 __global__ void __launch_bounds__(256)
 k_rowfill(Dims d, int seg, const int *utt_off, AView A, RowView rv, int2 *nodes, int assign_nodes, int *host_counts,
-          int seq, const float *gather_h, bf16_t *gather_xh) {
+          int seq, HidRows gather) {
     __shared__ int s_pslot[TBS_MAX_BEAM];
-    __shared__ int s_pair0, s_cnt;
+    __shared__ int s_row0, s_rows;
     const int u = blockIdx.x;
     if (threadIdx.x < WAVE) rowfill_lists(d, seg, utt_off, A, rv, nodes, assign_nodes, host_counts, seq, u, threadIdx.x,
-                                          gather_h != nullptr, s_pslot, &s_pair0, &s_cnt);
-    if (gather_h == nullptr) return;   // (one wave launched)
+                                          gather.out != nullptr, gather.parents != 0, s_pslot, &s_row0, &s_rows);
+    if (gather.out == nullptr) return;   // (one wave launched)
     __syncthreads();
-    const int cnt = s_cnt, pair0 = s_pair0, H4 = d.H >> 2, total = cnt * H4;
-    for (int base = threadIdx.x; base < total; base += 256 * 4) {
-        float4 v[4];
-        int at[4];
+    const int row0 = s_row0, H4 = d.H >> 2, total = s_rows * H4;
+    for (int l = 0; l < (gather.parents ? d.L : 1); ++l) {
+        const float *src = gather.pool_h + l * gather.pool_rows * d.H;
+        uint2 *dst = static_cast<uint2 *>(gather.out) + l * gather.stride * H4;
+        for (int base = threadIdx.x; base < total; base += 256 * 4) {
+            float4 v[4];
+            int at[4];
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int idx = min(base + k * 256, total - 1);
-            const int h = idx / H4, i = idx - h * H4;
-            v[k] = reinterpret_cast<const float4 *>(gather_h + (long)s_pslot[h] * d.H)[i];
-            at[k] = (pair0 + h) * H4 + i;
+            for (int k = 0; k < 4; ++k) {
+                const int idx = min(base + k * 256, total - 1);
+                const int h = idx / H4, i = idx - h * H4;
+                v[k] = reinterpret_cast<const float4 *>(src + (long)s_pslot[h] * d.H)[i];
+                at[k] = (row0 + h) * H4 + i;
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (base + k * 256 < total)
+                    dst[at[k]] = make_uint2(rowfill_bf16(v[k].x) | (rowfill_bf16(v[k].y) << 16),
+                                            rowfill_bf16(v[k].z) | (rowfill_bf16(v[k].w) << 16));
         }
-#pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (base + k * 256 < total)
-                reinterpret_cast<uint2 *>(gather_xh)[at[k]] =
-                    make_uint2(rowfill_bf16(v[k].x) | (rowfill_bf16(v[k].y) << 16),
-                               rowfill_bf16(v[k].z) | (rowfill_bf16(v[k].w) << 16));
     }
 }
 
 hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt_off, AView A, RowView rv,
-                          int2 *nodes, int assign_nodes, int *host_counts, int seq, const float *gather_h,
-                          bf16_t *gather_xh) {
-    if (gather_h && (d.H & 3)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_rowfill, dim3(d.U), dim3(gather_h ? 256 : WAVE), 0, st, d, seg, utt_off, A, rv, nodes,
-                       assign_nodes, host_counts, seq, gather_h, gather_xh);
+                          int2 *nodes, int assign_nodes, int *host_counts, int seq, const HidRows *gather) {
+    if (gather && ((d.H & 3) || (gather->parents && !A.parents))) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_rowfill, dim3(d.U), dim3(gather ? 256 : WAVE), 0, st, d, seg, utt_off, A, rv, nodes,
+                       assign_nodes, host_counts, seq, gather ? *gather : HidRows{});
     return hipGetLastError();
 }
 

@@ -45,6 +45,7 @@ __global__ void __launch_bounds__(1024)
 k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, AView An, BView B, RowView rv,
         int2 *nodes, float *__restrict__ row_stats_arg, float *__restrict__ delta_nb_arg, FixedView fx, int tiles_n) {
     const bool on = SLOTS || fx.on;
+    if (on) An.parents = nullptr;   // (the row lists' predictor step asks for them)
     constexpr bool FEW = SLOTS == 2;
     float *row_stats = SLOTS ? nullptr : row_stats_arg, *delta_nb = SLOTS ? nullptr : delta_nb_arg;
     constexpr int TT = 64;

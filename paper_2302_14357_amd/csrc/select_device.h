@@ -401,6 +401,12 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
                 An.count[u] = total;
                 if (out) out->total = total;
             }
+            if (An.parents) {   // (row lists: how many hypotheses the new ones come from)
+                const int h = keep ? (int)(((float)s_sel[lane] + 0.5f) * rcp_n) : -1;
+                int n = 0;
+                for (int g = 0; g < H; ++g) n += __ballot(h == g) != 0;
+                if (lane == 0) An.parents[u] = n;
+            }
             const bool by_frame = !FEW && !SHORT && !logits.none() && sel_dist_form(nc, sp) == SEL_BY_FRAME;
             if (keep) {
                 const int c = s_sel[lane];

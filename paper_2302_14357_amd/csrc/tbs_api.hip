@@ -122,6 +122,12 @@ struct tbs_ctx {
     void *xh[2];
     void *htop;
     float *gates;
+    // row lists: the recurrent half of the gates by parents (see by_parent): input rows [layers, U*N, H] (xh[0] where it
+    // holds them) and the products of layers >= 1, [layers - 1, U*N, 4H]; layer 0's go to `gates`
+    bool hid_ok;        // there is memory for them, and the weights are aligned as the products read them
+    bool hid;           // this round's are formed so
+    void *xpar;
+    float *hid_gates;
 
     int *h_begin, *h_begin_dev;   // pinned: what tbs_begin tells the kernels of a batch's utterances (see launch_init_batch)
 
@@ -201,6 +207,7 @@ int dev_alloc(tbs_ctx *c, T **p, size_t n) {
 int alloc_aview(tbs_ctx *c, AView *a, long UN, int S, int U) {
     int rc = 0;
     rc |= dev_alloc(c, &a->count, U);
+    rc |= dev_alloc(c, &a->parents, U);
     rc |= dev_alloc(c, &a->logs, UN);
     rc |= dev_alloc(c, &a->node, UN);
     rc |= dev_alloc(c, &a->hash, UN);
@@ -406,6 +413,8 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     rc |= dev_alloc(c, &c->rv.pair_pslot, UN);
     rc |= dev_alloc(c, &c->rv.pair_frame0, UN);
     rc |= dev_alloc(c, &c->rv.pair_tok, UN);
+    rc |= dev_alloc(c, &c->rv.pair_par, UN);
+    rc |= dev_alloc(c, &c->rv.par_slot, UN);
     rc |= dev_alloc(c, &c->rv.utt_sp, U);
     rc |= dev_alloc(c, &c->rv.utt_par, U);
     rc |= dev_alloc(c, &c->rv.pair_u, UN);
@@ -538,6 +547,20 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
             *to[i] = p;
             p += (n[i] + 255) & ~255l;
         }
+    }
+    // (a context that gets no memory for it forms the gates of every hypothesis whole)
+    c->hid_ok = d.N > 1;
+    c->hid = false;
+    c->xpar = c->xh[0];
+    c->hid_gates = nullptr;
+    for (int l = 1; l < d.L; ++l)
+        if ((reinterpret_cast<uintptr_t>(w->w_ih[l]) | reinterpret_cast<uintptr_t>(w->w_hh[l])) & 15) c->hid_ok = false;
+    if (c->hid_ok && d.L > 1) {
+        char *p = nullptr;
+        if (dev_alloc(c, &c->hid_gates, (size_t)(d.L - 1) * UN * 4 * d.H) ||
+            (d.L > 2 && dev_alloc(c, &p, (size_t)d.L * UN * d.H * elem_bytes(c))))
+            c->hid_ok = false;
+        if (p) c->xpar = p;
     }
     // Pinned memory, in one allocation: the row lists' counts, the slot layout's words, a batch's figures, a push's
     // descriptors, the ends of a launch over whole segments, small results.
@@ -786,6 +809,7 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->pred_ahead = 0;
     c->join_ahead = false;
     c->expanded_ahead = false;
+    c->hid = false;
     c->n_launches = 0;
     c->n_frames = frames;
     c->state = ST_BEGUN;
@@ -844,7 +868,8 @@ static int segment_begin(tbs_ctx *c, int32_t seg_index, int32_t *rows_host) {
     c->round = 0;
     c->pred_ahead = 0;
     c->join_ahead = false;
-    AView &A = c->A[c->a_cur];
+    AView A = c->A[c->a_cur];
+    A.parents = nullptr;   // (they are carried into the segment)
     HIPCHK(c, launch_segment_begin(c->stream, c->cur, c->seg, c->utt_T, c->B, A, c->rv, c->pool_p, c->pool_h,
                                    c->pool_c, c->pool_rows));
     HIPCHK(c, launch_rowfill(c->stream, c->cur, c->seg, c->utt_off, A, c->rv, c->nodes, 0, c->h_counts_dev, ++c->seq));
@@ -980,6 +1005,22 @@ static bool round_fused_ok(const tbs_ctx *c) {
 
 static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused);
 
+// Does the predictor step of a round that makes at most M hypotheses form the recurrent half of the gates by parents (see
+// pred_kernels.hip)?  Wherever it would have to pass the gates through memory in any case; a layer small enough for the product
+// that updates the cell itself has that instead.  (Debug bit 18: never.)
+static bool by_parent(const tbs_ctx *c, int M) {
+    if (!c->hid_ok || (c->cfg.debug & (1 << 18))) return false;
+    for (int l = 0; l < c->cur.L && !(c->cfg.debug & 8); ++l)
+        if (lstm_small(c, M, l, false)) return false;
+    return true;
+}
+static HidRows hid_rows(const tbs_ctx *c) {
+    return {c->pool_h, c->hid ? c->xpar : c->xh[0], c->pool_rows, (long)c->d.U * c->d.N, c->hid};
+}
+static bool gather_in_rowfill(const tbs_ctx *c) {
+    return c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 && (long)c->cur.U * c->cur.N <= 1024;
+}
+
 int tbs_select_merge(tbs_ctx *c, int32_t *live_host) {
     if (!c) return TBS_EINVAL;
     if (c->state != ST_EXPANDED) return TBS_ESTATE;
@@ -989,9 +1030,15 @@ int tbs_select_merge(tbs_ctx *c, int32_t *live_host) {
 
 // fused: the state is "joined"; one kernel runs the expansion and select/merge
 static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
-    AView &A = c->A[c->a_cur], &An = c->A[c->a_cur ^ 1];
+    const AView A = c->A[c->a_cur];
+    AView An = c->A[c->a_cur ^ 1];
     const int drop = c->cfg.max_rounds_per_segment > 0 && c->round >= c->cfg.max_rounds_per_segment;
     bool gathered = false;
+    // (the utterances that take part in this round are the most that can in the next)
+    const int most = std::min(c->cur.U, c->h_counts[TBS_CNT_UTTS]) * c->cur.N;
+    c->hid = by_parent(c, most);
+    if (!c->hid) An.parents = nullptr;
+    const HidRows rows = hid_rows(c);
     {
         ProfScope ps(c, fused ? TBS_K_ROUND : TBS_K_SELECT, c->h_counts[TBS_CNT_PAIRS]);
         if (fused)
@@ -1000,20 +1047,17 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
         else
             HIPCHK(c, launch_select_merge(c->stream, c->cur, c->round, drop, c->logits, c->row_lc, c->dphi,
                                           c->cand_score, c->cand_tok, A, An, c->B, c->rv, c->nodes));
-        // small batches: the row list kernel also writes the first LSTM layer's input rows
-        const bool fused_gather = c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 &&
-                                  (long)c->cur.U * c->cur.N <= 1024;
+        // small batches: the row list kernel also writes the rows of h that the predictor step reads
+        gathered = gather_in_rowfill(c);
         HIPCHK(c, launch_rowfill(c->stream, c->cur, c->seg, c->utt_off, An, c->rv, c->nodes, 1, c->h_counts_dev,
-                                 ++c->seq, fused_gather ? c->pool_h : nullptr,
-                                 fused_gather ? (bf16_t *)c->xh[0] : nullptr));
-        gathered = fused_gather;
+                                 ++c->seq, gathered ? &rows : nullptr));
     }
     // Otherwise the first kernel of the predictor step goes out before the counts are known, on the
     // largest grid the round could need (it sizes itself from device memory): it runs while the host
     // waits for the counts and enqueues the rest, which would otherwise leave the GPU idle.
     if (!gathered) {
         ProfScope ps(c, TBS_K_PREDICTOR, 0);
-        HIPCHK(c, launch_pred_gather_h(c->stream, c->cur, c->cfg.dtype, c->cur.U * c->cur.N, c->rv, c->pool_h, c->xh[0]));
+        HIPCHK(c, launch_pred_gather_h(c->stream, c->cur, c->cfg.dtype, most, c->rv, rows));
     }
     // Small batches: the LSTM layers of the predictor step go out now, sized for every hypothesis
     // the round could have created and reading the number it did create from device memory.  The
@@ -1059,9 +1103,27 @@ static int64_t predictor_madds(const tbs_ctx *c, int64_t pairs) {   // multiply-
 
 static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const int *any_dev) {   // part: 0 all, 1 the LSTM layers, 2 the projection
     const Dims &d = c->cur;
-    AView &A = c->A[c->a_cur];
-    // (the input rows of the first layer were gathered behind select/merge)
-    for (int l = 0; l < d.L && part != 2; ++l) {
+    const long UN = (long)c->d.U * c->d.N;
+    // (the rows of h were gathered behind select/merge)
+    if (c->hid && part != 2) {
+        if (m_dev || any_dev) return TBS_ESTATE;   // (predictor_all_fused was not asked)
+        const int eb = elem_bytes(c), pars = c->h_counts[TBS_CNT_PARS];
+        for (int l = 0; l < d.L; ++l)
+            HIPCHK(c, gemm(c, (char *)c->xpar + (size_t)l * UN * d.H * eb, c->w.w_hh[l], nullptr,
+                           l == 0 ? c->gates : c->hid_gates + (size_t)(l - 1) * UN * 4 * d.H, pars, 4 * d.H, d.H, nullptr, 4L * d.H));
+        for (int l = 0; l < d.L; ++l) {
+            const bool last = l + 1 == d.L;
+            char *out = last ? (char *)c->htop : (char *)c->xh[1] + (size_t)(l & 1) * UN * d.H * eb;
+            CellIn in{c->gates, c->emb_gates, c->rv.pair_par, c->rv.pair_tok, nullptr, out};
+            if (l > 0) {
+                HIPCHK(c, gemm(c, (char *)c->xh[1] + (size_t)((l - 1) & 1) * UN * d.H * eb, c->w.w_ih[l], c->w.b_lstm[l], c->gates, M,
+                               4 * d.H, d.H, nullptr, 4L * d.H));
+                in = CellIn{c->gates, c->hid_gates + (size_t)(l - 1) * UN * 4 * d.H, nullptr, c->rv.pair_par, nullptr, out};
+            }
+            HIPCHK(c, launch_lstm_pointwise(c->stream, d, c->cfg.dtype, M, l, c->rv, in, c->pool_h, c->pool_c, c->pool_rows));
+        }
+    }
+    for (int l = 0; l < d.L && part != 2 && !c->hid; ++l) {
         const int K = l == 0 ? d.H : 2 * d.H;
         if (!(c->cfg.debug & 8) && lstm_small(c, M, l, c->fixed)) {
             // small problem: the cell update runs in the epilogue of the gate GEMM
@@ -1092,8 +1154,10 @@ static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const
         else
             HIPCHK(c, gemm(c, c->xh[l & 1], c->wcat[l], c->w.b_lstm[l], c->gates, M, 4 * d.H, K, nullptr,
                            4L * d.H));
-        HIPCHK(c, launch_lstm_pointwise(c->stream, d, c->cfg.dtype, M, l, A, c->rv, c->gates, c->pool_h, c->pool_c,
-                                        c->pool_rows, c->xh[(l + 1) & 1], c->htop, l == 0 ? c->emb_gates : nullptr));
+        const bool last = l + 1 == d.L;
+        const CellIn in{c->gates, l == 0 ? c->emb_gates : nullptr, nullptr, c->rv.pair_tok,
+                        last ? nullptr : c->pool_h + (size_t)(l + 1) * c->pool_rows * d.H, last ? c->htop : c->xh[(l + 1) & 1]};
+        HIPCHK(c, launch_lstm_pointwise(c->stream, d, c->cfg.dtype, M, l, c->rv, in, c->pool_h, c->pool_c, c->pool_rows));
     }
     if (part == 1) return TBS_OK;
     if (!(c->cfg.debug & 16) && proj_small(c, M, c->fixed)) {
@@ -1216,7 +1280,8 @@ static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
     const Dims &d = c->cur;
     c->seg = seg_index;
     c->round = 1;
-    AView &A = c->A[c->a_cur], &An = c->A[c->a_cur ^ 1];
+    AView A = c->A[c->a_cur], An = c->A[c->a_cur ^ 1];
+    A.parents = An.parents = nullptr;   // (its layers update the cell inside the products)
     const int *rows_dev = c->rv.counts + TBS_CNT_ROWS, *pairs_dev = c->rv.counts + TBS_CNT_PAIRS;
     // A = ChooseNBest(B), B = [], the row list, the joiner input rows
     HIPCHK(c, launch_segment_begin(c->stream, d, c->seg, c->utt_T, c->B, A, c->rv, c->pool_p, c->pool_h, c->pool_c,
@@ -1236,11 +1301,12 @@ static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
         HIPCHK(c, launch_select_merge(c->stream, d, c->round, drop, c->logits, c->row_lc, c->dphi, c->cand_score,
                                       c->cand_tok, A, An, c->B, c->rv, c->nodes));
     }
-    const bool fused_gather = c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (d.H & 3) == 0 && (long)d.U * d.N <= 1024;
+    c->hid = false;
+    const HidRows gather = hid_rows(c);
+    const bool gathered = gather_in_rowfill(c);
     HIPCHK(c, launch_rowfill(c->stream, d, c->seg, c->utt_off, An, c->rv, c->nodes, 1, c->h_counts_dev, ++c->seq,
-                             fused_gather ? c->pool_h : nullptr, fused_gather ? (bf16_t *)c->xh[0] : nullptr));
-    if (!fused_gather)
-        HIPCHK(c, launch_pred_gather_h(c->stream, d, c->cfg.dtype, d.U * d.N, c->rv, c->pool_h, c->xh[0]));
+                             gathered ? &gather : nullptr));
+    if (!gathered) HIPCHK(c, launch_pred_gather_h(c->stream, d, c->cfg.dtype, d.U * d.N, c->rv, gather));
     c->a_cur ^= 1;
     const int rc = predictor_launch(c, d.U * d.N, pairs_dev);
     if (rc) return rc;
@@ -1927,7 +1993,9 @@ int tbs_debug_rebuild(tbs_ctx *c, int32_t seg_index, int32_t *rows_host) {
     c->round = 0;
     c->prep_ahead = false;
     HIPCHK(c, launch_set_sp(c->stream, c->cur, seg_index, c->utt_T, c->rv));
-    HIPCHK(c, launch_rowfill(c->stream, c->cur, c->seg, c->utt_off, c->A[c->a_cur], c->rv, c->nodes, 0, c->h_counts_dev,
+    AView A = c->A[c->a_cur];
+    A.parents = nullptr;
+    HIPCHK(c, launch_rowfill(c->stream, c->cur, c->seg, c->utt_off, A, c->rv, c->nodes, 0, c->h_counts_dev,
                              ++c->seq));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (rows_host) *rows_host = c->h_counts[TBS_CNT_ROWS];

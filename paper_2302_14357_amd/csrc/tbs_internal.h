@@ -12,6 +12,7 @@ typedef uint16_t bf16_t;  // raw bf16 bit pattern
 // Group A (hypotheses still emitting in this segment), structure of arrays, [U, N].
 struct AView {
     int *count;     // [U]
+    int *parents;   // [U] different hypotheses that those of the list were made from (row lists only; null: not wanted)
     double *logs;   // log score
     int *node;      // trie node of the token sequence
     u64 *hash;      // hash of the token sequence
@@ -45,17 +46,19 @@ struct RowView {
     int *pair_pslot; // [pairs] slot of the hypothesis it was made from (source of the recurrent state)
     int *pair_frame0; // [pairs] row in enc_proj of the pair's first frame of the segment
     int *pair_tok;   // [pairs] last token of the pair's hypothesis (-1 if carried into the segment)
+    int *pair_par;   // [pairs] place of the hypothesis it was made from among the parents ...
+    int *par_slot;   // [parents] ... every hypothesis that new ones were made from, once: its predictor-state slot
     int *row_enc;    // [rows] frame row in enc_proj
     int *row_slot;   // [rows] predictor-state slot
     int *counts;     // [8]: 0 pairs, 1 rows, 2 trie nodes used, 3 error flags, 4 live utterances,
                      //      5 frames joined (sum of S' over live utterances), 6 number of the launch that
                      //      published the figures (host mirror), 7 the other slot of 2 (they alternate),
                      //      8 and 9 running sums of 4 and 5 over the row lists made since the batch began
-                     //      (joiner invocations and frames joined, per utterance summed)
+                     //      (joiner invocations and frames joined, per utterance summed), 10 parents
 };
 
 enum { TBS_CNT_PAIRS = 0, TBS_CNT_ROWS = 1, TBS_CNT_NODES = 2, TBS_CNT_ERR = 3, TBS_CNT_UTTS = 4, TBS_CNT_FRAMES = 5,
-       TBS_CNT_SEQ = 6, TBS_CNT_NODE_BASE = 7, TBS_CNT_ACC_CALLS = 8, TBS_CNT_ACC_JOINED = 9, TBS_CNT_SIZE = 10 };
+       TBS_CNT_SEQ = 6, TBS_CNT_NODE_BASE = 7, TBS_CNT_ACC_CALLS = 8, TBS_CNT_ACC_JOINED = 9, TBS_CNT_PARS = 10, TBS_CNT_SIZE = 11 };
 enum { TBS_ERRF_BCAP = 1, TBS_ERRF_NODES = 2 };
 
 // Slot layout of small shapes: hypothesis i of utterance u is pair j = u*N + i whether or not it
@@ -243,10 +246,17 @@ hipError_t launch_joiner_prep_pairs(hipStream_t st, const Dims &d, int act, cons
                                     RowView rv, bf16_t *amat);
 hipError_t launch_joiner_prep_fixed(hipStream_t st, const Dims &d, int dtype, int act, const void *enc, const float *pool_p,
                                     RowView rv, void *amat);
-// gather_h / gather_xh not null: also writes gather_xh[pair, :] = bf16(gather_h[parent slot, :]) (H wide)
+// Rows of h that the gate products of new hypotheses read, as bf16 or fp32 (fp32 models): row j the parent's of pair j (parents
+// 0, the first layer only), or row p that of parent p, for every layer (out: [layers, stride, H]).
+struct HidRows {
+    const float *pool_h;
+    void *out;
+    long pool_rows, stride;
+    int parents;
+};
+// gather not null (bf16, H a multiple of 4): also writes those rows
 hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt_off, AView A, RowView rv,
-                          int2 *nodes, int assign_nodes, int *host_counts, int seq, const float *gather_h = nullptr,
-                          bf16_t *gather_xh = nullptr);
+                          int2 *nodes, int assign_nodes, int *host_counts, int seq, const HidRows *gather = nullptr);
 // row_begin (bf16 only, with rows_dev): only the rows [*row_begin, *rows_dev), `rows` sizing the launch
 hipError_t launch_joiner_prep(hipStream_t st, const Dims &d, int dtype, int act, int rows, const void *enc,
                               const float *pool_p, RowView rv, void *amat, const int *rows_dev = nullptr,
@@ -326,11 +336,18 @@ bool round_s1_fits(const Dims &d);
 // (tiles_n: partials per row, in column order: the vocabulary's 64-column tiles, or their 16-column pieces)
 hipError_t launch_round_s1(hipStream_t st, const Dims &d, int round, int drop, const float *part, int tiles_n, AView A,
                            AView An, BView B, RowView rv, int2 *nodes, const FixedView *fx);
-hipError_t launch_pred_gather_h(hipStream_t st, const Dims &d, int dtype, int pairs, RowView rv, const float *pool_h,
-                                void *xh);
-hipError_t launch_lstm_pointwise(hipStream_t st, const Dims &d, int dtype, int pairs, int layer, AView A, RowView rv,
-                                 const float *gates, float *pool_h, float *pool_c, long pool_rows, void *xh_next,
-                                 void *htop, const float *emb_gates);
+// rows: the most there can be
+hipError_t launch_pred_gather_h(hipStream_t st, const Dims &d, int dtype, int rows, RowView rv, const HidRows &g);
+// Cell update of one layer: the gates of pair j are ga[ga_row[j]] + gb[gb_row[j]] (row j where a list of rows is null, the first
+// alone where gb is).  out [pairs, H], or with h_par_next [pairs, 2H] = the next layer's input and its parent's h.
+struct CellIn {
+    const float *ga, *gb;
+    const int *ga_row, *gb_row;
+    const float *h_par_next;   // h of the next layer, by state slot
+    void *out;
+};
+hipError_t launch_lstm_pointwise(hipStream_t st, const Dims &d, int dtype, int pairs, int layer, RowView rv, const CellIn &in,
+                                 float *pool_h, float *pool_c, long pool_rows);
 hipError_t launch_finalize(hipStream_t st, const Dims &d, BView B, const int2 *nodes, int *res_count, int *res_len,
                            double *res_logs, int *res_tok, int max_len);
 hipError_t launch_hyps_dump(hipStream_t st, const Dims &d, int group, AView A, BView B, const int2 *nodes, int cap,

@@ -540,7 +540,8 @@ __device__ __forceinline__ void xcd_finish(const XcdPlace &w, XcdShared &sh, SM 
     const XcdArgs &g = xcd_args();
     const XcdScratch<SMAX> sc(scratch, g.d);
     const int drop = g.max_rounds > 0 && round >= g.max_rounds, u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
-    const AView An = g.A[a ^ 1];
+    AView An = g.A[a ^ 1];
+    An.parents = nullptr;   // (the gates of every new hypothesis are formed whole)
     SelectIn in{};
     in.lc = sc.lc;
     in.slot_rows = 1;

@@ -649,6 +649,37 @@ def test_decode_cell_update_inside_and_outside_the_gate_gemm(debug):
     _check_decode(shape, model, offsets, enc, 4, 3, debug=debug)
 
 
+@pytest.mark.parametrize("dtype,hidden,layers,V,U,N,S,debug,peaked", [
+    ("bf16", 64, 1, 96, 6, 5, 3, 256, True), ("bf16", 72, 2, 96, 70, 16, 2, 256, False), ("bf16", 64, 3, 96, 6, 2, 4, 256, True),
+    ("bf16", 128, 4, 96, 5, 32, 3, 256 + 8, False), ("bf16", 128, 2, 2100, 7, 5, 3, 8 + 32, True), ("bf16", 1024, 2, 300, 130, 8, 1, 512, False),
+    ("f32", 36, 2, 60, 5, 4, 5, 256 + 8, True), ("f32", 37, 1, 60, 4, 3, 7, 256 + 8, True), ("f32", 64, 3, 1100, 66, 16, 2, 8, False)])
+def test_recurrent_products_by_parents_equal_those_by_hypothesis(dtype, hidden, layers, V, U, N, S, debug, peaked):
+    """The recurrent half of the gates once per parent (as wherever a layer does not update the cell inside its product) and, with
+    debug bit 18, for every new hypothesis: batches over 1024 hypotheses and under (whose row list kernel gathers the rows), one to
+    four layers, widths that are no whole pieces, beams up to the largest, empty utterances.  One layer is the same sum: the same
+    bits.  More layers add the two halves separately; a gate moves by a few fp32 units, which moves a score by no more than what
+    `tolerance` derives.  And the oracle's results on the default form."""
+    import dataclasses
+    shape = dataclasses.replace(small_bf16_shape(n_utts=U, vocab=V, d=64, hidden=hidden, layers=layers), dtype=dtype)
+    if peaked:
+        shape = _peaked(shape, 8.0, 8.0)
+    lengths = np.random.default_rng(hidden + U).integers(0, 8 if U > 50 else 20, U)
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=lengths)
+    kw = dict(max_rounds_per_segment=5)
+    one, st1 = _gpu_decode(shape, model, offsets, enc, N, S, debug=debug, **kw)
+    two, st2 = _gpu_decode(shape, model, offsets, enc, N, S, debug=debug | (1 << 18), **kw)
+    assert not st1["path"]["fixed_places"]
+    if layers == 1:
+        assert one == two and st1["joiner_calls"] == st2["joiner_calls"]
+    else:
+        tol, score_tol = tolerance(shape, model)
+        close = [u for u, (g, r) in enumerate(zip(one, two)) if [y for y, _ in g] != [y for y, _ in r]]
+        assert len(close) <= U // 8   # (a decision closer than the arithmetic can tell apart)
+        for u, (g, r) in enumerate(zip(one, two)):
+            assert u in close or all(abs(a[1] - b[1]) <= score_tol for a, b in zip(g, r)), u
+    _check_decode(shape, model, offsets, enc, N, S, max_rounds=5, debug=debug)
+
+
 @pytest.mark.parametrize("d,hidden,N,S", [(128, 128, 4, 3), (144, 128, 5, 7), (80, 256, 8, 2)])
 def test_decode_joiner_rows_from_the_projection_epilogue(d, hidden, N, S):
     """Where the predictor projection is a small GEMM its epilogue also forms the joiner input rows
