@@ -80,6 +80,11 @@ k_gemm_bf16(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const fl
         M = me - mb;
         if (M <= 0) return;
         tiles_m = (M + BM - 1) / BM;
+    } else if (m_end) {
+        // enqueued before the host knew the number of rows: M is the most there can be
+        M = min(M, *m_end);
+        if (M <= 0) return;
+        tiles_m = (M + BM - 1) / BM;
     }
     int tile_m, tile_n;
     if (!gemm_tile_of(xcd, idx, tiles_m, tiles_n, group_m, tile_m, tile_n)) return;
@@ -832,13 +837,13 @@ hipError_t launch_gemm_join(hipStream_t st, const bf16_t *A, const bf16_t *B, co
 // 1 = 64x64 tiles, 2 = 128x128, 3 = 256x256 (all k_gemm_bf16), 4 = k_gemm_small
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel, const int *m_dev, bool xcd_rows,
-                            bool bias_late) {
+                            bool bias_late, int m_likely) {
     if (M <= 0) return hipSuccess;
-    if (m_dev && !gemm_small_fits(M, N, K, INT_MAX)) return hipErrorInvalidValue;   // only k_gemm_small reads its row count
+    const int Mc = m_likely > 0 ? min(m_likely, M) : M;   // (the rows that the kernel is chosen for)
     if ((kernel == 0 || kernel == 4) && K % GS_BK == 0) {
         const int tiles_m = (M + 63) / 64, tiles_n = (N + 63) / 64;
         const int ns_max = gemm_small_stages();
-        if (ns_max >= 2 && ((long)tiles_m * tiles_n <= GS_TILES || kernel == 4 || m_dev)) {
+        if (ns_max >= 2 && (gs_tiles(Mc, N) <= GS_TILES || kernel == 4)) {
             const int ns = gs_two_per_cu(tiles_m, tiles_n) ? 2 : (K / GS_BK < ns_max ? (K / GS_BK < 2 ? 2 : K / GS_BK) : ns_max);
             const int grid = xcd_rows ? 8 * ((tiles_m + 7) / 8) * tiles_n : 8 * ((tiles_m + 1) / 2) * ((tiles_n + 3) / 4);
             PartEp pe{};
@@ -853,22 +858,22 @@ hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, co
         // measured on MI355X: 256x256 tiles (8 waves, 128x64 per wave) once they fill the chip 1.5
         // times over, 128x128 (two workgroups per CU) for mid sizes, 64x64 so that small problems
         // still spread over the CUs
-        long t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-        long t128 = (long)((M + 127) / 128) * ((N + 127) / 128);
+        long t256 = (long)((Mc + 255) / 256) * ((N + 255) / 256);
+        long t128 = (long)((Mc + 127) / 128) * ((N + 127) / 128);
         kernel = t256 >= 384 ? 3 : (t128 >= 256 ? 2 : 1);
     }
     if (bias_late && bias) {   // (for the bits of k_gemm_small, whatever the size)
         switch (kernel) {
-            case 1: return gemm_launch<1, 1, 2, 2, 64, 4, true>(st, A, B, bias, C, M, N, K, out_row, ldc);
-            case 2: return gemm_launch<2, 2, 2, 2, 64, 2, true>(st, A, B, bias, C, M, N, K, out_row, ldc);
-            case 3: return gemm_launch<4, 2, 2, 4, 64, 1, true>(st, A, B, bias, C, M, N, K, out_row, ldc);
+            case 1: return gemm_launch<1, 1, 2, 2, 64, 4, true>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);
+            case 2: return gemm_launch<2, 2, 2, 2, 64, 2, true>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);
+            case 3: return gemm_launch<4, 2, 2, 4, 64, 1, true>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);
             default: return hipErrorInvalidValue;
         }
     }
     switch (kernel) {
-        case 1: return gemm_launch<1, 1, 2, 2, 64, 4>(st, A, B, bias, C, M, N, K, out_row, ldc);   // 64x64, 4 waves
-        case 2: return gemm_launch<2, 2, 2, 2, 64, 2>(st, A, B, bias, C, M, N, K, out_row, ldc);   // 128x128, 4 waves
-        case 3: return gemm_launch<4, 2, 2, 4, 64, 1>(st, A, B, bias, C, M, N, K, out_row, ldc);   // 256x256, 8 waves
+        case 1: return gemm_launch<1, 1, 2, 2, 64, 4>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);   // 64x64, 4 waves
+        case 2: return gemm_launch<2, 2, 2, 2, 64, 2>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);   // 128x128, 4 waves
+        case 3: return gemm_launch<4, 2, 2, 4, 64, 1>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);   // 256x256, 8 waves
         default: return hipErrorInvalidValue;
     }
 }

@@ -65,7 +65,7 @@ struct tbs_ctx {
     int *h_counts_dev;  // device view of the same memory
     int seq;            // number of the last scan asked to publish its counts there
     bool prep_ahead;    // the joiner input rows of the coming call are already being made (see tbs_segment_begin)
-    int pred_ahead;     // predictor kernels of this round already enqueued (see tbs_select_merge): 1 the LSTM layers, 2 all
+    int pred_ahead;     // predictor kernels of this round already enqueued (see tbs_select_merge): 1 the LSTM layers, 2 all, 3 the recurrent products
     bool join_ahead;    // and so is the joiner GEMM of the next round
     bool expanded_ahead; // tbs_joiner_segment already ran the expansion, piece by piece behind the GEMM of each piece
     // slot layout (small shapes inside tbs_decode / tbs_push_segment, see FixedView)
@@ -128,6 +128,8 @@ struct tbs_ctx {
     bool hid;           // this round's are formed so
     void *xpar;
     float *hid_gates;
+#define TBS_SEEN 8
+    int pars_seen[TBS_SEEN];   // parents in the first rounds (the last: in those behind too) of the segment before, 0: not known
 
     int *h_begin, *h_begin_dev;   // pinned: what tbs_begin tells the kernels of a batch's utterances (see launch_init_batch)
 
@@ -277,12 +279,12 @@ int check_err_flags(tbs_ctx *c) {
 int elem_bytes(const tbs_ctx *c) { return c->cfg.dtype == 1 ? 2 : 4; }
 
 hipError_t gemm(tbs_ctx *c, const void *A, const void *B, const float *bias, float *C, int M, int N, int K,
-                const int *out_row, long ldc) {
-    ProfScope ps(c, TBS_K_GEMM, (int64_t)M * N * K);
+                const int *out_row, long ldc, const int *m_dev = nullptr, int m_likely = 0) {
+    ProfScope ps(c, TBS_K_GEMM, m_dev ? 0 : (int64_t)M * N * K);
     if (c->cfg.dtype == 1)
-        return launch_gemm_bf16(c->stream, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, 0, nullptr, false,
-                                c->xcd_sums);
-    return launch_gemm_f32(c->stream, (const float *)A, (const float *)B, bias, C, M, N, K, out_row, ldc);
+        return launch_gemm_bf16(c->stream, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, 0, m_dev, false,
+                                c->xcd_sums, m_likely);
+    return launch_gemm_f32(c->stream, (const float *)A, (const float *)B, bias, C, M, N, K, out_row, ldc, m_dev);
 }
 
 }  // namespace
@@ -551,6 +553,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     // (a context that gets no memory for it forms the gates of every hypothesis whole)
     c->hid_ok = d.N > 1;
     c->hid = false;
+    memset(c->pars_seen, 0, sizeof(c->pars_seen));
     c->xpar = c->xh[0];
     c->hid_gates = nullptr;
     for (int l = 1; l < d.L; ++l)
@@ -714,7 +717,7 @@ static bool fixed_layout_ok(const tbs_ctx *c) {
 static hipError_t joiner_rows(tbs_ctx *c, int rows, const int *rows_dev) {
     if (c->cfg.dtype == 1 && c->cur.S >= 2 && !(c->cfg.debug & 8192))
         return launch_joiner_prep_pairs(c->stream, c->cur, c->cfg.act, (const bf16_t *)c->enc, c->pool_p, c->rv,
-                                        (bf16_t *)c->amat);
+                                        (bf16_t *)c->amat, rows_dev ? rows / c->cur.S : c->h_counts[TBS_CNT_PAIRS]);
     return launch_joiner_prep(c->stream, c->cur, c->cfg.dtype, c->cfg.act, rows, c->enc, c->pool_p, c->rv, c->amat,
                               rows_dev);
 }
@@ -1020,6 +1023,14 @@ static HidRows hid_rows(const tbs_ctx *c) {
 static bool gather_in_rowfill(const tbs_ctx *c) {
     return c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 && (long)c->cur.U * c->cur.N <= 1024;
 }
+// Are the recurrent products enqueued before the host knows the round's counts (they read theirs from device memory)?  Only where
+// no kernel stands between the row list and them: one that gathers the rows hides the host's round trip, and a product that has to
+// wait for its count starts 1 us later.  And only where the same round of the segment before made hypotheses: a launch that finds none
+// costs 4.5 us.  (ms per decode, large widths, behind the host / ahead of it: 13 utterances N = 8 S = 5 6.43 / 6.10, 40 N = 8 S = 3, two
+// layers 10.64 / 10.42, 100 N = 5 S = 4, two layers 10.76 / 10.64, 300 N = 5 S = 2 13.23 / 13.30, 256 N = 10 S = 3, two layers 139.7 / 140.6.)
+static bool hid_ahead(const tbs_ctx *c) {
+    return gather_in_rowfill(c) && !(c->cfg.debug & 64) && c->pars_seen[std::min(c->round, TBS_SEEN) - 1] > 0;
+}
 
 int tbs_select_merge(tbs_ctx *c, int32_t *live_host) {
     if (!c) return TBS_EINVAL;
@@ -1067,17 +1078,20 @@ static int select_merge_impl(tbs_ctx *c, int32_t *live_host, bool fused) {
     // A round that created nothing (the last of every segment) pays launches that leave at once,
     // which is why no more than this goes out early: measured, the layers alone beat layers +
     // projection and layers + projection + next joiner GEMM (23.5 / 24.2 / 24.7 ms per decode).
+    // (By parents the recurrent products alone, at any size: the host comes with the rest while they run; see hid_ahead.)
     c->pred_ahead = 0;
     c->join_ahead = false;
     c->a_cur ^= 1;   // (the new hypotheses are the current group from here on)
-    if (!(c->cfg.debug & 64) && predictor_all_fused(c, c->cur.U * c->cur.N, false)) {
+    if (c->hid ? hid_ahead(c) : !(c->cfg.debug & 64) && predictor_all_fused(c, c->cur.U * c->cur.N, false)) {
         ProfScope ps(c, TBS_K_PREDICTOR, 0);
-        const int rc = predictor_launch(c, c->cur.U * c->cur.N, c->rv.counts + TBS_CNT_PAIRS, 1);
+        const int rc = c->hid ? predictor_launch(c, most, c->rv.counts + TBS_CNT_PARS, 3)
+                              : predictor_launch(c, c->cur.U * c->cur.N, c->rv.counts + TBS_CNT_PAIRS, 1);
         if (rc) return rc;
-        c->pred_ahead = 1;
+        c->pred_ahead = c->hid ? 3 : 1;
     }
     HIPCHK(c, wait_counts(c));
     if (live_host) *live_host = c->h_counts[TBS_CNT_PAIRS];
+    c->pars_seen[std::min(c->round, TBS_SEEN) - 1] = c->h_counts[TBS_CNT_PARS];
     c->state = ST_SELECTED;
     return check_err_flags(c);
 }
@@ -1101,16 +1115,19 @@ static int64_t predictor_madds(const tbs_ctx *c, int64_t pairs) {   // multiply-
     return n;
 }
 
-static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const int *any_dev) {   // part: 0 all, 1 the LSTM layers, 2 the projection
+static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const int *any_dev) {   // part: 0 all, 1 the LSTM layers, 2 the projection; by parents 3 the recurrent products, 4 the rest
     const Dims &d = c->cur;
     const long UN = (long)c->d.U * c->d.N;
     // (the rows of h were gathered behind select/merge)
     if (c->hid && part != 2) {
-        if (m_dev || any_dev) return TBS_ESTATE;   // (predictor_all_fused was not asked)
-        const int eb = elem_bytes(c), pars = c->h_counts[TBS_CNT_PARS];
-        for (int l = 0; l < d.L; ++l)
+        const int eb = elem_bytes(c);
+        // (m_dev: chosen for as many parents as the same round of the segment before had)
+        for (int l = 0; l < d.L && part != 4; ++l)
             HIPCHK(c, gemm(c, (char *)c->xpar + (size_t)l * UN * d.H * eb, c->w.w_hh[l], nullptr,
-                           l == 0 ? c->gates : c->hid_gates + (size_t)(l - 1) * UN * 4 * d.H, pars, 4 * d.H, d.H, nullptr, 4L * d.H));
+                           l == 0 ? c->gates : c->hid_gates + (size_t)(l - 1) * UN * 4 * d.H, m_dev ? M : c->h_counts[TBS_CNT_PARS], 4 * d.H,
+                           d.H, nullptr, 4L * d.H, m_dev ? c->rv.counts + TBS_CNT_PARS : nullptr, c->pars_seen[std::min(c->round, TBS_SEEN) - 1]));
+        if (part == 3) return TBS_OK;
+        if (m_dev || any_dev) return TBS_ESTATE;
         for (int l = 0; l < d.L; ++l) {
             const bool last = l + 1 == d.L;
             char *out = last ? (char *)c->htop : (char *)c->xh[1] + (size_t)(l & 1) * UN * d.H * eb;
@@ -1200,15 +1217,21 @@ int tbs_predictor_step(tbs_ctx *c) {
         // the kernels went out behind select/merge, before the counts were known; now they are
         const int level = c->pred_ahead;
         c->pred_ahead = 0;
-        c->prep_ahead = pairs > 0;   // (with no pairs the projection made no joiner input rows)
+        c->prep_ahead = level == 2 && pairs > 0;   // (with no pairs the projection made no joiner input rows)
         // (work of the launches that went out with their size unknown; the projection, if it goes
         // out now, counts itself)
         if (c->prof_kernel == TBS_K_GEMM)
-            c->prof_units += predictor_madds(c, pairs) - (level == 1 ? (int64_t)pairs * c->cur.Dj * c->cur.H : 0);
+            c->prof_units += level == 3 ? 4 * (int64_t)c->cur.H * c->cur.H * c->h_counts[TBS_CNT_PARS] * c->cur.L
+                                        : predictor_madds(c, pairs) - (level == 1 ? (int64_t)pairs * c->cur.Dj * c->cur.H : 0);
         if (c->prof_kernel == TBS_K_PREDICTOR) c->prof_units += pairs;
         if (level == 1 && pairs > 0) {
             ProfScope ps(c, TBS_K_PREDICTOR, 0);
             const int rc = predictor_launch(c, pairs, nullptr, 2);
+            if (rc) return rc;
+        }
+        if (level == 3 && pairs > 0) {
+            ProfScope ps(c, TBS_K_PREDICTOR, 0);
+            const int rc = predictor_launch(c, pairs, nullptr, 4);
             if (rc) return rc;
         }
     } else if (pairs > 0) {
@@ -1257,67 +1280,68 @@ int tbs_result(tbs_ctx *c, int32_t *tokens, int32_t *lens, double *logscores, in
 // the most the batch can have; the host's round trip after the first row list (7-8 us with
 // nothing for the GPU to run) disappears.  Not while a kernel family is being timed (the brackets
 // want the counts at launch).
-static bool segment_ahead_ok(const tbs_ctx *c) {
+static bool segment_ahead_ok(const tbs_ctx *c, int utts) {
     const Dims &d = c->cur;
-    return !(c->cfg.debug & 64) && c->prof_kernel < 0 && d.R >= 1 && joiner_small(c, d.U * d.N * d.S, false) &&
-           predictor_all_fused(c, d.U * d.N, false);
+    if ((c->cfg.debug & 64) || c->prof_kernel >= 0 || d.R < 1) return false;
+    if (joiner_small(c, d.U * d.N * d.S, false) && predictor_all_fused(c, d.U * d.N, false)) return true;
+    return by_parent(c, utts * d.N) && gather_in_rowfill(c) && c->cfg.joiner_chunk_rows == 0;   // (as hid_ahead)
 }
 
-// the joiner GEMM of a call whose row count is known on the device only
-static hipError_t joiner_ahead(tbs_ctx *c, const int *rows_dev) {
+// the joiner GEMM of a call whose row count is known on the device only (utts: utterances that can take part)
+static hipError_t joiner_ahead(tbs_ctx *c, int utts, const int *rows_dev) {
     const Dims &d = c->cur;
-    const int M = d.U * d.N * d.S;
-    if (c->cfg.dtype == 1)
-        return launch_gemm_bf16(c->stream, (const bf16_t *)c->amat, (const bf16_t *)c->w.w_out, c->w.b_out, c->logits, M, d.V,
-                                d.Dj, nullptr, d.Vl, 0, rows_dev);
-    return launch_gemm_f32(c->stream, (const float *)c->amat, (const float *)c->w.w_out, c->w.b_out, c->logits, M, d.V, d.Dj,
-                           nullptr, d.Vl, rows_dev);
+    return gemm(c, c->amat, c->w.w_out, c->w.b_out, c->logits, utts * d.N * d.S, d.V, d.Dj, nullptr, d.Vl, rows_dev);
 }
 
-static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index) {
+static int segment_begin_ahead(tbs_ctx *c, int32_t seg_index, int utts) {
     if (c->state != ST_BEGUN && c->state != ST_READY && c->state != ST_SELECTED) return TBS_ESTATE;
     if (c->state != ST_BEGUN && c->h_counts[TBS_CNT_PAIRS] != 0) return TBS_ESTATE;  // A not empty yet
     const Dims &d = c->cur;
     c->seg = seg_index;
     c->round = 1;
     AView A = c->A[c->a_cur], An = c->A[c->a_cur ^ 1];
-    A.parents = An.parents = nullptr;   // (its layers update the cell inside the products)
+    A.parents = nullptr;   // (they are carried into the segment)
     const int *rows_dev = c->rv.counts + TBS_CNT_ROWS, *pairs_dev = c->rv.counts + TBS_CNT_PAIRS;
+    const int most = utts * d.N;
+    c->hid = by_parent(c, most);
+    if (!c->hid) An.parents = nullptr;
     // A = ChooseNBest(B), B = [], the row list, the joiner input rows
     HIPCHK(c, launch_segment_begin(c->stream, d, c->seg, c->utt_T, c->B, A, c->rv, c->pool_p, c->pool_h, c->pool_c,
                                    c->pool_rows));
     HIPCHK(c, launch_rowfill(c->stream, d, c->seg, c->utt_off, A, c->rv, c->nodes, 0, c->h_counts_dev, ++c->seq));
-    HIPCHK(c, joiner_rows(c, d.U * d.N * d.S, rows_dev));
+    HIPCHK(c, joiner_rows(c, most * d.S, rows_dev));
     // first round: joiner, expansion, select/merge, row list, predictor step
-    HIPCHK(c, joiner_ahead(c, rows_dev));
+    HIPCHK(c, joiner_ahead(c, utts, rows_dev));
     c->n_launches += 1;
     const int drop = c->cfg.max_rounds_per_segment > 0 && c->round >= c->cfg.max_rounds_per_segment;
     if (round_fused_ok(c)) {
         HIPCHK(c, launch_round(c->stream, d, c->round, drop, c->logits, A, An, c->B, c->rv, c->nodes, c->row_stats,
                                c->delta_nb));
     } else {
-        HIPCHK(c, launch_expand(c->stream, d, d.U * d.N, c->logits, A, c->rv, c->row_lc, c->dphi, c->cand_score,
+        HIPCHK(c, launch_expand(c->stream, d, most, c->logits, A, c->rv, c->row_lc, c->dphi, c->cand_score,
                                 c->cand_tok, c->row_stats, c->delta_nb, (c->cfg.debug & 2) != 0, pairs_dev, 0, c->xcd_sums));
         HIPCHK(c, launch_select_merge(c->stream, d, c->round, drop, c->logits, c->row_lc, c->dphi, c->cand_score,
                                       c->cand_tok, A, An, c->B, c->rv, c->nodes));
     }
-    c->hid = false;
     const HidRows gather = hid_rows(c);
     const bool gathered = gather_in_rowfill(c);
     HIPCHK(c, launch_rowfill(c->stream, d, c->seg, c->utt_off, An, c->rv, c->nodes, 1, c->h_counts_dev, ++c->seq,
                              gathered ? &gather : nullptr));
-    if (!gathered) HIPCHK(c, launch_pred_gather_h(c->stream, d, c->cfg.dtype, d.U * d.N, c->rv, gather));
+    if (!gathered) HIPCHK(c, launch_pred_gather_h(c->stream, d, c->cfg.dtype, most, c->rv, gather));
     c->a_cur ^= 1;
-    const int rc = predictor_launch(c, d.U * d.N, pairs_dev);
+    // (By parents: the recurrent products only, see select_merge_impl.)
+    const bool layers = !c->hid || hid_ahead(c);
+    const int rc = !layers ? TBS_OK : c->hid ? predictor_launch(c, most, c->rv.counts + TBS_CNT_PARS, 3) : predictor_launch(c, most, pairs_dev);
     if (rc) return rc;
     c->prep_ahead = false;
-    c->pred_ahead = 2;
+    c->pred_ahead = !layers ? 0 : c->hid ? 3 : 2;
     c->join_ahead = false;
-    if (c->round + 1 <= d.R) {   // and the joiner GEMM of the second round
-        HIPCHK(c, joiner_ahead(c, rows_dev));
+    if (!c->hid && c->round + 1 <= d.R) {   // and the joiner GEMM of the second round
+        HIPCHK(c, joiner_ahead(c, utts, rows_dev));
         c->join_ahead = true;
     }
     HIPCHK(c, wait_counts(c));
+    c->pars_seen[0] = c->h_counts[TBS_CNT_PARS];
     c->state = ST_SELECTED;
     return check_err_flags(c);
 }
@@ -1697,9 +1721,10 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
 // one segment: the head of the outer loop of Algorithm 1 and its inner loop (while Length(A) > 0)
 static int run_segment(tbs_ctx *c, int32_t seg_index) {
     if (c->fixed) return run_segment_fixed(c, seg_index);
-    int rc, rows = 0, live = 0;
-    if (segment_ahead_ok(c)) {
-        if ((rc = segment_begin_ahead(c, seg_index))) return rc;
+    int rc, rows = 0, live = 0, utts = 0;
+    for (int u = 0; u < c->cur.U; ++u) utts += c->h_T[u] > seg_index * c->cur.S;   // (that have frames in the segment)
+    if (segment_ahead_ok(c, utts)) {
+        if ((rc = segment_begin_ahead(c, seg_index, utts))) return rc;
     } else {
         if ((rc = segment_begin(c, seg_index, &rows))) return rc;
         if (rows == 0) return TBS_OK;

@@ -241,9 +241,9 @@ hipError_t launch_segment_begin(hipStream_t st, const Dims &d, int seg, const in
                                 AView A, RowView rv, float *pool_p, float *pool_h, float *pool_c, long pool_rows,
                                 const FixedView *fx = nullptr);
 // joiner input rows in the slot layout: every row j*S + t with t < pair_len[j]
-// the same by pairs (bf16; the pair count is read from the row lists' counts in device memory)
+// the same by pairs (bf16; the pair count is read from the row lists' counts in device memory, at most `pairs`)
 hipError_t launch_joiner_prep_pairs(hipStream_t st, const Dims &d, int act, const bf16_t *enc, const float *pool_p,
-                                    RowView rv, bf16_t *amat);
+                                    RowView rv, bf16_t *amat, int pairs);
 hipError_t launch_joiner_prep_fixed(hipStream_t st, const Dims &d, int dtype, int act, const void *enc, const float *pool_p,
                                     RowView rv, void *amat);
 // Rows of h that the gate products of new hypotheses read, as bf16 or fp32 (fp32 models): row j the parent's of pair j (parents
@@ -282,11 +282,11 @@ hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, 
                               // a round's products: ms per decode with slots / row lists) 640: 12.5 / 16.0, 800: 10.6 /
                               // 11.4, 960: 12.5 / 13.5, 1200: 20.8 / 22.1, 1440: 15.4 / 15.2, 1600: 13.9 / 13.4 and
                               // 25.5 / 24.5, 1920: 18.8 / 17.3
-// m_dev (launch_gemm_bf16 only where gemm_small_fits; the fused forms always): the launch is enqueued
-// before the host knows the row count; M is an upper bound and the count is read from *m_dev
+// m_dev: the launch is enqueued before the host knows the row count; M is an upper bound and the count is read from *m_dev
+// (m_likely: rows to choose the kernel for, 0: M)
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel = 0, const int *m_dev = nullptr,
-                            bool xcd_rows = false, bool bias_late = false);
+                            bool xcd_rows = false, bool bias_late = false, int m_likely = 0);
 // rows per XCD when k_gemm_small gives every XCD a row range of its own (PartEp::xcd_rows)
 inline int gemm_small_xcd_rows(int M, int tile) { return tile * ((((M + tile - 1) / tile) + 7) / 8); }
 hipError_t launch_gemm_bf16_rows(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C,
