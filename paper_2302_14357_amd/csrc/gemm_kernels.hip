@@ -833,6 +833,266 @@ hipError_t launch_gemm_join(hipStream_t st, const bf16_t *A, const bf16_t *B, co
     return hipGetLastError();
 }
 
+// ------------------------------------------------------------------ problems of a few tiles a CU
+// One tile of (32 TM) x (64 TN) a workgroup of eight waves, waves of (16 TM) x (16 TN) in blocks of 16 x 16 (the same sums in the
+// same order as blocks of 32 x 32: the same bits).  The edge of a tile is chosen per problem, so that the tiles fill the
+// CUs in whole turns (gemm_tile_shape): with 128 x 128 tiles 2560 x 4096 is 640 of them, 2.5 a CU, and the chip waits for
+// the CUs that have three; 160 x 256 is one each.  K tiles of 64 pass through NS stages of LDS by direct loads, a stage asked for
+// again as soon as every wave has its last fragments, the fragments of the next 32 columns read while the matrix
+// instructions take the last ones (the waits stand in the code: the compiler would read each pair of fragments right in front of its
+// instruction, and wait for it).  What bounds it, 2560 x 4096 x 1024 (26 us; parts switched off in a copy): stores of the fp32
+// result 8.5 (5 TB/s, all at the end), start and first K tile 3.5, matrix instructions 11, fragment reads and loads beside them 3.
+// us a product with the kernels that were chosen for these sizes before (k_gemm_small, 64 x 64 and 128 x 128 tiles) and with this
+// one, operands in the caches: K = 1024, N = 4096: M = 150 8.6 / 6.7, 333 9.4 / 7.6, 500 9.9 / 8.3, 900 15.6 / 12.9, 1500 21.9 / 17.7, 2560 33.9 / 25.9,
+// 4500 49.4 / 46.4; N = 1024: M = 1500 9.2 / 7.6, 2560 11.7 / 10.7, 10240 32.9 / 26.2.
+typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
+#define GT_BK 64
+#define GT_LDS_READ (15 | (7 << 4) | (0 << 8) | (3 << 14))   // s_waitcnt: LDS reads only
+template <int TM, int TN, int NS>
+__global__ void __launch_bounds__(512, 2)
+k_gemm_tile(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const float *__restrict__ bias, float *__restrict__ C, int M, int N,
+            int K, const int *__restrict__ out_row, long ldc, const int *__restrict__ m_dev) {
+    constexpr int BM = 32 * TM, BN = 64 * TN;
+    constexpr int RA = BM / 64, RH = (BM % 64) / 32, RB = BN / 64;   // direct loads a wave and stage: passes of 64 rows (eight a wave), half a pass by four waves
+    constexpr int STAGE = (BM + BN) * GT_BK;
+    constexpr bool EARLY = TM * TN <= 24;   // (registers for what the epilogue needs from memory, asked for first)
+    extern __shared__ __attribute__((aligned(16))) bf16_t smem[];   // NS stages
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave >> 2, wn = wave & 3;
+    if (m_dev) M = min(M, *m_dev);   // (enqueued before the host knew the number of rows: M is the most there can be)
+    const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
+    // (the 8 XCDs form a 2 x 4 grid over the tiles, as in k_gemm_small)
+    const int tmx = (tiles_m + 1) >> 1, tnx = (tiles_n + 3) >> 2;
+    const int xcd = blockIdx.x & 7, j = blockIdx.x >> 3;
+    const int jn = j / max(tmx, 1), tile_m = (xcd >> 2) * tmx + j - jn * tmx, tile_n = (xcd & 3) * tnx + jn;
+    if (jn >= tnx || tile_m >= tiles_m || tile_n >= tiles_n) return;   // before any barrier
+    const int kt_n = K / GT_BK;   // (at least NS)
+    // row wave * 8 + lane / 8 of a pass; position lane % 8 of its row in LDS receives chunk position ^ swz(row)
+    const int lrow = wave * 8 + (lane >> 3), lch = ((lane & 7) ^ gemm_swz<GT_BK>(lrow)) * 8;
+    unsigned oa[RA + RH], ob[RB];   // (elements: operands are smaller than 2^32 of them, see the launcher)
+#pragma unroll
+    for (int i = 0; i < RA + RH; ++i) oa[i] = (unsigned)min(tile_m * BM + i * 64 + lrow, M - 1) * (unsigned)K + lch;
+#pragma unroll
+    for (int i = 0; i < RB; ++i) ob[i] = (unsigned)min(tile_n * BN + i * 64 + lrow, N - 1) * (unsigned)K + lch;
+    const int frow = lane & 15, fq = lane >> 4;
+    // a lane's part of the result: row frow of every block of 16, columns 4 fq .. + 3
+    const int m0 = tile_m * BM + wm * 16 * TM + frow, n0 = tile_n * BN + wn * 16 * TN + fq * 4;
+    float bv[TN][4];
+    int orow[TM];
+    auto epilogue_loads = [&]() {
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) bv[b][q] = bias ? bias[min(n0 + b * 16 + q, N - 1)] : 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            const int r = min(m0 + i * 16, M - 1);
+            orow[i] = out_row ? out_row[r] : r;
+        }
+    };
+    if (EARLY) epilogue_loads();
+    asm volatile("" ::: "memory");
+    const bf16_t *pa = A, *pb = B;
+    auto fetch = [&](int stage) {
+        bf16_t *dst = smem + stage * STAGE + wave * 8 * GT_BK;
+#pragma unroll
+        for (int i = 0; i < RA + RH; ++i)
+            if (i < RA || wave < 4)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa + oa[i]),
+                                                 (__attribute__((address_space(3))) void *)(dst + i * 64 * GT_BK), 16, 0, 0);
+#pragma unroll
+        for (int i = 0; i < RB; ++i)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb + ob[i]),
+                                             (__attribute__((address_space(3))) void *)(dst + (BM + i * 64) * GT_BK), 16, 0, 0);
+        pa += GT_BK;
+        pb += GT_BK;
+    };
+    // waits for this wave's share of all but the youngest `stages` stages
+#define GT_WAIT(stages)                                                                        \
+    {                                                                                          \
+        if (RH && wave < 4) __builtin_amdgcn_s_waitcnt(GS_VMCNT((stages) * (RA + RH + RB)));   \
+        else __builtin_amdgcn_s_waitcnt(GS_VMCNT((stages) * (RA + RB)));                       \
+    }
+#pragma unroll
+    for (int q = 0; q < NS; ++q) fetch(q);
+    // fragments: a lane reads row frow of a block, chunk 4 h + fq of it for half h of the K tile
+    const int fa = (wm * 16 * TM + frow) * GT_BK, fb = (BM + wn * 16 * TN + frow) * GT_BK, fsw = gemm_swz<GT_BK>(frow);
+    const int ch[2] = {(fq ^ fsw) * 8, ((4 + fq) ^ fsw) * 8};
+    bf16x8 xa[2][TM], xb[2][TN];
+    auto read = [&](int h, int stage) {
+        const bf16_t *s = smem + stage * STAGE + ch[h];
+#pragma unroll
+        for (int b = 0; b < TN; ++b) xb[h][b] = *reinterpret_cast<const bf16x8 *>(s + fb + b * 16 * GT_BK);
+#pragma unroll
+        for (int i = 0; i < TM; ++i) xa[h][i] = *reinterpret_cast<const bf16x8 *>(s + fa + i * 16 * GT_BK);
+    };
+    floatx4 acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) acc[i][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    auto mma = [&](int h) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)   // (weights first: a lane then holds four columns of one row)
+                acc[i][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xb[h][b], xa[h][i], acc[i][b], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    int stage = 0;
+    // the first half of the K tile in `stage`, whose fragments are on their way; its second half is read meanwhile
+    auto first_half = [&]() {
+        __builtin_amdgcn_s_waitcnt(GT_LDS_READ);
+        __builtin_amdgcn_sched_barrier(0);
+        read(1, stage);
+        mma(0);
+        __builtin_amdgcn_s_waitcnt(GT_LDS_READ);
+    };
+    auto barrier = [&]() {   // every wave has read the stage and its share of the next has landed
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    GT_WAIT(NS - 1);
+    barrier();
+    read(0, 0);
+    for (int kt = 0; kt < kt_n - NS; ++kt) {
+        first_half();
+        GT_WAIT(NS - 2);
+        barrier();
+        const int next = stage + 1 == NS ? 0 : stage + 1;
+        read(0, next);
+        fetch(stage);
+        stage = next;
+        mma(1);
+    }
+#pragma unroll
+    for (int q = 0; q < NS; ++q) {   // the last NS K tiles: nothing more to ask for
+        first_half();
+        if (q < NS - 1) {
+            constexpr int L = NS - 2;
+            if (q == 0) GT_WAIT(L)
+            else if (q == 1) GT_WAIT((L > 1 ? L - 1 : 0))
+            else GT_WAIT(0)
+            barrier();
+            stage = stage + 1 == NS ? 0 : stage + 1;
+            read(0, stage);
+        }
+        mma(1);
+    }
+    if (!EARLY) epilogue_loads();
+    if (out_row == nullptr && (tile_m + 1) * BM <= M && (tile_n + 1) * BN <= N) {
+        float *at = C + (long)m0 * ldc + n0;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int b = 0; b < TN; ++b)
+                *reinterpret_cast<float4 *>(at + (long)i * 16 * ldc + b * 16) =
+                    make_float4(acc[i][b][0] + bv[b][0], acc[i][b][1] + bv[b][1], acc[i][b][2] + bv[b][2], acc[i][b][3] + bv[b][3]);
+        return;
+    }
+    // (edge tiles and scattered rows; all row numbers are there before the first store, outside any branch)
+#pragma unroll
+    for (int i = 0; i < TM; ++i) asm volatile("" : "+v"(orow[i]));
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+            const int col = n0 + b * 16;
+            if (m0 + i * 16 >= M || col >= N) continue;
+            float *at = C + (long)orow[i] * ldc + col;
+            const float v[4] = {acc[i][b][0] + bv[b][0], acc[i][b][1] + bv[b][1], acc[i][b][2] + bv[b][2], acc[i][b][3] + bv[b][3]};
+            if (col + 4 <= N) *reinterpret_cast<float4 *>(at) = make_float4(v[0], v[1], v[2], v[3]);
+            else {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (col + q < N) at[q] = v[q];
+            }
+        }
+#undef GT_WAIT
+}
+
+#define GT_SHAPE(TM, TN, NS) (100 * (TM) + 10 * (TN) + (NS))
+// tiles of the XCD that has most
+static long gt_tiles(int M, int N, int TM, int TN) {
+    const int tm = (M + 32 * TM - 1) / (32 * TM), tn = (N + 64 * TN - 1) / (64 * TN);
+    return (long)((tm + 1) / 2) * ((tn + 3) / 4);
+}
+// Which tile for a product?  The one whose estimated time is least: 4.2 us, 1.07 us a turn of the CUs for every 32 x 64 x 1024 of
+// a tile, and 2.5 us (two workgroups a CU: 1.5) for every turn behind the first; measured times lie within 12 % of it (above).
+// 0: the persistent 256 x 256 tiles, whose turns overlap: from three turns on (7680 x 4096 73 us against 70 with two turns here, 10240 x 4096 98 against
+// 94, 51200 x 4096 458 against 484 to 514).  Where one turn does, four stages (900 x 4096 13.6 -> 12.9 us with 128 x 128, 500 x 4096 9.1 -> 8.3 with
+// 64 x 128), else two, so that two workgroups of the smaller tiles share a CU.
+static int gemm_tile_shape(int M, int N, int K) {
+    if ((long)((M + 255) / 256) * ((N + 255) / 256) > 3 * 256) return 0;
+    static const int tms[] = {8, 7, 6, 5, 4, 3, -4, -3, -2, -1};   // (TN = 4; negative: TN = 2)
+    double best = 1e30;
+    int shape = 0;
+    for (int t : tms) {
+        const int TM = t > 0 ? t : -t, TN = t > 0 ? 4 : 2;
+        const long turns = (gt_tiles(M, N, TM, TN) + 31) / 32;
+        const double us = 4.2 + 1.07 * TM * TN * (K / 1024.0) * turns + (TN == 4 ? 2.5 : 1.5) * (turns - 1);
+        if (us < best) {
+            best = us;
+            shape = GT_SHAPE(TM, TN, TN == 2 && turns == 1 && K >= 4 * GT_BK ? 4 : 2);
+        }
+    }
+    return shape;
+}
+
+template <int TM, int TN, int NS>
+static hipError_t gt_launch(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M, int N, int K,
+                            const int *out_row, long ldc, const int *m_dev) {
+    const int shm = NS * (32 * TM + 64 * TN) * GT_BK * (int)sizeof(bf16_t);
+    static bool attr_set = false;
+    if (!attr_set) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_gemm_tile<TM, TN, NS>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, shm);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    hipLaunchKernelGGL((k_gemm_tile<TM, TN, NS>), dim3((unsigned)(8 * gt_tiles(M, N, TM, TN))), dim3(512), shm, st, A, B, bias, C, M, N, K,
+                       out_row, ldc, m_dev);
+    return hipGetLastError();
+}
+
+// can k_gemm_tile run the product?  (whole K tiles, at least as many as it has stages; 16-byte stores; 32-bit offsets)
+static bool gt_fits(const float *C, int M, int N, int K, long ldc, int ns) {
+    return K % GT_BK == 0 && K >= ns * GT_BK && ldc % 4 == 0 && (reinterpret_cast<uintptr_t>(C) & 15) == 0 && ((long)M + 1) * K < 0xFFFFFFFFl &&
+           ((long)N + 1) * K < 0xFFFFFFFFl;
+}
+
+static hipError_t gt_launch_shape(hipStream_t st, int shape, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M, int N,
+                                  int K, const int *out_row, long ldc, const int *m_dev) {
+    switch (shape) {
+#define GT_CASE(TM, TN, NS) \
+    case GT_SHAPE(TM, TN, NS): return gt_launch<TM, TN, NS>(st, A, B, bias, C, M, N, K, out_row, ldc, m_dev)
+        GT_CASE(8, 4, 2);
+        GT_CASE(7, 4, 2);
+        GT_CASE(6, 4, 2);
+        GT_CASE(5, 4, 2);
+        GT_CASE(4, 4, 2);
+        GT_CASE(3, 4, 2);
+        GT_CASE(4, 2, 2);
+        GT_CASE(3, 2, 2);
+        GT_CASE(2, 2, 2);
+        GT_CASE(1, 2, 2);
+        GT_CASE(4, 2, 4);
+        GT_CASE(3, 2, 4);
+        GT_CASE(2, 2, 4);
+        GT_CASE(1, 2, 4);
+#undef GT_CASE
+        default: return hipErrorInvalidValue;
+    }
+}
+
+// a product by a shape of k_gemm_tile (the tests run every one; *m_dev rows of M, result row r at out_row[r] of C)
+extern "C" int gemm_tile_run(int shape, const void *A, const void *B, const float *bias, float *C, int M, int N, int K, const int *out_row,
+                             long ldc, const int *m_dev, void *stream) {
+    if (shape < 100 || M < 1 || N < 1 || !gt_fits(C, M, N, K, ldc, shape % 10)) return (int)hipErrorInvalidValue;
+    return (int)gt_launch_shape((hipStream_t)stream, shape, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, m_dev);
+}
+
 // kernel: 0 = by size (what the decode uses); 1..4 force one (tests run every kernel on every shape):
 // 1 = 64x64 tiles, 2 = 128x128, 3 = 256x256 (all k_gemm_bf16), 4 = k_gemm_small
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
@@ -840,6 +1100,10 @@ hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, co
                             bool bias_late, int m_likely) {
     if (M <= 0) return hipSuccess;
     const int Mc = m_likely > 0 ? min(m_likely, M) : M;   // (the rows that the kernel is chosen for)
+    if (kernel == 0) {
+        const int shape = gemm_tile_shape(Mc, N, K);
+        if (shape && gt_fits(C, M, N, K, ldc, shape % 10)) return gt_launch_shape(st, shape, A, B, bias, C, M, N, K, out_row, ldc, m_dev);
+    }
     if ((kernel == 0 || kernel == 4) && K % GS_BK == 0) {
         const int tiles_m = (M + 63) / 64, tiles_n = (N + 63) / 64;
         const int ns_max = gemm_small_stages();

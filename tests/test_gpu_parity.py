@@ -50,6 +50,43 @@ def test_gemm_bf16_tiles(M, N, K, kernel):
     np.testing.assert_allclose(got, want, rtol=1e-4, atol=1e-4 * math.sqrt(K))
 
 
+@pytest.mark.parametrize("tm,tn,ns", [(8, 4, 2), (7, 4, 2), (6, 4, 2), (5, 4, 2), (4, 4, 2), (3, 4, 2), (4, 2, 2), (3, 2, 2), (2, 2, 2),
+                                      (1, 2, 2), (4, 2, 4), (3, 2, 4), (2, 2, 4), (1, 2, 4)])
+def test_gemm_bf16_tile_shapes(tm, tn, ns):
+    """Every tile shape of the kernel for products of a few tiles a CU: one row and a few columns past whole tiles, one short of
+    them, a single row, several tiles on every XCD, as few K tiles as it has stages, one more, and many; rows scattered, fewer rows than
+    the launch is sized for, and nothing written beside the result.  Against fp64 as above, and bit for bit against the kernel for
+    small problems, whose sums it keeps."""
+    import ctypes
+    import torch
+    from paper_2302_14357_amd import gemm_bf16, load_library
+    run = load_library().gemm_tile_run
+    run.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 4 + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_long] + [ctypes.c_void_p] * 2
+    bm, bn = 32 * tm, 64 * tn
+    rng = np.random.default_rng(100 * tm + 10 * tn + ns)
+    for M, N, K, live in [(1, 3, 64 * ns, 1), (bm, bn, 64 * (ns + 1), bm), (bm + 1, bn + 5, 64 * ns + 64, bm + 1),
+                          (5 * bm - 1, 9 * bn - 2, 640, 5 * bm - 1), (3 * bm + 7, 2 * bn, 256, bm + 2), (2 * bm, bn, 256, 0)]:
+        a, b = _bf16_values(rng, (M, K)), _bf16_values(rng, (N, K), 0.1)
+        bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32))
+        ldc = (N + 3) // 4 * 4 + 4
+        where = torch.from_numpy(rng.permutation(M + 3)[:M].astype(np.int32)) if M % 2 == 0 else None
+        out = torch.full((M + 3, ldc), 7.0, device="cuda")
+        da, db, dbias, n = a.cuda(), b.cuda(), bias.cuda(), torch.tensor([live], dtype=torch.int32, device="cuda")
+        dwhere = where.cuda() if where is not None else None
+        rc = run(100 * tm + 10 * tn + ns, da.data_ptr(), db.data_ptr(), dbias.data_ptr(), out.data_ptr(), M, N, K,
+                 dwhere.data_ptr() if where is not None else None, ldc, n.data_ptr() if live < M else None, torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        rows = (where if where is not None else torch.arange(M))[:live].long()
+        want = torch.full((M + 3, ldc), 7.0)
+        want[rows, :N] = (a[:live].double() @ b.double().T + bias.double()).float()
+        np.testing.assert_allclose(out.cpu().numpy(), want.numpy(), rtol=1e-4, atol=1e-4 * math.sqrt(K))
+        untouched = torch.ones(M + 3, ldc, dtype=torch.bool)
+        untouched[rows, :N] = False
+        assert (out.cpu()[untouched] == 7.0).all()
+        if K % 128 == 0 and live > 0:
+            assert torch.equal(out[rows.cuda(), :N], gemm_bf16(da, db, dbias, kernel=4)[:live]), (M, N, K)
+
+
 # ------------------------------------------------------------------ joiner + expansion on chosen inputs
 
 def _teacher_forced_state(rng, U, N, S, Dj):
