@@ -520,7 +520,7 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
                const float *dphi, const float *cand_score, const int *cand_tok, AView A, AView An, BView B,
                RowView rv, const int2 *nodes) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // B list of this utterance
-    TBS_SELECT_ARRAYS(s_select);
+    TBS_SELECT_ARRAYS_ANY(s_select);
     const int u = blockIdx.x;
     const int pair0 = rv.utt_pair0[u];
     const SelectFigs fg = select_figs(u, A, B, rv);

@@ -80,7 +80,7 @@ k_round(Dims d, int round, int drop, const float *__restrict__ logits, AView A, 
     const bool sel_wave = own_wave ? (int)threadIdx.x >= N * TT : (int)threadIdx.x < WAVE;
     const int sel_lane = (int)threadIdx.x & 63;
     __shared__ SelectOut s_out;
-    TBS_SELECT_ARRAYS(s_select);
+    TBS_SELECT_ARRAYS_ANY(s_select);
     // Slot layout: everything the round has to know of the utterance lies side by side and comes
     // with one request.  What the kernel before this one wrote is asked for by the vector unit, a lane
     // per value, and handed to the scalar registers by lane reads: a request of the scalar unit for

@@ -149,55 +149,39 @@ __device__ __forceinline__ SelectFigs select_figs(int u, const AView &A, const B
     return f;
 }
 
-// LDS of the select step, as a struct for a kernel that sizes it (CANDS: candidates there is room for; DNEW: values of the frame distributions made by lane or by
+// LDS of the select step.  CANDS: candidates there is room for; DNEW: values of the frame distributions made by lane or by
 // frame (1 where every caller makes them ahead; 0: the caller makes them behind the step, from s_kh and s_ktok); PF: frames of a
-// segment whose candidates' logits are asked for ahead, PC: such candidates), or below as arrays of their own.
-template <int CANDS, int DNEW, int PF, int PC>
-struct SelectShared {
-    static constexpr int dnew = DNEW, pf = PF, pc = PC;
-    double s_key[CANDS];
-    int s_ctok[CANDS];
-    double s_alogs[TBS_MAX_BEAM];
-    u64 s_ahash[TBS_MAX_BEAM];
-    int s_anode[TBS_MAX_BEAM], s_alen[TBS_MAX_BEAM], s_aslot[TBS_MAX_BEAM];
-    double s_bkey[TBS_MAX_BEAM];
-    int s_match[TBS_MAX_BEAM];
-    int s_sel[TBS_MAX_BEAM];      // candidate index by rank
-    double s_thr;
-    int s_have_thr;
-    float s_dnew[DNEW > 0 ? DNEW : 1];   // frame distributions of the new hypotheses, [frame][hypothesis]
-    float s_xpre[PF * PC];        // logits of the candidates' tokens, [frame][candidate]
-    int s_kh[TBS_MAX_BEAM], s_ktok[TBS_MAX_BEAM];   // kept candidates, by place: hypothesis they extend, token
-    __device__ __forceinline__ double &thr() { return s_thr; }
-    __device__ __forceinline__ int &have_thr() { return s_have_thr; }
-};
-// For any caller.  (Arrays of their own: the compiler leaves out what a kernel does not use, and knows that a store to one does not
+// segment whose candidates' logits are asked for ahead, PC: such candidates.
+// (Arrays of their own: the compiler leaves out what a kernel does not use, and knows that a store to one does not
 // change another, which it does not of a struct's: with a struct 64 utterances N = 16 S = 5 took 70 us a launch of k_round instead of 63.)
+template <int DNEW, int PF, int PC>
 struct SelectArrays {
-    static constexpr int dnew = TBS_MAX_SEG * TBS_MAX_BEAM, pf = SEL_PRE_FRAMES, pc = SEL_PRE_CANDS;
+    static constexpr int dnew = DNEW, pf = PF, pc = PC;
     double *s_key;
     int *s_ctok;
     double *s_alogs;
     u64 *s_ahash;
     int *s_anode, *s_alen, *s_aslot;
     double *s_bkey;
-    int *s_match, *s_sel;
+    int *s_match, *s_sel;         // s_sel: candidate index by rank
     double *s_thr;
     int *s_have_thr;
-    float *s_dnew, *s_xpre;
-    int *s_kh, *s_ktok;
-    __device__ __forceinline__ double &thr() { return *s_thr; }
-    __device__ __forceinline__ int &have_thr() { return *s_have_thr; }
+    float *s_dnew, *s_xpre;       // frame distributions of the new hypotheses, [frame][hypothesis]; logits of the candidates' tokens, [frame][candidate]
+    int *s_kh, *s_ktok;           // kept candidates, by place: hypothesis they extend, token
+    __device__ __forceinline__ double &thr() const { return *s_thr; }
+    __device__ __forceinline__ int &have_thr() const { return *s_have_thr; }
 };
-#define TBS_SELECT_ARRAYS(name)                                                                                            \
-    __shared__ double name##_key[CAND_MAX], name##_alogs[TBS_MAX_BEAM], name##_bkey[TBS_MAX_BEAM], name##_thr;             \
+#define TBS_SELECT_ARRAYS(name, CANDS, DNEW, PF, PC)                                                                       \
+    __shared__ double name##_key[CANDS], name##_alogs[TBS_MAX_BEAM], name##_bkey[TBS_MAX_BEAM], name##_thr;                \
     __shared__ u64 name##_ahash[TBS_MAX_BEAM];                                                                             \
-    __shared__ int name##_ctok[CAND_MAX], name##_anode[TBS_MAX_BEAM], name##_alen[TBS_MAX_BEAM], name##_aslot[TBS_MAX_BEAM]; \
+    __shared__ int name##_ctok[CANDS], name##_anode[TBS_MAX_BEAM], name##_alen[TBS_MAX_BEAM], name##_aslot[TBS_MAX_BEAM];  \
     __shared__ int name##_match[TBS_MAX_BEAM], name##_sel[TBS_MAX_BEAM], name##_have_thr, name##_kh[TBS_MAX_BEAM],         \
         name##_ktok[TBS_MAX_BEAM];                                                                                         \
-    __shared__ float name##_dnew[TBS_MAX_SEG * TBS_MAX_BEAM], name##_xpre[SEL_PRE_FRAMES * SEL_PRE_CANDS];                 \
-    SelectArrays name{name##_key,   name##_ctok, name##_alogs, name##_ahash,     name##_anode, name##_alen, name##_aslot, name##_bkey, \
-                      name##_match, name##_sel,  &name##_thr,  &name##_have_thr, name##_dnew,  name##_xpre, name##_kh,    name##_ktok}
+    __shared__ float name##_dnew[(DNEW) > 0 ? (DNEW) : 1], name##_xpre[(PF) * (PC)];                                       \
+    SelectArrays<DNEW, PF, PC> name{name##_key,   name##_ctok, name##_alogs, name##_ahash,     name##_anode, name##_alen, name##_aslot, name##_bkey, \
+                                    name##_match, name##_sel,  &name##_thr,  &name##_have_thr, name##_dnew,  name##_xpre, name##_kh,    name##_ktok}
+// (for any caller)
+#define TBS_SELECT_ARRAYS_ANY(name) TBS_SELECT_ARRAYS(name, CAND_MAX, (TBS_MAX_SEG * TBS_MAX_BEAM), SEL_PRE_FRAMES, SEL_PRE_CANDS)
 
 // Constants, known when the code is made: SHORT: at most SEL_PRE_FRAMES frames; FEW: that, and at most a wave's width of
 // candidates.

@@ -526,7 +526,7 @@ __device__ __forceinline__ void xcd_rank(SM &sm, const double *blogs, int nB, in
             if (cands) {
                 if (mine == mine && rank < N) sm.s_sel[rank] = c;
             } else if (rank == N - 1) {
-                sm.s_thr = mine;
+                sm.thr() = mine;
             }
         }
     }
@@ -1108,7 +1108,7 @@ k_xcd_decode(XcdArgs args) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     __shared__ XcdShared sh;
     __shared__ SelectOut s_out;
-    __shared__ SelectShared<(SMAX > 5 ? 64 : XR_CANDS), (SMAX > 5 ? 0 : 1), (SMAX > 5 ? 1 : SMAX), FEW ? 64 : XR_CANDS> s_select;
+    TBS_SELECT_ARRAYS(s_select, (SMAX > 5 ? 64 : XR_CANDS), (SMAX > 5 ? 0 : 1), (SMAX > 5 ? 1 : SMAX), (FEW ? 64 : XR_CANDS));
     XcdPlace w;
     w.tid = threadIdx.x;
     w.lane = w.tid & 63;
@@ -1210,6 +1210,12 @@ k_xcd_decode(XcdArgs args) {
                     sh.fig[k][tid] = tid == TBS_FIG_NB ? g.B.count[u] : (tid == TBS_FIG_PAR ? g.rv.utt_par[u] : g.fig[u * TBS_FIG_SIZE + tid]);
                 }
         }
+        // (thread i: length and first frame of utterance i, for every segment of the launch)
+        int my_T = 0, my_off = 0;
+        if (tid < w.nu && !(PUSH && args.push_step)) {
+            my_T = args.utt_T[sh.utt[tid]];
+            my_off = args.utt_off[sh.utt[tid]];
+        }
         XcdBarrier bar{&args.ctl->bar[w.x * 16], 0u, 0u};
         const int seg0 = args.seg0, seg1 = args.seg1, R = args.d.R, Dj = args.d.Dj, Hh = args.d.H;
         for (int seg = seg0; seg < seg1 && status == XR_DONE; ++seg) {
@@ -1217,9 +1223,9 @@ k_xcd_decode(XcdArgs args) {
             {
                 const XcdArgs &g = xcd_args();
                 if (tid < w.nu && !(PUSH && g.push_step)) {
-                    const int u = sh.utt[tid], left = g.utt_T[u] - seg * g.d.S;
+                    const int left = my_T - seg * g.d.S;
                     sh.sp[tid] = left < 0 ? 0 : min(left, g.d.S);
-                    sh.f0[tid] = g.utt_off[u] + seg * g.d.S;
+                    sh.f0[tid] = my_off + seg * g.d.S;
                 }
                 __syncthreads();
                 const u64 some = __ballot(lane < w.nu && sh.sp[min(lane, w.nu - 1)] > 0);
