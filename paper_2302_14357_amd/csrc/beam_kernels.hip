@@ -515,12 +515,16 @@ hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt
 // new A are written back once, so the kernel costs a handful of memory round
 // trips instead of one per list operation.
 
+// SMALL: at most SEL_PRE_FRAMES frames and SEL_PRE_CANDS candidates, whose distributions are made ahead: what the longest segments
+// and widest beams need is left out, 13 KB of LDS instead of 41 beside list B (so that more than three workgroups fit a CU: 1024
+// utterances N = 10 S = 5 25.6 -> 20.6 us a launch).
+template <bool SMALL>
 __global__ void __launch_bounds__(2 * WAVE)
 k_select_merge(Dims d, int round, int drop, const float *logits, const float *row_lc,
                const float *dphi, const float *cand_score, const int *cand_tok, AView A, AView An, BView B,
                RowView rv, const int2 *nodes) {
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];   // B list of this utterance
-    TBS_SELECT_ARRAYS_ANY(s_select);
+    TBS_SELECT_ARRAYS(s_select, (SMALL ? SEL_PRE_CANDS : CAND_MAX), (SMALL ? 1 : TBS_MAX_SEG * TBS_MAX_BEAM), SEL_PRE_FRAMES, SEL_PRE_CANDS);
     const int u = blockIdx.x;
     const int pair0 = rv.utt_pair0[u];
     const SelectFigs fg = select_figs(u, A, B, rv);
@@ -532,12 +536,12 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
     in.slot_rows = 0;
     const int lane = (int)threadIdx.x & (WAVE - 1);
     const bool first = __builtin_amdgcn_readfirstlane((int)threadIdx.x) < WAVE;
-    if (first) select_merge_utt(s_select, 1, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
+    if (first) select_merge_utt(s_select, 1, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
     __syncthreads();
-    if (first) select_merge_utt(s_select, 4, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
-    else select_merge_utt(s_select, 3, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
+    if (first) select_merge_utt(s_select, 4, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
+    else select_merge_utt(s_select, 3, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
     __syncthreads();
-    if (first) select_merge_utt(s_select, 5, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn);
+    if (first) select_merge_utt(s_select, 5, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
 }
 
 extern "C" int select_dist_form(int candidates, int frames) { return sel_dist_form(candidates, frames); }
@@ -546,18 +550,24 @@ hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int dro
                                const float *row_lc, const float *dphi, const float *cand_score,
                                const int *cand_tok, AView A, AView An, BView B, RowView rv, const int2 *nodes) {
     const size_t shm = (size_t)d.BCAP * (sizeof(double) + sizeof(u64) + 3 * sizeof(int));
+    const bool small = sel_dist_form(d.N * d.N, d.S) == SEL_AHEAD;
     // the longest B list the library accepts (2048 entries) needs 56 KB of dynamic LDS on top of
     // the kernel's static arrays: more than the default limit, so the limit is raised once
     static bool attr_set = false;
     if (!attr_set) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_select_merge),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 2048 * (int)(sizeof(double) + sizeof(u64) + 3 * sizeof(int)));
+        const int most = 2048 * (int)(sizeof(double) + sizeof(u64) + 3 * sizeof(int));
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_select_merge<false>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
+        if (e == hipSuccess)
+            e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_select_merge<true>), hipFuncAttributeMaxDynamicSharedMemorySize, most);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL(k_select_merge, dim3(d.U), dim3(2 * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
-                       cand_score, cand_tok, A, An, B, rv, nodes);
+    if (small)
+        hipLaunchKernelGGL(k_select_merge<true>, dim3(d.U), dim3(2 * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
+                           cand_score, cand_tok, A, An, B, rv, nodes);
+    else
+        hipLaunchKernelGGL(k_select_merge<false>, dim3(d.U), dim3(2 * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
+                           cand_score, cand_tok, A, An, B, rv, nodes);
     return hipGetLastError();
 }
 

@@ -851,7 +851,7 @@ typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 template <int TM, int TN, int NS>
 __global__ void __launch_bounds__(512, 2)
 k_gemm_tile(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const float *__restrict__ bias, float *__restrict__ C, int M, int N,
-            int K, const int *__restrict__ out_row, long ldc, const int *__restrict__ m_dev) {
+            int K, const int *__restrict__ out_row, long ldc, const int *__restrict__ m_dev, GemmBatch more) {
     constexpr int BM = 32 * TM, BN = 64 * TN;
     constexpr int RA = BM / 64, RH = (BM % 64) / 32, RB = BN / 64;   // direct loads a wave and stage: passes of 64 rows (eight a wave), half a pass by four waves
     constexpr int STAGE = (BM + BN) * GT_BK;
@@ -860,6 +860,11 @@ k_gemm_tile(const bf16_t *__restrict__ A, const bf16_t *__restrict__ B, const fl
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave >> 2, wn = wave & 3;
     if (m_dev) M = min(M, *m_dev);   // (enqueued before the host knew the number of rows: M is the most there can be)
+    if (blockIdx.y > 0) {            // (another product of the same sizes)
+        A += (long)blockIdx.y * more.a;
+        B = more.B[blockIdx.y - 1];
+        C = more.C + (long)(blockIdx.y - 1) * more.c;
+    }
     const int tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     // (the 8 XCDs form a 2 x 4 grid over the tiles, as in k_gemm_small)
     const int tmx = (tiles_m + 1) >> 1, tnx = (tiles_n + 3) >> 2;
@@ -1023,14 +1028,14 @@ static long gt_tiles(int M, int N, int TM, int TN) {
 // 0: the persistent 256 x 256 tiles, whose turns overlap: from three turns on (7680 x 4096 73 us against 70 with two turns here, 10240 x 4096 98 against
 // 94, 51200 x 4096 458 against 484 to 514).  Where one turn does, four stages (900 x 4096 13.6 -> 12.9 us with 128 x 128, 500 x 4096 9.1 -> 8.3 with
 // 64 x 128), else two, so that two workgroups of the smaller tiles share a CU.
-static int gemm_tile_shape(int M, int N, int K) {
-    if ((long)((M + 255) / 256) * ((N + 255) / 256) > 3 * 256) return 0;
+static int gemm_tile_shape(int M, int N, int K, int products = 1) {
+    if ((long)((M + 255) / 256) * ((N + 255) / 256) * products > 3 * 256) return 0;
     static const int tms[] = {8, 7, 6, 5, 4, 3, -4, -3, -2, -1};   // (TN = 4; negative: TN = 2)
     double best = 1e30;
     int shape = 0;
     for (int t : tms) {
         const int TM = t > 0 ? t : -t, TN = t > 0 ? 4 : 2;
-        const long turns = (gt_tiles(M, N, TM, TN) + 31) / 32;
+        const long turns = (products * gt_tiles(M, N, TM, TN) + 31) / 32;
         const double us = 4.2 + 1.07 * TM * TN * (K / 1024.0) * turns + (TN == 4 ? 2.5 : 1.5) * (turns - 1);
         if (us < best) {
             best = us;
@@ -1042,7 +1047,7 @@ static int gemm_tile_shape(int M, int N, int K) {
 
 template <int TM, int TN, int NS>
 static hipError_t gt_launch(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M, int N, int K,
-                            const int *out_row, long ldc, const int *m_dev) {
+                            const int *out_row, long ldc, const int *m_dev, const GemmBatch &more) {
     const int shm = NS * (32 * TM + 64 * TN) * GT_BK * (int)sizeof(bf16_t);
     static bool attr_set = false;
     if (!attr_set) {
@@ -1051,8 +1056,8 @@ static hipError_t gt_launch(hipStream_t st, const bf16_t *A, const bf16_t *B, co
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    hipLaunchKernelGGL((k_gemm_tile<TM, TN, NS>), dim3((unsigned)(8 * gt_tiles(M, N, TM, TN))), dim3(512), shm, st, A, B, bias, C, M, N, K,
-                       out_row, ldc, m_dev);
+    hipLaunchKernelGGL((k_gemm_tile<TM, TN, NS>), dim3((unsigned)(8 * gt_tiles(M, N, TM, TN)), (unsigned)(1 + more.n)), dim3(512), shm, st, A, B, bias,
+                       C, M, N, K, out_row, ldc, m_dev, more);
     return hipGetLastError();
 }
 
@@ -1063,10 +1068,10 @@ static bool gt_fits(const float *C, int M, int N, int K, long ldc, int ns) {
 }
 
 static hipError_t gt_launch_shape(hipStream_t st, int shape, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M, int N,
-                                  int K, const int *out_row, long ldc, const int *m_dev) {
+                                  int K, const int *out_row, long ldc, const int *m_dev, const GemmBatch &more = GemmBatch{}) {
     switch (shape) {
 #define GT_CASE(TM, TN, NS) \
-    case GT_SHAPE(TM, TN, NS): return gt_launch<TM, TN, NS>(st, A, B, bias, C, M, N, K, out_row, ldc, m_dev)
+    case GT_SHAPE(TM, TN, NS): return gt_launch<TM, TN, NS>(st, A, B, bias, C, M, N, K, out_row, ldc, m_dev, more)
         GT_CASE(8, 4, 2);
         GT_CASE(7, 4, 2);
         GT_CASE(6, 4, 2);
@@ -1091,6 +1096,20 @@ extern "C" int gemm_tile_run(int shape, const void *A, const void *B, const floa
                              long ldc, const int *m_dev, void *stream) {
     if (shape < 100 || M < 1 || N < 1 || !gt_fits(C, M, N, K, ldc, shape % 10)) return (int)hipErrorInvalidValue;
     return (int)gt_launch_shape((hipStream_t)stream, shape, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, m_dev);
+}
+
+// Products of the same sizes as one launch (1 + more.n of them, without biases), where k_gemm_tile serves them; otherwise one after the other.
+hipError_t launch_gemm_bf16_batch(hipStream_t st, const bf16_t *A, const bf16_t *B, float *C, int M, int N, int K, long ldc, const int *m_dev,
+                                  int m_likely, const GemmBatch &more) {
+    if (M <= 0) return hipSuccess;
+    const int shape = gemm_tile_shape(m_likely > 0 ? min(m_likely, M) : M, N, K, 1 + more.n);
+    bool fits = shape && gt_fits(C, M, N, K, ldc, shape % 10);
+    if (more.n > 0) fits = fits && gt_fits(more.C, M, N, K, ldc, shape % 10) && more.c % 4 == 0;
+    if (fits) return gt_launch_shape(st, shape, A, B, nullptr, C, M, N, K, nullptr, ldc, m_dev, more);
+    hipError_t e = launch_gemm_bf16(st, A, B, nullptr, C, M, N, K, nullptr, ldc, 0, m_dev, false, false, m_likely);
+    for (int i = 0; i < more.n && e == hipSuccess; ++i)
+        e = launch_gemm_bf16(st, A + (i + 1) * more.a, more.B[i], nullptr, more.C + i * more.c, M, N, K, nullptr, ldc, 0, m_dev, false, false, m_likely);
+    return e;
 }
 
 // kernel: 0 = by size (what the decode uses); 1..4 force one (tests run every kernel on every shape):

@@ -1121,11 +1121,26 @@ static int predictor_launch(tbs_ctx *c, int M, const int *m_dev, int part, const
     // (the rows of h were gathered behind select/merge)
     if (c->hid && part != 2) {
         const int eb = elem_bytes(c);
-        // (m_dev: chosen for as many parents as the same round of the segment before had)
-        for (int l = 0; l < d.L && part != 4; ++l)
-            HIPCHK(c, gemm(c, (char *)c->xpar + (size_t)l * UN * d.H * eb, c->w.w_hh[l], nullptr,
-                           l == 0 ? c->gates : c->hid_gates + (size_t)(l - 1) * UN * 4 * d.H, m_dev ? M : c->h_counts[TBS_CNT_PARS], 4 * d.H,
-                           d.H, nullptr, 4L * d.H, m_dev ? c->rv.counts + TBS_CNT_PARS : nullptr, c->pars_seen[std::min(c->round, TBS_SEEN) - 1]));
+        // (m_dev: chosen for as many parents as the same round of the segment before had; bf16: all layers' in one launch)
+        if (part != 4) {
+            const int rows = m_dev ? M : c->h_counts[TBS_CNT_PARS], likely = m_dev ? c->pars_seen[std::min(c->round, TBS_SEEN) - 1] : 0;
+            const int *rows_dev = m_dev ? c->rv.counts + TBS_CNT_PARS : nullptr;
+            if (c->cfg.dtype == 1) {
+                GemmBatch more{};
+                more.n = d.L - 1;
+                for (int l = 1; l < d.L; ++l) more.B[l - 1] = (const bf16_t *)c->w.w_hh[l];
+                more.C = c->hid_gates;
+                more.a = UN * d.H;
+                more.c = UN * 4 * d.H;
+                ProfScope ps(c, TBS_K_GEMM, m_dev ? 0 : (int64_t)rows * 4 * d.H * d.H * d.L);
+                HIPCHK(c, launch_gemm_bf16_batch(c->stream, (const bf16_t *)c->xpar, (const bf16_t *)c->w.w_hh[0], c->gates, rows, 4 * d.H, d.H,
+                                                 4L * d.H, rows_dev, likely, more));
+            } else {
+                for (int l = 0; l < d.L; ++l)
+                    HIPCHK(c, gemm(c, (char *)c->xpar + (size_t)l * UN * d.H * eb, c->w.w_hh[l], nullptr,
+                                   l == 0 ? c->gates : c->hid_gates + (size_t)(l - 1) * UN * 4 * d.H, rows, 4 * d.H, d.H, nullptr, 4L * d.H));
+            }
+        }
         if (part == 3) return TBS_OK;
         if (m_dev || any_dev) return TBS_ESTATE;
         for (int l = 0; l < d.L; ++l) {

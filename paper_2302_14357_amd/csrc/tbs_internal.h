@@ -287,6 +287,15 @@ hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, 
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel = 0, const int *m_dev = nullptr,
                             bool xcd_rows = false, bool bias_late = false, int m_likely = 0);
+// further products of a launch: the i-th takes A + (i + 1) a and B[i] to C + i c
+struct GemmBatch {
+    int n;
+    const bf16_t *B[TBS_MAX_LAYERS - 1];
+    float *C;
+    long a, c;
+};
+hipError_t launch_gemm_bf16_batch(hipStream_t st, const bf16_t *A, const bf16_t *B, float *C, int M, int N, int K, long ldc, const int *m_dev,
+                                  int m_likely, const GemmBatch &more);
 // rows per XCD when k_gemm_small gives every XCD a row range of its own (PartEp::xcd_rows)
 inline int gemm_small_xcd_rows(int M, int tile) { return tile * ((((M + tile - 1) / tile) + 7) / 8); }
 hipError_t launch_gemm_bf16_rows(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C,
