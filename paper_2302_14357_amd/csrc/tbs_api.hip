@@ -535,7 +535,7 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
         c->x_lds = xcd_lds_bytes(cfg->dtype, d);
         c->x_hb_bytes = xu * 2 * (d.R + 1) * d.N * xcd_row_bytes(cfg->dtype, d.H);
         int none = dev_alloc(c, &c->x_ctl, 2);
-        none |= dev_alloc(c, &c->x_desc, xu * d.N);
+        none |= dev_alloc(c, &c->x_desc, 2 * xu * d.N);
         const long n[3] = {c->x_hb_bytes,
                            (xu * d.N * d.S + 16 * XR_XCDS) * xcd_row_bytes(cfg->dtype, d.Dj),   // (every XCD's rows in whole tiles of 16)
                            xcd_frag_bytes(cfg->dtype, 4 * d.H, d.H)};
@@ -1637,6 +1637,7 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
     g.cand_tok = c->cand_tok;
     g.all_utts = c->d.U;
     g.desc = c->x_desc;
+    g.desc_half = std::min(c->d.U, XR_XCDS * XR_POS) * c->d.N;
     g.host = c->h_xcd_dev;
     g.host_rounds = c->h_xcd_dev + 4 * XR_XCDS * XR_WGS;
     const int *ends = c->h_xcd, *rounds = c->h_xcd + 4 * XR_XCDS * XR_WGS;

@@ -214,7 +214,8 @@ struct XcdArgs {
     float *row_lc, *dphi, *cand_score;   // long segments: what the expansion leaves [U*N, S], [U*N], [U*N, N] ...
     int *cand_tok;                       // ... for the select step
     int all_utts;           // utterances there is room for in A and B
-    int4 *desc;             // [U*N] state slot (-1: no hypothesis), parent's slot, last token
+    int4 *desc;             // [2][desc_half >= U*N] state slot (-1: no hypothesis), parent's slot, last token: of even and odd segments
+    int desc_half;
     XcdCtl *ctl, *ctl_next;
     int *host;              // pinned [workgroups, 4]: joiner calls, frames joined, nodes taken, (seq << 8) | how it ended
     int *host_rounds;       // pinned [XCDs, XR_SEGS]: rounds of each segment

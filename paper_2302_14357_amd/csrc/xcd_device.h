@@ -243,6 +243,7 @@ struct XcdPlace {
     int x, r;        // XCD, workgroup within it
     int u_base, nu;  // its utterances in `order`
     int n_act;       // those up to the last that has frames in this segment
+    int half;        // of the descriptors: this segment's (the next one's lists are made while others still read this one's)
     int N;           // beam
     int tid, lane, wave;
 };
@@ -252,7 +253,11 @@ struct XcdShared {   // LDS
     int sum, made;
     int sp[XR_POS], f0[XR_POS], utt[XR_POS];
     int fig[XR_TURNS][TBS_FIG_SIZE];   // (of this workgroup's utterances)
+    int more[XR_TURNS], next[XR_TURNS];   // and whether this launch has another segment of theirs, and the list A that it begins with
 };
+__device__ __forceinline__ int4 *desc_of(const XcdArgs &g, const XcdPlace &w, int half) {
+    return g.desc + (long)half * g.desc_half + (long)w.u_base * g.d.N;
+}
 
 // LDS behind the weights
 template <int SMAX>
@@ -340,13 +345,14 @@ __device__ __forceinline__ const typename XcdType<F32>::quad *enc_of(const XcdAr
     return static_cast<const typename XcdType<F32>::quad *>(g.enc) + ((long)frame * g.d.Dj + c0) / 4;
 }
 
-// A = ChooseNBest(B); B = []; d = (s, 0, ..., 0)   (Algorithm 1, head of the outer loop), a workgroup per utterance
+// A = ChooseNBest(B); B = []; d = (s, 0, ..., 0)   (Algorithm 1, head of the outer loop), a workgroup per utterance: of a
+// launch's first segment.  Those behind it find it done, see xcd_next.
 template <int NT>
 __device__ __forceinline__ void xcd_head(const XcdPlace &w, XcdShared &sh, double *s_bl) {
     const XcdArgs &g = xcd_args();
     const Dims &d = g.d;
     const int N = d.N, S = d.S, tid = w.tid;
-    int4 *desc = g.desc + (long)w.u_base * N;
+    int4 *desc = desc_of(g, w, w.half);
     for (int i = w.r, k = 0; i < w.n_act; i += XR_WGS, ++k) {
         const int u = __builtin_amdgcn_readfirstlane(sh.utt[i]), sp = __builtin_amdgcn_readfirstlane(sh.sp[i]);
         const int nB = __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_NB]);
@@ -414,7 +420,7 @@ __device__ __forceinline__ void xcd_carry(const XcdPlace &w, XcdShared &sh) {
     const XcdArgs &g = xcd_args();
     const Dims &d = g.d;
     const int N = d.N, S = d.S, P = w.n_act * N;
-    const rsrc_t r_desc = rsrc_of(g.desc + (long)w.u_base * N, (long)w.nu * N * 16);
+    const rsrc_t r_desc = rsrc_of(desc_of(g, w, w.half), (long)w.nu * N * 16);
     unsigned char *amat = amat_of<F32>(g, w);
     const float rcp_n = __builtin_amdgcn_rcpf((float)N);   // p / N as (p + 0.5) * (1 / N): exact for p < 1024
     const int ownG = own_tiles(tiles_gate(d), w.r), nP = own_tiles(tiles_proj(d), w.r) * 4, per = nP + ownG;
@@ -507,7 +513,7 @@ __device__ __forceinline__ void xcd_joiner(const XcdPlace &w, const unsigned cha
 // place without a candidate holds NaN and beats nothing).  (By the select wave alone, ranking a B of 85 entries was 2 us.)
 template <int NW, class SM>
 __device__ __forceinline__ void xcd_rank(SM &sm, const double *blogs, int nB, int nc, int N, int wave, int lane) {
-    const int gc = (nc + 15) >> 4, groups = gc + (nB >= N ? (nB + 15) >> 4 : 0);
+    const int gc = (nc + 15) >> 4, groups = gc + ((nB + 15) >> 4);
     for (int gr = wave < N ? wave : wave - 1; gr < groups; gr += NW - 1) {
         const bool cands = gr < gc;   // (uniform)
         const double *v = cands ? sm.s_key : blogs;
@@ -525,10 +531,59 @@ __device__ __forceinline__ void xcd_rank(SM &sm, const double *blogs, int nB, in
         if (lane < 16 && c < n) {
             if (cands) {
                 if (mine == mine && rank < N) sm.s_sel[rank] = c;
-            } else if (rank == N - 1) {
-                sm.thr() = mine;
+            } else if (rank < N) {
+                sm.s_match[rank] = c;   // (for xcd_next; the merge is done with it)
+                if (rank == N - 1) sm.thr() = mine;
             }
         }
+    }
+}
+
+// The head of the outer loop for an utterance whose list A is empty, by a wave beside the select wave (xcd_finish, which then has
+// little to do) while the other utterances' rounds go on: what the select step left of B in LDS and its ranking make the next
+// segment's list.  The segment itself then begins with xcd_carry.  As a step of its own, behind the last round's barrier and with a
+// barrier of its own: ms per decode, 64 utterances N = 5 S = 1 13.0 (now 12.1), S = 3 9.97 (9.86), S = 20 the same, 200 utterances 15.2 (14.9),
+// 16 fp32 12.4 (12.1), one 4.82 (4.70).  (By the select wave behind its own part: S = 1 12.3.)
+template <int SMAX, class SM>
+__device__ __forceinline__ void xcd_next(const XcdPlace &w, XcdShared &sh, const SM &sm, const SelectOut &s_out, unsigned char *scratch, int round,
+                                         int i, int k) {
+    if (!__builtin_amdgcn_readfirstlane(sh.more[k])) return;
+    const XcdArgs &g = xcd_args();
+    const Dims &d = g.d;
+    const int lane = w.lane, N = w.N;
+    if (!(g.max_rounds > 0 && round >= g.max_rounds)) {   // (does the select wave keep a candidate? its test, see select_merge_utt)
+        const int c = lane < N ? sm.s_sel[lane] : -1;
+        const bool have_thr = sm.have_thr() != 0;
+        if (__ballot(c >= 0 && (!have_thr || sm.s_key[max(c, 0)] > sm.thr())) != 0) return;
+    }
+    const XcdScratch<SMAX> sc(scratch, d);
+    const int S = d.S, cnt = min(__builtin_amdgcn_readfirstlane(s_out.nB), N), u = __builtin_amdgcn_readfirstlane(sh.utt[i]);
+    const int parity = __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_PAR]) ^ 1;
+    const double *blogs = reinterpret_cast<const double *>(sc.b_list);
+    const u64 *bhash = reinterpret_cast<const u64 *>(blogs + d.BCAP);
+    const int *bnode = reinterpret_cast<const int *>(bhash + d.BCAP), *blen = bnode + d.BCAP, *bslot = blen + d.BCAP;
+    if (lane < N) {
+        int4 ds = make_int4(-1, 0, 0, 0);
+        if (lane < cnt) {
+            const int e = sm.s_match[lane], slot = bslot[e], dst = tbs_slot_id(u, parity, 0, lane, d.R, N);
+            const long at = (long)u * N + lane;
+            g.A[0].logs[at] = blogs[e];
+            g.A[0].node[at] = bnode[e];
+            g.A[0].hash[at] = bhash[e];
+            g.A[0].len[at] = blen[e];
+            g.A[0].pslot[at] = slot;
+            g.A[0].slot[at] = dst;
+            g.A[0].pnode[at] = -1;
+            g.A[0].token[at] = -1;
+            ds = make_int4(dst, slot, 0, 0);
+        }
+        desc_of(g, w, w.half ^ 1)[i * N + lane] = ds;
+    }
+    for (int h = 0; h < cnt; ++h)
+        if (lane < S) g.A[0].dhat[((long)u * N + h) * S + lane] = lane == 0 ? 0.f : -INFINITY;   // (S <= 64)
+    if (lane == 0) {   // (the figures take their values when the segment begins)
+        g.rv.utt_par[u] = parity;
+        sh.next[k] = cnt;
     }
 }
 
@@ -563,7 +618,7 @@ __device__ __forceinline__ void xcd_finish(const XcdPlace &w, XcdShared &sh, SM 
             An.node[(long)u * N + lane] = node;
             ds = make_int4(s_out.slot[lane], s_out.pslot[lane], tok, 0);
         }
-        g.desc[((long)w.u_base + i) * N + lane] = ds;
+        desc_of(g, w, w.half)[i * N + lane] = ds;
     }
     const bool any_full = __ballot(full) != 0;
     if (lane == 0) {
@@ -662,7 +717,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
         const int H = sp > 0 ? __builtin_amdgcn_readfirstlane(sh.fig[k][TBS_FIG_CNT]) : 0;
         if (H == 0) {   // (the same for the whole workgroup)
             const XcdArgs &g = xcd_args();
-            if (tid < N) g.desc[((long)w.u_base + i) * N + tid] = make_int4(-1, 0, 0, 0);
+            if (tid < N) desc_of(g, w, w.half)[i * N + tid] = make_int4(-1, 0, 0, 0);
             continue;
         }
         __syncthreads();
@@ -675,6 +730,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
         }
         __syncthreads();
         if (wave == N) xcd_finish<SMAX, FEW>(w, sh, sm, s_out, scratch, round, a, i, k, sp, H);
+        else if (wave == 0) xcd_next<SMAX>(w, sh, sm, s_out, scratch, round, i, k);
         __syncthreads();
         const int made = __builtin_amdgcn_readfirstlane(sh.made);
         live += made;
@@ -694,7 +750,7 @@ __device__ __forceinline__ void xcd_expand_long(const XcdPlace &w, XcdShared &sh
     const Dims &d = g.d;
     const int N = w.N, S = d.S, P = w.n_act * N;
     const long pair0 = (long)w.u_base * N;
-    const rsrc_t r_desc = rsrc_of(g.desc + pair0, (long)w.nu * N * 16);
+    const rsrc_t r_desc = rsrc_of(desc_of(g, w, w.half), (long)w.nu * N * 16);
     const rsrc_t r_logits = rsrc_of(g.logits + pair0 * S * d.Vl, (long)w.nu * N * S * d.Vl * 4);
     const rsrc_t r_dhat = rsrc_of(g.A[a].dhat, (long)g.all_utts * N * S * 4);
     LongShared &sm = *reinterpret_cast<LongShared *>(scratch);
@@ -729,7 +785,7 @@ __device__ __forceinline__ int xcd_select_long(const XcdPlace &w, XcdShared &sh,
         const Dims &d = g.d;
         const long pair = (long)w.u_base * N + (long)i * N;
         if (H == 0) {   // (the same for the whole workgroup)
-            if (tid < N) g.desc[pair + tid] = make_int4(-1, 0, 0, 0);
+            if (tid < N) desc_of(g, w, w.half)[i * N + tid] = make_int4(-1, 0, 0, 0);
             continue;
         }
         const XcdScratch<SMAX> sc(scratch, d);
@@ -768,6 +824,7 @@ __device__ __forceinline__ int xcd_select_long(const XcdPlace &w, XcdShared &sh,
         if (wave != N) xcd_rank<NW>(sm, reinterpret_cast<const double *>(scratch), s_out.nB, nc, N, wave, lane);
         __syncthreads();
         if (wave == N) xcd_finish<SMAX, true>(w, sh, sm, s_out, scratch, round, a, i, k, sp, H);
+        else if (wave == 0) xcd_next<SMAX>(w, sh, sm, s_out, scratch, round, i, k);
         __syncthreads();
         const int made = __builtin_amdgcn_readfirstlane(sh.made), total = made & (XR_FULL_TRIE - 1);
         if (wave < total) {   // (at most N < NW)
@@ -806,7 +863,7 @@ __device__ __forceinline__ void xcd_gates(const XcdPlace &w, const unsigned char
     const Dims &d = g.d;
     const int own = own_tiles(tiles_gate(d), w.r), lane = w.lane;
     const int P = w.n_act * d.N, ptiles = (P + 15) >> 4;
-    const rsrc_t r_desc = rsrc_of(g.desc + (long)w.u_base * d.N, (long)w.nu * d.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
+    const rsrc_t r_desc = rsrc_of(desc_of(g, w, w.half), (long)w.nu * d.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
     const int groups = min(own, max(1, NW / ptiles));   // (few rows: the tiles of columns by different waves)
     for (int task = w.wave; task < ptiles * groups; task += NW) {
         const int rt = task / groups, gi = task - rt * groups;
@@ -862,7 +919,7 @@ __device__ __forceinline__ int xcd_project(const XcdPlace &w, XcdShared &sh, Xcd
     const int own = own_tiles(d.Dj >> 4, w.r), lane = w.lane, S = d.S;
     const int P = w.n_act * w.N, ptiles = (P + 15) >> 4;
     const int per = own > 0 ? NW / own : 0;                  // row tiles at a time (own <= 2)
-    const rsrc_t r_desc = rsrc_of(g.desc + (long)w.u_base * w.N, (long)w.nu * w.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
+    const rsrc_t r_desc = rsrc_of(desc_of(g, w, w.half), (long)w.nu * w.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
     unsigned char *amat = amat_of<false>(g, w);
     const float rcp_n = __builtin_amdgcn_rcpf((float)w.N);
     float *s_p = reinterpret_cast<float *>(scratch);         // [per * 16 hypotheses][own * 16]
@@ -1012,7 +1069,7 @@ __device__ __forceinline__ void xcd_gates_f32(const XcdPlace &w, const float4 *w
     const Dims &d = g.d;
     const int own = own_tiles(tiles_gate(d), w.r), lane = w.lane, pieces = f32_pieces(d.H);
     const int P = w.n_act * d.N, tiles = ((P + 15) >> 4) * own;
-    const rsrc_t r_desc = rsrc_of(g.desc + (long)w.u_base * d.N, (long)w.nu * d.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
+    const rsrc_t r_desc = rsrc_of(desc_of(g, w, w.half), (long)w.nu * d.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
     const float4 *wfrag = static_cast<const float4 *>(g.w_gate);
     for (int t0 = 0; t0 < tiles; t0 += at_once) {
         const int n = min(at_once, tiles - t0);
@@ -1057,7 +1114,7 @@ __device__ __forceinline__ void xcd_project_f32(const XcdPlace &w, XcdShared &sh
     const Dims &d = g.d;
     const int own = own_tiles(tiles_proj(d), w.r), lane = w.lane, pieces = f32_pieces(d.H), S = d.S;
     const int P = w.n_act * d.N, ptiles = (P + 15) >> 4;
-    const rsrc_t r_desc = rsrc_of(g.desc + (long)w.u_base * d.N, (long)w.nu * d.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
+    const rsrc_t r_desc = rsrc_of(desc_of(g, w, w.half), (long)w.nu * d.N * 16), r_hb = rsrc_of(g.hb, g.hb_bytes);
     unsigned char *amat = amat_of<true>(g, w);
     const float rcp_n = __builtin_amdgcn_rcpf((float)w.N);
     if (own == 0) return;
@@ -1222,18 +1279,34 @@ k_xcd_decode(XcdArgs args) {
             // frames of the XCD's utterances in this segment; utterances beyond the last that has any are left out
             {
                 const XcdArgs &g = xcd_args();
+                const int left = my_T - seg * g.d.S;   // (a push has one segment, and its figures already)
                 if (tid < w.nu && !(PUSH && g.push_step)) {
-                    const int left = my_T - seg * g.d.S;
                     sh.sp[tid] = left < 0 ? 0 : min(left, g.d.S);
                     sh.f0[tid] = my_off + seg * g.d.S;
                 }
+                if (tid < w.nu && (tid & (XR_WGS - 1)) == w.r) {   // (one of this workgroup's)
+                    const int k = tid / XR_WGS;
+                    sh.more[k] = seg + 1 < seg1 && left > g.d.S;
+                    if (seg > seg0) {
+                        sh.fig[k][TBS_FIG_SP] = left < 0 ? 0 : min(left, g.d.S);
+                        sh.fig[k][TBS_FIG_CNT] = 0;
+                        if (left > 0) {
+                            sh.fig[k][TBS_FIG_CNT] = sh.next[k];
+                            sh.fig[k][TBS_FIG_NB] = 0;
+                            sh.fig[k][TBS_FIG_PAR] ^= 1;
+                        }
+                    }
+                }
+                w.half = seg & 1;
                 __syncthreads();
                 const u64 some = __ballot(lane < w.nu && sh.sp[min(lane, w.nu - 1)] > 0);
                 w.n_act = some ? 64 - __clzll(some) : 0;
                 if (w.n_act == 0) break;   // (the same for the whole XCD; utterances come in falling length, or there is one step)
             }
-            xcd_head<NT>(w, sh, reinterpret_cast<double *>(scratch));
-            if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
+            if (seg == seg0) {
+                xcd_head<NT>(w, sh, reinterpret_cast<double *>(scratch));
+                if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
+            }
             xcd_carry<NT, SMAX, F32>(w, sh);
             if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
             int a = 0, round = 0;
