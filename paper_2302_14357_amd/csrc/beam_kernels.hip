@@ -90,23 +90,28 @@ __device__ __forceinline__ unsigned seg_bf16(float f) {   // nearest, ties to ev
     return v >> 16;
 }
 #define SEG_THREADS 256
+// Row lists: one workgroup moves all of an utterance's survivors, 120 to 200 KB read and written at the large widths, and 256 utterances are one
+// workgroup a CU: 16 waves keep four times the requests in flight (256 utterances, two layers 34.5 -> 30.6 us a launch; 1024, where four
+// workgroups of 256 threads shared a CU, 70.0 and 70.4: 3.6 TB/s).
+#define SEG_THREADS_WIDE 1024
 #define SEG_ENC_LOADS ((TBS_FIXED_SMAX * 1024 / 4 + SEG_THREADS - 1) / SEG_THREADS)   // 8-byte pieces of S rows of up to 1024 columns, per thread
 // four encoder values of a frame, in the storage type of the model
 template <bool F32> struct SegPiece { typedef uint2 type; };
 template <> struct SegPiece<true> { typedef float4 type; };
-template <bool F32>
-__global__ void __launch_bounds__(SEG_THREADS)
+template <bool F32, int NT>
+__global__ void __launch_bounds__(NT)
 k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv, float *pool_p,
                 float *pool_h, float *pool_c, long pool_rows, FixedView fx) {
     __shared__ int s_src[TBS_MAX_BEAM], s_dst[TBS_MAX_BEAM];
     __shared__ int s_n;
     typedef typename SegPiece<F32>::type EP;
-    __shared__ EP s_enc[TBS_FIXED_SMAX * 1024 / 4];   // the segment's frames, [frame][4 columns]
+    constexpr bool ROWS = NT == SEG_THREADS;   // (joiner input rows: the slot layout alone)
+    __shared__ EP s_enc[ROWS ? TBS_FIXED_SMAX * 1024 / 4 : 1];   // the segment's frames, [frame][4 columns]
     const int parts = fx.parts > 1 ? fx.parts : 1;
     const int u = blockIdx.x / parts, part = blockIdx.x - u * parts, tid = threadIdx.x;
     const bool first = part == 0;
     // Everything the head of the kernel needs is requested at once, before anything is known:
-    // the utterance's figures and, per thread, one entry of B (the first SEG_THREADS entries
+    // the utterance's figures and, per thread, one entry of B (the first NT entries
     // cover every list but the very longest), so that the ranking below starts after one memory
     // round trip instead of four.
     __shared__ double s_bl[2048];           // BCAP is at most 2048
@@ -122,16 +127,16 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
     // kernel: they are asked for now, behind the entries of B (requests come back in order), and wait
     // in registers until the ranking is done.  Asked for whether wanted or not, from an address that
     // exists in either case: a request behind a condition would make every later wait a wait for all.
-    const bool rows_here = fx.on && fx.amat != nullptr && sp > 0;
+    const bool rows_here = ROWS && fx.on && fx.amat != nullptr && sp > 0;
     const int cp = d.Dj >> 2;   // pieces of four columns in a row
     EP ev[SEG_ENC_LOADS];
-    {
+    if constexpr (ROWS) {
         const EP *ebase = rows_here ? static_cast<const EP *>(fx.enc) + ((long)fx.utt_off[u] + (long)seg * d.S) * cp
                                     : reinterpret_cast<const EP *>(pool_p);
         const int pieces = rows_here ? sp * cp : 1;
 #pragma unroll
         for (int q = 0; q < SEG_ENC_LOADS; ++q)
-            ev[q] = ebase[min(tid + q * SEG_THREADS, pieces - 1)];   // (rows follow each other)
+            ev[q] = ebase[min(tid + q * NT, pieces - 1)];   // (rows follow each other)
     }
     if (tid == 0) {
         if (first) rv.utt_sp[u] = sp;
@@ -159,9 +164,9 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
     const int parity = par_old ^ 1;   // the arena the survivors are not in
     // the scores go through LDS: ranking by counting reads every score once per entry
     if (tid < nB) s_bl[tid] = my_logs;
-    for (int i = tid + SEG_THREADS; i < nB; i += SEG_THREADS) s_bl[i] = B.logs[bb + i];
+    for (int i = tid + NT; i < nB; i += NT) s_bl[i] = B.logs[bb + i];
     __syncthreads();
-    for (int i = tid; i < nB; i += SEG_THREADS) {
+    for (int i = tid; i < nB; i += NT) {
         const double si = s_bl[i];
         int rank = 0;
         for (int j = 0; j < nB; ++j) {
@@ -196,7 +201,7 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
     if (rows_here) {
 #pragma unroll
         for (int q = 0; q < SEG_ENC_LOADS; ++q)
-            if (tid + q * SEG_THREADS < sp * cp) s_enc[tid + q * SEG_THREADS] = ev[q];
+            if (tid + q * NT < sp * cp) s_enc[tid + q * NT] = ev[q];
     }
     __syncthreads();
     if (tid == 0 && parts == 1) {   // (every thread has read the old values by now)
@@ -238,7 +243,7 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
         using UNIT = decltype(unit_tag);
         const int up = d.Dj / w, uh = d.H / w, widest = max(up, uh);
         const float rcp_w = __builtin_amdgcn_rcpf((float)widest);   // (item / widest exactly, items < 2^16)
-        for (int it = part * SEG_THREADS + tid; it < n * widest; it += parts * SEG_THREADS) {
+        for (int it = part * NT + tid; it < n * widest; it += parts * NT) {
             const int k = (int)(((float)it + 0.5f) * rcp_w), j = it - k * widest;
             const long src = s_src[k], dst = s_dst[k];
             const int jp = min(j, up - 1), jh = min(j, uh - 1);
@@ -295,11 +300,14 @@ hipError_t launch_segment_begin(hipStream_t st, const Dims &d, int seg, const in
     if (f.parts > 1 && !f.on) return hipErrorInvalidValue;   // (only the slot layout's round kernel finishes what the parts leave)
     const dim3 grid(d.U * (f.parts > 1 ? f.parts : 1)), block(SEG_THREADS);
     if (f.on && f.f32)
-        hipLaunchKernelGGL(k_segment_begin<true>, grid, block, 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h, pool_c,
+        hipLaunchKernelGGL((k_segment_begin<true, SEG_THREADS>), grid, block, 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h, pool_c,
+                           pool_rows, f);
+    else if (f.on)
+        hipLaunchKernelGGL((k_segment_begin<false, SEG_THREADS>), grid, block, 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h, pool_c,
                            pool_rows, f);
     else
-        hipLaunchKernelGGL(k_segment_begin<false>, grid, block, 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h, pool_c,
-                           pool_rows, f);
+        hipLaunchKernelGGL((k_segment_begin<false, SEG_THREADS_WIDE>), grid, dim3(SEG_THREADS_WIDE), 0, st, d, seg, utt_T, B, A, rv, pool_p, pool_h,
+                           pool_c, pool_rows, f);
     return hipGetLastError();
 }
 

@@ -208,8 +208,8 @@ int dev_alloc(tbs_ctx *c, T **p, size_t n) {
 
 int alloc_aview(tbs_ctx *c, AView *a, long UN, int S, int U) {
     int rc = 0;
-    rc |= dev_alloc(c, &a->count, U);
-    rc |= dev_alloc(c, &a->parents, U);
+    rc |= dev_alloc(c, &a->count, 2 * (size_t)U);
+    a->parents = a->count + U;
     rc |= dev_alloc(c, &a->logs, UN);
     rc |= dev_alloc(c, &a->node, UN);
     rc |= dev_alloc(c, &a->hash, UN);
@@ -414,9 +414,9 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     rc |= dev_alloc(c, &c->rv.pair_slot, UN);
     rc |= dev_alloc(c, &c->rv.pair_pslot, UN);
     rc |= dev_alloc(c, &c->rv.pair_frame0, UN);
-    rc |= dev_alloc(c, &c->rv.pair_tok, UN);
-    rc |= dev_alloc(c, &c->rv.pair_par, UN);
-    rc |= dev_alloc(c, &c->rv.par_slot, UN);
+    rc |= dev_alloc(c, &c->rv.pair_tok, 3 * UN);
+    c->rv.pair_par = c->rv.pair_tok + UN;
+    c->rv.par_slot = c->rv.pair_par + UN;
     rc |= dev_alloc(c, &c->rv.utt_sp, U);
     rc |= dev_alloc(c, &c->rv.utt_par, U);
     rc |= dev_alloc(c, &c->rv.pair_u, UN);
