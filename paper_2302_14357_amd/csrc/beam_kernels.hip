@@ -513,11 +513,12 @@ hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt
 }
 
 // ------------------------------------------------------------------ select + merge
-// Second half of the inner loop of Algorithm 1, one utterance per workgroup of two
+// Second half of the inner loop of Algorithm 1, one utterance per workgroup of four
 // waves: the first stages the lists and merges the blank expansions while the
-// second ranks the candidates; the first goes on when both are done (a chain of
-// dependent instructions on either: 256 utterances N = 10 S = 3 14.2 us with one
-// wave, 11.8 with two, 64 utterances N = 5 S = 20 12.2 and 10.5).  The
+// second builds the candidates' keys, all rank both lists, and the first goes on (a chain of
+// dependent instructions everywhere: 256 utterances N = 10 S = 3 14.2 us with one
+// wave, 12.1 with two of which the second ranked the candidates, 9.5 so; 1024
+utterances S = 5 20.2 with two, 19.1).  The
 // utterance's B list, its A entries and its H*N candidates are staged in LDS
 // with one round of parallel loads, all list work happens there, and B and the
 // new A are written back once, so the kernel costs a handful of memory round
@@ -526,8 +527,9 @@ hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt
 // SMALL: at most SEL_PRE_FRAMES frames and SEL_PRE_CANDS candidates, whose distributions are made ahead: what the longest segments
 // and widest beams need is left out, 13 KB of LDS instead of 41 beside list B (so that more than three workgroups fit a CU: 1024
 // utterances N = 10 S = 5 25.6 -> 20.6 us a launch).
+#define SEL_WAVES 4
 template <bool SMALL>
-__global__ void __launch_bounds__(2 * WAVE)
+__global__ void __launch_bounds__(SEL_WAVES * WAVE)
 k_select_merge(Dims d, int round, int drop, const float *logits, const float *row_lc,
                const float *dphi, const float *cand_score, const int *cand_tok, AView A, AView An, BView B,
                RowView rv, const int2 *nodes) {
@@ -543,13 +545,21 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
     in.lc = row_lc + fg.urow0;
     in.slot_rows = 0;
     const int lane = (int)threadIdx.x & (WAVE - 1);
-    const bool first = __builtin_amdgcn_readfirstlane((int)threadIdx.x) < WAVE;
-    if (first) select_merge_utt(s_select, 1, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
-    __syncthreads();
-    if (first) select_merge_utt(s_select, 4, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
-    else select_merge_utt(s_select, 3, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
-    __syncthreads();
-    if (first) select_merge_utt(s_select, 5, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x) / WAVE;
+    auto phase = [&](const int p) {
+        select_merge_utt(s_select, p, d, round, drop, u, lane, LogitsPlain{logits}, in, fg, A, An, B, rv, nodes, s_dyn, nullptr, false, SMALL);
+    };
+    const int H = fg.sp > 0 ? fg.cntA : 0;   // (the same for the whole workgroup)
+    if (H > 0) {
+        if (wave == 0) phase(1);
+        __syncthreads();
+        if (wave == 0) phase(6);
+        else if (wave == 1) phase(7);
+        __syncthreads();
+        sel_rank_waves(s_select, reinterpret_cast<const double *>(s_dyn), *s_select.s_nb, H * d.N, d.N, wave, SEL_WAVES, lane);
+        __syncthreads();
+    }
+    if (wave == 0) phase(5);
 }
 
 extern "C" int select_dist_form(int candidates, int frames) { return sel_dist_form(candidates, frames); }
@@ -571,10 +581,10 @@ hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int dro
         attr_set = true;
     }
     if (small)
-        hipLaunchKernelGGL(k_select_merge<true>, dim3(d.U), dim3(2 * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
+        hipLaunchKernelGGL(k_select_merge<true>, dim3(d.U), dim3(SEL_WAVES * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
                            cand_score, cand_tok, A, An, B, rv, nodes);
     else
-        hipLaunchKernelGGL(k_select_merge<false>, dim3(d.U), dim3(2 * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
+        hipLaunchKernelGGL(k_select_merge<false>, dim3(d.U), dim3(SEL_WAVES * WAVE), shm, st, d, round, drop, logits, row_lc, dphi,
                            cand_score, cand_tok, A, An, B, rv, nodes);
     return hipGetLastError();
 }

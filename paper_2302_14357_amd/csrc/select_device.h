@@ -165,7 +165,7 @@ struct SelectArrays {
     double *s_bkey;
     int *s_match, *s_sel;         // s_sel: candidate index by rank
     double *s_thr;
-    int *s_have_thr;
+    int *s_have_thr, *s_nb;       // s_nb: entries of B behind the merge
     float *s_dnew, *s_xpre;       // frame distributions of the new hypotheses, [frame][hypothesis]; logits of the candidates' tokens, [frame][candidate]
     int *s_kh, *s_ktok;           // kept candidates, by place: hypothesis they extend, token
     __device__ __forceinline__ double &thr() const { return *s_thr; }
@@ -175,13 +175,44 @@ struct SelectArrays {
     __shared__ double name##_key[CANDS], name##_alogs[TBS_MAX_BEAM], name##_bkey[TBS_MAX_BEAM], name##_thr;                \
     __shared__ u64 name##_ahash[TBS_MAX_BEAM];                                                                             \
     __shared__ int name##_ctok[CANDS], name##_anode[TBS_MAX_BEAM], name##_alen[TBS_MAX_BEAM], name##_aslot[TBS_MAX_BEAM];  \
-    __shared__ int name##_match[TBS_MAX_BEAM], name##_sel[TBS_MAX_BEAM], name##_have_thr, name##_kh[TBS_MAX_BEAM],         \
+    __shared__ int name##_match[TBS_MAX_BEAM], name##_sel[TBS_MAX_BEAM], name##_have_thr, name##_nb, name##_kh[TBS_MAX_BEAM],         \
         name##_ktok[TBS_MAX_BEAM];                                                                                         \
     __shared__ float name##_dnew[(DNEW) > 0 ? (DNEW) : 1], name##_xpre[(PF) * (PC)];                                       \
     SelectArrays<DNEW, PF, PC> name{name##_key,   name##_ctok, name##_alogs, name##_ahash,     name##_anode, name##_alen, name##_aslot, name##_bkey, \
-                                    name##_match, name##_sel,  &name##_thr,  &name##_have_thr, name##_dnew,  name##_xpre, name##_kh,    name##_ktok}
+                                    name##_match, name##_sel,  &name##_thr,  &name##_have_thr, &name##_nb, name##_dnew,  name##_xpre, name##_kh,    name##_ktok}
 // (for any caller)
 #define TBS_SELECT_ARRAYS_ANY(name) TBS_SELECT_ARRAYS(name, CAND_MAX, (TBS_MAX_SEG * TBS_MAX_BEAM), SEL_PRE_FRAMES, SEL_PRE_CANDS)
+
+// ChooseNBestExpansions and ChooseNthScore by several waves (this one `place` of `places`), 16 entries of a list a wave, four lanes
+// sharing one: the rank of an entry is the number of those that beat it (larger score, or equal score and earlier place; a
+// place without a candidate holds NaN and beats nothing).  (By one wave ranking a B of 85 entries was 2 us.)
+template <class SM>
+__device__ __forceinline__ void sel_rank_waves(SM &sm, const double *blogs, int nB, int nc, int N, int place, int places, int lane) {
+    const int gc = (nc + 15) >> 4, groups = gc + ((nB + 15) >> 4);
+    for (int gr = place; gr < groups; gr += places) {
+        const bool cands = gr < gc;   // (uniform)
+        const double *v = cands ? sm.s_key : blogs;
+        const int n = cands ? nc : nB, c = 16 * (cands ? gr : gr - gc) + (lane & 15);
+        const int per = (n + 3) >> 2, j0 = (lane >> 4) * per, j1 = min(j0 + per, n);
+        const double mine = v[min(c, n - 1)];
+        int rank = 0;
+#pragma unroll 4
+        for (int j = j0; j < j1; ++j) {
+            const double o = v[j];
+            rank += (o > mine) || (o == mine && j < c);
+        }
+        rank += __shfl_xor(rank, 32);
+        rank += __shfl_xor(rank, 16);
+        if (lane < 16 && c < n) {
+            if (cands) {
+                if (mine == mine && rank < N) sm.s_sel[rank] = c;
+            } else if (rank < N) {
+                sm.s_match[rank] = c;   // (for who makes the next segment's list; the merge is done with it)
+                if (rank == N - 1) sm.thr() = mine;
+            }
+        }
+    }
+}
 
 // Constants, known when the code is made: SHORT: at most SEL_PRE_FRAMES frames; FEW: that, and at most a wave's width of
 // candidates.
@@ -189,8 +220,8 @@ struct SelectArrays {
 // phase 0: the whole step.  phase 1: only what does not depend on the expansion (B and A staged in
 // LDS); phase 2: the rest, by the same wave: a caller whose expansion runs in the same kernel does
 // phase 1 beside it.  Phases 3, 4 and 5 are the parts of phase 2 (see below), for a caller that has two
-// waves for them; the wave of phase 5 is the one that did phase 1 and 4 (`out->nB` is its).  Phase 6 is phase 4 without the
-// threshold, for a caller that ranks B by several waves.  (The phase is
+// waves for them; the wave of phase 5 is the one that did phase 1 and 4 (`out->nB` is its).  Phases 6 and 7 are phases 4
+// and 3 without the ranking, for a caller that ranks by several waves (sel_rank_waves).  (The phase is
 // an argument, not a template parameter: the code is inlined, and the phase known there.)
 template <class SM, class LG>
 __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const Dims &d, int round, int drop, int u, int lane,
@@ -247,7 +278,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
         // nothing of each other; "finish" needs both.  phase 0 and 2: one wave does all three; phase 3:
         // candidates only, phase 4: merge only, phase 5: finish only: a caller with a second wave to
         // spare runs 3 and 4 side by side and 5 behind a barrier.
-        const bool do_cand = PHASE == 0 || PHASE == 2 || PHASE == 3;
+        const bool do_cand = PHASE == 0 || PHASE == 2 || PHASE == 3 || PHASE == 7;
         const bool do_merge = PHASE == 0 || PHASE == 2 || PHASE == 4 || PHASE == 6;
         const bool do_finish = PHASE == 0 || PHASE == 2 || PHASE == 5;
         if (PHASE == 0) sel_sync();   // (A's scores, staged just above, are read by other lanes below)
@@ -331,6 +362,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
             if (lane == 0) {
                 B.count[u] = nB;
                 if (out) out->nB = nB;
+                else *sm.s_nb = nB;
             }
 
             // --- threshold = ChooseNthScore(B, N), only defined when B holds N entries.  The rank of an
@@ -351,7 +383,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
             // candidates of a hypothesis arrive sorted by exactly that rule, hypotheses in order, so
             // "earlier place" decides equal scores.  (A place without a candidate holds NaN and never
             // compares as better.)
-            sel_rank(s_key, nc, lane, [&](int c, int rank, double kc) {
+            if (PHASE != 7) sel_rank(s_key, nc, lane, [&](int c, int rank, double kc) {
                 if (kc == kc && rank < N) s_sel[rank] = c;
             });
             if (pre_x) {

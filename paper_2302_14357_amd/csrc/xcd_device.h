@@ -513,37 +513,6 @@ __device__ __forceinline__ void xcd_joiner(const XcdPlace &w, const unsigned cha
     }
 }
 
-// ChooseNBestExpansions and ChooseNthScore, by all waves but the select wave (wave N), 16 entries of a list a wave, four lanes
-// sharing one: the rank of an entry is the number of those that beat it (larger score, or equal score and earlier place; a
-// place without a candidate holds NaN and beats nothing).  (By the select wave alone, ranking a B of 85 entries was 2 us.)
-template <int NW, class SM>
-__device__ __forceinline__ void xcd_rank(SM &sm, const double *blogs, int nB, int nc, int N, int wave, int lane) {
-    const int gc = (nc + 15) >> 4, groups = gc + ((nB + 15) >> 4);
-    for (int gr = wave < N ? wave : wave - 1; gr < groups; gr += NW - 1) {
-        const bool cands = gr < gc;   // (uniform)
-        const double *v = cands ? sm.s_key : blogs;
-        const int n = cands ? nc : nB, c = 16 * (cands ? gr : gr - gc) + (lane & 15);
-        const int per = (n + 3) >> 2, j0 = (lane >> 4) * per, j1 = min(j0 + per, n);
-        const double mine = v[min(c, n - 1)];
-        int rank = 0;
-#pragma unroll 4
-        for (int j = j0; j < j1; ++j) {
-            const double o = v[j];
-            rank += (o > mine) || (o == mine && j < c);
-        }
-        rank += __shfl_xor(rank, 32);
-        rank += __shfl_xor(rank, 16);
-        if (lane < 16 && c < n) {
-            if (cands) {
-                if (mine == mine && rank < N) sm.s_sel[rank] = c;
-            } else if (rank < N) {
-                sm.s_match[rank] = c;   // (for xcd_next; the merge is done with it)
-                if (rank == N - 1) sm.thr() = mine;
-            }
-        }
-    }
-}
-
 // The head of the outer loop for an utterance whose list A is empty, by a wave beside the select wave (xcd_finish, which then has
 // little to do) while the other utterances' rounds go on: what the select step left of B in LDS and its ranking make the next
 // segment's list.  The segment itself then begins with xcd_carry.  As a step of its own, behind the last round's barrier and with a
@@ -727,7 +696,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
         }
         __syncthreads();
         if (wave != N) {
-            xcd_rank<NW>(sm, reinterpret_cast<const double *>(scratch), s_out.nB, H * N, N, wave, lane);
+            sel_rank_waves(sm, reinterpret_cast<const double *>(scratch), s_out.nB, H * N, N, wave < N ? wave : wave - 1, NW - 1, lane);
             if (wave < H) {
                 const int q = lane / SMAX, tq = lane - q * SMAX;
                 if (q < N) sm.s_xpre[tq * SM::pc + wave * N + q] = xpre;
@@ -826,7 +795,7 @@ __device__ __forceinline__ int xcd_select_long(const XcdPlace &w, XcdShared &sh,
             sm.s_key[c] = tok >= 0 ? sm.s_alogs[wave] + (double)sc.cs[c] : nan("");
         }
         __syncthreads();
-        if (wave != N) xcd_rank<NW>(sm, reinterpret_cast<const double *>(scratch), s_out.nB, nc, N, wave, lane);
+        if (wave != N) sel_rank_waves(sm, reinterpret_cast<const double *>(scratch), s_out.nB, nc, N, wave < N ? wave : wave - 1, NW - 1, lane);
         __syncthreads();
         if (wave == N) xcd_finish<SMAX, true>(w, sh, sm, s_out, scratch, round, a, i, k, sp, H);
         else if (wave == 0) xcd_next<SMAX>(w, sh, sm, s_out, scratch, round, i, k);
