@@ -1020,14 +1020,17 @@ static bool by_parent(const tbs_ctx *c, int M) {
 static HidRows hid_rows(const tbs_ctx *c) {
     return {c->pool_h, c->hid ? c->xpar : c->xh[0], c->pool_rows, (long)c->d.U * c->d.N, c->hid};
 }
+// Does the row list kernel gather those rows too, and the recurrent products then go out ahead of the counts (hid_ahead)?  A launch fewer; but
+// in large batches a workgroup of four waves an utterance gathers more slowly than a kernel of a workgroup a row (ms per decode, large widths,
+// apart / together: 256 utterances N = 10 S = 3, two layers 128.9 / 127.6, 1024 N = 10 S = 5 259.1 / 260.9).
 static bool gather_in_rowfill(const tbs_ctx *c) {
-    return c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 && (long)c->cur.U * c->cur.N <= 1024;
+    return c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 && (long)c->cur.U * c->cur.N <= 4096;
 }
 // Are the recurrent products enqueued before the host knows the round's counts (they read theirs from device memory)?  Only where
 // no kernel stands between the row list and them: one that gathers the rows hides the host's round trip, and a product that has to
 // wait for its count starts 1 us later.  And only where the same round of the segment before made hypotheses: a launch that finds none
 // costs 4.5 us.  (ms per decode, large widths, behind the host / ahead of it: 13 utterances N = 8 S = 5 6.43 / 6.10, 40 N = 8 S = 3, two
-// layers 10.64 / 10.42, 100 N = 5 S = 4, two layers 10.76 / 10.64, 300 N = 5 S = 2 13.23 / 13.30, 256 N = 10 S = 3, two layers 139.7 / 140.6.)
+// layers 10.64 / 10.42, 100 N = 5 S = 4, two layers 10.76 / 10.64; and behind a gather kernel 300 N = 5 S = 2 13.23 / 13.30, 256 N = 10 S = 3, two layers 139.7 / 140.6.)
 static bool hid_ahead(const tbs_ctx *c) {
     return gather_in_rowfill(c) && !(c->cfg.debug & 64) && c->pars_seen[std::min(c->round, TBS_SEEN) - 1] > 0;
 }
