@@ -518,7 +518,7 @@ hipError_t launch_rowfill(hipStream_t st, const Dims &d, int seg, const int *utt
 // second builds the candidates' keys, all rank both lists, and the first goes on (a chain of
 // dependent instructions everywhere: 256 utterances N = 10 S = 3 14.2 us with one
 // wave, 12.1 with two of which the second ranked the candidates, 9.5 so; 1024
-utterances S = 5 20.2 with two, 19.1).  The
+// utterances S = 5 20.2 with two, 19.1).  The
 // utterance's B list, its A entries and its H*N candidates are staged in LDS
 // with one round of parallel loads, all list work happens there, and B and the
 // new A are written back once, so the kernel costs a handful of memory round
