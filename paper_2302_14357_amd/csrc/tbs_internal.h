@@ -222,6 +222,7 @@ struct XcdArgs {
 };
 bool xcd_fits(const Dims &d);
 hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g);
+hipError_t launch_xcd_push(hipStream_t st, const XcdArgs &g);          // (a push of a stream: one segment, push_step not null)
 hipError_t launch_xcd_decode_long(hipStream_t st, const XcdArgs &g);   // (its segments of more than five frames)
 bool xcd_f32_fits(const Dims &d);
 int xcd_f32_lds_bytes(const Dims &d);

@@ -609,7 +609,7 @@ __device__ __forceinline__ void xcd_finish(const XcdPlace &w, XcdShared &sh, SM 
 // makes the new list.
 // (Each role reads the arguments it needs for itself and asks for what it waits for longest before all else.)
 // Returns the hypotheses made (and XR_FULL_TRIE where an utterance's share of the trie was full).
-template <int NT, int NV4, int SMAX, bool FEW, class SM>
+template <int NT, int NV4, int SMAX, bool FEW, bool PUSH, class SM>
 __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &sm, SelectOut &s_out, unsigned char *scratch, int round,
                                          int a, int &calls, int &joined, int &nodes_made) {
     constexpr int NW = NT / 64;
@@ -704,7 +704,7 @@ __device__ __forceinline__ int xcd_round(const XcdPlace &w, XcdShared &sh, SM &s
         }
         __syncthreads();
         if (wave == N) xcd_finish<SMAX, FEW>(w, sh, sm, s_out, scratch, round, a, i, k, sp, H);
-        else if (wave == 0) xcd_next<SMAX>(w, sh, sm, s_out, scratch, round, i, k);
+        else if (!PUSH && wave == 0) xcd_next<SMAX>(w, sh, sm, s_out, scratch, round, i, k);
         __syncthreads();
         const int made = __builtin_amdgcn_readfirstlane(sh.made);
         live += made;
@@ -1132,10 +1132,14 @@ __device__ __forceinline__ void xcd_project_f32(const XcdPlace &w, XcdShared &sh
 }
 
 // NT threads, room for a wave per hypothesis and one for the select step; FEW: beams up to 8 (see select_merge_utt).
-template <int NT, int NV4, int SMAX, bool FEW, bool F32>
+// PUSH: a push of a stream, one segment whose figures and frames come with the launch.  (A kernel of its own: a launch runs through its code
+// once for a push, and
+// what the one does not need of the other's, it does not fetch: 64 streams N = 5 S = 3, three frames a push, utterances of 60 to 150 frames 5.74 -> 5.56 ms, 100
+// of N = 8 8.22 -> 7.87, 64 utterances as a batch 3.83 -> 3.78.)
+template <int NT, int NV4, int SMAX, bool FEW, bool F32, bool PUSH>
 __global__ void __launch_bounds__(NT)
 k_xcd_decode(XcdArgs args) {
-    constexpr bool PUSH = !F32 && SMAX <= 5;   // (other models' streams have row lists)
+    static_assert(!PUSH || (!F32 && SMAX <= 5), "other models' streams have row lists");
     extern __shared__ __attribute__((aligned(16))) unsigned char s_dyn[];
     __shared__ XcdShared sh;
     __shared__ SelectOut s_out;
@@ -1208,8 +1212,8 @@ k_xcd_decode(XcdArgs args) {
             const int pH = F32 ? f32_pieces(d.H) : d.H >> 5;
             int2 step = make_int2(0, 0);
             int4 rows = make_int4(0, 0, 0, 0);
-            if (PUSH && g.push_step && tid < w.nu) step = g.push_step[w.u_base + tid];
-            if (PUSH && g.push_step && w.r < w.nu) rows = g.push_rows[w.u_base + w.r];
+            if (PUSH && tid < w.nu) step = g.push_step[w.u_base + tid];
+            if (PUSH && w.r < w.nu) rows = g.push_rows[w.u_base + w.r];
             if (l.wG < 0) wG = nullptr;
             else load_frags(wG, g.w_gate, pH, 0, own_tiles(tiles_gate(d), w.r) * pH, w.r, w.wave, NW, lane);
             load_rows<F32>(wJ, g.w_out, d.V, d.Dj, own_tiles(tiles_joiner(d), w.r), w.r, w.wave, NW, lane);
@@ -1218,7 +1222,7 @@ k_xcd_decode(XcdArgs args) {
             // A push brings its frames and figures with it: who has the utterance appends the frames to its buffer, while the
             // weights come (the first that reads them does so behind a barrier).  With a copy of the figures and a kernel that
             // appends in front of the launch a push of one segment of 64 streams took 116 us, now 107.
-            if (PUSH && g.push_step) {
+            if (PUSH) {
                 if (tid < w.nu) {
                     sh.sp[tid] = step.x;
                     sh.f0[tid] = step.y;
@@ -1243,7 +1247,7 @@ k_xcd_decode(XcdArgs args) {
         }
         // (thread i: length and first frame of utterance i, for every segment of the launch)
         int my_T = 0, my_off = 0;
-        if (tid < w.nu && !(PUSH && args.push_step)) {
+        if (tid < w.nu && !PUSH) {
             my_T = args.utt_T[sh.utt[tid]];
             my_off = args.utt_off[sh.utt[tid]];
         }
@@ -1254,11 +1258,11 @@ k_xcd_decode(XcdArgs args) {
             {
                 const XcdArgs &g = xcd_args();
                 const int left = my_T - seg * g.d.S;   // (a push has one segment, and its figures already)
-                if (tid < w.nu && !(PUSH && g.push_step)) {
+                if (tid < w.nu && !PUSH) {
                     sh.sp[tid] = left < 0 ? 0 : min(left, g.d.S);
                     sh.f0[tid] = my_off + seg * g.d.S;
                 }
-                if (tid < w.nu && (tid & (XR_WGS - 1)) == w.r) {   // (one of this workgroup's)
+                if (!PUSH && tid < w.nu && (tid & (XR_WGS - 1)) == w.r) {   // (one of this workgroup's)
                     const int k = tid / XR_WGS;
                     sh.more[k] = seg + 1 < seg1 && left > g.d.S;
                     if (seg > seg0) {
@@ -1300,7 +1304,7 @@ k_xcd_decode(XcdArgs args) {
                     if (xcd_barrier(bar, sh.sum) < 0) { status = XR_STUCK; break; }
                     live = xcd_select_long<NT, SMAX>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
                 } else {
-                    live = xcd_round<NT, NV4, SMAX, FEW>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
+                    live = xcd_round<NT, NV4, SMAX, FEW, PUSH>(w, sh, s_select, s_out, scratch, round, a, calls, joined, nodes_made);
                 }
                 a ^= 1;
                 xcd_arrive(bar, live);
@@ -1382,32 +1386,32 @@ static XcdLds lds_of(const Dims &d) {
     return d.S == 1 ? xcd_lds<1, F32>(d, nw, limit) : d.S <= 3 ? xcd_lds<3, F32>(d, nw, limit) : xcd_lds<5, F32>(d, nw, limit);
 }
 
-template <int NT, int NV4, int SMAX, bool FEW, bool F32>
+template <int NT, int NV4, int SMAX, bool FEW, bool F32, bool PUSH = false>
 static hipError_t xcd_launch_t(hipStream_t st, const XcdArgs &g, int shm) {
     static int attr_for = 0;
     if (shm > attr_for) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_xcd_decode<NT, NV4, SMAX, FEW, F32>),
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_xcd_decode<NT, NV4, SMAX, FEW, F32, PUSH>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, shm);
         if (e != hipSuccess) return e;
         attr_for = shm;
     }
-    hipLaunchKernelGGL((k_xcd_decode<NT, NV4, SMAX, FEW, F32>), dim3(XR_XCDS * XR_WGS), dim3(NT), shm, st, g);
+    hipLaunchKernelGGL((k_xcd_decode<NT, NV4, SMAX, FEW, F32, PUSH>), dim3(XR_XCDS * XR_WGS), dim3(NT), shm, st, g);
     return hipGetLastError();
 }
 
-template <int NT, int NV4, bool FEW, bool F32>
+template <int NT, int NV4, bool FEW, bool F32, bool PUSH>
 static hipError_t xcd_launch_s(hipStream_t st, const XcdArgs &g, int shm) {
-    if (g.d.S == 1) return xcd_launch_t<NT, NV4, 1, FEW, F32>(st, g, shm);
-    if (g.d.S <= 3) return xcd_launch_t<NT, NV4, 3, FEW, F32>(st, g, shm);
-    return xcd_launch_t<NT, NV4, 5, FEW, F32>(st, g, shm);
+    if (g.d.S == 1) return xcd_launch_t<NT, NV4, 1, FEW, F32, PUSH>(st, g, shm);
+    if (g.d.S <= 3) return xcd_launch_t<NT, NV4, 3, FEW, F32, PUSH>(st, g, shm);
+    return xcd_launch_t<NT, NV4, 5, FEW, F32, PUSH>(st, g, shm);
 }
 
-template <int NT, bool FEW, bool F32>
+template <int NT, bool FEW, bool F32, bool PUSH = false>
 static hipError_t xcd_launch(hipStream_t st, const XcdArgs &g) {
     const int nv4 = nv4_of(g.d), shm = lds_of<F32>(g.d).bytes;
-    if (nv4 == 1) return xcd_launch_s<NT, 1, FEW, F32>(st, g, shm);
-    if (nv4 == 2) return xcd_launch_s<NT, 2, FEW, F32>(st, g, shm);
-    return xcd_launch_s<NT, 4, FEW, F32>(st, g, shm);
+    if (nv4 == 1) return xcd_launch_s<NT, 1, FEW, F32, PUSH>(st, g, shm);
+    if (nv4 == 2) return xcd_launch_s<NT, 2, FEW, F32, PUSH>(st, g, shm);
+    return xcd_launch_s<NT, 4, FEW, F32, PUSH>(st, g, shm);
 }
 
 // the shapes both types have in common

@@ -9,7 +9,8 @@ bool xcd_fits(const Dims &d) {
 
 hipError_t launch_xcd_decode(hipStream_t st, const XcdArgs &g) {
     if (!xcd_fits(g.d) || !xcd_batch_fits(g)) return hipErrorInvalidValue;
-    if (g.d.S > 5) return launch_xcd_decode_long(st, g);
+    if (g.d.S > 5) return g.push_step ? hipErrorInvalidValue : launch_xcd_decode_long(st, g);
+    if (g.push_step) return launch_xcd_push(st, g);
     return g.d.N <= 7 ? xcd_launch<512, true, false>(st, g) : xcd_launch<768, false, false>(st, g);
 }
 
