@@ -1817,20 +1817,22 @@ int tbs_push_segment(tbs_ctx *c, const void *enc_proj, const int32_t *frame_offs
             any = any || take[u] > 0;
         }
         int ran = 0, rc = TBS_OK;   // (both forms wait for the device: what the host wrote has been read by then)
-        const bool fused = step == 0 && append && any && c->xcd && c->prof_kernel < 0 && push_fused_ok(enc_proj, row_bytes, most);
+        // (a step that has no frames to append, as all but a push's first, brings its figures alone)
+        const bool brings = step == 0 && append;
+        const bool fused = any && c->xcd && c->prof_kernel < 0 && (!brings || push_fused_ok(enc_proj, row_bytes, most));
         if (fused) {
             const int *order = c->h_begin + (size_t)U * TBS_FIG_SIZE;
             int4 *rows = reinterpret_cast<int4 *>(c->h_desc);
             int2 *steps = reinterpret_cast<int2 *>(c->h_desc + 4 * Um);
             for (int i = 0; i < U; ++i) {
                 const int u = order[i];
-                rows[i] = make_int4(src[u], dst[u], cnt[u], 0);
+                rows[i] = brings ? make_int4(src[u], dst[u], cnt[u], 0) : make_int4(0, 0, 0, 0);
                 steps[i] = make_int2(take[u], first[u]);
             }
             for (int u = 0; u < U; ++u) c->h_T[u] = take[u];
-            if ((rc = run_segments_xcd(c, 0, 1, &ran, enc_proj, row_bytes))) return rc;
+            if ((rc = run_segments_xcd(c, 0, 1, &ran, brings ? enc_proj : c->stream_enc, row_bytes))) return rc;
         }
-        if (step == 0 && append && ran == 0) {
+        if (brings && ran == 0) {
             HIPCHK(c, hipMemcpyAsync(c->utt_T, take, sizeof(int) * (2 * (size_t)Um + 1 + 3 * (size_t)U), hipMemcpyHostToDevice,
                                      c->stream));
             HIPCHK(c, launch_stream_copy(c->stream, U, enc_proj, c->stream_enc, c->d_desc, row_bytes));

@@ -686,6 +686,22 @@ def test_decode_cell_update_inside_and_outside_the_gate_gemm(debug):
     _check_decode(shape, model, offsets, enc, 4, 3, debug=debug)
 
 
+@pytest.mark.parametrize("U,N,layers", [(103, 10, 1), (256, 16, 2), (241, 17, 1)])
+def test_rows_gathered_in_the_row_list_kernel_equal_those_of_their_own(U, N, layers):
+    """The parents' rows of h gathered by the row list kernel, the recurrent products behind it enqueued ahead of the counts, and (debug
+    bit 5) by a kernel of their own: one hypothesis list's size over 1024, the largest that is gathered so, and one beyond."""
+    shape = small_bf16_shape(n_utts=U, vocab=96, d=128, hidden=512, layers=layers)
+    lengths = np.random.default_rng(U).integers(0, 9, U)
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=lengths)
+    one, st1 = _gpu_decode(shape, model, offsets, enc, N, 2, debug=256)
+    two, st2 = _gpu_decode(shape, model, offsets, enc, N, 2, debug=256 | 32)
+    assert not st1["path"]["fixed_places"] and st1["joiner_calls"] == st2["joiner_calls"]
+    tol, score_tol = tolerance(shape, model)
+    differ = [u for u, (g, r) in enumerate(zip(one, two)) if [y for y, _ in g] != [y for y, _ in r]]
+    assert len(differ) <= U // 32   # (a product may run in another kernel: decisions closer than the arithmetic can tell apart)
+    assert all(abs(a[1] - b[1]) <= score_tol for u, (g, r) in enumerate(zip(one, two)) if u not in differ for a, b in zip(g, r))
+
+
 @pytest.mark.parametrize("dtype,hidden,layers,V,U,N,S,debug,peaked", [
     ("bf16", 64, 1, 96, 6, 5, 3, 256, True), ("bf16", 72, 2, 96, 70, 16, 2, 256, False), ("bf16", 64, 3, 96, 6, 2, 4, 256, True),
     ("bf16", 128, 4, 96, 5, 32, 3, 256 + 8, False), ("bf16", 128, 2, 2100, 7, 5, 3, 8 + 32, True), ("bf16", 1024, 2, 300, 130, 8, 1, 512, False),
