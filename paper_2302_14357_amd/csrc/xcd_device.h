@@ -1133,9 +1133,8 @@ __device__ __forceinline__ void xcd_project_f32(const XcdPlace &w, XcdShared &sh
 
 // NT threads, room for a wave per hypothesis and one for the select step; FEW: beams up to 8 (see select_merge_utt).
 // PUSH: a push of a stream, one segment whose figures and frames come with the launch.  (A kernel of its own: a launch runs through its code
-// once for a push, and
-// what the one does not need of the other's, it does not fetch: 64 streams N = 5 S = 3, three frames a push, utterances of 60 to 150 frames 5.74 -> 5.56 ms, 100
-// of N = 8 8.22 -> 7.87, 64 utterances as a batch 3.83 -> 3.78.)
+// once for a push, and what the one does not need of the other's, it does not fetch.  Utterances of 60 to 150 frames, ms: 64 streams N = 5 S = 3, three
+// frames a push, 5.74 -> 5.56, 100 of N = 8 8.22 -> 7.87, 64 utterances as a batch 3.83 -> 3.78.)
 template <int NT, int NV4, int SMAX, bool FEW, bool F32, bool PUSH>
 __global__ void __launch_bounds__(NT)
 k_xcd_decode(XcdArgs args) {
