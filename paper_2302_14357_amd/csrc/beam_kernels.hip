@@ -10,6 +10,7 @@
 // "the same tokens" when hash and length agree and a walk up the trie agrees.
 #include "tbs_internal.h"
 #include "select_device.h"
+#include <algorithm>
 
 // ------------------------------------------------------------------ batch init
 __global__ void k_init_batch(Dims d, BView B, AView A0, AView A1, RowView rv, int2 *nodes, float *pool_p,
@@ -168,11 +169,7 @@ k_segment_begin(Dims d, int seg, const int *utt_T, BView B, AView A, RowView rv,
     __syncthreads();
     for (int i = tid; i < nB; i += NT) {
         const double si = s_bl[i];
-        int rank = 0;
-        for (int j = 0; j < nB; ++j) {
-            const double sj = s_bl[j];
-            rank += (sj > si) || (sj == si && j < i);
-        }
+        const int rank = rank_in_list<8>(s_bl, nB, i);
         if (rank < d.N) {
             const long a = (long)u * d.N + rank, b = bb + i;
             const bool mine = i == tid;
@@ -562,6 +559,14 @@ k_select_merge(Dims d, int round, int drop, const float *logits, const float *ro
     if (wave == 0) phase(5);
 }
 
+// the rank of entry i, counted by `parts` lanes (tests ask it; holes: NaN marks a place without an entry)
+extern "C" int rank_of_entry(const double *v, int n, int parts, int holes, int i) {
+    int beaten = 0;
+    for (int p = 0, per = (n + parts - 1) / parts; p < parts; ++p)
+        beaten += rank_beaten<4>(v, std::min(p * per, n), std::min((p + 1) * per, n), v[i], i);
+    return holes ? beaten : rank_placed(v, n, v[i], i, beaten);
+}
+
 extern "C" int select_dist_form(int candidates, int frames) { return sel_dist_form(candidates, frames); }
 
 hipError_t launch_select_merge(hipStream_t st, const Dims &d, int round, int drop, const float *logits,
@@ -615,12 +620,8 @@ k_finalize(Dims d, BView B, const int2 *nodes, int *res_count, int *res_len, dou
     if (lane < d.N) s_len[lane] = 0;
     __syncthreads();
     for (int i = lane; i < nB; i += WAVE) {
-        double si = bl[i];
-        int rank = 0;
-        for (int j = 0; j < nB; ++j) {
-            double sj = bl[j];
-            rank += (sj > si) || (sj == si && j < i);
-        }
+        const double si = bl[i];
+        const int rank = rank_in_list<1>(bl, nB, i);
         if (rank < d.N) {
             long o = (long)u * d.N + rank;
             int len = B.len[(long)u * d.BCAP + i];

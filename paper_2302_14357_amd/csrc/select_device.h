@@ -3,6 +3,7 @@
 // test, and the new list A with its frame distributions.  Shared by the kernel that does this for
 // every utterance of a batch and the kernel that runs a whole round of one utterance.
 #pragma once
+#include "rank_order.h"
 #include "tbs_internal.h"
 
 #define WAVE 64
@@ -69,37 +70,27 @@ __device__ __forceinline__ void pair_mark_dead(const RowView &rv, int j, int u, 
 // What the expansion step left for this utterance: logarithms and tokens of the N best expansions
 // of each of its hypotheses [H, N], the logarithm of each blank expansion [H], and per frame of each
 // hypothesis log(alpha_t / Z_t) - m_t [H, S'] (any of them in LDS or in device memory).
-// Ranks by counting: the rank of entry i of v[0..n) is the number of entries that beat it (larger
-// value, or equal value and earlier place; NaN beats nothing).  Every entry is read from LDS by all
+// Ranks by counting: the rank of entry i of v[0..n) is the number of entries that beat it (rank_order.h; HOLES: a list in
+// which NaN marks a place without an entry).  Every entry is read from LDS by all
 // lanes that need it.  Up to 32 entries the wave's lanes share an entry's count (two lanes each up to
 // 32, four up to 16), each counting over a part of the list, and add their counts up.
 // fn(i, rank, value) is called once per entry, by one lane.
-template <class F>
+template <bool HOLES, class F>
 __device__ __forceinline__ void sel_rank(const double *v, int n, int lane, F fn) {
+    auto place = [&](double mine, int i, int beaten) { return HOLES ? beaten : rank_placed(v, n, mine, i, beaten); };
     if (n <= 32) {
         const int parts = n <= 16 ? 4 : 2, width = WAVE / parts;   // lanes per part
         const int i = lane & (width - 1), part = lane / width;
         const int per = (n + parts - 1) / parts, j0 = part * per, j1 = min(j0 + per, n);
         const double mine = v[min(i, n - 1)];
-        int rank = 0;
-#pragma unroll 4
-        for (int j = j0; j < j1; ++j) {
-            const double o = v[j];
-            rank += (o > mine) || (o == mine && j < i);
-        }
+        int rank = rank_beaten<4>(v, j0, j1, mine, i);
         rank += __shfl_xor(rank, 32);
         if (parts == 4) rank += __shfl_xor(rank, 16);
-        if (part == 0 && i < n) fn(i, rank, mine);
+        if (part == 0 && i < n) fn(i, place(mine, i, rank), mine);
     } else {
         for (int i = lane; i < n; i += WAVE) {
             const double mine = v[i];
-            int rank = 0;
-#pragma unroll 4
-            for (int j = 0; j < n; ++j) {
-                const double o = v[j];
-                rank += (o > mine) || (o == mine && j < i);
-            }
-            fn(i, rank, mine);
+            fn(i, place(mine, i, rank_beaten<4>(v, 0, n, mine, i)), mine);
         }
     }
 }
@@ -184,8 +175,8 @@ struct SelectArrays {
 #define TBS_SELECT_ARRAYS_ANY(name) TBS_SELECT_ARRAYS(name, CAND_MAX, (TBS_MAX_SEG * TBS_MAX_BEAM), SEL_PRE_FRAMES, SEL_PRE_CANDS)
 
 // ChooseNBestExpansions and ChooseNthScore by several waves (this one `place` of `places`), 16 entries of a list a wave, four lanes
-// sharing one: the rank of an entry is the number of those that beat it (larger score, or equal score and earlier place; a
-// place without a candidate holds NaN and beats nothing).  (By one wave ranking a B of 85 entries was 2 us.)
+// sharing one: the rank of an entry is the number of those that beat it (rank_order.h; a place without a candidate holds NaN, an
+// entry of B may have a score that is NaN and takes a place all the same).  (By one wave ranking a B of 85 entries was 2 us.)
 template <class SM>
 __device__ __forceinline__ void sel_rank_waves(SM &sm, const double *blogs, int nB, int nc, int N, int place, int places, int lane) {
     const int gc = (nc + 15) >> 4, groups = gc + ((nB + 15) >> 4);
@@ -195,18 +186,13 @@ __device__ __forceinline__ void sel_rank_waves(SM &sm, const double *blogs, int 
         const int n = cands ? nc : nB, c = 16 * (cands ? gr : gr - gc) + (lane & 15);
         const int per = (n + 3) >> 2, j0 = (lane >> 4) * per, j1 = min(j0 + per, n);
         const double mine = v[min(c, n - 1)];
-        int rank = 0;
-#pragma unroll 4
-        for (int j = j0; j < j1; ++j) {
-            const double o = v[j];
-            rank += (o > mine) || (o == mine && j < c);
-        }
+        int rank = rank_beaten<4>(v, j0, j1, mine, c);
         rank += __shfl_xor(rank, 32);
         rank += __shfl_xor(rank, 16);
         if (lane < 16 && c < n) {
             if (cands) {
                 if (mine == mine && rank < N) sm.s_sel[rank] = c;
-            } else if (rank < N) {
+            } else if ((rank = rank_placed(v, n, mine, c, rank)) < N) {
                 sm.s_match[rank] = c;   // (for who makes the next segment's list; the merge is done with it)
                 if (rank == N - 1) sm.thr() = mine;
             }
@@ -367,13 +353,13 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
 
             // --- threshold = ChooseNthScore(B, N), only defined when B holds N entries.  The rank of an
             // entry is the number of entries that beat it (larger score, or equal score and earlier
-            // place); every lane counts for its own entries against the whole list, read from LDS at
-            // one address for all lanes.  (Ranking by one ballot per entry was measured at ~270 ns per
+            // place; a NaN comes behind all numbers, and as a threshold lets no candidate pass); every lane
+            // counts for its own entries against the whole list, read from LDS at one address for all lanes.  (Ranking by one ballot per entry was measured at ~270 ns per
             // entry on the single wave: readlane and ballot results are needed at once, so nothing
             // overlaps.)
             const bool have_thr_m = nB >= N;
             if (lane == 0) s_have_thr = have_thr_m;
-            if (have_thr_m && PHASE != 6) sel_rank(s_blogs, nB, lane, [&](int i, int rank, double si) {
+            if (have_thr_m && PHASE != 6) sel_rank<false>(s_blogs, nB, lane, [&](int i, int rank, double si) {
                 if (rank == N - 1) s_thr = si;
             });
         }
@@ -383,7 +369,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
             // candidates of a hypothesis arrive sorted by exactly that rule, hypotheses in order, so
             // "earlier place" decides equal scores.  (A place without a candidate holds NaN and never
             // compares as better.)
-            if (PHASE != 7) sel_rank(s_key, nc, lane, [&](int c, int rank, double kc) {
+            if (PHASE != 7) sel_rank<true>(s_key, nc, lane, [&](int c, int rank, double kc) {
                 if (kc == kc && rank < N) s_sel[rank] = c;
             });
             if (pre_x) {

@@ -376,12 +376,7 @@ __device__ __forceinline__ void xcd_head(const XcdPlace &w, XcdShared &sh, doubl
         const int cnt = min(nB, N);
         for (int e = tid; e < nB; e += NT) {
             const double si = s_bl[e];
-            int rank = 0;
-#pragma unroll 8
-            for (int j = 0; j < nB; ++j) {
-                const double sj = s_bl[j];
-                rank += (sj > si) || (sj == si && j < e);
-            }
+            const int rank = rank_in_list<4>(s_bl, nB, e);
             if (rank < N) {
                 const bool mine = e == tid;
                 const long at = (long)u * N + rank, b = bb + e;
@@ -514,8 +509,8 @@ __device__ __forceinline__ void xcd_joiner(const XcdPlace &w, const unsigned cha
 }
 
 // The head of the outer loop for an utterance whose list A is empty, by a wave beside the select wave (xcd_finish, which then has
-// little to do) while the other utterances' rounds go on: what the select step left of B in LDS and its ranking make the next
-// segment's list.  The segment itself then begins with xcd_carry.  As a step of its own, behind the last round's barrier and with a
+// little to do) while the other utterances' rounds go on: what the select step left of B in LDS and its ranking, which gives every
+// place below the list's length exactly one entry whatever the scores are (rank_order.h), make the next segment's list.  The segment itself then begins with xcd_carry.  As a step of its own, behind the last round's barrier and with a
 // barrier of its own: ms per decode, 64 utterances N = 5 S = 1 13.0 (now 12.1), S = 3 9.97 (9.86), S = 20 the same, 200 utterances 15.2 (14.9),
 // 16 fp32 12.4 (12.1), one 4.82 (4.70).  (By the select wave behind its own part: S = 1 12.3.)
 template <int SMAX, class SM>

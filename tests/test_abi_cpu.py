@@ -2,9 +2,11 @@
 header declares, and rejects bad configurations before touching a GPU."""
 
 import ctypes as C
+import math
 import os
 import re
 
+import numpy as np
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -165,3 +167,37 @@ def test_barrier_of_an_xcd_in_every_order(ahead, behind, live):
     assert _barrier_runs(L.xcd_barrier_reads, groups, live, ahead, behind) == want
     # (the model sees the mistake it is here for: a sum taken at every barrier)
     assert _barrier_runs(lambda w, due, seen, ends: L.xcd_barrier_reads(w, due, seen, 1), groups, live, ahead, behind) != want
+
+
+def _rank_lists():
+    """Lists of scores as a call with frames that are no numbers makes them, among others."""
+    nan, inf = math.nan, math.inf
+    rng = np.random.default_rng(5)
+    lists = [[nan] * 5, [nan], [-1.0, nan, -3.0, nan, -2.0], [nan, nan, -5.0, -1.0, -1.0], [-inf] * 4, [-inf, nan, -inf], [-2.0] * 6,
+             [inf, nan, -inf, inf, 0.0], [-4.0, -1.0, -1.0, -9.0]]
+    for n in (16, 17, 32, 33, 64, 85, 320):
+        v = rng.integers(-6, 0, n).astype(float)
+        v[rng.random(n) < 0.3] = nan
+        v[rng.random(n) < 0.1] = -inf
+        lists.append(v.tolist())
+    return lists
+
+
+@pytest.mark.parametrize("parts", [1, 2, 4])
+def test_ranks_of_scores_that_are_no_numbers(parts):
+    """Every entry of a list B has a rank of its own, whatever the scores are: larger first, equal ones by place, NaN behind all.  Who makes the
+    next segment's list reads the entry of every rank below the list's length; with NaN that beats nothing and that nothing beats,
+    the order of candidate lists, whose NaN mark places without a candidate, some ranks have several entries and others none."""
+    L, _ = _lib()
+    L.rank_of_entry.argtypes = [C.c_void_p] + [C.c_int] * 4
+    holes = False
+    for values in _rank_lists():
+        v = np.array(values, np.float64)
+        n = len(v)
+        got = [L.rank_of_entry(v.ctypes.data, n, parts, 0, i) for i in range(n)]
+        order = sorted(range(n), key=lambda i: (math.isnan(v[i]), 0.0 if math.isnan(v[i]) else -v[i], i))
+        assert [order.index(i) for i in range(n)] == got, values
+        cands = [L.rank_of_entry(v.ctypes.data, n, parts, 1, i) for i in range(n)]
+        assert [r for r, x in zip(cands, v) if x == x] == [r for r, x in zip(got, v) if x == x]   # (numbers have the same ranks)
+        holes = holes or sorted(cands) != list(range(n))
+    assert holes   # (the lists see the mistake they are here for)

@@ -1734,3 +1734,72 @@ def test_large_batches_keep_to_the_other_forms(dtype, N, S, few, many):
     for a, b in zip(got[0], got[1]):
         assert [h[0] for h in a] == [h[0] for h in b]
         np.testing.assert_allclose([h[1] for h in a], [h[1] for h in b], rtol=1e-6, atol=1e-5)
+
+
+def _bad_batches(offsets, enc, u, S, act):
+    """The frames of a batch with some of utterance u's that are no numbers (or, where the activation makes numbers of those,
+    infinite): the last one of its second segment, all of that segment's, all it has."""
+    lo, hi = int(offsets[u]), int(offsets[u + 1])
+    assert hi - lo > 2 * S
+    for a, b in [(lo + 2 * S - 1, lo + 2 * S), (lo + S, lo + 2 * S), (lo, hi)]:
+        bad = enc.copy()
+        bad[a:b] = math.nan if act == "tanh" else math.inf
+        if act == "relu":
+            bad[a:b, ::2] = -math.inf
+        yield bad
+
+
+def _check_bad_utterance(got, clean, bad_u, V, N):
+    for u, (g, c) in enumerate(zip(got, clean)):
+        if u != bad_u:
+            assert g == c, u
+    assert 1 <= len(got[bad_u]) <= N
+    assert len({y for y, _ in got[bad_u]}) == len(got[bad_u])
+    assert all(0 < k < V for y, _ in got[bad_u] for k in y)
+
+
+@pytest.mark.parametrize("dtype,act,d,hidden,layers,V,N,S,debugs", [
+    ("bf16", "tanh", 128, 128, 1, 96, 5, 1, (0, 65536, 256)), ("bf16", "tanh", 128, 128, 1, 96, 4, 1, (0, 32768 + 65536, 512 + 256)),
+    ("bf16", "tanh", 128, 256, 1, 96, 5, 3, (0, 65536, 131072, 256, 256 + 128)), ("bf16", "relu", 128, 128, 1, 200, 10, 5, (0, 65536, 256)),
+    ("bf16", "tanh", 128, 128, 1, 96, 5, 8, (0, 65536)), ("bf16", "relu", 128, 128, 1, 96, 3, 40, (0, 65536)),
+    ("f32", "tanh", 64, 64, 1, 40, 5, 3, (0, 65536, 256)), ("bf16", "tanh", 64, 72, 2, 96, 20, 2, (0, 2)),
+    ("bf16", "tanh", 64, 64, 3, 2100, 5, 3, (0, 8)), ("bf16", "tanh", 64, 64, 1, 4200, 12, 9, (0,))])
+def test_an_utterance_whose_frames_are_no_numbers(dtype, act, d, hidden, layers, V, N, S, debugs):
+    """Encoder frames come from the caller and nobody looks at them.  An utterance some of whose are NaN (or infinite) has scores that are
+    NaN; it is decoded to an end, the same twice, and the others of the batch give the bits they give without it: whole
+    segments in one launch, in four kernels a round and by row lists, every form of the expansion and the select step."""
+    import dataclasses
+    lengths = np.array([2 * S + 1 + (7 * i) % (2 * S + 5) for i in range(9)])
+    shape = dataclasses.replace(small_bf16_shape(n_utts=9, vocab=V, d=d, hidden=hidden, layers=layers), dtype=dtype, act=act)
+    model, offsets, enc = build_case(shape, n_utts=9, lengths=lengths)
+    kw = dict(rounds_capacity=64 if S > 16 else 0)
+    by_form = []
+    for debug in debugs:
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug, **kw)
+        clean = tbs.decode(tbs.upload_frames(enc), offsets)
+        bad_results = []
+        for bad in _bad_batches(offsets, enc, 4, S, act):
+            frames = tbs.upload_frames(bad)
+            got = tbs.decode(frames, offsets)
+            _check_bad_utterance(got, clean, 4, V, N)
+            assert repr(tbs.decode(frames, offsets)) == repr(got)
+            bad_results.append(repr(got[4]))
+        tbs.close()
+        by_form.append(bad_results)
+    if len(debugs) > 1 and debugs[:2] == (0, 65536):   # (these keep the order of sums)
+        assert by_form[0] == by_form[1]
+
+
+@pytest.mark.parametrize("debug", [0, 65536, 256])
+def test_a_stream_whose_frames_are_no_numbers(debug):
+    """The same pushed in pieces."""
+    N, S = 5, 3
+    shape = small_bf16_shape(n_utts=9, vocab=120, d=256, hidden=128)
+    model, offsets, enc = build_case(shape, n_utts=9, lengths=np.array([7 + 3 * i for i in range(9)]))
+    tbs = make_tbs(shape, model, offsets, N, S, stream_buffer_frames=12, debug=debug)
+    _push_in_pieces(tbs, shape, offsets, enc, lambda u, c: 1 + (u + 2 * c) % 5)
+    clean = tbs.result()
+    for bad in _bad_batches(offsets, enc, 4, S, "tanh"):
+        _push_in_pieces(tbs, shape, offsets, bad, lambda u, c: 1 + (u + 2 * c) % 5)
+        _check_bad_utterance(tbs.result(), clean, 4, 120, N)
+    tbs.close()
