@@ -92,6 +92,7 @@ __global__ void k_joiner_prep_pairs(int Dj, int act, const bf16_t *__restrict__ 
 
 hipError_t launch_joiner_prep_pairs(hipStream_t st, const Dims &d, int act, const bf16_t *enc, const float *pool_p,
                                     RowView rv, bf16_t *amat, int pairs) {
+    if (pairs <= 0) return hipSuccess;
     const long n = (long)pairs * (d.Dj / 8);
     hipLaunchKernelGGL(k_joiner_prep_pairs, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, d.Dj, act, enc, pool_p,
                        rv.pair_row0, rv.pair_len, rv.pair_frame0, rv.pair_slot, amat, rv.counts + TBS_CNT_PAIRS);

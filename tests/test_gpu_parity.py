@@ -1803,3 +1803,43 @@ def test_a_stream_whose_frames_are_no_numbers(debug):
         _push_in_pieces(tbs, shape, offsets, bad, lambda u, c: 1 + (u + 2 * c) % 5)
         _check_bad_utterance(tbs.result(), clean, 4, 120, N)
     tbs.close()
+
+
+@pytest.mark.parametrize("dtype,S,debug", [("bf16", 3, 0), ("bf16", 3, 8192), ("bf16", 1, 0), ("f32", 3, 0)])
+def test_a_round_without_hypotheses_is_no_error(dtype, S, debug):
+    """A caller that drives the steps may make one more round behind the one that made nothing, or one over lists that it has emptied:
+    every step has nothing to do and says so, and the next segment begins as if the round had not been."""
+    import dataclasses
+    from paper_2302_14357_amd import BUF
+    N = 4
+    shape = dataclasses.replace(small_bf16_shape(n_utts=3, vocab=60), dtype=dtype)
+    model, offsets, enc = build_case(shape, n_utts=3, lengths=np.array([2 * S, 2 * S - 1, 0]))
+    want = None
+    for extra in (0, 2):
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug)
+        tbs.begin(tbs.upload_frames(enc), offsets)
+        for seg in range(2):
+            rows = tbs.segment_begin(seg)
+            while rows > 0:
+                tbs.joiner_segment()
+                tbs.expand()
+                live = tbs.select_merge()
+                tbs.predictor_step()
+                rows = tbs.counts()["rows"]
+                assert (rows > 0) == (live > 0)
+            for _ in range(extra):
+                tbs.joiner_segment()
+                tbs.expand()
+                assert tbs.select_merge() == 0
+                tbs.predictor_step()
+                assert tbs.counts()["rows"] == 0
+        got = tbs.result()
+        want = want or got
+        assert got == want
+        if extra:
+            tbs.debug_write(BUF.A_COUNT, np.zeros(3, np.int32))
+            assert tbs.debug_rebuild(0) == 0
+            tbs.joiner_segment()
+            tbs.expand()
+            assert tbs.select_merge() == 0
+        tbs.close()
