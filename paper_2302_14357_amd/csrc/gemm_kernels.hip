@@ -1118,7 +1118,7 @@ hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, co
                             int N, int K, const int *out_row, long ldc, int kernel, const int *m_dev, bool xcd_rows,
                             bool bias_late, int m_likely) {
     if (M <= 0) return hipSuccess;
-    const int Mc = m_likely > 0 ? min(m_likely, M) : M;   // (the rows that the kernel is chosen for)
+    const int Mc = m_likely <= 0 ? M : m_dev ? min(m_likely, M) : m_likely;   // (the rows that the kernel is chosen for)
     if (kernel == 0) {
         const int shape = gemm_tile_shape(Mc, N, K);
         if (shape && gt_fits(C, M, N, K, ldc, shape % 10)) return gt_launch_shape(st, shape, A, B, bias, C, M, N, K, out_row, ldc, m_dev);

@@ -940,6 +940,13 @@ static int joiner_expand_pieces(tbs_ctx *c, int rows, int piece) {
     return TBS_OK;
 }
 
+static int utts_in_segment(const tbs_ctx *c, int seg_index) {   // (that have frames in it)
+    int n = 0;
+    for (int u = 0; u < c->cur.U; ++u) n += c->h_T[u] > seg_index * c->cur.S;
+    return n;
+}
+static bool first_round_by_bound(const tbs_ctx *c, int utts);
+
 int tbs_joiner_segment(tbs_ctx *c) {
     if (!c) return TBS_EINVAL;
     if (c->state != ST_READY) return TBS_ESTATE;
@@ -968,9 +975,10 @@ int tbs_joiner_segment(tbs_ctx *c) {
     }
     c->prep_ahead = false;
     {
+        const int utts = c->round == 1 ? utts_in_segment(c, c->seg) : 0;
+        const int likely = utts > 0 && first_round_by_bound(c, utts) ? utts * c->cur.N * c->cur.S : 0;
         ProfScope ps(c, TBS_K_JOINER, rows);
-        HIPCHK(c, gemm(c, c->amat, c->w.w_out, c->w.b_out, c->logits, rows, c->cur.V, c->cur.Dj, nullptr,
-                       c->cur.Vl));
+        HIPCHK(c, gemm(c, c->amat, c->w.w_out, c->w.b_out, c->logits, rows, c->cur.V, c->cur.Dj, nullptr, c->cur.Vl, nullptr, likely));
     }
     c->n_launches += 1;
     c->state = ST_JOINED;
@@ -1301,8 +1309,14 @@ int tbs_result(tbs_ctx *c, int32_t *tokens, int32_t *lens, double *logscores, in
 static bool segment_ahead_ok(const tbs_ctx *c, int utts) {
     const Dims &d = c->cur;
     if ((c->cfg.debug & 64) || c->prof_kernel >= 0 || d.R < 1) return false;
-    if (joiner_small(c, d.U * d.N * d.S, false) && predictor_all_fused(c, d.U * d.N, false)) return true;
-    return by_parent(c, utts * d.N) && gather_in_rowfill(c) && c->cfg.joiner_chunk_rows == 0;   // (as hid_ahead)
+    return (joiner_small(c, d.U * d.N * d.S, false) && predictor_all_fused(c, d.U * d.N, false)) || first_round_by_bound(c, utts);
+}
+
+// By parents a segment's first round is enqueued ahead of its counts under the conditions of hid_ahead, and the joiner's kernel chosen for
+// the most rows that the round can have.  Which kernel it is decides where the bias is added, so whoever makes such a round
+// with its counts known (a caller that drives the steps, a kernel family being timed, debug bit 6) has the same one.
+static bool first_round_by_bound(const tbs_ctx *c, int utts) {
+    return by_parent(c, utts * c->cur.N) && gather_in_rowfill(c) && c->cfg.joiner_chunk_rows == 0;
 }
 
 // the joiner GEMM of a call whose row count is known on the device only (utts: utterances that can take part)
@@ -1740,8 +1754,8 @@ static int run_segments_xcd(tbs_ctx *c, int seg0, int seg1, int *ran, const void
 // one segment: the head of the outer loop of Algorithm 1 and its inner loop (while Length(A) > 0)
 static int run_segment(tbs_ctx *c, int32_t seg_index) {
     if (c->fixed) return run_segment_fixed(c, seg_index);
-    int rc, rows = 0, live = 0, utts = 0;
-    for (int u = 0; u < c->cur.U; ++u) utts += c->h_T[u] > seg_index * c->cur.S;   // (that have frames in the segment)
+    int rc, rows = 0, live = 0;
+    const int utts = utts_in_segment(c, seg_index);
     if (segment_ahead_ok(c, utts)) {
         if ((rc = segment_begin_ahead(c, seg_index, utts))) return rc;
     } else {

@@ -1843,3 +1843,47 @@ def test_a_round_without_hypotheses_is_no_error(dtype, S, debug):
             tbs.expand()
             assert tbs.select_merge() == 0
         tbs.close()
+
+
+@pytest.mark.parametrize("M,N,K", [(64, 64, 128), (300, 200, 256), (1000, 1025, 640), (2050, 4096, 1024), (37, 100, 72), (700, 513, 520)])
+def test_gemm_bf16_kernels_give_the_same_bits(M, N, K):
+    """Whichever kernel makes a product without a bias: all add up K in the same order.  (The recurrent products' is chosen for the rows
+    that the segment before had.)"""
+    import torch
+    from paper_2302_14357_amd import gemm_bf16
+    rng = np.random.default_rng(M + N + K)
+    a, b = _bf16_values(rng, (M, K)).cuda(), _bf16_values(rng, (N, K), 0.1).cuda()
+    first = gemm_bf16(a, b, kernel=1)
+    for kernel in (0, 2, 3) + ((4,) if K % 128 == 0 else ()):
+        assert torch.equal(first, gemm_bf16(a, b, kernel=kernel)), kernel
+
+
+@pytest.mark.parametrize("U,N,S,d,hidden,layers,V", [(400, 10, 5, 128, 64, 1, 4096), (240, 10, 5, 128, 64, 1, 4096), (400, 10, 5, 64, 64, 1, 4096),
+                                                     (130, 8, 3, 64, 64, 2, 300), (60, 6, 7, 72, 72, 1, 96)])
+def test_decode_equals_its_steps(U, N, S, d, hidden, layers, V):
+    """tbs_decode, whose segments' first rounds may be enqueued for the most rows there can be (here also where that is beyond what tiles
+    of a few a CU serve and the rows there are do not reach it), and the same driven step by step: the same bits.
+    (Expansion and select step as two kernels throughout: the one for both, which steps do without, adds up a row in another order.)"""
+    shape = small_bf16_shape(n_utts=U, vocab=V, d=d, hidden=hidden, layers=layers)
+    lengths = np.random.default_rng(U).integers(S, 2 * S + 2, U)
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=lengths)
+    results = []
+    for debug in (128, 128 + 64):   # (64: nothing is enqueued ahead)
+        tbs = make_tbs(shape, model, offsets, N, S, debug=debug)
+        frames = tbs.upload_frames(enc)
+        results.append(tbs.decode(frames, offsets))
+        assert not tbs.path()["fixed_places"]
+        if len(results) == 1:
+            tbs.begin(frames, offsets)
+            for seg in range(_segments(offsets, S)):
+                rows = tbs.segment_begin(seg)
+                while rows > 0:
+                    tbs.joiner_segment()
+                    tbs.expand()
+                    tbs.select_merge()
+                    tbs.predictor_step()
+                    rows = tbs.counts()["rows"]
+            results.append(tbs.result())
+        tbs.close()
+    for other in results[1:]:
+        assert results[0] == other
