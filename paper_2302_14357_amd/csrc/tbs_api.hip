@@ -129,7 +129,7 @@ struct tbs_ctx {
     void *xpar;
     float *hid_gates;
 #define TBS_SEEN 8
-    int pars_seen[TBS_SEEN];   // parents in the first rounds (the last: in those behind too) of the segment before, 0: not known
+    int pars_seen[TBS_SEEN];   // parents in the first rounds (the last: in those behind too) of the segment before, of this batch; 0: not known
 
     int *h_begin, *h_begin_dev;   // pinned: what tbs_begin tells the kernels of a batch's utterances (see launch_init_batch)
 
@@ -553,7 +553,6 @@ int tbs_init(const tbs_config *cfg, const tbs_weights *w, tbs_ctx **out) {
     // (a context that gets no memory for it forms the gates of every hypothesis whole)
     c->hid_ok = d.N > 1;
     c->hid = false;
-    memset(c->pars_seen, 0, sizeof(c->pars_seen));
     c->xpar = c->xh[0];
     c->hid_gates = nullptr;
     for (int l = 1; l < d.L; ++l)
@@ -813,6 +812,8 @@ static int begin_batch(tbs_ctx *c, const void *enc, const int32_t *offsets, int3
     c->join_ahead = false;
     c->expanded_ahead = false;
     c->hid = false;
+    memset(c->pars_seen, 0, sizeof(c->pars_seen));
+    c->pars_seen[0] = U;   // (the first segment's first round extends the empty hypothesis of every utterance)
     c->n_launches = 0;
     c->n_frames = frames;
     c->state = ST_BEGUN;

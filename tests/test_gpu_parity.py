@@ -1887,3 +1887,36 @@ def test_decode_equals_its_steps(U, N, S, d, hidden, layers, V):
         tbs.close()
     for other in results[1:]:
         assert results[0] == other
+
+
+def test_what_goes_out_ahead_does_not_hang_on_the_batch_before():
+    """The recurrent products go out ahead of a round's counts where the same round of the segment before made hypotheses: of this
+    batch's segments.  Batches of one segment have none before theirs, so each has as many launches behind any other batch as on
+    its own (a batch's last round, which makes nothing, would otherwise have one more behind a batch with more rounds)."""
+    from paper_2302_14357_amd import KERNEL
+    shape = small_bf16_shape(n_utts=1, vocab=60, hidden=72)   # (three or four rounds a segment)
+    N, S = 4, 4
+    model, offsets, enc = build_case(shape, n_utts=12, lengths=np.full(12, S))
+    tbs = make_tbs(shape, model, offsets, N, S, debug=256)
+    frames = [tbs.upload_frames(enc[u * S:(u + 1) * S]) for u in range(12)]
+    one = np.array([0, S], np.int32)
+
+    def decode(u):
+        tbs.profile_select(KERNEL.GEMM)
+        tbs.decode(frames[u], one)
+        return tbs.profile_read()["launches"], tbs.stats()["launches"]
+
+    alone = [decode(u) for u in range(12)]
+    rounds = [r for _, r in alone]
+    most, least = int(np.argmax(rounds)), int(np.argmin(rounds))
+    assert rounds[most] > rounds[least]
+    fresh = {}
+    for u in (most, least):
+        tbs.close()
+        tbs = make_tbs(shape, model, offsets, N, S, debug=256)
+        fresh[u] = decode(u)
+    for first in (most, least):
+        for then in (most, least):
+            decode(first)
+            assert decode(then) == fresh[then], (first, then)
+    tbs.close()
