@@ -70,14 +70,13 @@ __device__ __forceinline__ void pair_mark_dead(const RowView &rv, int j, int u, 
 // What the expansion step left for this utterance: logarithms and tokens of the N best expansions
 // of each of its hypotheses [H, N], the logarithm of each blank expansion [H], and per frame of each
 // hypothesis log(alpha_t / Z_t) - m_t [H, S'] (any of them in LDS or in device memory).
-// Ranks by counting: the rank of entry i of v[0..n) is the number of entries that beat it (rank_order.h; HOLES: a list in
-// which NaN marks a place without an entry).  Every entry is read from LDS by all
+// Ranks by counting: the rank of entry i of v[0..n) is the number of entries that beat it (rank_order.h; a NaN's means
+// nothing).  Every entry is read from LDS by all
 // lanes that need it.  Up to 32 entries the wave's lanes share an entry's count (two lanes each up to
 // 32, four up to 16), each counting over a part of the list, and add their counts up.
 // fn(i, rank, value) is called once per entry, by one lane.
-template <bool HOLES, class F>
+template <class F>
 __device__ __forceinline__ void sel_rank(const double *v, int n, int lane, F fn) {
-    auto place = [&](double mine, int i, int beaten) { return HOLES ? beaten : rank_placed(v, n, mine, i, beaten); };
     if (n <= 32) {
         const int parts = n <= 16 ? 4 : 2, width = WAVE / parts;   // lanes per part
         const int i = lane & (width - 1), part = lane / width;
@@ -86,11 +85,11 @@ __device__ __forceinline__ void sel_rank(const double *v, int n, int lane, F fn)
         int rank = rank_beaten<4>(v, j0, j1, mine, i);
         rank += __shfl_xor(rank, 32);
         if (parts == 4) rank += __shfl_xor(rank, 16);
-        if (part == 0 && i < n) fn(i, place(mine, i, rank), mine);
+        if (part == 0 && i < n) fn(i, rank, mine);
     } else {
         for (int i = lane; i < n; i += WAVE) {
             const double mine = v[i];
-            fn(i, place(mine, i, rank_beaten<4>(v, 0, n, mine, i)), mine);
+            fn(i, rank_beaten<4>(v, 0, n, mine, i), mine);
         }
     }
 }
@@ -175,8 +174,10 @@ struct SelectArrays {
 #define TBS_SELECT_ARRAYS_ANY(name) TBS_SELECT_ARRAYS(name, CAND_MAX, (TBS_MAX_SEG * TBS_MAX_BEAM), SEL_PRE_FRAMES, SEL_PRE_CANDS)
 
 // ChooseNBestExpansions and ChooseNthScore by several waves (this one `place` of `places`), 16 entries of a list a wave, four lanes
-// sharing one: the rank of an entry is the number of those that beat it (rank_order.h; a place without a candidate holds NaN, an
-// entry of B may have a score that is NaN and takes a place all the same).  (By one wave ranking a B of 85 entries was 2 us.)
+// sharing one: the rank of an entry is the number of those that beat it (rank_order.h).  Numbers take their places: NaN is a place
+// without a candidate, and an entry of B whose score it is comes behind them all (left to who makes the next segment's list;
+// placed here, by one comparison an entry, 25 utterances N = 8 S = 2 took 5955 us a decode instead of 5847).  (By one wave ranking a B
+// of 85 entries was 2 us.)
 template <class SM>
 __device__ __forceinline__ void sel_rank_waves(SM &sm, const double *blogs, int nB, int nc, int N, int place, int places, int lane) {
     const int gc = (nc + 15) >> 4, groups = gc + ((nB + 15) >> 4);
@@ -189,10 +190,10 @@ __device__ __forceinline__ void sel_rank_waves(SM &sm, const double *blogs, int 
         int rank = rank_beaten<4>(v, j0, j1, mine, c);
         rank += __shfl_xor(rank, 32);
         rank += __shfl_xor(rank, 16);
-        if (lane < 16 && c < n) {
+        if (lane < 16 && c < n && mine == mine && rank < N) {
             if (cands) {
-                if (mine == mine && rank < N) sm.s_sel[rank] = c;
-            } else if ((rank = rank_placed(v, n, mine, c, rank)) < N) {
+                sm.s_sel[rank] = c;
+            } else {
                 sm.s_match[rank] = c;   // (for who makes the next segment's list; the merge is done with it)
                 if (rank == N - 1) sm.thr() = mine;
             }
@@ -353,14 +354,18 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
 
             // --- threshold = ChooseNthScore(B, N), only defined when B holds N entries.  The rank of an
             // entry is the number of entries that beat it (larger score, or equal score and earlier
-            // place; a NaN comes behind all numbers, and as a threshold lets no candidate pass); every lane
+            // place; NaN comes behind all numbers, and as the threshold lets no candidate pass); every lane
             // counts for its own entries against the whole list, read from LDS at one address for all lanes.  (Ranking by one ballot per entry was measured at ~270 ns per
             // entry on the single wave: readlane and ballot results are needed at once, so nothing
             // overlaps.)
             const bool have_thr_m = nB >= N;
-            if (lane == 0) s_have_thr = have_thr_m;
-            if (have_thr_m && PHASE != 6) sel_rank<false>(s_blogs, nB, lane, [&](int i, int rank, double si) {
-                if (rank == N - 1) s_thr = si;
+            if (lane == 0) {
+                s_have_thr = have_thr_m;
+                s_thr = nan("");   // (unless N numbers are in the list)
+            }
+            if (PHASE == 6 && lane < N) s_match[lane] = -1;   // (places of the ranking to come, see sel_rank_waves)
+            if (have_thr_m && PHASE != 6) sel_rank(s_blogs, nB, lane, [&](int i, int rank, double si) {
+                if (si == si && rank == N - 1) s_thr = si;
             });
         }
         if (do_cand) {
@@ -369,7 +374,7 @@ __device__ __forceinline__ void select_merge_utt(SM &sm, const int PHASE, const 
             // candidates of a hypothesis arrive sorted by exactly that rule, hypotheses in order, so
             // "earlier place" decides equal scores.  (A place without a candidate holds NaN and never
             // compares as better.)
-            if (PHASE != 7) sel_rank<true>(s_key, nc, lane, [&](int c, int rank, double kc) {
+            if (PHASE != 7) sel_rank(s_key, nc, lane, [&](int c, int rank, double kc) {
                 if (kc == kc && rank < N) s_sel[rank] = c;
             });
             if (pre_x) {

@@ -509,8 +509,8 @@ __device__ __forceinline__ void xcd_joiner(const XcdPlace &w, const unsigned cha
 }
 
 // The head of the outer loop for an utterance whose list A is empty, by a wave beside the select wave (xcd_finish, which then has
-// little to do) while the other utterances' rounds go on: what the select step left of B in LDS and its ranking, which gives every
-// place below the list's length exactly one entry whatever the scores are (rank_order.h), make the next segment's list.  The segment itself then begins with xcd_carry.  As a step of its own, behind the last round's barrier and with a
+// little to do) while the other utterances' rounds go on: what the select step left of B in LDS and its ranking make the next
+// segment's list.  The segment itself then begins with xcd_carry.  As a step of its own, behind the last round's barrier and with a
 // barrier of its own: ms per decode, 64 utterances N = 5 S = 1 13.0 (now 12.1), S = 3 9.97 (9.86), S = 20 the same, 200 utterances 15.2 (14.9),
 // 16 fp32 12.4 (12.1), one 4.82 (4.70).  (By the select wave behind its own part: S = 1 12.3.)
 template <int SMAX, class SM>
@@ -531,6 +531,16 @@ __device__ __forceinline__ void xcd_next(const XcdPlace &w, XcdShared &sh, const
     const double *blogs = reinterpret_cast<const double *>(sc.b_list);
     const u64 *bhash = reinterpret_cast<const u64 *>(blogs + d.BCAP);
     const int *bnode = reinterpret_cast<const int *>(bhash + d.BCAP), *blen = bnode + d.BCAP, *bslot = blen + d.BCAP;
+    // (places that no number has taken: scores that are NaN, behind all numbers, so that every place of the list has an entry)
+    if (__builtin_expect(__ballot(lane < cnt && sm.s_match[min(lane, cnt - 1)] < 0) != 0, 0)) {
+        const int nB = __builtin_amdgcn_readfirstlane(s_out.nB);
+        for (int i = lane; i < nB; i += 64) {
+            const double v = blogs[i];
+            const int rank = v != v ? rank_placed(blogs, nB, v, i, 0) : N;
+            if (rank < N) sm.s_match[rank] = i;
+        }
+        sel_sync();
+    }
     if (lane < N) {
         int4 ds = make_int4(-1, 0, 0, 0);
         if (lane < cnt) {
