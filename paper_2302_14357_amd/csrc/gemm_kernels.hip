@@ -1091,10 +1091,14 @@ static hipError_t gt_launch_shape(hipStream_t st, int shape, const bf16_t *A, co
     }
 }
 
-// a product by a shape of k_gemm_tile (the tests run every one; *m_dev rows of M, result row r at out_row[r] of C)
+// a product by a shape of k_gemm_tile, or by kernel 1 to 4 of launch_gemm_bf16 (the tests run every one; *m_dev rows of M, result row r at
+// out_row[r] of C)
 extern "C" int gemm_tile_run(int shape, const void *A, const void *B, const float *bias, float *C, int M, int N, int K, const int *out_row,
                              long ldc, const int *m_dev, void *stream) {
-    if (shape < 100 || M < 1 || N < 1 || !gt_fits(C, M, N, K, ldc, shape % 10)) return (int)hipErrorInvalidValue;
+    if (M < 1 || N < 1 || K < 8 || K % 8) return (int)hipErrorInvalidValue;
+    if (shape >= 1 && shape <= 4)
+        return (int)launch_gemm_bf16((hipStream_t)stream, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, shape, m_dev);
+    if (shape < 100 || !gt_fits(C, M, N, K, ldc, shape % 10)) return (int)hipErrorInvalidValue;
     return (int)gt_launch_shape((hipStream_t)stream, shape, (const bf16_t *)A, (const bf16_t *)B, bias, C, M, N, K, out_row, ldc, m_dev);
 }
 

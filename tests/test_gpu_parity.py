@@ -1920,3 +1920,44 @@ def test_what_goes_out_ahead_does_not_hang_on_the_batch_before():
             decode(first)
             assert decode(then) == fresh[then], (first, then)
     tbs.close()
+
+
+@pytest.mark.parametrize("kernel", [1, 2, 3, 4])
+@pytest.mark.parametrize("M,N,K,lives", [(300, 200, 128, (0, 1, 64, 255, 299)), (9000, 4096, 128, (0, 4097, 8999)), (700, 130, 200, (0, 513))])
+def test_gemm_bf16_with_a_row_count_from_device_memory(M, N, K, lives, kernel):
+    """Fewer rows than the launch is sized for, down to none and up to several tiles of a persistent workgroup, rows scattered or in
+    place: the same bits as a product of those rows, and nothing written beside them."""
+    import ctypes
+    import torch
+    from paper_2302_14357_amd import gemm_bf16, load_library
+    if kernel == 4 and K % 128:
+        return
+    run = load_library().gemm_tile_run
+    run.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 4 + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_long] + [ctypes.c_void_p] * 2
+    rng = np.random.default_rng(M + kernel)
+    a, b = _bf16_values(rng, (M, K)).cuda(), _bf16_values(rng, (N, K), 0.1).cuda()
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+    ldc = N + 5
+    for live in lives:
+        where = torch.from_numpy(rng.permutation(M + 3)[:M].astype(np.int32)).cuda() if live % 2 else None
+        n, out = torch.tensor([live], dtype=torch.int32, device="cuda"), torch.full((M + 3, ldc), 7.0, device="cuda")
+        rc = run(kernel, a.data_ptr(), b.data_ptr(), bias.data_ptr(), out.data_ptr(), M, N, K, where.data_ptr() if where is not None else None, ldc,
+                 n.data_ptr(), torch.cuda.current_stream().cuda_stream)
+        assert rc == 0
+        rows = (where if where is not None else torch.arange(M, device="cuda"))[:live].long()
+        want = torch.full((M + 3, ldc), 7.0, device="cuda")
+        if live:
+            want[rows, :N] = gemm_bf16(a[:live].contiguous(), b, bias, kernel=kernel)
+        assert torch.equal(out, want), live
+
+
+@pytest.mark.parametrize("U,N,layers", [(103, 10, 1), (256, 16, 2), (241, 17, 1)])
+def test_rows_gathered_by_either_kernel_give_the_same_bits(U, N, layers):
+    """The parents' rows of h gathered by the row list kernel, with the products behind it enqueued ahead of the counts, and by a kernel of
+    their own: the same rows, and products that add up in the same order whichever kernel makes them."""
+    shape = small_bf16_shape(n_utts=U, vocab=96, d=128, hidden=512, layers=layers)
+    model, offsets, enc = build_case(shape, n_utts=U, lengths=np.random.default_rng(U).integers(0, 9, U))
+    one, st1 = _gpu_decode(shape, model, offsets, enc, N, 2, debug=256)
+    two, st2 = _gpu_decode(shape, model, offsets, enc, N, 2, debug=256 | 32)
+    assert not st1["path"]["fixed_places"]
+    assert one == two and st1["joiner_calls"] == st2["joiner_calls"]
