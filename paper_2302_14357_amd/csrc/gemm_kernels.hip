@@ -14,6 +14,7 @@
 // workgroups resident on one XCD (ids equal modulo 8) work on a compact block of
 // tiles and share their operand rows in that XCD's L2.
 #include "tbs_internal.h"
+#include <algorithm>
 #include <climits>
 
 typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
@@ -836,15 +837,15 @@ hipError_t launch_gemm_join(hipStream_t st, const bf16_t *A, const bf16_t *B, co
 // ------------------------------------------------------------------ problems of a few tiles a CU
 // One tile of (32 TM) x (64 TN) a workgroup of eight waves, waves of (16 TM) x (16 TN) in blocks of 16 x 16 (the same sums in the
 // same order as blocks of 32 x 32: the same bits).  The edge of a tile is chosen per problem, so that the tiles fill the
-// CUs in whole turns (gemm_tile_shape): with 128 x 128 tiles 2560 x 4096 is 640 of them, 2.5 a CU, and the chip waits for
+// CUs in whole turns (gemm_choice): with 128 x 128 tiles 2560 x 4096 is 640 of them, 2.5 a CU, and the chip waits for
 // the CUs that have three; 160 x 256 is one each.  K tiles of 64 pass through NS stages of LDS by direct loads, a stage asked for
 // again as soon as every wave has its last fragments, the fragments of the next 32 columns read while the matrix
 // instructions take the last ones (the waits stand in the code: the compiler would read each pair of fragments right in front of its
 // instruction, and wait for it).  What bounds it, 2560 x 4096 x 1024 (26 us; parts switched off in a copy): stores of the fp32
 // result 8.5 (5 TB/s, all at the end), start and first K tile 3.5, matrix instructions 11, fragment reads and loads beside them 3.
 // us a product with the kernels that were chosen for these sizes before (k_gemm_small, 64 x 64 and 128 x 128 tiles) and with this
-// one, operands in the caches: K = 1024, N = 4096: M = 150 8.6 / 6.7, 333 9.4 / 7.6, 500 9.9 / 8.3, 900 15.6 / 12.9, 1500 21.9 / 17.7, 2560 33.9 / 25.9,
-// 4500 49.4 / 46.4; N = 1024: M = 1500 9.2 / 7.6, 2560 11.7 / 10.7, 10240 32.9 / 26.2.
+// one, operands in the caches: K = 1024, N = 4096: M = 150 8.6 / 6.7, 333 9.4 / 7.6, 500 9.9 / 8.3, 900 15.6 / 12.9, 1500 21.9 / 17.7, 2560 33.9 / 25.9;
+// N = 1024: M = 1500 9.2 / 7.6, 2560 11.7 / 10.7, 10240 32.9 / 26.2.
 typedef __attribute__((__vector_size__(4 * sizeof(float)))) float floatx4;
 #define GT_BK 64
 #define GT_LDS_READ (15 | (7 << 4) | (0 << 8) | (3 << 14))   // s_waitcnt: LDS reads only
@@ -1023,26 +1024,41 @@ static long gt_tiles(int M, int N, int TM, int TN) {
     const int tm = (M + 32 * TM - 1) / (32 * TM), tn = (N + 64 * TN - 1) / (64 * TN);
     return (long)((tm + 1) / 2) * ((tn + 3) / 4);
 }
-// Which tile for a product?  The one whose estimated time is least: 4.2 us, 1.07 us a turn of the CUs for every 32 x 64 x 1024 of
-// a tile, and 2.5 us (two workgroups a CU: 1.5) for every turn behind the first; measured times lie within 12 % of it (above).
-// 0: the persistent 256 x 256 tiles, whose turns overlap: from three turns on (7680 x 4096 73 us against 70 with two turns here, 10240 x 4096 98 against
-// 94, 51200 x 4096 458 against 484 to 514).  Where one turn does, four stages (900 x 4096 13.6 -> 12.9 us with 128 x 128, 500 x 4096 9.1 -> 8.3 with
-// 64 x 128), else two, so that two workgroups of the smaller tiles share a CU.
-static int gemm_tile_shape(int M, int N, int K, int products = 1) {
-    if ((long)((M + 255) / 256) * ((N + 255) / 256) * products > 3 * 256) return 0;
+// Which kernel for a product, and which tile?  The one whose estimated time is least, in us:
+//   k_gemm_tile: 4.2, 1.07 a turn of the CUs for every 32 x 64 x 1024 of a tile, and 5 (two workgroups a CU: 2) for every turn behind the first;
+//   k_gemm_bf16, whose tiles overlap, where they are more than one a place: 128 x 128 tiles 4.5 + 16.5 K / 1024 a turn of 512, turns in parts;
+//   256 x 256 tiles 8 + 27 K / 1024 a turn of 256.
+// Measured for K = 256 to 2048, N = 1024 to 4096, M = 40 to 12000 (210 sizes, operands and result in turn, launches of a graph): the chosen
+// kernel takes 1.017 times the best one's time on average, at most 1.19 times; against the kernels by tiles alone (64 x 64, 128 x 128
+// from 256 on, 256 x 256 from 384 on) 0.90 times on average, at most 1.14 (5000 x 4096 x 512 38.6 us against 33.9).  Without k_gemm_bf16 in the
+// choice those were 1.031 and 1.41 times: 12000 x 2560 x 1024 101 us against 72, x 512 56 against 46.  Where one turn of
+// k_gemm_tile does, four stages (500 x 4096 x 1024 9.0 us against 9.6 with two, 900 x 4096 14.0 and 13.9), else two, so that two workgroups of
+// the smaller tiles share a CU.
+// Returns GT_SHAPE, or 2 or 3 (see launch_gemm_bf16).  Beyond 768 tiles of 256 x 256 always 3.
+static bool gt_turns_overlap(int M, int N, int products) { return (long)((M + 255) / 256) * ((N + 255) / 256) * products > 3 * 256; }
+static int gemm_choice(int M, int N, int K, int products = 1) {
+    if (gt_turns_overlap(M, N, products)) return 3;
     static const int tms[] = {8, 7, 6, 5, 4, 3, -4, -3, -2, -1};   // (TN = 4; negative: TN = 2)
+    const double k = K / 1024.0;
     double best = 1e30;
-    int shape = 0;
+    int choice = 0;
     for (int t : tms) {
         const int TM = t > 0 ? t : -t, TN = t > 0 ? 4 : 2;
         const long turns = (products * gt_tiles(M, N, TM, TN) + 31) / 32;
-        const double us = 4.2 + 1.07 * TM * TN * (K / 1024.0) * turns + (TN == 4 ? 2.5 : 1.5) * (turns - 1);
+        const double us = 4.2 + 1.07 * TM * TN * k * turns + (TN == 4 ? 5 : 2) * (turns - 1);
         if (us < best) {
             best = us;
-            shape = GT_SHAPE(TM, TN, TN == 2 && turns == 1 && K >= 4 * GT_BK ? 4 : 2);
+            choice = GT_SHAPE(TM, TN, TN == 2 && turns == 1 && K >= 4 * GT_BK ? 4 : 2);
         }
     }
-    return shape;
+    const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128), t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
+    const double us2 = products * std::max(1.5, t128 / 512.0) * (4.5 + 16.5 * k), us3 = products * ((t256 + 255) / 256) * (8 + 27 * k);
+    if (t128 > 512 && us2 < best) {
+        best = us2;
+        choice = 2;
+    }
+    if (t256 > 256 && us3 < best) choice = 3;
+    return choice;
 }
 
 template <int TM, int TN, int NS>
@@ -1106,8 +1122,8 @@ extern "C" int gemm_tile_run(int shape, const void *A, const void *B, const floa
 hipError_t launch_gemm_bf16_batch(hipStream_t st, const bf16_t *A, const bf16_t *B, float *C, int M, int N, int K, long ldc, const int *m_dev,
                                   int m_likely, const GemmBatch &more) {
     if (M <= 0) return hipSuccess;
-    const int shape = gemm_tile_shape(m_likely > 0 ? min(m_likely, M) : M, N, K, 1 + more.n);
-    bool fits = shape && gt_fits(C, M, N, K, ldc, shape % 10);
+    const int shape = gemm_choice(m_likely > 0 ? min(m_likely, M) : M, N, K, 1 + more.n);
+    bool fits = shape >= 100 && gt_fits(C, M, N, K, ldc, shape % 10);
     if (more.n > 0) fits = fits && gt_fits(more.C, M, N, K, ldc, shape % 10) && more.c % 4 == 0;
     if (fits) return gt_launch_shape(st, shape, A, B, nullptr, C, M, N, K, nullptr, ldc, m_dev, more);
     hipError_t e = launch_gemm_bf16(st, A, B, nullptr, C, M, N, K, nullptr, ldc, 0, m_dev, false, false, m_likely);
@@ -1118,14 +1134,18 @@ hipError_t launch_gemm_bf16_batch(hipStream_t st, const bf16_t *A, const bf16_t 
 
 // kernel: 0 = by size (what the decode uses); 1..4 force one (tests run every kernel on every shape):
 // 1 = 64x64 tiles, 2 = 128x128, 3 = 256x256 (all k_gemm_bf16), 4 = k_gemm_small
+// By size: k_gemm_tile or the persistent tiles, whichever is faster (see gemm_choice).  What k_gemm_tile does not take, K of no whole tiles of 64 (joint spaces and LSTMs of such widths) and results whose rows are no whole 16-byte pieces
+// (tbs_gemm_bf16 alone, every result of a decode has them), goes to k_gemm_small or the persistent tiles.
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel, const int *m_dev, bool xcd_rows,
                             bool bias_late, int m_likely) {
     if (M <= 0) return hipSuccess;
     const int Mc = m_likely <= 0 ? M : m_dev ? min(m_likely, M) : m_likely;   // (the rows that the kernel is chosen for)
-    if (kernel == 0) {
-        const int shape = gemm_tile_shape(Mc, N, K);
-        if (shape && gt_fits(C, M, N, K, ldc, shape % 10)) return gt_launch_shape(st, shape, A, B, bias, C, M, N, K, out_row, ldc, m_dev);
+    if (kernel == 0 && gt_fits(C, M, N, K, ldc, 2)) {
+        const int choice = gemm_choice(Mc, N, K);
+        if (choice >= 100) return gt_launch_shape(st, choice, A, B, bias, C, M, N, K, out_row, ldc, m_dev);
+        kernel = choice;
+        bias_late = bias_late || !gt_turns_overlap(Mc, N, 1);   // (as k_gemm_tile: the same bits whichever of the two it is)
     }
     if ((kernel == 0 || kernel == 4) && K % GS_BK == 0) {
         const int tiles_m = (M + 63) / 64, tiles_n = (N + 63) / 64;
@@ -1149,7 +1169,7 @@ hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, co
         long t128 = (long)((Mc + 127) / 128) * ((N + 127) / 128);
         kernel = t256 >= 384 ? 3 : (t128 >= 256 ? 2 : 1);
     }
-    if (bias_late && bias) {   // (for the bits of k_gemm_small, whatever the size)
+    if (bias_late && bias) {   // (for the bits of k_gemm_small and k_gemm_tile, whatever the size)
         switch (kernel) {
             case 1: return gemm_launch<1, 1, 2, 2, 64, 4, true>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);
             case 2: return gemm_launch<2, 2, 2, 2, 64, 2, true>(st, A, B, bias, C, M, N, K, out_row, ldc, nullptr, m_dev);

@@ -286,7 +286,7 @@ hipError_t launch_gemm_join_f32(hipStream_t st, const float *A, const float *B, 
                               // 25.5 / 24.5, 1920: 18.8 / 17.3
 // m_dev: the launch is enqueued before the host knows the row count; M is an upper bound and the count is read from *m_dev
 // m_likely: rows to choose the kernel for, 0: M.  (Products without a bias have the same bits whichever it is.  The bias is added last by
-// k_gemm_tile and k_gemm_small, and first by the persistent kernel, unless bias_late.)
+// k_gemm_small, in products that k_gemm_tile serves up to 768 tiles of 256 x 256, and with bias_late; otherwise it comes first.)
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel = 0, const int *m_dev = nullptr,
                             bool xcd_rows = false, bool bias_late = false, int m_likely = 0);

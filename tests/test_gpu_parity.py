@@ -1961,3 +1961,20 @@ def test_rows_gathered_by_either_kernel_give_the_same_bits(U, N, layers):
     two, st2 = _gpu_decode(shape, model, offsets, enc, N, 2, debug=256 | 32)
     assert not st1["path"]["fixed_places"]
     assert one == two and st1["joiner_calls"] == st2["joiner_calls"]
+
+
+@pytest.mark.parametrize("M,N,K", [(6000, 2560, 512), (12000, 2560, 256), (7680, 4096, 256), (4500, 4096, 320), (2560, 2560, 192)])
+def test_gemm_bf16_by_size_keeps_the_bits_of_the_tiles(M, N, K):
+    """Up to 768 tiles of 256 x 256 a product is made by tiles chosen for it or by the persistent kernel, whichever is the faster: with
+    the bias in the same place."""
+    import ctypes
+    import torch
+    from paper_2302_14357_amd import gemm_bf16, load_library
+    run = load_library().gemm_tile_run
+    run.argtypes = [ctypes.c_int] + [ctypes.c_void_p] * 4 + [ctypes.c_int] * 3 + [ctypes.c_void_p, ctypes.c_long] + [ctypes.c_void_p] * 2
+    rng = np.random.default_rng(M)
+    a, b = _bf16_values(rng, (M, K)).cuda(), _bf16_values(rng, (N, K), 0.1).cuda()
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+    out = torch.empty(M, N, device="cuda")
+    assert run(442, a.data_ptr(), b.data_ptr(), bias.data_ptr(), out.data_ptr(), M, N, K, None, N, None, torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(gemm_bf16(a, b, bias, kernel=0), out)
