@@ -291,7 +291,7 @@ def main():
         # the expansion kernel, whichever took longer in total
         dom = max((k for k in ("gemm", "expand") if k in kernels), key=lambda k: kernels[k]["total_ms"])
         d = kernels[dom]
-        roofline = {"kernel": {"gemm": "k_gemm_small / k_gemm_bf16 (all launches)", "expand": "k_expand_reg"}[dom],
+        roofline = {"kernel": {"gemm": "k_gemm_small / k_gemm_tile / k_gemm_bf16 (all launches)", "expand": "k_expand_reg"}[dom],
                     "bound": d["bound"], "achieved": d["achieved"], "peak": d["peak"], "unit": d["unit"],
                     "frac": d["frac"], "traffic": read_traffic(dom, args.workload), "avg_us": d["avg_us"],
                     "launches": d["launches"],

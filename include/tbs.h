@@ -302,7 +302,7 @@ int tbs_last_hip_error(const tbs_ctx *ctx);
 /* Plain bf16 GEMM of the joiner's own kernels, C[M,N] = A[M,K] * B[N,K]^T +
  * bias[N] with float32 accumulation and output, exported so that the MFMA
  * tilings can be checked and timed on their own.  All pointers DEVICE, row-major,
- * K a multiple of 8.  kernel: 0 = the choice the decode makes for this size;
+ * K a multiple of 8.  kernel: 0 = the choice the decode makes for this size (N a multiple of 4);
  * 1, 2, 3 = 64x64, 128x128, 256x256 workgroup tiles of the persistent kernel;
  * 4 = the multi-stage kernel for small problems (K a multiple of 128, else
  * TBS_EINVAL).  Asynchronous on `stream`. */

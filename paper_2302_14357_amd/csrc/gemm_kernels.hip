@@ -765,7 +765,7 @@ static int gemm_small_stages() {
 
 // The *_fits functions say whether the kernel can run the problem and has at most max_tiles tiles of
 // 64 x 64: GS_TILES by default (what pays where kernels are sized by the round's rows: beyond one turn
-// and a quarter of workgroups on the 256 CUs the persistent kernel's larger tiles do better), more
+// and a quarter of workgroups on the 256 CUs the other kernels' larger tiles do better), more
 // where the caller has measured otherwise (the slot layout, whose other savings outweigh a second
 // turn).  The launchers themselves take any number of tiles.
 static long gs_tiles(int M, int N) { return (long)((M + 63) / 64) * ((N + 63) / 64); }
@@ -775,7 +775,7 @@ static long gs_tiles(int M, int N) { return (long)((M + 63) / 64) * ((N + 63) / 
 // utterances 24.5 -> 21.1).
 static bool gs_two_per_cu(int tiles_m, int tiles_n) { return (long)tiles_m * tiles_n > 256; }
 
-bool gemm_small_fits(int M, int N, int K, int max_tiles) {   // what launch_gemm_bf16 sends to k_gemm_small by itself
+bool gemm_small_fits(int M, int N, int K, int max_tiles) {
     return K % GS_BK == 0 && gemm_small_stages() >= 2 && gs_tiles(M, N) <= max_tiles;
 }
 
@@ -1133,13 +1133,14 @@ hipError_t launch_gemm_bf16_batch(hipStream_t st, const bf16_t *A, const bf16_t 
 }
 
 // kernel: 0 = by size (what the decode uses); 1..4 force one (tests run every kernel on every shape):
-// 1 = 64x64 tiles, 2 = 128x128, 3 = 256x256 (all k_gemm_bf16), 4 = k_gemm_small
+// 1 = 64x64 tiles, 2 = 128x128, 3 = 256x256 (all k_gemm_bf16), 4 = k_gemm_small (xcd_rows: 4 alone)
 // By size: k_gemm_tile or the persistent tiles, whichever is faster (see gemm_choice).  What k_gemm_tile does not take, K of no whole tiles of 64 (joint spaces and LSTMs of such widths) and results whose rows are no whole 16-byte pieces
 // (tbs_gemm_bf16 alone, every result of a decode has them), goes to k_gemm_small or the persistent tiles.
 hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C, int M,
                             int N, int K, const int *out_row, long ldc, int kernel, const int *m_dev, bool xcd_rows,
                             bool bias_late, int m_likely) {
     if (M <= 0) return hipSuccess;
+    if (xcd_rows && kernel != 4) return hipErrorInvalidValue;
     const int Mc = m_likely <= 0 ? M : m_dev ? min(m_likely, M) : m_likely;   // (the rows that the kernel is chosen for)
     if (kernel == 0 && gt_fits(C, M, N, K, ldc, 2)) {
         const int choice = gemm_choice(Mc, N, K);
@@ -1162,9 +1163,9 @@ hipError_t launch_gemm_bf16(hipStream_t st, const bf16_t *A, const bf16_t *B, co
     }
     if (kernel == 4) return hipErrorInvalidValue;   // k_gemm_small needs K in multiples of 128
     if (kernel == 0) {
-        // measured on MI355X: 256x256 tiles (8 waves, 128x64 per wave) once they fill the chip 1.5
-        // times over, 128x128 (two workgroups per CU) for mid sizes, 64x64 so that small problems
-        // still spread over the CUs
+        // (of the persistent kernels, for what k_gemm_tile does not take: 256x256 tiles (8 waves, 128x64 per wave) once they
+        // fill the chip 1.5 times over, 128x128 (two workgroups per CU) for mid sizes, 64x64 so that small problems
+        // still spread over the CUs)
         long t256 = (long)((Mc + 255) / 256) * ((N + 255) / 256);
         long t128 = (long)((Mc + 127) / 128) * ((N + 127) / 128);
         kernel = t256 >= 384 ? 3 : (t128 >= 256 ? 2 : 1);

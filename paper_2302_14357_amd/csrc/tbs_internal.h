@@ -303,7 +303,7 @@ hipError_t launch_gemm_bf16_batch(hipStream_t st, const bf16_t *A, const bf16_t 
 inline int gemm_small_xcd_rows(int M, int tile) { return tile * ((((M + tile - 1) / tile) + 7) / 8); }
 hipError_t launch_gemm_bf16_rows(hipStream_t st, const bf16_t *A, const bf16_t *B, const float *bias, float *C,
                                  int m_max, int N, int K, long ldc, const int *m_begin, const int *m_end);
-#define GS_TILES 320          // tiles of 64 x 64 up to which the small-problem GEMM kernel is chosen by size
+#define GS_TILES 320          // tiles of 64 x 64 up to which the row lists take the small-problem GEMM kernel's fused forms
 #define GS_TILES_FIXED 1024   // the same for the slot layout (measured on the Librispeech-like shape: 96 to 256
                               // utterances decode 5-16 % faster in it than with row lists, 320 the same)
 bool gemm_small_fits(int M, int N, int K, int max_tiles = GS_TILES);
