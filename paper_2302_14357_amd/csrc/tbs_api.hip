@@ -1030,8 +1030,9 @@ static HidRows hid_rows(const tbs_ctx *c) {
     return {c->pool_h, c->hid ? c->xpar : c->xh[0], c->pool_rows, (long)c->d.U * c->d.N, c->hid};
 }
 // Does the row list kernel gather those rows too, and the recurrent products then go out ahead of the counts (hid_ahead)?  A launch fewer; but
-// in large batches a workgroup of four waves an utterance gathers more slowly than a kernel of a workgroup a row (ms per decode, large widths,
-// apart / together: 256 utterances N = 10 S = 3, two layers 128.9 / 127.6, 1024 N = 10 S = 5 259.1 / 260.9).
+// in large batches a workgroup of four waves an utterance gathers more slowly than a kernel of a workgroup a row (ms per decode, large widths
+// N = 10, apart / together by U N: two layers S = 3 2000 6.11 / 6.08, 2560 128.9 / 127.6, 4000 10.31 / 10.28, 5000 12.92 / 12.86, 6400 16.15 / 16.15; one
+// layer S = 5 4000 9.44 / 9.41, 6400 14.50 / 14.46, 10240 259.1 / 260.9.  The line lies where little hangs on it.)
 static bool gather_in_rowfill(const tbs_ctx *c) {
     return c->cfg.dtype == 1 && !(c->cfg.debug & 32) && (c->cur.H & 3) == 0 && (long)c->cur.U * c->cur.N <= 4096;
 }
