@@ -1026,11 +1026,13 @@ static long gt_tiles(int M, int N, int TM, int TN) {
 }
 // Which kernel for a product, and which tile?  The one whose estimated time is least, in us:
 //   k_gemm_tile: 4.2, 1.07 a turn of the CUs for every 32 x 64 x 1024 of a tile, and 5 (two workgroups a CU: 2) for every turn behind the first;
-//   k_gemm_bf16, whose tiles overlap, where they are more than one a place: 128 x 128 tiles 4.5 + 16.5 K / 1024 a turn of 512, turns in parts;
-//   256 x 256 tiles 8 + 27 K / 1024 a turn of 256.
+//   k_gemm_bf16, whose tiles overlap, where they are more than one a place: 128 x 128 tiles 5 + 18.5 K / 1024 a turn of 512, turns in parts;
+//   256 x 256 tiles 9 + 30 K / 1024 a turn of 256.  (Both an eighth above what they were measured at: behind a decode's other kernels
+//   k_gemm_tile loses less than they do.  256 utterances N = 10 S = 3 with two layers, ms of products a decode 66.2, without the eighth 66.4,
+//   k_gemm_tile alone 67.3.)
 // Measured for K = 256 to 2048, N = 1024 to 4096, M = 40 to 12000 (210 sizes, operands and result in turn, launches of a graph): the chosen
-// kernel takes 1.017 times the best one's time on average, at most 1.19 times; against the kernels by tiles alone (64 x 64, 128 x 128
-// from 256 on, 256 x 256 from 384 on) 0.90 times on average, at most 1.14 (5000 x 4096 x 512 38.6 us against 33.9).  Without k_gemm_bf16 in the
+// kernel takes 1.018 times the best one's time on average, at most 1.23 times; against the kernels by tiles alone (64 x 64, 128 x 128
+// from 256 on, 256 x 256 from 384 on) 0.90 times on average, at most 1.17 (4000 x 2560 x 512 25.9 us against 22.1).  Without k_gemm_bf16 in the
 // choice those were 1.031 and 1.41 times: 12000 x 2560 x 1024 101 us against 72, x 512 56 against 46.  Where one turn of
 // k_gemm_tile does, four stages (500 x 4096 x 1024 9.0 us against 9.6 with two, 900 x 4096 14.0 and 13.9), else two, so that two workgroups of
 // the smaller tiles share a CU.
@@ -1052,7 +1054,7 @@ static int gemm_choice(int M, int N, int K, int products = 1) {
         }
     }
     const long t128 = (long)((M + 127) / 128) * ((N + 127) / 128), t256 = (long)((M + 255) / 256) * ((N + 255) / 256);
-    const double us2 = products * std::max(1.5, t128 / 512.0) * (4.5 + 16.5 * k), us3 = products * ((t256 + 255) / 256) * (8 + 27 * k);
+    const double us2 = products * std::max(1.5, t128 / 512.0) * (5 + 18.5 * k), us3 = products * ((t256 + 255) / 256) * (9 + 30 * k);
     if (t128 > 512 && us2 < best) {
         best = us2;
         choice = 2;
