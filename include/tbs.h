@@ -23,6 +23,8 @@
  *  - Every call returns 0 or a negative TBS_E* code; nothing throws or aborts.
  *    Kernels are enqueued on the context's stream; calls that take a HOST
  *    output pointer synchronise that stream before returning.
+ *  - Encoder frames are not checked.  NaN or infinite ones make the scores of their utterance NaN or
+ *    -inf and its hypotheses meaningless; the batch's other utterances are not touched.
  *  - A context is not thread-safe.
  */
 #ifndef TBS_H
